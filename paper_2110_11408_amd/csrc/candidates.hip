@@ -6,8 +6,9 @@
 // before the sequential part of CompaSO.
 //
 // Two stages: most particles are settled by the densest particle of their own
-// sub-cell; the rest (sub-cell maxima and particles of sparse cells) search
-// their neighbourhood with sub-cell pruning.
+// sub-cell or of a face-adjacent one; the rest (sub-cell maxima and particles
+// of sparse cells) are listed and searched by half a wavefront each, with
+// pruning by the densest particle of every dense cell and sub-cell.
 #include "hf_internal.h"
 
 namespace hf {
@@ -48,40 +49,12 @@ __device__ __forceinline__ uint64_t dkey(float d, uint32_t orig) {
     return ((uint64_t)__float_as_uint(d) << 32) | (uint64_t)(0xffffffffu - orig);
 }
 
-// Slot t = (dense cell d, sub-cell s < nsub_max); sub-cells beyond the cell's
-// own box's count are left alone.
-__global__ __launch_bounds__(kBlock) void k_submax(int64_t nslots, Boxes bx,
-                                                   const uint32_t *__restrict__ dcells,
-                                                   const uint32_t *__restrict__ off,
-                                                   const uint32_t *__restrict__ subtab,
-                                                   const float *__restrict__ dens_s,
-                                                   const float4 *__restrict__ spos,
-                                                   uint64_t *__restrict__ submax,
-                                                   int32_t *__restrict__ subarg) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nslots) return;
-    const int nsub = bx.nsub_max;
-    const int64_t d = t / nsub;
-    const int s = (int)(t - d * nsub);
-    if (s >= bx.geo[box_of(bx, off[dcells[d]])].nsub) return;
-    const uint32_t *tab = subtab + d * (nsub + 1);
-    uint64_t best = 0;
-    int32_t arg = -1;
-    for (uint32_t j = tab[s]; j < tab[s + 1]; j++) {
-        const uint64_t kk = dkey(dens_s[j], orig_of(spos[j]));
-        if (arg < 0 || kk > best) {
-            best = kk;
-            arg = (int32_t)j;
-        }
-    }
-    submax[d * (nsub + 1) + s] = best;
-    subarg[d * (nsub + 1) + s] = arg;
-}
-
-// The same table with one wavefront per dense cell, for at most 64 sub-cells:
-// the cell's particles are sorted by sub-cell, so each 64-particle step
-// reduces the runs of equal sub-cells (maximum key and its particle) and the
-// first lane of each run merges the result into the cell's row in LDS.
+// One wavefront per dense cell: the cell's particles are sorted by sub-cell,
+// so each 64-particle step reduces the runs of equal sub-cells (maximum key
+// and its particle) and the first lane of each run merges the result into the
+// cell's row in LDS.  Entry nsub_max of the row (sub-cells end before it) is
+// the densest particle of the whole cell.
+constexpr int kSubMost = 216;  // 6^3 sub-cells at most
 __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
                                                         const uint32_t *__restrict__ dcells,
                                                         const uint32_t *__restrict__ off,
@@ -90,8 +63,8 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
                                                         const float4 *__restrict__ spos,
                                                         uint64_t *__restrict__ submax,
                                                         int32_t *__restrict__ subarg) {
-    __shared__ uint64_t s_best[kBlock / 64][64];
-    __shared__ int32_t s_arg[kBlock / 64][64];
+    __shared__ uint64_t s_best[kBlock / 64][kSubMost];
+    __shared__ int32_t s_arg[kBlock / 64][kSubMost];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t d = (int64_t)blockIdx.x * (kBlock / 64) + wave;
     if (d >= ndc) return;
@@ -101,8 +74,10 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
     const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(off[c + 1]);
     const int nsub = __builtin_amdgcn_readfirstlane(bx.geo[box_of(bx, a)].nsub);
     const int64_t row = d * (bx.nsub_max + 1);
-    s_best[wave][lane] = 0ull;
-    s_arg[wave][lane] = -1;
+    for (int v = lane; v < nsub; v += 64) {
+        s_best[wave][v] = 0ull;
+        s_arg[wave][v] = -1;
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     for (uint32_t j0 = a; j0 < b; j0 += 64) {
@@ -129,11 +104,45 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         __builtin_amdgcn_wave_barrier();
     }
-    if (lane < nsub) {
-        submax[row + lane] = s_best[wave][lane];
-        subarg[row + lane] = s_arg[wave][lane];
+    uint64_t top = 0ull;
+    int32_t targ = -1;
+    for (int v = lane; v < nsub; v += 64) {
+        const uint64_t best = s_best[wave][v];
+        const int32_t arg = s_arg[wave][v];
+        submax[row + v] = best;
+        subarg[row + v] = arg;
+        if (arg >= 0 && (targ < 0 || best > top)) {
+            top = best;
+            targ = arg;
+        }
+    }
+    for (int dd = 32; dd >= 1; dd >>= 1) {
+        const uint32_t olo = __shfl_xor((uint32_t)top, dd, 64), ohi = __shfl_xor((uint32_t)(top >> 32), dd, 64);
+        const int32_t oarg = __shfl_xor(targ, dd, 64);
+        const uint64_t ok = ((uint64_t)ohi << 32) | olo;
+        if (oarg >= 0 && (targ < 0 || ok > top)) {
+            top = ok;
+            targ = oarg;
+        }
+    }
+    if (lane == 0) {
+        submax[row + bx.nsub_max] = top;
+        subarg[row + bx.nsub_max] = targ;
     }
 }
+
+// The hard cases of stage 1, listed on the device in nseg segments of `cap`
+// entries: workgroup b of the stage appends its cases to segment b mod nseg
+// with one atomic, so no address sees more than a 64th of the workgroups (a
+// count and list pass of its own over all particles took 60 us on the 256^3
+// box, and its read-back by the host another 25 us of an idle device).
+// Counters lie kSegStride words apart.
+constexpr uint32_t kSegs = 64, kSegStride = 16;
+struct HardList {
+    int32_t *list;
+    uint32_t *count;
+    uint32_t nseg, cap;
+};
 
 // Stage 1, one thread per particle: a member at or above the floor that is not
 // the densest particle of its sub-cell is decided at once when that densest
@@ -142,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
 // sub-cell's densest is decided when the densest particle of a face-adjacent
 // sub-cell of the same cell is denser and in its group, where such sub-cells
 // lie within b of each other entirely (s sqrt(6) < b).  Every other member at
-// or above the floor is flagged as a hard case.
+// or above the floor is listed as a hard case.
 __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, const float4 *__restrict__ sloc,
                                                        const float4 *__restrict__ spos,
                                                        const uint32_t *__restrict__ f_sparse,
@@ -152,15 +161,15 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, cons
                                                        const int32_t *__restrict__ subarg,
                                                        const float *__restrict__ dens_s,
                                                        const int32_t *__restrict__ gkey,
-                                                       int32_t *__restrict__ cflag,
-                                                       uint32_t *__restrict__ f_hard) {
+                                                       int32_t *__restrict__ cflag, HardList hl) {
+    __shared__ uint32_t s_cnt[kBlock / 64], s_base;
     const int64_t i = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
+    const int64_t ic = i < n ? i : n - 1;
+    const Geo &g = bx.geo[box_of(bx, (uint32_t)ic)];
     bool is_hard = false;
-    cflag[i] = 0;
-    const int key = gkey[i];
-    const float di = dens_s[i];
+    if (i < n) cflag[i] = 0;
+    const int key = i < n ? gkey[i] : -1;
+    const float di = dens_s[ic];
     if (key >= 0 && (double)di >= g.floor_nuc) {
         is_hard = true;
         // everything indexed by i in one round of loads
@@ -223,348 +232,222 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, cons
             }
         }
     }
-    f_hard[i] = is_hard ? 1u : 0u;
-}
-
-// Four particles per thread (i0, i0 + kBlock, ...), their flags loaded
-// together: the kernel streams the flags, and one load in flight per thread
-// leaves most of the bandwidth unused.
-constexpr int kHardIlp = 4;
-__global__ __launch_bounds__(kBlock) void k_hard_list(int64_t n, const uint32_t *__restrict__ f_hard,
-                                                      const uint32_t *__restrict__ s_hard,
-                                                      int32_t *__restrict__ hard) {
-    const int64_t i0 = (int64_t)blockIdx.x * (kBlock * kHardIlp) + threadIdx.x;
-    uint32_t f[kHardIlp];
-#pragma unroll
-    for (int u = 0; u < kHardIlp; u++) {
-        const int64_t i = i0 + (int64_t)u * kBlock;
-        f[u] = i < n ? f_hard[i] : 0u;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t hm = __ballot(is_hard);
+    if (lane == 0) s_cnt[w] = (uint32_t)__popcll(hm);
+    __syncthreads();
+    const uint32_t seg = blockIdx.x % hl.nseg;
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int x = 0; x < kBlock / 64; x++) t += s_cnt[x];
+        s_base = t ? atomicAdd(hl.count + seg * kSegStride, t) : 0u;
     }
-#pragma unroll
-    for (int u = 0; u < kHardIlp; u++) {
-        const int64_t i = i0 + (int64_t)u * kBlock;
-        if (f[u]) hard[s_hard[i]] = (int32_t)i;
+    __syncthreads();
+    if (is_hard) {
+        uint32_t at = s_base;
+        for (int x = 0; x < w; x++) at += s_cnt[x];
+        hl.list[(int64_t)seg * hl.cap + at + (uint32_t)__popcll(hm & ((1ull << lane) - 1ull))] = (int32_t)i;
     }
 }
 
-// Whether particle i has a denser particle of its group within b in the
-// stencil cells tt0..tt1-1 (cell 0 of the order is its own).  In dense cells
-// only sub-cells within b that hold a denser particle are visited, their
-// densest particle first.
-__device__ bool has_denser_within_b(int i, int tt0, int tt1, const Geo &g, int tstride,
-                                    const float4 *__restrict__ sloc,
-                                    const float4 *__restrict__ spos, const uint32_t *__restrict__ off,
-                                    const uint32_t *__restrict__ cellmap, const uint32_t *__restrict__ subtab,
-                                    const uint64_t *__restrict__ submax, const int32_t *__restrict__ subarg,
-                                    const float *__restrict__ dens_s, const int32_t *__restrict__ gkey) {
-    const int key = gkey[i];
-    const float di = dens_s[i];
-    const float4 li = sloc[i];
-    const float4 pi = spos[i];
-    const uint32_t oi = orig_of(pi);
-    const uint64_t mykey = dkey(di, oi);
-    const uint32_t c = __float_as_uint(li.w);
-    const int k = g.ksub, nsub = g.nsub;
-    const float subb = g.cellb / (float)k, inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)(k * k);
-    int cx, cy, cz;
-    cell_xyz(g, c, cx, cy, cz);
-    for (int tt = tt0; tt < tt1; tt++) {
-        int ox, oy, oz;
-        stencil_offset(tt, ox, oy, oz);
-        const float xs = li.x - (float)ox * g.cellb, ys = li.y - (float)oy * g.cellb,
-                    zs = li.z - (float)oz * g.cellb;
-        // nothing of this cell lies within b
-        const float gx = ox < 0 ? li.x : (ox > 0 ? g.cellb - li.x : 0.0f);
-        const float gy = oy < 0 ? li.y : (oy > 0 ? g.cellb - li.y : 0.0f);
-        const float gz = oz < 0 ? li.z : (oz > 0 ? g.cellb - li.z : 0.0f);
-        if (gx * gx + gy * gy + gz * gz >= g.b2b_hi) continue;
-        const uint32_t nb = cell_id(g, cx + ox, cy + oy, cz + oz);
-        const uint32_t a = off[nb], b = off[nb + 1];
-        if (b - a < (uint32_t)kDenseMin) {
-            // sparse cell: densities four at a time (their loads together),
-            // then the few denser ones in full
-            for (uint32_t a0 = a; a0 < b; a0 += 4) {
-                float dj[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++) dj[u] = a0 + u < b ? dens_s[a0 + u] : -1.0f;
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const uint32_t j = a0 + u;
-                    if (dj[u] < di || (int)j == i) continue;
-                    if (denser_within_b(j, dens_s, gkey, spos, key, di, oi, pi, g)) return true;
-                }
-            }
-            continue;
-        }
-        const int64_t base = (int64_t)cellmap[nb] * tstride;
-        for (int s0 = 0; s0 < nsub; s0 += 3) {
-            // three sub-cell maxima per round of loads (the thread-per-case
-            // kernel waits on memory: small batches keep it at eight
-            // wavefronts per SIMD, which hide more than longer batches would)
-            uint64_t mx[3];
-#pragma unroll
-            for (int u = 0; u < 3; u++) mx[u] = s0 + u < nsub ? submax[base + s0 + u] : 0ull;
-#pragma unroll
-            for (int u = 0; u < 3; u++) {
-                const int s2 = s0 + u;
-                if (!(mx[u] > mykey)) continue;
-                const int sz = div_small(s2, inv_k2), syx = s2 - sz * k * k, sy = div_small(syx, inv_k),
-                          sx = syx - sy * k;
-                const float ex = fmaxf(fmaxf(sx * subb - 1e-5f - xs, xs - (sx + 1) * subb - 1e-5f), 0.0f);
-                const float ey = fmaxf(fmaxf(sy * subb - 1e-5f - ys, ys - (sy + 1) * subb - 1e-5f), 0.0f);
-                const float ez = fmaxf(fmaxf(sz * subb - 1e-5f - zs, zs - (sz + 1) * subb - 1e-5f), 0.0f);
-                if (ex * ex + ey * ey + ez * ez >= g.b2b_hi) continue;
-                const int32_t top = subarg[base + s2];
-                if (denser_within_b(top, dens_s, gkey, spos, key, di, oi, pi, g)) return true;
-                // the rest of the sub-cell: densities four at a time, then the
-                // denser ones in full
-                const uint32_t u1 = subtab[base + s2 + 1];
-                for (uint32_t j0 = subtab[base + s2]; j0 < u1; j0 += 4) {
-                    float dj[4];
-#pragma unroll
-                    for (int v = 0; v < 4; v++) dj[v] = j0 + v < u1 ? dens_s[j0 + v] : -1.0f;
-#pragma unroll
-                    for (int v = 0; v < 4; v++) {
-                        const uint32_t j = j0 + v;
-                        if (dj[v] < di || (int32_t)j == top || (int)j == i) continue;
-                        if (denser_within_b(j, dens_s, gkey, spos, key, di, oi, pi, g))
-                            return true;
-                    }
-                }
-            }
-        }
+// Stage 2, half a wavefront per hard case: whether a denser particle of the
+// group lies within b.  Each step is one round of loads over the 27 stencil
+// cells (one per lane) or 32 sub-cells, and the search stops at the first
+// denser particle:
+//   the ranges of the stencil cells; the particles of the sparse ones (their
+//   densities together, the denser ones in full);
+//   the densest particle of every dense cell (a cell without a denser particle
+//   is dropped: mostly all but a few);
+//   the sub-cells of the cells left, 32 at a time: those within b that hold a
+//   denser particle test their densest one, then the rest, a long sub-cell
+//   with all lanes.
+// The search is a chain of dependent loads, so what counts is the number of
+// rounds a case takes and the cases in flight.  One thread per case for the
+// own cell and then for the face neighbours (nine or more rounds per dense
+// cell, the chain of a wavefront its longest case's) took 146 us on a box of
+// 20 000 particles, 178 us on the 64^3 box and 455 us on the 256^3 one.
+// Workgroup c serves the segments that the workgroups of its own XCD filled.
+__global__ __launch_bounds__(kBlock) void k_cand_search(HardList hl, Boxes bx, const float4 *__restrict__ sloc,
+                                                        const float4 *__restrict__ spos,
+                                                        const uint32_t *__restrict__ off,
+                                                        const uint32_t *__restrict__ cellmap,
+                                                        const uint32_t *__restrict__ subtab,
+                                                        const uint64_t *__restrict__ submax,
+                                                        const int32_t *__restrict__ subarg,
+                                                        const float *__restrict__ dens_s,
+                                                        const int32_t *__restrict__ gkey,
+                                                        const int32_t *__restrict__ gid_of,
+                                                        uint32_t *__restrict__ gccnt,
+                                                        int32_t *__restrict__ cflag,
+                                                        int32_t *__restrict__ nhard) {
+    constexpr int kHalves = kBlock / 32;
+    __shared__ int64_t s_base[kHalves][27];  // sub-table bases of a case's open dense cells
+    __shared__ int8_t s_tt[kHalves][27];     // and their stencil order index
+    const int hw = threadIdx.x >> 5, ln = threadIdx.x & 31, hsh = threadIdx.x & 32;
+    auto hballot = [&](bool p) { return (uint32_t)(__ballot(p) >> hsh); };
+    if (blockIdx.x == 0 && threadIdx.x < kSegs) {
+        int32_t t = threadIdx.x < hl.nseg ? (int32_t)hl.count[threadIdx.x * kSegStride] : 0;
+        for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
+        if (threadIdx.x == 0) *nhard = t;
     }
-    return false;
-}
-
-// Hard cases, one thread each, searching the stencil cells tt0..tt1-1: the
-// particle's own cell (stage 1, where a denser neighbour is nearly always
-// found), then the face neighbours (stage 2).  With `rest`, the cases left are
-// appended to it (one atomic per wavefront), so that the few exhaustive
-// searches (mostly the actual candidates) do not hold up waves of quick ones;
-// without it, the cases left are candidates.  Held to 64 VGPRs (eight
-// wavefronts per SIMD): a few values spill to scratch, which costs less than
-// the two wavefronts per SIMD it buys.
-__global__ __launch_bounds__(kBlock, 8) void k_cand_hard(const uint32_t *__restrict__ nhard_p, int stage, int tt0,
-                                                      int tt1, Boxes bx,
-                                                      const int32_t *__restrict__ hard,
-                                                      const float4 *__restrict__ sloc,
-                                                      const float4 *__restrict__ spos,
-                                                      const uint32_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ cellmap,
-                                                      const uint32_t *__restrict__ subtab,
-                                                      const uint64_t *__restrict__ submax,
-                                                      const int32_t *__restrict__ subarg,
-                                                      const float *__restrict__ dens_s,
-                                                      const int32_t *__restrict__ gkey,
-                                                      const int32_t *__restrict__ gid_of,
-                                                      uint32_t *__restrict__ gccnt,
-                                                      int32_t *__restrict__ cflag,
-                                                      int32_t *__restrict__ rest,
-                                                      uint32_t *__restrict__ nrest) {
-    // a list built on the device fills only the first blocks of its grid:
-    // those are spread over all XCDs by the plain block order, not gathered
-    // on one
-    const int64_t t = (int64_t)(stage == 1 ? xcd_block() : blockIdx.x) * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    const bool valid = t < (int64_t)*nhard_p;
-    const int i = valid ? hard[t] : -1;
-    bool left = false;
-    if (valid && !has_denser_within_b(i, tt0, tt1, bx.geo[box_of(bx, (uint32_t)i)], bx.nsub_max + 1, sloc, spos,
-                                      off, cellmap, subtab, submax, subarg, dens_s, gkey)) {
-        if (rest) {
-            left = true;
-        } else {
-            cflag[i] = 1;
-            atomicAdd(&gccnt[gid_of[i]], 1u);
-        }
-    }
-    if (!rest) return;
-    // append the cases left: one atomic per wavefront
-    const uint64_t m = __ballot(left);
-    if (m == 0ull) return;
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(nrest, (uint32_t)__popcll(m));
-    base = lane_get(base, leader);
-    if (left) rest[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = i;
-}
-
-// Stage 3, one wavefront per case (grid-stride over the list, its length read
-// on the device): the stencil cells tt0..26 are searched by all lanes at once.
-// A lane takes one stencil cell (its range; the particles of a sparse cell),
-// then the sub-cells of the dense cells are taken 64 at a time (densest
-// particle first, then the rest of the sub-cell); the wavefront stops at the
-// first denser particle of the group within b.  The cases that reach this
-// stage are mostly the true candidates, which need every cell.
-__global__ __launch_bounds__(kBlock) void k_cand_wave(const uint32_t *__restrict__ ncase_p, int tt0, Boxes bx,
-                                                      const int32_t *__restrict__ cases,
-                                                      const float4 *__restrict__ sloc,
-                                                      const float4 *__restrict__ spos,
-                                                      const uint32_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ cellmap,
-                                                      const uint32_t *__restrict__ subtab,
-                                                      const uint64_t *__restrict__ submax,
-                                                      const int32_t *__restrict__ subarg,
-                                                      const float *__restrict__ dens_s,
-                                                      const int32_t *__restrict__ gkey,
-                                                      const int32_t *__restrict__ gid_of,
-                                                      uint32_t *__restrict__ gccnt,
-                                                      int32_t *__restrict__ cflag) {
-    __shared__ int64_t s_base[kBlock / 64][27];  // sub-table base of the lane's dense cells
-    __shared__ int8_t s_tt[kBlock / 64][27];     // and their stencil order index
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const uint32_t ncase = *ncase_p;
-    const uint32_t nwaves = gridDim.x * (kBlock / 64);
+    const bool full = hl.nseg == kSegs;  // then the grid is a multiple of 8 workgroups
+    const uint32_t u = blockIdx.x * kHalves + (uint32_t)hw, nu = gridDim.x * kHalves;
+    const uint32_t seg = full ? (blockIdx.x & 7u) + 8u * (uint32_t)hw : u % hl.nseg;
+    const uint32_t step = nu / hl.nseg;
+    uint32_t k = full ? blockIdx.x >> 3 : u / hl.nseg;
+    if (k >= step) return;  // a surplus half of the last round of segments
+    const uint32_t cnt = hl.count[seg * kSegStride];
     const int tstride = bx.nsub_max + 1;
-    for (uint32_t q = blockIdx.x * (kBlock / 64) + (uint32_t)wave; q < ncase; q += nwaves) {
-        const int i = __builtin_amdgcn_readfirstlane(cases[q]);
-        const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, (uint32_t)i))];
-        const int k = g.ksub, nsub = g.nsub;
-        const float subb = g.cellb / (float)k;
+    for (; k < cnt; k += step) {
+        const int i = hl.list[(int64_t)seg * hl.cap + k];
+        const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
         const int key = gkey[i];
         const float di = dens_s[i];
         const float4 li = sloc[i];
         const float4 pi = spos[i];
         const uint32_t oi = orig_of(pi);
         const uint64_t mykey = dkey(di, oi);
-        const uint32_t c = __float_as_uint(li.w);
         int cx, cy, cz;
-        cell_xyz(g, c, cx, cy, cz);
-        // one stencil cell per lane
-        const int tt = tt0 + lane;
-        bool in_reach = false, dense = false, found = false;
-        float xs = 0.0f, ys = 0.0f, zs = 0.0f;
-        uint32_t a = 0, b = 0, nb = 0;
-        if (tt < 27) {
+        cell_xyz(g, __float_as_uint(li.w), cx, cy, cz);
+        bool found = false, dense = false;
+        uint32_t nb = 0;
+        if (ln < 27) {
             int ox, oy, oz;
-            stencil_offset(tt, ox, oy, oz);
-            xs = li.x - (float)ox * g.cellb;
-            ys = li.y - (float)oy * g.cellb;
-            zs = li.z - (float)oz * g.cellb;
+            stencil_offset(ln, ox, oy, oz);
             const float gx = ox < 0 ? li.x : (ox > 0 ? g.cellb - li.x : 0.0f);
             const float gy = oy < 0 ? li.y : (oy > 0 ? g.cellb - li.y : 0.0f);
             const float gz = oz < 0 ? li.z : (oz > 0 ? g.cellb - li.z : 0.0f);
-            in_reach = gx * gx + gy * gy + gz * gz < g.b2b_hi;
-            if (in_reach) {
+            if (gx * gx + gy * gy + gz * gz < g.b2b_hi) {
                 nb = cell_id(g, cx + ox, cy + oy, cz + oz);
-                a = off[nb];
-                b = off[nb + 1];
+                const uint32_t a = off[nb], b = off[nb + 1];
                 dense = b - a >= (uint32_t)kDenseMin;
+                if (!dense) {
+                    float dj[kDenseMin - 1];
+#pragma unroll
+                    for (int v = 0; v < kDenseMin - 1; v++) dj[v] = a + v < b ? dens_s[a + v] : -1.0f;
+#pragma unroll
+                    for (int v = 0; v < kDenseMin - 1; v++)
+                        if (a + v < b && dj[v] >= di && (int)(a + v) != i && !found)
+                            found = denser_within_b(a + v, dens_s, gkey, spos, key, di, oi, pi, g);
+                }
             }
         }
-        // sparse cells: the lane's own particles
-        if (in_reach && !dense) {
-            for (uint32_t j = a; j < b && !found; j++)
-                if ((int)j != i && dens_s[j] >= di &&
-                    denser_within_b(j, dens_s, gkey, spos, key, di, oi, pi, g))
-                    found = true;
+        if (hballot(found)) continue;
+        bool open = false;
+        int64_t base = 0;
+        if (dense) {
+            base = (int64_t)cellmap[nb] * tstride;
+            const uint64_t mx = submax[base + bx.nsub_max];
+            const int32_t top = subarg[base + bx.nsub_max];
+            open = mx > mykey;
+            if (open) found = denser_within_b(top, dens_s, gkey, spos, key, di, oi, pi, g);
         }
-        if (__ballot(found)) continue;
-        // dense cells: their sub-table bases, then (cell, sub-cell) tasks
-        const uint64_t dm = __ballot(in_reach && dense);
-        if (dm == 0ull) {
-            if (lane == 0) {
-                cflag[i] = 1;
-                atomicAdd(&gccnt[gid_of[i]], 1u);
-            }
-            continue;
+        if (hballot(found)) continue;
+        const uint32_t om = hballot(open);
+        if (open) {
+            const int slot = __popc(om & ((1u << ln) - 1u));
+            s_base[hw][slot] = base;
+            s_tt[hw][slot] = (int8_t)ln;
         }
-        if (in_reach && dense) {
-            const int slot = __popcll(dm & ((1ull << lane) - 1ull));
-            s_base[wave][slot] = (int64_t)cellmap[nb] * tstride;
-            s_tt[wave][slot] = (int8_t)tt;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         __builtin_amdgcn_wave_barrier();
-        const int ntask = __popcll(dm) * nsub;
-        for (int t0 = 0; t0 < ntask; t0 += 64) {
-            const int tq = t0 + lane;
+        const int ks = g.ksub, nsub = g.nsub;
+        const float subb = g.cellb / (float)ks;
+        const float inv_nsub = 1.0f / (float)nsub, inv_k = 1.0f / (float)ks, inv_k2 = 1.0f / (float)(ks * ks);
+        const int ntask = __popc(om) * nsub;
+        for (int t0 = 0; t0 < ntask; t0 += 32) {
+            const int tq = t0 + ln;
+            uint32_t u0 = 0, u1 = 0;  // the sub-cell's particles still to be looked at
+            int32_t top = -1;
             if (tq < ntask) {
-                const int r = div_small(tq, 1.0f / (float)nsub), sl = tq - r * nsub;
-                const int64_t base = s_base[wave][r];
-                if (submax[base + sl] > mykey) {
+                const int r = div_small(tq, inv_nsub), sl = tq - r * nsub;
+                const int64_t row = s_base[hw][r] + sl;
+                const uint64_t mx = submax[row];
+                const int32_t arg = subarg[row];
+                const uint32_t b0 = subtab[row], b1 = subtab[row + 1];
+                if (mx > mykey) {
                     int ox, oy, oz;
-                    stencil_offset(s_tt[wave][r], ox, oy, oz);
-                    const float txs = li.x - (float)ox * g.cellb, tys = li.y - (float)oy * g.cellb,
-                                tzs = li.z - (float)oz * g.cellb;
-                    const int sz = div_small(sl, 1.0f / (float)(k * k)), syx = sl - sz * k * k,
-                              sy = div_small(syx, 1.0f / (float)k), sx = syx - sy * k;
-                    const float ex = fmaxf(fmaxf(sx * subb - 1e-5f - txs, txs - (sx + 1) * subb - 1e-5f), 0.0f);
-                    const float ey = fmaxf(fmaxf(sy * subb - 1e-5f - tys, tys - (sy + 1) * subb - 1e-5f), 0.0f);
-                    const float ez = fmaxf(fmaxf(sz * subb - 1e-5f - tzs, tzs - (sz + 1) * subb - 1e-5f), 0.0f);
+                    stencil_offset(s_tt[hw][r], ox, oy, oz);
+                    const float xs = li.x - (float)ox * g.cellb, ys = li.y - (float)oy * g.cellb,
+                                zs = li.z - (float)oz * g.cellb;
+                    const int sz = div_small(sl, inv_k2), syx = sl - sz * ks * ks, sy = div_small(syx, inv_k),
+                              sx = syx - sy * ks;
+                    const float ex = fmaxf(fmaxf(sx * subb - 1e-5f - xs, xs - (sx + 1) * subb - 1e-5f), 0.0f);
+                    const float ey = fmaxf(fmaxf(sy * subb - 1e-5f - ys, ys - (sy + 1) * subb - 1e-5f), 0.0f);
+                    const float ez = fmaxf(fmaxf(sz * subb - 1e-5f - zs, zs - (sz + 1) * subb - 1e-5f), 0.0f);
                     if (ex * ex + ey * ey + ez * ez < g.b2b_hi) {
-                        const int32_t top = subarg[base + sl];
+                        top = arg;
                         found = denser_within_b(top, dens_s, gkey, spos, key, di, oi, pi, g);
-                        const uint32_t u1 = subtab[base + sl + 1];
-                        for (uint32_t j = subtab[base + sl]; j < u1 && !found; j++)
-                            if ((int32_t)j != top && (int)j != i && dens_s[j] >= di &&
-                                denser_within_b(j, dens_s, gkey, spos, key, di, oi, pi, g))
-                                found = true;
+                        u0 = b0;
+                        u1 = b1;
                     }
                 }
             }
-            if (__ballot(found)) break;
+            if (hballot(found)) break;
+            // the rest of the sub-cells: short ones by their own lane, the
+            // others by all lanes
+            constexpr uint32_t kShort = 8;
+            if (u1 - u0 <= kShort) {
+                float dj[kShort];
+#pragma unroll
+                for (uint32_t v = 0; v < kShort; v++) dj[v] = u0 + v < u1 ? dens_s[u0 + v] : -1.0f;
+#pragma unroll
+                for (uint32_t v = 0; v < kShort; v++) {
+                    const uint32_t j = u0 + v;
+                    if (j < u1 && dj[v] >= di && (int32_t)j != top && (int)j != i && !found)
+                        found = denser_within_b(j, dens_s, gkey, spos, key, di, oi, pi, g);
+                }
+            }
+            for (uint32_t m = hballot(u1 - u0 > kShort); m && !hballot(found); m &= m - 1) {
+                const int src = __ffs(m) - 1;
+                const uint32_t c0 = __shfl(u0, src, 32), c1 = __shfl(u1, src, 32);
+                for (uint32_t j0 = c0; j0 < c1 && !hballot(found); j0 += 32) {
+                    const uint32_t j = j0 + (uint32_t)ln;
+                    if (j < c1 && (int)j != i && dens_s[j] >= di)
+                        found = denser_within_b(j, dens_s, gkey, spos, key, di, oi, pi, g);
+                }
+            }
+            if (hballot(found)) break;
         }
-        if (!__ballot(found) && lane == 0) {
+        if (!hballot(found) && ln == 0) {
             cflag[i] = 1;
             atomicAdd(&gccnt[gid_of[i]], 1u);
         }
-        __builtin_amdgcn_wave_barrier();
     }
 }
 
 }  // namespace
 
 void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
-    const int nsub = bx.nsub_max;
-    const int64_t nslots = w.ndcells * nsub;
-    if (nslots > 0 && nsub <= 64)
+    if (w.ndcells > 0)
         hipLaunchKernelGGL(k_submax_wave, dim3((unsigned)((w.ndcells + kBlock / 64 - 1) / (kBlock / 64))),
                            dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.ssub, w.dens_s, w.spos, w.submax,
                            w.subarg);
-    else if (nslots > 0)
-        hipLaunchKernelGGL(k_submax, dim3((unsigned)((nslots + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                           nslots, bx, w.dcells, w.off, w.subtab, w.dens_s, w.spos, w.submax, w.subarg);
-    const unsigned blocks = (unsigned)((n + kBlock - 1) / kBlock);
-    // candidate flags live in the owner array until the assignment overwrites
-    // it; the hard-case flags and their scan reuse the dense-cell flag arrays
-    hipLaunchKernelGGL(k_cand_quick, dim3(blocks), dim3(kBlock), 0, s, n, bx, w.sloc, w.spos, w.f_sparse, w.ssub,
-                       w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, w.owner, w.f_dcell);
-    scan_u32(w.f_dcell, w.s_dcell, n, w.scan_tmp, s);
-    hipLaunchKernelGGL(k_hard_list, dim3((unsigned)((n + kBlock * kHardIlp - 1) / (kBlock * kHardIlp))), dim3(kBlock),
-                       0, s, n, w.f_dcell, w.s_dcell, w.hardlist);
-    uint32_t nh = 0;
-    WordSrc src{};
-    src.p[0] = w.s_dcell + n;
-    if (read_words(src, 1, w.host, &nh, s) != hipSuccess) nh = 0;  // the caller's next read reports it
-    w.nhard = nh;
-    if (nh > 0) {
-        // three stages, each on the cases the one before left, listed on the
-        // device (counts in counters[8] and [10]; surplus threads exit):
-        // the own cell and the 6 face neighbours one thread per case, then the
-        // 20 edge and corner neighbours one wavefront per case.  The first
-        // list is kept in the (free) chunk-flag array, the second in the hard
-        // list, which stage 1 has read by then.
-        int32_t *rest1 = reinterpret_cast<int32_t *>(w.f_chunk);
-        int32_t *rest2 = w.hardlist;
-        uint32_t *n1 = reinterpret_cast<uint32_t *>(w.counters + 8);
-        uint32_t *n2 = reinterpret_cast<uint32_t *>(w.counters + 10);
-        fill_u32(n1, 0u, 3, s);  // counters 8..10 (9 is the acceptance's, also zero here)
-        const dim3 grid((unsigned)((nh + kBlock - 1) / kBlock));
-        hipLaunchKernelGGL(k_cand_hard, grid, dim3(kBlock), 0, s, w.s_dcell + n, 1, 0, 1, bx, w.hardlist, w.sloc,
-                           w.spos, w.off, w.cnt, w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of,
-                           w.gccnt, w.owner, rest1, n1);
-        hipLaunchKernelGGL(k_cand_hard, grid, dim3(kBlock), 0, s, n1, 2, 1, 7, bx, rest1, w.sloc, w.spos, w.off,
-                           w.cnt, w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of, w.gccnt, w.owner,
-                           rest2, n2);
-        // a fixed grid of wavefronts striding over the list
-        const int64_t waves = nh < 8192 ? nh : 8192;
-        hipLaunchKernelGGL(k_cand_wave, dim3((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0,
-                           s, n2, 7, bx, rest2, w.sloc, w.spos, w.off, w.cnt, w.subtab, w.submax, w.subarg,
-                           w.dens_s, w.gkey, w.gid_of, w.gccnt, w.owner);
-    }
+    // The hard cases go to the chunk and dense-cell flag and scan arrays (4 n
+    // words in one run, free at this stage; the segments hold at most
+    // 2 (n + 255) words, and a single segment at most n), their counts to the
+    // radix counts (at least n / 8 words, of which n / 16 + 16 are used).
+    const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    HardList hl;
+    hl.list = reinterpret_cast<int32_t *>(w.f_chunk);
+    hl.count = w.rhist;
+    hl.nseg = nb < kSegs ? nb : kSegs;
+    hl.cap = (nb + hl.nseg - 1) / hl.nseg * kBlock;
+    fill_u32(hl.count, 0u, (int64_t)hl.nseg * kSegStride, s);
+    // candidate flags live in the owner array until the assignment overwrites it
+    hipLaunchKernelGGL(k_cand_quick, dim3(nb), dim3(kBlock), 0, s, n, bx, w.sloc, w.spos, w.f_sparse, w.ssub,
+                       w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, w.owner, hl);
+    // half-wavefronts striding over the segments: as many as fit the chip (six
+    // wavefronts per SIMD at 79 VGPRs), and no more than one per four particles
+    // (one particle in thirty is a hard case); their total goes to counters[8]
+    const int64_t fit = 6 * (int64_t)(w.ncu > 0 ? w.ncu : 1);
+    int64_t blocks = (n / 4 + kBlock / 32 - 1) / (kBlock / 32);
+    if (blocks > fit) blocks = fit;
+    if (blocks < 8) blocks = 8;
+    blocks = (blocks + 7) & ~(int64_t)7;
+    hipLaunchKernelGGL(k_cand_search, dim3((unsigned)blocks), dim3(kBlock), 0, s, hl, bx, w.sloc, w.spos, w.off,
+                       w.cnt, w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of, w.gccnt, w.owner,
+                       w.counters + 8);
 }
 
 }  // namespace hf

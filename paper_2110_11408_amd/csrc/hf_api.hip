@@ -497,10 +497,11 @@ hf_status run_compaso(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, int
     HIP_OK(c, hipEventRecord(c->ev[4], s));
     hf::launch_candidates(n, bx, w, s);
     hf::scan_u32(w.gccnt, w.gcoff, G, w.scan_tmp, s);
-    uint32_t NC32 = 0;
-    st = read_dev(c, s, {w.gcoff + G}, &NC32);
+    uint32_t rc[2] = {0, 0};  // candidates, hard cases
+    st = read_dev(c, s, {w.gcoff + G, w.counters + 8}, rc);
     if (st != HF_OK) return st;
-    int64_t NC = NC32;
+    const int64_t NC = rc[0];
+    w.nhard = rc[1];
     hf::launch_candidates_sort(n, G, NC, w, s);
     HIP_OK(c, hipEventRecord(c->ev[5], s));
     hf::launch_accept(n, G, NC, c->stats.n_members, bx, w, s);
