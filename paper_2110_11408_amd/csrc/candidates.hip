@@ -10,6 +10,7 @@
 // of sparse cells) are listed and searched by half a wavefront each, with
 // pruning by the densest particle of every dense cell and sub-cell.
 #include "hf_internal.h"
+#include "scan_tile.h"
 
 namespace hf {
 
@@ -161,13 +162,12 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, cons
                                                        const int32_t *__restrict__ subarg,
                                                        const float *__restrict__ dens_s,
                                                        const int32_t *__restrict__ gkey,
-                                                       int32_t *__restrict__ cflag, HardList hl) {
+                                                       HardList hl) {
     __shared__ uint32_t s_cnt[kBlock / 64], s_base;
     const int64_t i = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     const int64_t ic = i < n ? i : n - 1;
     const Geo &g = bx.geo[box_of(bx, (uint32_t)ic)];
     bool is_hard = false;
-    if (i < n) cflag[i] = 0;
     const int key = i < n ? gkey[i] : -1;
     const float di = dens_s[ic];
     if (key >= 0 && (double)di >= g.floor_nuc) {
@@ -278,7 +278,6 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(HardList hl, Boxes bx, c
                                                         const int32_t *__restrict__ gkey,
                                                         const int32_t *__restrict__ gid_of,
                                                         uint32_t *__restrict__ gccnt,
-                                                        int32_t *__restrict__ cflag,
                                                         int32_t *__restrict__ nhard) {
     constexpr int kHalves = kBlock / 32;
     __shared__ int64_t s_base[kHalves][27];  // sub-table bases of a case's open dense cells
@@ -410,44 +409,216 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(HardList hl, Boxes bx, c
             if (hballot(found)) break;
         }
         if (!hballot(found) && ln == 0) {
-            cflag[i] = 1;
+            // a candidate: marked in the list, counted for its group
+            hl.list[(int64_t)seg * hl.cap + k] = ~i;
             atomicAdd(&gccnt[gid_of[i]], 1u);
         }
     }
 }
 
-}  // namespace
+// ------------------------------------------------------------ candidate lists
+// Size classes of the groups with candidates: four per octave.
+constexpr int kClasses = 128;
+__device__ __forceinline__ int size_class(uint32_t m) {
+    return (int)(__float_as_uint((float)m) >> 21) - (int)(0x3f800000u >> 21);
+}
 
-void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
-    if (w.ndcells > 0)
-        hipLaunchKernelGGL(k_submax_wave, dim3((unsigned)((w.ndcells + kBlock / 64 - 1) / (kBlock / 64))),
-                           dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.ssub, w.dens_s, w.spos, w.submax,
-                           w.subarg);
-    // The hard cases go to the chunk and dense-cell flag and scan arrays (4 n
-    // words in one run, free at this stage; the segments hold at most
-    // 2 (n + 255) words, and a single segment at most n), their counts to the
-    // radix counts (at least n / 8 words, of which n / 16 + 16 are used).
+__global__ __launch_bounds__(kBlock) void k_gc_sums(const int32_t *__restrict__ groups_p,
+                                                    const uint32_t *__restrict__ gccnt,
+                                                    uint32_t *__restrict__ sums) {
+    const int64_t G = *groups_p, base = (int64_t)blockIdx.x * kScanTile;
+    uint32_t s = 0;
+    if (base < G) tile_each(gccnt, base, G, [&](uint32_t x) { s += x; });
+    const uint32_t tot = block_sum(s);
+    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
+}
+
+// First candidate of every group (gcoff[G] and counters[kCntCand]: their
+// total), and the number of groups with candidates per size class.  The group
+// count is read on the device.
+__global__ __launch_bounds__(kBlock) void k_gc_offsets(const uint32_t *__restrict__ gccnt,
+                                                       const int32_t *__restrict__ g_size,
+                                                       const uint32_t *__restrict__ sums, bool scanned,
+                                                       uint32_t *__restrict__ gcoff,
+                                                       uint32_t *__restrict__ nclass,
+                                                       int32_t *__restrict__ counters) {
+    __shared__ uint32_t buf[kScanLds];
+    __shared__ uint32_t s_class[kClasses];
+    const int64_t G = counters[kCntGroups], base = (int64_t)blockIdx.x * kScanTile;
+    if (base >= G && blockIdx.x > 0) return;
+    if (threadIdx.x < kClasses) s_class[threadIdx.x] = 0u;
+    uint32_t v[kScanItems];
+    tile_load(gccnt, base, G, buf, v, [](uint32_t x) { return x; });
+    uint32_t s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) s += v[k];
+    uint32_t tot;
+    uint32_t run = block_excl_scan(s, &tot);
+    const uint32_t toff = blockIdx.x > 0 ? tile_offset(sums, blockIdx.x, scanned) : 0u;
+    run += toff;
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) {
+        const int64_t g = base + (int64_t)threadIdx.x * kScanItems + k;
+        if (g >= G) break;
+        gcoff[g] = run;
+        run += v[k];
+        if (v[k]) atomicAdd(&s_class[size_class((uint32_t)g_size[g])], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < kClasses && s_class[threadIdx.x]) atomicAdd(&nclass[threadIdx.x], s_class[threadIdx.x]);
+    if (base + kScanTile >= G && threadIdx.x == 0) {
+        gcoff[G] = toff + tot;
+        counters[kCntCand] = (int32_t)(toff + tot);
+    }
+}
+
+// The candidates of the hard-case list into their groups' slots (any order
+// inside a group), with the slots' halo records cleared.
+__global__ __launch_bounds__(kBlock) void k_cand_scatter(HardList hl, const int32_t *__restrict__ gid_of,
+                                                         const uint32_t *__restrict__ gcoff,
+                                                         uint32_t *__restrict__ gcfill,
+                                                         int32_t *__restrict__ cand,
+                                                         int32_t *__restrict__ h_nuc,
+                                                         uint32_t *__restrict__ h_count) {
+    const uint32_t seg = blockIdx.x % hl.nseg, nb = gridDim.x / hl.nseg;
+    const uint32_t cnt = hl.count[seg * kSegStride];
+    for (uint32_t k = (blockIdx.x / hl.nseg) * kBlock + threadIdx.x; k < cnt; k += nb * kBlock) {
+        const int32_t e = hl.list[(int64_t)seg * hl.cap + k];
+        if (e >= 0) continue;
+        const int i = ~e, gi = gid_of[i];
+        const uint32_t slot = gcoff[gi] + atomicAdd(&gcfill[gi], 1u);
+        cand[slot] = i;
+        h_nuc[slot] = -1;
+        h_count[slot] = 0u;
+    }
+}
+
+// Order candidates of a group by "denser" (density desc, original index asc):
+// the rank of a candidate is the number of denser candidates in its group.
+__global__ __launch_bounds__(kBlock) void k_cand_rank(const int32_t *__restrict__ ncand_p,
+                                                      const int32_t *__restrict__ gid_of,
+                                                      const uint32_t *__restrict__ gcoff,
+                                                      const int32_t *__restrict__ cand,
+                                                      const float *__restrict__ dens_s,
+                                                      const float4 *__restrict__ spos,
+                                                      int32_t *__restrict__ cand_sorted) {
+    const int64_t NC = *ncand_p;
+    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < NC;
+         s += (int64_t)gridDim.x * blockDim.x) {
+        const int me = cand[s];
+        const int gi = gid_of[me];
+        const uint32_t a = gcoff[gi], b = gcoff[gi + 1];
+        const float dm = dens_s[me];
+        const uint32_t om = orig_of(spos[me]);
+        uint32_t rank = 0;
+        for (uint32_t t = a; t < b; t++) {
+            const int o = cand[t];
+            rank += denser(dens_s[o], orig_of(spos[o]), dm, om) ? 1u : 0u;
+        }
+        cand_sorted[a + rank] = me;
+    }
+}
+
+// The groups with candidates (of every box), the larger size classes first, so
+// that the acceptance kernels start the longest walks first.  The order inside
+// a class is that of arrival: nothing but the schedule depends on it, and the
+// classes differ by a quarter octave (a radix sort by size, three to four
+// passes of four launches, cost 60 us on a list of a few hundred groups).
+__global__ __launch_bounds__(kBlock) void k_group_list(const uint32_t *__restrict__ gccnt,
+                                                       const int32_t *__restrict__ g_size,
+                                                       const uint32_t *__restrict__ nclass,
+                                                       uint32_t *__restrict__ fill,
+                                                       int32_t *__restrict__ glist,
+                                                       int32_t *__restrict__ counters) {
+    __shared__ uint32_t s_start[kClasses], s_cnt[kClasses], s_at[kClasses];
+    const int64_t G = counters[kCntGroups];
+    // larger classes first: class c starts after the classes above it
+    const int rc = kClasses - 1 - (int)threadIdx.x;
+    uint32_t tot;
+    const uint32_t before = block_excl_scan(rc >= 0 ? nclass[rc] : 0u, &tot);
+    if (rc >= 0) s_start[rc] = before;
+    if (blockIdx.x == 0 && threadIdx.x == 0) counters[kCntListed] = (int32_t)tot;
+    for (int64_t g0 = (int64_t)blockIdx.x * kBlock; g0 < G; g0 += (int64_t)gridDim.x * kBlock) {
+        if (threadIdx.x < kClasses) s_cnt[threadIdx.x] = 0u;
+        __syncthreads();
+        const int64_t g = g0 + threadIdx.x;
+        const bool in = g < G && gccnt[g] != 0u;
+        int c = 0;
+        uint32_t rank = 0;
+        if (in) {
+            c = size_class((uint32_t)g_size[g]);
+            rank = atomicAdd(&s_cnt[c], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < kClasses && s_cnt[threadIdx.x])
+            s_at[threadIdx.x] = atomicAdd(&fill[threadIdx.x], s_cnt[threadIdx.x]);
+        __syncthreads();
+        if (in) glist[s_start[c] + s_at[c] + rank] = (int32_t)g;
+        __syncthreads();
+    }
+}
+
+// The hard cases go to the chunk and dense-cell flag and scan arrays (4 n words
+// in one run, free at this stage; the segments hold at most 2 (n + 255) words,
+// and a single segment at most n), their counts to the radix counts (at least
+// n / 8 words, of which n / 16 + 16 are used).
+HardList hard_list(int64_t n, const Work &w) {
     const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
     HardList hl;
     hl.list = reinterpret_cast<int32_t *>(w.f_chunk);
     hl.count = w.rhist;
     hl.nseg = nb < kSegs ? nb : kSegs;
     hl.cap = (nb + hl.nseg - 1) / hl.nseg * kBlock;
-    fill_u32(hl.count, 0u, (int64_t)hl.nseg * kSegStride, s);
-    // candidate flags live in the owner array until the assignment overwrites it
-    hipLaunchKernelGGL(k_cand_quick, dim3(nb), dim3(kBlock), 0, s, n, bx, w.sloc, w.spos, w.f_sparse, w.ssub,
-                       w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, w.owner, hl);
+    return hl;
+}
+
+}  // namespace
+
+SegClear candidates_clear(int64_t n, const Work &w) {
+    // the counts of the hard-case segments, and the class counts and fills of
+    // the group list in the scanned radix counts (257 words at least)
+    static_assert(2 * kClasses <= 257, "class counts fit the smallest radix count array");
+    return SegClear{{w.rhist, w.rscan}, {(int)(hard_list(n, w).nseg * kSegStride), 2 * kClasses}};
+}
+
+void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
+    if (w.ndcells > 0)
+        hipLaunchKernelGGL(k_submax_wave, dim3((unsigned)((w.ndcells + kBlock / 64 - 1) / (kBlock / 64))),
+                           dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.ssub, w.dens_s, w.spos, w.submax,
+                           w.subarg);
+    const HardList hl = hard_list(n, w);
+    hipLaunchKernelGGL(k_cand_quick, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, bx, w.sloc,
+                       w.spos, w.f_sparse, w.ssub, w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, hl);
     // half-wavefronts striding over the segments: as many as fit the chip (six
     // wavefronts per SIMD at 79 VGPRs), and no more than one per four particles
-    // (one particle in thirty is a hard case); their total goes to counters[8]
+    // (one particle in thirty is a hard case); their total goes to a counter
     const int64_t fit = 6 * (int64_t)(w.ncu > 0 ? w.ncu : 1);
     int64_t blocks = (n / 4 + kBlock / 32 - 1) / (kBlock / 32);
     if (blocks > fit) blocks = fit;
     if (blocks < 8) blocks = 8;
     blocks = (blocks + 7) & ~(int64_t)7;
     hipLaunchKernelGGL(k_cand_search, dim3((unsigned)blocks), dim3(kBlock), 0, s, hl, bx, w.sloc, w.spos, w.off,
-                       w.cnt, w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of, w.gccnt, w.owner,
-                       w.counters + 8);
+                       w.cnt, w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of, w.gccnt,
+                       w.counters + kCntHard);
+    const int64_t tiles = scan_tiles(n);  // of the groups: at most one per particle
+    hipLaunchKernelGGL(k_gc_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, w.counters + kCntGroups, w.gccnt,
+                       w.scan_tmp);
+    const bool scanned = scan_sums(w.scan_tmp, tiles, tiles, 1, s);
+    hipLaunchKernelGGL(k_gc_offsets, dim3((unsigned)tiles), dim3(kBlock), 0, s, w.gccnt, w.g_size, w.scan_tmp,
+                       scanned, w.gcoff, w.rscan, w.counters);
+}
+
+void launch_candidate_lists(int64_t n, Work &w, hipStream_t s) {
+    // grids that stride over counts known on the device
+    const HardList hl = hard_list(n, w);
+    auto cap = [](int64_t want, int64_t most) { return (unsigned)(want < most ? want : most); };
+    const unsigned per = cap((int64_t)hl.cap / (16 * kBlock) + 1, 16);
+    hipLaunchKernelGGL(k_cand_scatter, dim3(hl.nseg * per), dim3(kBlock), 0, s, hl, w.gid_of, w.gcoff, w.gcfill,
+                       w.cand, w.h_nuc, w.h_count);
+    hipLaunchKernelGGL(k_cand_rank, dim3(cap(n / (64 * kBlock) + 1, 1024)), dim3(kBlock), 0, s,
+                       w.counters + kCntCand, w.gid_of, w.gcoff, w.cand, w.dens_s, w.spos, w.cand_sorted);
+    hipLaunchKernelGGL(k_group_list, dim3(cap(n / (32 * kBlock) + 1, 1024)), dim3(kBlock), 0, s, w.gccnt, w.g_size,
+                       w.rscan, w.rscan + kClasses, w.glist, w.counters);
 }
 
 }  // namespace hf

@@ -22,6 +22,7 @@
 // ceil(sqrt(T)) (computed exactly with integer-square comparisons), so each
 // accepted nucleus costs one pass over the group plus a prefix scan.
 #include "hf_internal.h"
+#include "scan_tile.h"
 
 namespace hf {
 
@@ -41,28 +42,101 @@ __device__ __forceinline__ void stu(uint32_t *p, uint32_t v) {
 
 // ------------------------------------------------------------ segmentation
 
-__global__ __launch_bounds__(kBlock) void k_seg_count(int64_t n, const int32_t *__restrict__ gkey,
-                                                      uint32_t *__restrict__ gcnt) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = i < n ? gkey[i] : -1;
-    const WaveRun r = wave_run(k);
-    if (k >= 0 && r.rank == 0) atomicAdd(&gcnt[k], (uint32_t)r.len);
+// The members of every group are counted by the kernels that write the group
+// keys (gcnt[key], zero before).  Two prefix sums over the keys, of the counts
+// and of their non-zero ones, give every group its start and its ordinal.
+__global__ __launch_bounds__(kBlock) void k_seg_sums(int64_t n, const uint32_t *__restrict__ gcnt,
+                                                     uint32_t *__restrict__ msum, uint32_t *__restrict__ gsum) {
+    uint32_t m = 0, g = 0;
+    tile_each(gcnt, (int64_t)blockIdx.x * kScanTile, n, [&](uint32_t c) {
+        m += c;
+        g += c != 0u ? 1u : 0u;
+    });
+    m = block_sum(m);
+    g = block_sum(g);
+    if (threadIdx.x == 0) {
+        msum[blockIdx.x] = m;
+        gsum[blockIdx.x] = g;
+    }
 }
 
-__global__ __launch_bounds__(kBlock) void k_seg_groups(int64_t n, const uint32_t *__restrict__ gcnt,
-                                                       const uint32_t *__restrict__ goff,
-                                                       const uint32_t *__restrict__ gidx,
-                                                       int32_t *__restrict__ g_start,
-                                                       int32_t *__restrict__ g_size,
-                                                       int32_t *__restrict__ g_label) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    uint32_t c = gcnt[k];
-    if (!c) return;
-    uint32_t g = gidx[k];
-    g_start[g] = (int32_t)goff[k];
-    g_size[g] = (int32_t)c;
-    g_label[g] = (int32_t)k + 1;
+// Totals of two runs of tile sums (one workgroup): members, groups.
+__global__ __launch_bounds__(kBlock) void k_seg_totals(int64_t tiles, const uint32_t *__restrict__ msum,
+                                                       const uint32_t *__restrict__ gsum,
+                                                       int32_t *__restrict__ counters) {
+    uint32_t m = 0, g = 0;
+    for (int64_t t = threadIdx.x; t < tiles; t += kBlock) {
+        m += msum[t];
+        g += gsum[t];
+    }
+    m = block_sum(m);
+    g = block_sum(g);
+    if (threadIdx.x == 0) {
+        counters[kCntMembers] = (int32_t)m;
+        counters[kCntGroups] = (int32_t)g;
+    }
+}
+
+// The prefixes of a tile of keys, stored for the keys of groups only: the
+// group's start and ordinal by key, and by ordinal its start, size, label and
+// the zeros its later counts start from.  (Whole prefix arrays and a fill per
+// count array, with a kernel of their own for the per-group values, moved 32
+// bytes per particle more and cost six more launches.)  Also zeroed here: the
+// table-row bits (n / 32 + 1 words) and the words of `clear`.
+__global__ __launch_bounds__(kBlock) void k_seg_offsets(int64_t n, const uint32_t *__restrict__ gcnt,
+                                                        const uint32_t *__restrict__ msum,
+                                                        const uint32_t *__restrict__ gsum, bool scanned,
+                                                        uint32_t *__restrict__ goff, uint32_t *__restrict__ gidx,
+                                                        int32_t *__restrict__ g_start,
+                                                        int32_t *__restrict__ g_size,
+                                                        int32_t *__restrict__ g_label,
+                                                        uint32_t *__restrict__ gccnt,
+                                                        uint32_t *__restrict__ gcfill,
+                                                        int32_t *__restrict__ g_nh,
+                                                        int32_t *__restrict__ gflag,
+                                                        uint32_t *__restrict__ tflag, SegClear clear,
+                                                        int32_t *__restrict__ counters) {
+    __shared__ uint32_t buf[kScanLds];
+    const int64_t base = (int64_t)blockIdx.x * kScanTile;
+    const int64_t word = (int64_t)blockIdx.x * (kScanTile / 32) + threadIdx.x;
+    if (threadIdx.x <= kScanTile / 32 && word <= (n >> 5)) tflag[word] = 0u;
+    if (blockIdx.x == 0)
+        for (int k = 0; k < SegClear::kRuns; k++)
+            for (int t = threadIdx.x; t < clear.len[k]; t += kBlock) clear.p[k][t] = 0u;
+    uint32_t v[kScanItems];
+    tile_load(gcnt, base, n, buf, v, [](uint32_t x) { return x; });
+    uint32_t m = 0, g = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) {
+        m += v[k];
+        g += v[k] != 0u ? 1u : 0u;
+    }
+    uint32_t mt, gt;
+    uint32_t moff = block_excl_scan(m, &mt), goffs = block_excl_scan(g, &gt);
+    const uint32_t m0 = blockIdx.x > 0 ? tile_offset(msum, blockIdx.x, scanned) : 0u;
+    const uint32_t g0 = blockIdx.x > 0 ? tile_offset(gsum, blockIdx.x, scanned) : 0u;
+    moff += m0;
+    goffs += g0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; k++) {
+        if (!v[k]) continue;
+        const int64_t key = base + (int64_t)threadIdx.x * kScanItems + k;
+        goff[key] = moff;
+        gidx[key] = goffs;
+        g_start[goffs] = (int32_t)moff;
+        g_size[goffs] = (int32_t)v[k];
+        g_label[goffs] = (int32_t)key + 1;
+        gccnt[goffs] = 0u;
+        gcfill[goffs] = 0u;
+        g_nh[goffs] = 0;
+        gflag[goffs] = 0;
+        moff += v[k];
+        goffs++;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        counters[kCntMembers] = (int32_t)(m0 + mt);
+        counters[kCntGroups] = (int32_t)(g0 + gt);
+    }
 }
 
 // Members into group order: each run of equal keys among consecutive lanes
@@ -89,58 +163,6 @@ __global__ __launch_bounds__(kBlock) void k_seg_scatter(int64_t n, const int32_t
     gid_of[i] = (int32_t)gidx[k];
 }
 
-__global__ __launch_bounds__(kBlock) void k_cand_scatter(int64_t n, const int32_t *__restrict__ cflag,
-                                                         const int32_t *__restrict__ gid_of,
-                                                         const uint32_t *__restrict__ gcoff,
-                                                         uint32_t *__restrict__ gcfill,
-                                                         int32_t *__restrict__ cand) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || !cflag[i]) return;
-    int gi = gid_of[i];
-    cand[gcoff[gi] + atomicAdd(&gcfill[gi], 1u)] = (int32_t)i;
-}
-
-// Candidate slot -> group, via a marker per group start and a max-scan would be
-// heavier than a binary search over the group candidate offsets.
-__device__ __forceinline__ int group_of_slot(const uint32_t *gcoff, int G, uint32_t s) {
-    int lo = 0, hi = G - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (gcoff[mid] <= s) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// Order candidates of a group by "denser" (density desc, original index asc):
-// the rank of a candidate is the number of denser candidates in its group.
-__global__ __launch_bounds__(kBlock) void k_cand_rank(int64_t NC, int G, const uint32_t *__restrict__ gcoff,
-                                                      const int32_t *__restrict__ cand,
-                                                      const float *__restrict__ dens_s,
-                                                      const float4 *__restrict__ spos,
-                                                      int32_t *__restrict__ cand_sorted) {
-    int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= NC) return;
-    int gi = group_of_slot(gcoff, G, (uint32_t)s);
-    uint32_t a = gcoff[gi], b = gcoff[gi + 1];
-    int me = cand[s];
-    float dm = dens_s[me];
-    uint32_t om = orig_of(spos[me]);
-    uint32_t rank = 0;
-    for (uint32_t t = a; t < b; t++) {
-        int o = cand[t];
-        rank += denser(dens_s[o], orig_of(spos[o]), dm, om) ? 1u : 0u;
-    }
-    cand_sorted[a + rank] = me;
-}
-
-__global__ __launch_bounds__(kBlock) void k_glist(int G, const uint32_t *__restrict__ gccnt,
-                                                  const uint32_t *__restrict__ idx,
-                                                  int32_t *__restrict__ glist) {
-    int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= G) return;
-    if (gccnt[g]) glist[idx[g]] = g;
-}
-
 // ------------------------------------------------------- group extent
 // Every distance is a minimum image, which stands for the distance inside an
 // L0 group only while the group spans less than half the box along each axis.
@@ -158,7 +180,7 @@ __device__ __forceinline__ double mi_off(float a, float b, double L, double half
     return d;
 }
 
-__global__ __launch_bounds__(kBlock) void k_extent_far(int64_t M, Boxes bx, const int32_t *__restrict__ mem,
+__global__ __launch_bounds__(kBlock) void k_extent_far(const int32_t *__restrict__ members_p, Boxes bx, const int32_t *__restrict__ mem,
                                                        const int32_t *__restrict__ gid_of,
                                                        const int32_t *__restrict__ g_start,
                                                        const float4 *__restrict__ spos,
@@ -166,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void k_extent_far(int64_t M, Boxes bx, cons
                                                        int32_t *__restrict__ farlist,
                                                        uint32_t *__restrict__ nfar) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= M) return;
+    if (t >= (int64_t)*members_p) return;
     const int i = mem[t];
     const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
     const int gi = gid_of[i];
@@ -739,20 +761,28 @@ __global__ __launch_bounds__(kBlock) void k_out_flags(int64_t NC, Boxes bx, cons
         const Geo &g = bx.geo[box_of(bx, (uint32_t)nuc)];
         if (h_count[s] >= (uint32_t)g.n_l1_min) {
             const uint32_t o = orig_of(spos[nuc]);
-            tflag[o] = 1u;
+            atomicOr(&tflag[o >> 5], 1u << (o & 31u));
             lab = (int32_t)(o - g.orig_base) + 1;
         }
     }
     h_label[s] = lab;
 }
 
+// Kept halos with a nucleus below original index o: their bits before o's word
+// (tpos, the prefix sum of the words' set bits) and below o in it.
+__device__ __forceinline__ uint32_t table_pos(const uint32_t *__restrict__ tflag, const uint32_t *__restrict__ tpos,
+                                              uint32_t o) {
+    return tpos[o >> 5] + (uint32_t)__popc(tflag[o >> 5] & ((1u << (o & 31u)) - 1u));
+}
+
 // Rows of the halo table of every box: the kept halos are flagged at their
 // nucleus's original index, so a box's rows are the flags in its index range.
-__global__ __launch_bounds__(kBlock) void k_box_rows(Boxes bx, const uint32_t *__restrict__ tpos,
+__global__ __launch_bounds__(kBlock) void k_box_rows(Boxes bx, const uint32_t *__restrict__ tflag,
+                                                     const uint32_t *__restrict__ tpos,
                                                      int64_t *__restrict__ box_rows) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= bx.nbox) return;
-    box_rows[b] = (int64_t)tpos[bx.base[b + 1]] - (int64_t)tpos[bx.base[b]];
+    box_rows[b] = (int64_t)table_pos(tflag, tpos, bx.base[b + 1]) - (int64_t)table_pos(tflag, tpos, bx.base[b]);
 }
 
 // A halo's row in its box's table (ascending id); a box whose rows exceed its
@@ -763,6 +793,7 @@ __global__ __launch_bounds__(kBlock) void k_out_table(int64_t NC, Boxes bx, cons
                                                       const uint32_t *__restrict__ h_count,
                                                       const int32_t *__restrict__ g_label,
                                                       const float4 *__restrict__ spos,
+                                                      const uint32_t *__restrict__ tflag,
                                                       const uint32_t *__restrict__ tpos) {
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= NC) return;
@@ -771,8 +802,8 @@ __global__ __launch_bounds__(kBlock) void k_out_table(int64_t NC, Boxes bx, cons
     const int box = box_of(bx, (uint32_t)nuc);
     const Geo &g = bx.geo[box];
     if (h_count[s] < (uint32_t)g.n_l1_min || !g.halos) return;
-    const uint32_t b0 = tpos[bx.base[box]];
-    if ((int64_t)(tpos[bx.base[box + 1]] - b0) > g.halo_cap) return;
+    const uint32_t b0 = table_pos(tflag, tpos, bx.base[box]);
+    if ((int64_t)(table_pos(tflag, tpos, bx.base[box + 1]) - b0) > g.halo_cap) return;
     float4 p = spos[nuc];
     uint32_t o = orig_of(p);
     const int32_t lo = (int32_t)(o - g.orig_base);
@@ -787,7 +818,7 @@ __global__ __launch_bounds__(kBlock) void k_out_table(int64_t NC, Boxes bx, cons
     h.z = p.z;
     h.r = (float)cbrt((double)h_ienc[s] / g.K);
     h.mass = (float)h_count[s] * g.particle_mass;
-    g.halos[tpos[o] - b0] = h;
+    g.halos[table_pos(tflag, tpos, o) - b0] = h;
 }
 
 // Only the halo labels to return: halo_id was filled with 0, and only the
@@ -835,29 +866,6 @@ __global__ __launch_bounds__(kBlock) void k_out_split(int64_t n, const uint4 *__
     halo_id[o] = (int32_t)r.z;
 }
 
-// Groups with candidates in descending size, for the acceptance kernels: keys
-// (~size, group) of the groups listed, padding keys sort last.
-__global__ __launch_bounds__(kBlock) void k_glist_keys(int64_t len, const uint32_t *__restrict__ ngc_p,
-                                                       const int32_t *__restrict__ glist,
-                                                       const int32_t *__restrict__ g_size,
-                                                       uint64_t *__restrict__ keys) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= len) return;
-    uint64_t k = ~0ull;
-    if (t < (int64_t)*ngc_p) {
-        const int gi = glist[t];
-        k = ((uint64_t)(0xffffffffu - (uint32_t)g_size[gi]) << 32) | (uint32_t)gi;
-    }
-    keys[t] = k;
-}
-
-__global__ __launch_bounds__(kBlock) void k_glist_from_keys(int64_t len, const uint32_t *__restrict__ ngc_p,
-                                                            const uint64_t *__restrict__ keys,
-                                                            int32_t *__restrict__ glist) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < len && t < (int64_t)*ngc_p) glist[t] = (int32_t)(keys[t] & 0xffffffffu);
-}
-
 // ------------------------------------------------------------ group order
 // Members collected into group order (Sec. 2.3.5): the particles sorted by the
 // table row of their halo (particles of no halo after the last row), ascending
@@ -870,12 +878,13 @@ __global__ __launch_bounds__(kBlock) void k_glist_from_keys(int64_t len, const u
 // nucleus to its table row.
 __global__ __launch_bounds__(kBlock) void k_order_keys(int64_t n, int64_t nrows,
                                                        const int32_t *__restrict__ halo_id,
+                                                       const uint32_t *__restrict__ tflag,
                                                        const uint32_t *__restrict__ tpos,
                                                        uint64_t *__restrict__ keys) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t h = halo_id[i];
-    const uint64_t row = h > 0 ? (uint64_t)tpos[h - 1] : (uint64_t)nrows;
+    const uint64_t row = h > 0 ? (uint64_t)table_pos(tflag, tpos, (uint32_t)(h - 1)) : (uint64_t)nrows;
     keys[i] = (row << 32) | (uint64_t)i;
 }
 
@@ -894,31 +903,34 @@ __global__ __launch_bounds__(kBlock) void k_order_out(int64_t n, int64_t nrows, 
 
 }  // namespace
 
-void launch_segment(int64_t n, Work &w, hipStream_t s) {
-    fill_u32(w.gcnt, 0u, n + 1, s);
-    hipLaunchKernelGGL(k_seg_count, grid(n), dim3(kBlock), 0, s, n, w.gkey, w.gcnt);
-    scan_u32(w.gcnt, w.goff, n, w.scan_tmp, s);
-    scan_nz_u32(w.gcnt, w.gidx, n, w.scan_tmp, s);  // group ordinal of every key
+void launch_segment_totals(int64_t n, Work &w, hipStream_t s) {
+    const int64_t tiles = scan_tiles(n);
+    uint32_t *msum = w.scan_tmp, *gsum = w.scan_tmp + tiles;
+    hipLaunchKernelGGL(k_seg_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum);
+    hipLaunchKernelGGL(k_seg_totals, dim3(1), dim3(kBlock), 0, s, tiles, msum, gsum, w.counters);
 }
 
-void launch_segment_groups(int64_t n, int64_t G, Work &w, hipStream_t s) {
-    hipLaunchKernelGGL(k_seg_groups, grid(n), dim3(kBlock), 0, s, n, w.gcnt, w.goff, w.gidx, w.g_start,
-                       w.g_size, w.g_label);
+void launch_segment(int64_t n, Work &w, hipStream_t s) {
+    const int64_t tiles = scan_tiles(n);
+    uint32_t *msum = w.scan_tmp, *gsum = w.scan_tmp + tiles;
+    hipLaunchKernelGGL(k_seg_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum);
+    const bool scanned = scan_sums(w.scan_tmp, tiles, tiles, 2, s);
+    // flags of the extent check in h_ienc (free until the acceptance fills it)
+    hipLaunchKernelGGL(k_seg_offsets, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum, scanned,
+                       w.goff, w.gidx, w.g_start, w.g_size, w.g_label, w.gccnt, w.gcfill, w.g_nh, w.h_ienc,
+                       w.tflag, candidates_clear(n, w), w.counters);
     hipLaunchKernelGGL(k_seg_scatter, grid(n), dim3(kBlock), 0, s, n, w.gkey, w.goff, w.gidx, w.gcnt,
                        w.mem, w.gid_of);
-    fill_u32(w.gccnt, 0u, G + 1, s);
-    fill_u32(w.gcfill, 0u, G + 1, s);
 }
 
-void launch_extent(int64_t G, int64_t M, const Boxes &bx, Work &w, hipStream_t s) {
-    if (M <= 0) return;
-    // flags per group in g_nh and the flagged groups in glist (both free until
-    // the candidate stage fills them), their count in counters[12]
-    fill_i32(w.g_nh, 0, G + 1, s);
-    hipLaunchKernelGGL(k_extent_far, grid(M), dim3(kBlock), 0, s, M, bx, w.mem, w.gid_of, w.g_start, w.spos,
-                       w.g_nh, w.glist, reinterpret_cast<uint32_t *>(w.counters + 12));
-    const int64_t blocks = G < 1024 ? G : 1024;
-    hipLaunchKernelGGL(k_extent_span, dim3((unsigned)blocks), dim3(kBlock), 0, s,
+void launch_extent(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
+    // flags per group in h_ienc (zeroed with the group table) and the flagged
+    // groups in glist (both free until the candidate stage), their count in
+    // counters[12]; member and group counts are read on the device
+    hipLaunchKernelGGL(k_extent_far, grid(n), dim3(kBlock), 0, s, w.counters + kCntMembers, bx, w.mem, w.gid_of,
+                       w.g_start, w.spos, w.h_ienc, w.glist, reinterpret_cast<uint32_t *>(w.counters + 12));
+    const int64_t blocks = n / 64 + 1;
+    hipLaunchKernelGGL(k_extent_span, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(kBlock), 0, s,
                        reinterpret_cast<const uint32_t *>(w.counters + 12), bx, w.glist, w.g_start, w.g_size,
                        w.mem, w.spos, w.err);
 }
@@ -927,32 +939,6 @@ static int bits_for(int64_t x) {
     int b = 1;
     while (b < 32 && (x >> b) != 0) b++;
     return b;
-}
-
-void launch_candidates_sort(int64_t n, int64_t G, int64_t NC, Work &w, hipStream_t s) {
-    // gcoff already holds the exclusive scan of gccnt
-    hipLaunchKernelGGL(k_cand_scatter, grid(n), dim3(kBlock), 0, s, n, w.owner, w.gid_of, w.gcoff,
-                       w.gcfill, w.cand);
-    if (NC > 0)
-        hipLaunchKernelGGL(k_cand_rank, grid(NC), dim3(kBlock), 0, s, NC, (int)G, w.gcoff, w.cand,
-                           w.dens_s, w.spos, w.cand_sorted);
-    scan_nz_u32(w.gccnt, w.gcidx, G, w.scan_tmp, s);  // ordinal of every group with candidates
-    if (G > 0)
-        hipLaunchKernelGGL(k_glist, grid(G), dim3(kBlock), 0, s, (int)G, w.gccnt, w.gcidx, w.glist);
-    // the groups with candidates (of every box) in descending size, so that the
-    // acceptance kernels start the longest walks first: a stable sort of
-    // (~size, group) on the size bits (sizes are below n); the radix key
-    // arrays are free at this point
-    const int64_t len = G < NC ? G : NC;
-    if (len > 1) {
-        hipLaunchKernelGGL(k_glist_keys, grid(len), dim3(kBlock), 0, s, len, w.gcidx + G, w.glist, w.g_size,
-                           w.rkey[0]);
-        const uint64_t *sorted = radix_sort_keys(w.rkey[0], w.rkey[1], len, 32, bits_for(n), w, s);
-        hipLaunchKernelGGL(k_glist_from_keys, grid(len), dim3(kBlock), 0, s, len, w.gcidx + G, sorted, w.glist);
-    }
-    fill_i32(w.h_nuc, -1, NC + 1, s);
-    fill_u32(w.h_count, 0u, NC + 1, s);
-    fill_i32(w.g_nh, 0, G + 1, s);
 }
 
 void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx, Work &w, hipStream_t s) {
@@ -976,7 +962,7 @@ void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx,
     const bool bins = w.radius_bins;
     // six wavefronts per SIMD (its register use): 6 workgroups of 4 per CU
     hipLaunchKernelGGL(k_accept_small, dim3(cap((bound + kBlock / 64 - 1) / (kBlock / 64), 6 * ncu)), dim3(kBlock),
-                       0, s, w.gcidx + G, bins, bx, w.glist, w.g_start, w.g_size, w.gcoff, w.cand_sorted,
+                       0, s, reinterpret_cast<const uint32_t *>(w.counters + kCntListed), bins, bx, w.glist, w.g_start, w.g_size, w.gcoff, w.cand_sorted,
                        w.mem, w.spos, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh, mid_list, mid_count, big_list, big_count);
     // with radial bins every group is listed: at most bound medium groups
     const int64_t nmid = bins ? bound : M / kWaveHist + NC / (kWaveNuc + 1) + 1;
@@ -1008,22 +994,22 @@ void launch_assign(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
 }
 
 void launch_output_flags(int64_t n, int64_t NC, const Boxes &bx, Work &w, hipStream_t s) {
-    fill_u32(w.tflag, 0u, n + 1, s);
+    // the table-row bits were zeroed with the group table
     if (NC > 0)
         // the candidates' member labels go to the hard-case list (free after
         // the candidate stage)
         hipLaunchKernelGGL(k_out_flags, grid(NC), dim3(kBlock), 0, s, NC, bx, w.h_nuc, w.h_count, w.spos,
                            w.tflag, w.hardlist, w.counters);
-    scan_u32(w.tflag, w.tpos, n, w.scan_tmp, s);
+    scan_bits_u32(w.tflag, w.tpos, n / 32 + 1, w.scan_tmp, s);
 }
 
 void launch_output(int64_t n, int64_t NC, const Boxes &bx, Work &w, int32_t *halo_id, int32_t *l0_out,
                    float *dens_out, int64_t *box_rows, hipStream_t s) {
     if (NC > 0)
         hipLaunchKernelGGL(k_out_table, grid(NC), dim3(kBlock), 0, s, NC, bx, w.h_nuc, w.h_ienc, w.h_gid,
-                           w.h_count, w.g_label, w.spos, w.tpos);
+                           w.h_count, w.g_label, w.spos, w.tflag, w.tpos);
     if (box_rows)
-        hipLaunchKernelGGL(k_box_rows, grid(bx.nbox), dim3(kBlock), 0, s, bx, w.tpos, box_rows);
+        hipLaunchKernelGGL(k_box_rows, grid(bx.nbox), dim3(kBlock), 0, s, bx, w.tflag, w.tpos, box_rows);
     if (!l0_out && !dens_out) {
         fill_i32(halo_id, 0, n, s);
         hipLaunchKernelGGL(k_out_particles, grid(n), dim3(kBlock), 0, s, n, w.owner, w.hardlist, w.spos,
@@ -1040,7 +1026,7 @@ void launch_output(int64_t n, int64_t NC, const Boxes &bx, Work &w, int32_t *hal
 void launch_group_order(int64_t n, int64_t nrows, const int32_t *halo_id, Work &w, int32_t *members,
                         int64_t *halo_start, hipStream_t s) {
     // the radix key arrays are free once the output is written
-    hipLaunchKernelGGL(k_order_keys, grid(n), dim3(kBlock), 0, s, n, nrows, halo_id, w.tpos, w.rkey[0]);
+    hipLaunchKernelGGL(k_order_keys, grid(n), dim3(kBlock), 0, s, n, nrows, halo_id, w.tflag, w.tpos, w.rkey[0]);
     const uint64_t *sorted = radix_sort_keys(w.rkey[0], w.rkey[1], n, 32, bits_for(nrows + 1), w, s);
     hipLaunchKernelGGL(k_order_out, grid(n + 1), dim3(kBlock), 0, s, n, nrows, sorted, members, halo_start);
 }

@@ -203,7 +203,8 @@ __device__ __forceinline__ void test_candidates(int32_t *parent, Hooks &h, const
 // of their sub-cell (a valid forest: every parent is a member with a smaller
 // or equal sorted index).  The first particle of every dense sub-cell also
 // records the sub-cell's first member (-1 if none) in submem, laid out like
-// the sub-cell table.
+// the sub-cell table.  The smallest index and the member count of every
+// particle's set start here too.
 __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, const float4 *__restrict__ sloc,
                                                         const uint32_t *__restrict__ f_sparse,
                                                         const uint16_t *__restrict__ ssub,
@@ -211,9 +212,13 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
                                                         const uint32_t *__restrict__ subtab,
                                                         const float *__restrict__ dens_s,
                                                         int32_t *__restrict__ parent,
-                                                        int32_t *__restrict__ submem) {
+                                                        int32_t *__restrict__ submem,
+                                                        int32_t *__restrict__ minorig,
+                                                        uint32_t *__restrict__ gcnt) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    minorig[i] = 0x7fffffff;
+    gcnt[i] = 0u;
     const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
     const bool mem = is_member(dens_s, i, g.dl0);
     if (f_sparse[i]) {
@@ -618,59 +623,70 @@ __global__ __launch_bounds__(kBlock) void k_fof_roots(int64_t n, const int32_t *
     if (r >= 0 && run.rank == 0) atomicMin(&minorig[r], m);
 }
 
+// One atomic per run of equal keys among consecutive lanes (every lane of the
+// wavefront takes part; key < 0: none).
+__device__ __forceinline__ void count_members(int key, uint32_t *__restrict__ gcnt) {
+    const WaveRun r = wave_run(key);
+    if (key >= 0 && r.rank == 0) atomicAdd(&gcnt[key], (uint32_t)r.len);
+}
+
 // Group key (smallest original index of the group, in the call's numbering)
-// per sorted particle, and the L0 label (box-local) in original order.  A key
-// outside [0, n) would be an internal error; it is flagged instead of being
-// used as an index.
+// per sorted particle, the members of every key counted, and the L0 label
+// (box-local) in original order.  A key outside [0, n) would be an internal
+// error; it is flagged instead of being used as an index.
 __global__ __launch_bounds__(kBlock) void k_fof_keys(int64_t n, Boxes bx, const int32_t *__restrict__ root,
                                                      const int32_t *__restrict__ minorig,
                                                      const float4 *__restrict__ spos,
                                                      int32_t *__restrict__ gkey,
+                                                     uint32_t *__restrict__ gcnt,
                                                      int32_t *__restrict__ l0_out,
                                                      int32_t *__restrict__ err) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int box = box_of(bx, (uint32_t)i);
-    const int r = root[i];
-    int k = r < 0 ? -1 : minorig[r];
-    if (k >= n) {
-        flag_error(err, 4, box);
-        k = -1;
+    int k = -1;
+    if (i < n) {
+        const int r = root[i];
+        k = r < 0 ? -1 : minorig[r];
+        if (k >= n) {
+            flag_error(err, 4, box_of(bx, (uint32_t)i));
+            k = -1;
+        }
+        gkey[i] = k;
+        if (l0_out)
+            l0_out[orig_of(spos[i])] = k < 0 ? 0 : k + 1 - (int)bx.geo[box_of(bx, (uint32_t)i)].orig_base;
     }
-    gkey[i] = k;
-    if (l0_out) l0_out[orig_of(spos[i])] = k < 0 ? 0 : k + 1 - (int)bx.geo[box].orig_base;
+    count_members(k, gcnt);
 }
 
-// Group keys from caller-provided labels (1..n, 0 = none), in sorted order,
-// and with dens_in the caller's densities gathered into sorted order too (one
-// pass over the sorted records for both).
 // Label and density of each particle side by side, in input order (one
 // coalesced pass), so that the gather into sorted order below reads one
-// 8-byte element per particle instead of two random 4-byte ones.
+// 8-byte element per particle instead of two random 4-byte ones.  The member
+// counts start here.
 __global__ __launch_bounds__(kBlock) void k_pack_labels(int64_t n, const int32_t *__restrict__ l0_in,
                                                         const float *__restrict__ dens_in,
-                                                        uint2 *__restrict__ packed) {
+                                                        uint2 *__restrict__ packed,
+                                                        uint32_t *__restrict__ gcnt) {
     const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (o >= n) return;
     packed[o] = make_uint2((uint32_t)l0_in[o], __float_as_uint(dens_in[o]));
+    gcnt[o] = 0u;
 }
 
+// Group keys from caller-provided labels (1..n, 0 = none) and the caller's
+// densities, in sorted order, and the members of every key counted.
 __global__ __launch_bounds__(kBlock) void k_keys_from_labels(int64_t n, Boxes bx,
-                                                             const int32_t *__restrict__ l0_in,
                                                              const uint2 *__restrict__ packed,
                                                              const float4 *__restrict__ spos,
                                                              int32_t *__restrict__ gkey,
                                                              float *__restrict__ dens_s,
+                                                             uint32_t *__restrict__ gcnt,
                                                              int32_t *__restrict__ err) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int box = box_of(bx, (uint32_t)i);
-    const Geo &g = bx.geo[box];
-    const uint32_t o = orig_of(spos[i]);
-    int32_t lab;
-    if (packed) {
-        const uint2 v = packed[o];
-        lab = (int32_t)v.x;
+    int key = -1;
+    if (i < n) {
+        const int box = box_of(bx, (uint32_t)i);
+        const Geo &g = bx.geo[box];
+        const uint2 v = packed[orig_of(spos[i])];
+        int32_t lab = (int32_t)v.x;
         // the candidate search orders densities by their bit patterns, which
         // matches their values for non-negative numbers only: -0 becomes +0
         // (the same value), NaN and negative values are rejected
@@ -680,15 +696,15 @@ __global__ __launch_bounds__(kBlock) void k_keys_from_labels(int64_t n, Boxes bx
             db = 0u;
         }
         dens_s[i] = __uint_as_float(db);
-    } else {
-        lab = l0_in[o];
+        // labels are box-local (1 .. box size, 0 = outside every group)
+        if (lab < 0 || (int64_t)lab > g.n) {
+            flag_error(err, 2, box);
+            lab = 0;
+        }
+        key = lab > 0 ? lab - 1 + (int32_t)g.orig_base : -1;
+        gkey[i] = key;
     }
-    // labels are box-local (1 .. box size, 0 = outside every group)
-    if (lab < 0 || (int64_t)lab > g.n) {
-        flag_error(err, 2, box);
-        lab = 0;
-    }
-    gkey[i] = lab > 0 ? lab - 1 + (int32_t)g.orig_base : -1;
+    count_members(key, gcnt);
 }
 
 }  // namespace
@@ -697,7 +713,7 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     // the first members of the dense sub-cells go to the sub-cell maxima's
     // argument table (free until the candidate stage)
     hipLaunchKernelGGL(k_fof_phase_a, grid(n), dim3(kBlock), 0, s, n, bx, w.sloc, w.f_sparse, w.ssub, w.cnt,
-                       w.subtab, w.dens_s, w.parent, w.subarg);
+                       w.subtab, w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt);
     if (w.nchunks > 0)
         // one wavefront per workgroup: chunk costs differ widely, and a
         // finished wavefront's slot is free at once
@@ -716,25 +732,21 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
                            w.hardlist, w.sloc, w.spos, w.off, w.dens_s, w.parent);
     }
     // roots go to the owner array (free until the assignment stage)
-    fill_i32(w.minorig, 0x7fffffff, n, s);
     hipLaunchKernelGGL(k_fof_roots, grid(n), dim3(kBlock), 0, s, n, w.parent, w.spos, w.owner, w.minorig);
 }
 
 void launch_fof_labels(int64_t n, const Boxes &bx, Work &w, int32_t *l0_out, hipStream_t s) {
     hipLaunchKernelGGL(k_fof_keys, grid(n), dim3(kBlock), 0, s, n, bx, w.owner, w.minorig, w.spos, w.gkey,
-                       l0_out, w.err);
+                       w.gcnt, l0_out, w.err);
 }
 
 void launch_keys_from_labels(const int32_t *l0_in, const float *dens_in, int64_t n, const Boxes &bx, Work &w,
                              hipStream_t s) {
     // the packed copy lives in the second radix key array (free after binning)
-    uint2 *packed = nullptr;
-    if (dens_in) {
-        packed = reinterpret_cast<uint2 *>(w.rkey[1]);
-        hipLaunchKernelGGL(k_pack_labels, grid(n), dim3(kBlock), 0, s, n, l0_in, dens_in, packed);
-    }
-    hipLaunchKernelGGL(k_keys_from_labels, grid(n), dim3(kBlock), 0, s, n, bx, l0_in, packed, w.spos, w.gkey,
-                       w.dens_s, w.err);
+    uint2 *packed = reinterpret_cast<uint2 *>(w.rkey[1]);
+    hipLaunchKernelGGL(k_pack_labels, grid(n), dim3(kBlock), 0, s, n, l0_in, dens_in, packed, w.gcnt);
+    hipLaunchKernelGGL(k_keys_from_labels, grid(n), dim3(kBlock), 0, s, n, bx, packed, w.spos, w.gkey, w.dens_s,
+                       w.gcnt, w.err);
 }
 
 }  // namespace hf

@@ -237,7 +237,6 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->gccnt = c.take<uint32_t>(n1);
     w->gcoff = c.take<uint32_t>(n1);
     w->gcfill = c.take<uint32_t>(n1);
-    w->gcidx = c.take<uint32_t>(n1);
     w->glist = c.take<int32_t>(n1);
     w->cand = c.take<int32_t>(n1);
     w->cand_sorted = c.take<int32_t>(n1);
@@ -467,6 +466,40 @@ float elapsed(hipEvent_t a, hipEvent_t b) {
     return ms;
 }
 
+// The candidate stage on the segmented groups.  The counts that size the later
+// launches and the error flags of the steps so far (the kernels before this
+// point clamp what they index, whatever the flags) are copied to the host while
+// the device goes on with the candidate lists.
+struct Counts {
+    int64_t groups = 0, candidates = 0;
+};
+
+hf_status candidates(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, Counts *ct, hipStream_t s) {
+    hf::launch_candidates(pl.n, bx, w, s);
+    hf::WordSrc src{};
+    const int32_t *words[] = {w.counters + hf::kCntGroups, w.counters + hf::kCntMembers,
+                              w.counters + hf::kCntCand, w.counters + hf::kCntHard, w.err, w.err + 1};
+    for (int k = 0; k < 6; k++) src.p[k] = reinterpret_cast<const uint32_t *>(words[k]);
+    HIP_OK(c, hf::publish_words(src, 6, c->host, s));
+    HIP_OK(c, hipEventRecord(c->pub, s));
+    hf::launch_candidate_lists(pl.n, w, s);
+    HIP_OK(c, hipEventSynchronize(c->pub));
+    uint32_t r[6];
+    hf::collect_words(c->host, 6, r);
+    const hf_status st = err_status(c, r[4], r[5], &pl);
+    if (st != HF_OK) {
+        // a failed call also ends synchronized with its stream
+        HIP_OK(c, hipStreamSynchronize(s));
+        return st;
+    }
+    ct->groups = r[0];
+    ct->candidates = r[2];
+    w.nhard = r[3];
+    c->stats.n_groups = r[0];
+    c->stats.n_members = r[1];
+    return HF_OK;
+}
+
 // CompaSO on the binned particles with group keys in w.gkey.  Fills halo_id,
 // l0_out and dens_out (either may be null; the densities from w.dens_s), every
 // box's table and its row count (n_halos, host,
@@ -481,28 +514,15 @@ hf_status run_compaso(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, int
                       int32_t *l0_out, float *dens_out, int64_t *n_halos, hipStream_t s,
                       const GroupOut &go = GroupOut{}) {
     const int64_t n = pl.n;
+    hf_status st = HF_OK;
     HIP_OK(c, hipEventRecord(c->ev[3], s));
     hf::launch_segment(n, w, s);
-    // group and member counts, and the error flags of the steps so far (the
-    // kernels before this point clamp what they index, whatever the flags)
-    uint32_t r[4];
-    hf_status st = read_dev(c, s, {w.gidx + n, w.goff + n, w.err, w.err + 1}, r);
-    if (st == HF_OK) st = err_status(c, r[2], r[3], &pl);
-    if (st != HF_OK) return st;
-    int64_t G = r[0];
-    c->stats.n_groups = G;
-    c->stats.n_members = r[1];
-    hf::launch_segment_groups(n, G, w, s);
-    hf::launch_extent(G, c->stats.n_members, bx, w, s);
+    hf::launch_extent(n, bx, w, s);
     HIP_OK(c, hipEventRecord(c->ev[4], s));
-    hf::launch_candidates(n, bx, w, s);
-    hf::scan_u32(w.gccnt, w.gcoff, G, w.scan_tmp, s);
-    uint32_t rc[2] = {0, 0};  // candidates, hard cases
-    st = read_dev(c, s, {w.gcoff + G, w.counters + 8}, rc);
+    Counts ct;
+    st = candidates(c, pl, bx, w, &ct, s);
     if (st != HF_OK) return st;
-    const int64_t NC = rc[0];
-    w.nhard = rc[1];
-    hf::launch_candidates_sort(n, G, NC, w, s);
+    const int64_t G = ct.groups, NC = ct.candidates;
     HIP_OK(c, hipEventRecord(c->ev[5], s));
     hf::launch_accept(n, G, NC, c->stats.n_members, bx, w, s);
     HIP_OK(c, hipEventRecord(c->ev[6], s));
@@ -933,9 +953,9 @@ hf_status hf_l0_fof(hf_ctx *ctx, const float *pos, const float *density, int64_t
     hf::launch_fof(n, bx, w, s);
     hf::launch_fof_labels(n, bx, w, l0_id, s);
     HIP_OK(c, hipEventRecord(c->ev[3], s));
-    hf::launch_segment(n, w, s);
+    hf::launch_segment_totals(n, w, s);
     uint32_t r[4] = {0, 0, 0, 0};
-    st = read_dev(c, s, {w.gidx + n, w.goff + n, w.err, w.err + 1}, r);
+    st = read_dev(c, s, {w.counters + hf::kCntGroups, w.counters + hf::kCntMembers, w.err, w.err + 1}, r);
     if (st == HF_OK) st = err_status(c, r[2], r[3], &pl);
     const uint32_t G32 = r[0], M32 = r[1];
     c->stats.ms_bin = elapsed(c->ev[0], c->ev[1]);
@@ -1019,22 +1039,15 @@ hf_status hf_halo_stats(hf_ctx *ctx, const float *pos, const float *density, con
     HIP_OK(c, hipEventRecord(c->ev[2], s));
     HIP_OK(c, hipEventRecord(c->ev[3], s));
     hf::launch_segment(n, w, s);
-    uint32_t r[4];
-    st = read_dev(c, s, {w.gidx + n, w.goff + n, w.err, w.err + 1}, r);
-    if (st == HF_OK) st = err_status(c, r[2], r[3], &pl);
-    if (st != HF_OK) return st;
-    const int64_t G = r[0], M = r[1];
-    if (G != n_halos) return fail(c, HF_ERR_INVALID, "n_halos differs from the number of halo_id labels");
-    c->stats.n_groups = G;
-    c->stats.n_members = M;
-    hf::launch_segment_groups(n, G, w, s);
     HIP_OK(c, hipEventRecord(c->ev[4], s));
-    hf::launch_candidates(n, bx2, w, s);
-    hf::scan_u32(w.gccnt, w.gcoff, G, w.scan_tmp, s);
-    uint32_t NC32 = 0;
-    st = read_dev(c, s, {w.gcoff + G}, &NC32);
+    Counts ct;
+    st = candidates(c, pl, bx2, w, &ct, s);
+    if (st == HF_OK && ct.groups != n_halos) {
+        HIP_OK(c, hipStreamSynchronize(s));
+        st = fail(c, HF_ERR_INVALID, "n_halos differs from the number of halo_id labels");
+    }
     if (st != HF_OK) return st;
-    hf::launch_candidates_sort(n, G, NC32, w, s);
+    const int64_t G = ct.groups, M = c->stats.n_members, NC32 = ct.candidates;
     HIP_OK(c, hipEventRecord(c->ev[5], s));
     hf::launch_accept(n, G, NC32, M, bx2, w, s);
     HIP_OK(c, hipEventRecord(c->ev[6], s));

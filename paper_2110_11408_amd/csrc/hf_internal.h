@@ -250,12 +250,13 @@ struct Work {
     uint32_t *gcnt, *goff, *gidx;                     // key space [0, n]
     int32_t *mem;                                     // members grouped by group
     int32_t *g_start, *g_size, *g_label;              // per group
-    uint32_t *gccnt, *gcoff, *gcfill, *gcidx;          // candidates per group
+    uint32_t *gccnt, *gcoff, *gcfill;                  // candidates per group
     int32_t *glist;                                    // groups with candidates
     int32_t *cand, *cand_sorted;                       // candidates
     int32_t *h_nuc, *h_ienc, *h_gid, *g_nh;            // halo slots (= candidate slots)
     uint32_t *h_count;
-    uint32_t *tflag, *tpos;                            // table rows (original index space)
+    uint32_t *tflag, *tpos;                            // table rows: a bit per original index, and the
+                                                       // prefix sum of the words' set bits
     uint32_t *hist;                                    // R search histograms
     uint32_t *scan_tmp;
     double *gcom;                    // halo statistics only: centres per group (6 doubles)
@@ -267,6 +268,22 @@ struct Work {
     int32_t *btab;                   // box of every 2^bshift-th particle (Boxes::btab)
     int64_t *box_rows;               // halo-table rows of every box
     uint32_t *host;                                    // the lane's pinned host words (read_words)
+};
+
+// Words of Work::counters that several stages use (zero when a call begins).
+enum {
+    kCntHard = 8,       // hard cases of the candidate stage
+    kCntListed = 10,    // groups with candidates in glist
+    kCntCand = 13,      // candidates
+    kCntMembers = 14,   // members of all groups
+    kCntGroups = 15     // groups
+};
+
+// Runs of words that the segmentation zeroes on its way for the stage after it.
+struct SegClear {
+    static constexpr int kRuns = 2;
+    uint32_t *p[kRuns];
+    int len[kRuns];
 };
 
 // ------------------------------------------------------------------ launchers
@@ -288,8 +305,8 @@ void fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 // Exclusive scan: out[0..n] with out[n] = total.  tmp: scan_tmp_words(n) words.
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
-// Exclusive scan of the indicator in[i] != 0 (same layout and tmp as scan_u32).
-void scan_nz_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
+// Exclusive scan of the number of set bits of every word (same layout and tmp).
+void scan_bits_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
 int64_t scan_tmp_words(int64_t n);
 
 // Every launcher works on all boxes of the call at once: n is the particle
@@ -314,15 +331,20 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s);
 void launch_fof_labels(int64_t n, const Boxes &bx, Work &w, int32_t *l0_out, hipStream_t s);
 void launch_keys_from_labels(const int32_t *l0_in, const float *dens_in, int64_t n, const Boxes &bx, Work &w,
                              hipStream_t s);
+// From the keys and the member counts per key: the members by group and the
+// group table; member and group counts go to w.counters.
 void launch_segment(int64_t n, Work &w, hipStream_t s);
-void launch_segment_groups(int64_t n, int64_t G, Work &w, hipStream_t s);
+// Only the member and group counts.
+void launch_segment_totals(int64_t n, Work &w, hipStream_t s);
+SegClear candidates_clear(int64_t n, const Work &w);  // candidates.hip
 // Extent check of the L0 groups (sets err bit 8 when a group spans half its
-// box or more along an axis); M members in G groups.
-void launch_extent(int64_t G, int64_t M, const Boxes &bx, Work &w, hipStream_t s);
-void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s);   // candidates.hip
-// Candidates in descending density per group; the groups with candidates in
-// descending size (the largest first, over all boxes).
-void launch_candidates_sort(int64_t n, int64_t G, int64_t NC, Work &w, hipStream_t s);
+// box or more along an axis).
+void launch_extent(int64_t n, const Boxes &bx, Work &w, hipStream_t s);
+// Candidates (counts per group, first slot of every group, total in
+// w.counters), then their slots in descending density per group and the groups
+// with candidates in descending size (the largest first, over all boxes).
+void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s);
+void launch_candidate_lists(int64_t n, Work &w, hipStream_t s);
 // Groups with candidates (their count is read on the device; grid bound
 // min(G, NC)); M = members of all groups, n = particles.
 void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx, Work &w, hipStream_t s);

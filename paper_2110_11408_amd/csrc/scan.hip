@@ -1,143 +1,93 @@
-// Device-wide exclusive prefix sum of uint32 arrays and fill kernels.
+// Device-wide exclusive prefix sums of uint32 arrays (scan_tile.h), fill kernels
+// and the read-back of device words.
 //
-// Three passes per level: tile sums (coalesced reads), a recursive scan of the
-// tile sums, and a tile scan staged through LDS that adds each tile's offset.
 // (A single pass with decoupled look-back was slower here: on this chip the
 // chain of status words between thousands of tiles goes through memory that
 // every XCD must see, a few microseconds per link.)
-// Tiles are 256 threads x 16 items; LDS indices are padded by one word per 32
-// to keep the per-thread runs of 16 words off a single bank.
 #include "hf_internal.h"
+#include "scan_tile.h"
 
 namespace hf {
 
 namespace {
 
-constexpr int kIpt = 16;
-constexpr int kTile = kBlock * kIpt;
+// What is scanned: the values, or the set bits of every word.
+template <bool kBits>
+__device__ __forceinline__ uint32_t scan_val(uint32_t x) { return kBits ? (uint32_t)__popc(x) : x; }
 
-__device__ __forceinline__ int pad(int i) { return i + (i >> 5); }
-
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
-// Exclusive scan of one value per thread across the 256-thread block; *total
-// receives the block sum.
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *total) {
-    __shared__ uint32_t wsum[kBlock / 64];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    uint32_t inc = wave_incl_scan(v);
-    if (lane == 63) wsum[wid] = inc;
-    __syncthreads();
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < kBlock / 64; k++) {
-        if (k < wid) pre += wsum[k];
-        tot += wsum[k];
-    }
-    __syncthreads();
-    *total = tot;
-    return pre + inc - v;
-}
-
-// Full tiles are moved as 16-byte vectors (in and out are 16-byte aligned:
-// arena arrays, and the tile-sum arrays below are padded to four words); the
-// last, partial tile word by word.
-// kNz: scan the indicator in[i] != 0 instead of the values.
-template <bool kNz>
-__device__ __forceinline__ uint32_t val(uint32_t x) { return kNz ? (x != 0u ? 1u : 0u) : x; }
-
-template <bool kNz>
+template <bool kBits>
 __global__ __launch_bounds__(kBlock) void k_tile_sums(const uint32_t *__restrict__ in, int64_t n,
                                                       uint32_t *__restrict__ sums) {
-    const int64_t base = (int64_t)blockIdx.x * kTile;
     uint32_t s = 0;
-    if (base + kTile <= n) {
-        const uint4 *p = reinterpret_cast<const uint4 *>(in + base);
-#pragma unroll
-        for (int k = 0; k < kIpt / 4; k++) {
-            const uint4 v = p[k * kBlock + threadIdx.x];
-            s += (val<kNz>(v.x) + val<kNz>(v.y)) + (val<kNz>(v.z) + val<kNz>(v.w));
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < kIpt; k++) {
-            const int64_t i = base + k * kBlock + threadIdx.x;
-            if (i < n) s += val<kNz>(in[i]);
-        }
-    }
-    uint32_t tot;
-    block_excl_scan(s, &tot);
+    tile_each(in, (int64_t)blockIdx.x * kScanTile, n, [&](uint32_t x) { s += scan_val<kBits>(x); });
+    const uint32_t tot = block_sum(s);
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-template <bool kNz>
+template <bool kBits>
 __global__ __launch_bounds__(kBlock) void k_tile_scan(const uint32_t *__restrict__ in,
                                                       uint32_t *__restrict__ out, int64_t n,
-                                                      const uint32_t *__restrict__ tile_off) {
-    __shared__ uint32_t buf[kTile + kTile / 32];
-    const int64_t base = (int64_t)blockIdx.x * kTile;
-    const bool full = base + kTile <= n;
-    if (full) {
-        const uint4 *p = reinterpret_cast<const uint4 *>(in + base);
-#pragma unroll
-        for (int k = 0; k < kIpt / 4; k++) {
-            const int q = k * kBlock + threadIdx.x;
-            const uint4 v = p[q];
-            buf[pad(4 * q + 0)] = val<kNz>(v.x);
-            buf[pad(4 * q + 1)] = val<kNz>(v.y);
-            buf[pad(4 * q + 2)] = val<kNz>(v.z);
-            buf[pad(4 * q + 3)] = val<kNz>(v.w);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < kIpt; k++) {
-            const int idx = k * kBlock + threadIdx.x;
-            const int64_t i = base + idx;
-            buf[pad(idx)] = i < n ? val<kNz>(in[i]) : 0u;
-        }
-    }
-    __syncthreads();
-    uint32_t v[kIpt];
+                                                      const uint32_t *__restrict__ sums, bool scanned) {
+    __shared__ uint32_t buf[kScanLds];
+    const int64_t base = (int64_t)blockIdx.x * kScanTile;
+    uint32_t v[kScanItems];
+    tile_load(in, base, n, buf, v, scan_val<kBits>);
     uint32_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kIpt; k++) {
-        v[k] = buf[pad(threadIdx.x * kIpt + k)];
-        s += v[k];
-    }
+    for (int k = 0; k < kScanItems; k++) s += v[k];
     uint32_t tot;
     uint32_t run = block_excl_scan(s, &tot);
-    const uint32_t toff = tile_off ? tile_off[blockIdx.x] : 0u;
+    const uint32_t toff = blockIdx.x > 0 ? tile_offset(sums, blockIdx.x, scanned) : 0u;
     run += toff;
 #pragma unroll
-    for (int k = 0; k < kIpt; k++) {
-        buf[pad(threadIdx.x * kIpt + k)] = run;
+    for (int k = 0; k < kScanItems; k++) {
+        buf[scan_pad(threadIdx.x * kScanItems + k)] = run;
         run += v[k];
     }
     __syncthreads();
-    if (full) {
+    if (base + kScanTile <= n) {
         uint4 *p = reinterpret_cast<uint4 *>(out + base);
 #pragma unroll
-        for (int k = 0; k < kIpt / 4; k++) {
+        for (int k = 0; k < kScanItems / 4; k++) {
             const int q = k * kBlock + threadIdx.x;
-            p[q] = make_uint4(buf[pad(4 * q + 0)], buf[pad(4 * q + 1)], buf[pad(4 * q + 2)], buf[pad(4 * q + 3)]);
+            p[q] = make_uint4(buf[scan_pad(4 * q + 0)], buf[scan_pad(4 * q + 1)], buf[scan_pad(4 * q + 2)],
+                              buf[scan_pad(4 * q + 3)]);
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < kIpt; k++) {
+        for (int k = 0; k < kScanItems; k++) {
             const int idx = k * kBlock + threadIdx.x;
             const int64_t i = base + idx;
-            if (i < n) out[i] = buf[pad(idx)];
+            if (i < n) out[i] = buf[scan_pad(idx)];
         }
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = toff + tot;
+}
+
+// Exclusive scan of `tiles` words in place by one workgroup (one array of
+// `stride` words per workgroup).
+constexpr int kSumsThreads = 1024;
+__global__ __launch_bounds__(kSumsThreads) void k_sums_scan(uint32_t *__restrict__ sums, int64_t tiles,
+                                                            int64_t stride) {
+    uint32_t *p = sums + (int64_t)blockIdx.x * stride;
+    uint32_t run = 0;
+    for (int64_t t0 = 0; t0 < tiles; t0 += kSumsThreads * kScanItems) {
+        const int64_t b = t0 + (int64_t)threadIdx.x * kScanItems;
+        uint32_t v[kScanItems], s = 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++) {
+            v[k] = b + k < tiles ? p[b + k] : 0u;
+            s += v[k];
+        }
+        uint32_t tot;
+        uint32_t at = run + block_excl_scan<kSumsThreads>(s, &tot);
+#pragma unroll
+        for (int k = 0; k < kScanItems; k++) {
+            if (b + k < tiles) p[b + k] = at;
+            at += v[k];
+        }
+        run += tot;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill_u32(uint32_t *p, uint32_t v, int64_t n) {
@@ -205,39 +155,31 @@ hipError_t read_words(const WordSrc &src, int k, uint32_t *host, uint32_t *out, 
     return hipSuccess;
 }
 
-// Words of one tile-sum array (tiles + 1), rounded up to keep 16-byte alignment.
-static int64_t sums_words(int64_t tiles) { return (tiles + 1 + 3) & ~(int64_t)3; }
-
-int64_t scan_tmp_words(int64_t n) {
-    int64_t w = 0;
-    while (n > kTile) {
-        int64_t t = (n + kTile - 1) / kTile;
-        w += 2 * sums_words(t);
-        n = t;
-    }
-    return w + 16;
+bool scan_sums(uint32_t *sums, int64_t tiles, int64_t stride, int arrays, hipStream_t s) {
+    if (tiles <= kDirectTiles) return false;
+    hipLaunchKernelGGL(k_sums_scan, dim3((unsigned)arrays), dim3(kSumsThreads), 0, s, sums, tiles, stride);
+    return true;
 }
 
-template <bool kNz>
-void scan_impl(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
-    int64_t tiles = (n + kTile - 1) / kTile;
-    if (tiles < 1) tiles = 1;
-    if (tiles == 1) {
-        hipLaunchKernelGGL(k_tile_scan<kNz>, dim3(1), dim3(kBlock), 0, s, in, out, n, nullptr);
-        return;
+// Two runs of tile sums (the segmentation scans two quantities at once).
+int64_t scan_tmp_words(int64_t n) { return 2 * scan_tiles(n) + 16; }
+
+template <bool kBits>
+static void scan_impl(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
+    const int64_t tiles = scan_tiles(n);
+    bool scanned = false;
+    if (tiles > 1) {
+        hipLaunchKernelGGL(k_tile_sums<kBits>, dim3(tiles), dim3(kBlock), 0, s, in, n, tmp);
+        scanned = scan_sums(tmp, tiles, tiles, 1, s);
     }
-    uint32_t *sums = tmp;
-    uint32_t *sums_scan = tmp + sums_words(tiles);
-    hipLaunchKernelGGL(k_tile_sums<kNz>, dim3(tiles), dim3(kBlock), 0, s, in, n, sums);
-    scan_impl<false>(sums, sums_scan, tiles, tmp + 2 * sums_words(tiles), s);
-    hipLaunchKernelGGL(k_tile_scan<kNz>, dim3(tiles), dim3(kBlock), 0, s, in, out, n, sums_scan);
+    hipLaunchKernelGGL(k_tile_scan<kBits>, dim3(tiles), dim3(kBlock), 0, s, in, out, n, tmp, scanned);
 }
 
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
     scan_impl<false>(in, out, n, tmp, s);
 }
 
-void scan_nz_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
+void scan_bits_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
     scan_impl<true>(in, out, n, tmp, s);
 }
 
