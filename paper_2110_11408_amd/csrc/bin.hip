@@ -414,7 +414,11 @@ __global__ __launch_bounds__(kBlock) void k_bin_lists(int64_t n, const uint32_t 
                                                       int32_t *__restrict__ chunks,
                                                       uint32_t *__restrict__ dcells,
                                                       int32_t *__restrict__ sparse,
-                                                      uint32_t *__restrict__ cellmap) {
+                                                      uint32_t *__restrict__ cellmap,
+                                                      uint32_t *__restrict__ zero, int nzero) {
+    // the counts of the next stage's segmented list start here
+    if (blockIdx.x == 0)
+        for (int t = threadIdx.x; t < nzero; t += kBlock) zero[t] = 0u;
     // kListIlp particles per thread (i0, i0 + kBlock, ...): their flags and
     // list positions loaded together, the positions whatever the flags (one
     // round of loads instead of two)
@@ -581,7 +585,7 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
     hipLaunchKernelGGL(k_bin_lists, dim3(blocks((n + kListIlp - 1) / kListIlp)), dim3(kBlock), 0, s, n, w.f_chunk,
                        w.s_chunk,
                        w.f_dcell, w.s_dcell, w.f_sparse, w.s_sparse, w.sloc, w.chunks, w.dcells,
-                       w.sparse, w.cnt);
+                       w.sparse, w.cnt, w.rhist, (int)(seg_list(n, w).nseg * kSegStride));
 }
 
 void launch_subtab(int64_t n, const uint32_t *ndc_p, const Boxes &bx, Work &w, hipStream_t s) {

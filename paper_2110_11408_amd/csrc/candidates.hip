@@ -132,19 +132,6 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
     }
 }
 
-// The hard cases of stage 1, listed on the device in nseg segments of `cap`
-// entries: workgroup b of the stage appends its cases to segment b mod nseg
-// with one atomic, so no address sees more than a 64th of the workgroups (a
-// count and list pass of its own over all particles took 60 us on the 256^3
-// box, and its read-back by the host another 25 us of an idle device).
-// Counters lie kSegStride words apart.
-constexpr uint32_t kSegs = 64, kSegStride = 16;
-struct HardList {
-    int32_t *list;
-    uint32_t *count;
-    uint32_t nseg, cap;
-};
-
 // Stage 1, one thread per particle: a member at or above the floor that is not
 // the densest particle of its sub-cell is decided at once when that densest
 // particle belongs to its group and lies within b (the usual case inside an L0
@@ -162,8 +149,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, cons
                                                        const int32_t *__restrict__ subarg,
                                                        const float *__restrict__ dens_s,
                                                        const int32_t *__restrict__ gkey,
-                                                       HardList hl) {
-    __shared__ uint32_t s_cnt[kBlock / 64], s_base;
+                                                       SegList hl) {
     const int64_t i = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     const int64_t ic = i < n ? i : n - 1;
     const Geo &g = bx.geo[box_of(bx, (uint32_t)ic)];
@@ -232,22 +218,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, cons
             }
         }
     }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t hm = __ballot(is_hard);
-    if (lane == 0) s_cnt[w] = (uint32_t)__popcll(hm);
-    __syncthreads();
-    const uint32_t seg = blockIdx.x % hl.nseg;
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int x = 0; x < kBlock / 64; x++) t += s_cnt[x];
-        s_base = t ? atomicAdd(hl.count + seg * kSegStride, t) : 0u;
-    }
-    __syncthreads();
-    if (is_hard) {
-        uint32_t at = s_base;
-        for (int x = 0; x < w; x++) at += s_cnt[x];
-        hl.list[(int64_t)seg * hl.cap + at + (uint32_t)__popcll(hm & ((1ull << lane) - 1ull))] = (int32_t)i;
-    }
+    seg_append(hl, is_hard, (int32_t)i);
 }
 
 // Stage 2, half a wavefront per hard case: whether a denser particle of the
@@ -266,8 +237,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, cons
 // own cell and then for the face neighbours (nine or more rounds per dense
 // cell, the chain of a wavefront its longest case's) took 146 us on a box of
 // 20 000 particles, 178 us on the 64^3 box and 455 us on the 256^3 one.
-// Workgroup c serves the segments that the workgroups of its own XCD filled.
-__global__ __launch_bounds__(kBlock) void k_cand_search(HardList hl, Boxes bx, const float4 *__restrict__ sloc,
+__global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, const float4 *__restrict__ sloc,
                                                         const float4 *__restrict__ spos,
                                                         const uint32_t *__restrict__ off,
                                                         const uint32_t *__restrict__ cellmap,
@@ -289,16 +259,11 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(HardList hl, Boxes bx, c
         for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
         if (threadIdx.x == 0) *nhard = t;
     }
-    const bool full = hl.nseg == kSegs;  // then the grid is a multiple of 8 workgroups
-    const uint32_t u = blockIdx.x * kHalves + (uint32_t)hw, nu = gridDim.x * kHalves;
-    const uint32_t seg = full ? (blockIdx.x & 7u) + 8u * (uint32_t)hw : u % hl.nseg;
-    const uint32_t step = nu / hl.nseg;
-    uint32_t k = full ? blockIdx.x >> 3 : u / hl.nseg;
-    if (k >= step) return;  // a surplus half of the last round of segments
-    const uint32_t cnt = hl.count[seg * kSegStride];
+    const SegShare sh = seg_share<32>(hl);
     const int tstride = bx.nsub_max + 1;
-    for (; k < cnt; k += step) {
-        const int i = hl.list[(int64_t)seg * hl.cap + k];
+    for (uint32_t k = sh.k; k < sh.n; k += sh.step) {
+        int32_t *const entry = hl.list + (int64_t)sh.seg * hl.cap + k;
+        const int i = *entry;
         const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
         const int key = gkey[i];
         const float di = dens_s[i];
@@ -410,7 +375,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(HardList hl, Boxes bx, c
         }
         if (!hballot(found) && ln == 0) {
             // a candidate: marked in the list, counted for its group
-            hl.list[(int64_t)seg * hl.cap + k] = ~i;
+            *entry = ~i;
             atomicAdd(&gccnt[gid_of[i]], 1u);
         }
     }
@@ -474,7 +439,7 @@ __global__ __launch_bounds__(kBlock) void k_gc_offsets(const uint32_t *__restric
 
 // The candidates of the hard-case list into their groups' slots (any order
 // inside a group), with the slots' halo records cleared.
-__global__ __launch_bounds__(kBlock) void k_cand_scatter(HardList hl, const int32_t *__restrict__ gid_of,
+__global__ __launch_bounds__(kBlock) void k_cand_scatter(SegList hl, const int32_t *__restrict__ gid_of,
                                                          const uint32_t *__restrict__ gcoff,
                                                          uint32_t *__restrict__ gcfill,
                                                          int32_t *__restrict__ cand,
@@ -558,27 +523,13 @@ __global__ __launch_bounds__(kBlock) void k_group_list(const uint32_t *__restric
     }
 }
 
-// The hard cases go to the chunk and dense-cell flag and scan arrays (4 n words
-// in one run, free at this stage; the segments hold at most 2 (n + 255) words,
-// and a single segment at most n), their counts to the radix counts (at least
-// n / 8 words, of which n / 16 + 16 are used).
-HardList hard_list(int64_t n, const Work &w) {
-    const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
-    HardList hl;
-    hl.list = reinterpret_cast<int32_t *>(w.f_chunk);
-    hl.count = w.rhist;
-    hl.nseg = nb < kSegs ? nb : kSegs;
-    hl.cap = (nb + hl.nseg - 1) / hl.nseg * kBlock;
-    return hl;
-}
-
 }  // namespace
 
 SegClear candidates_clear(int64_t n, const Work &w) {
     // the counts of the hard-case segments, and the class counts and fills of
     // the group list in the scanned radix counts (257 words at least)
     static_assert(2 * kClasses <= 257, "class counts fit the smallest radix count array");
-    return SegClear{{w.rhist, w.rscan}, {(int)(hard_list(n, w).nseg * kSegStride), 2 * kClasses}};
+    return SegClear{{w.rhist, w.rscan}, {(int)(seg_list(n, w).nseg * kSegStride), 2 * kClasses}};
 }
 
 void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
@@ -586,18 +537,14 @@ void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
         hipLaunchKernelGGL(k_submax_wave, dim3((unsigned)((w.ndcells + kBlock / 64 - 1) / (kBlock / 64))),
                            dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.ssub, w.dens_s, w.spos, w.submax,
                            w.subarg);
-    const HardList hl = hard_list(n, w);
+    const SegList hl = seg_list(n, w);
     hipLaunchKernelGGL(k_cand_quick, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, bx, w.sloc,
                        w.spos, w.f_sparse, w.ssub, w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, hl);
     // half-wavefronts striding over the segments: as many as fit the chip (six
     // wavefronts per SIMD at 79 VGPRs), and no more than one per four particles
     // (one particle in thirty is a hard case); their total goes to a counter
-    const int64_t fit = 6 * (int64_t)(w.ncu > 0 ? w.ncu : 1);
-    int64_t blocks = (n / 4 + kBlock / 32 - 1) / (kBlock / 32);
-    if (blocks > fit) blocks = fit;
-    if (blocks < 8) blocks = 8;
-    blocks = (blocks + 7) & ~(int64_t)7;
-    hipLaunchKernelGGL(k_cand_search, dim3((unsigned)blocks), dim3(kBlock), 0, s, hl, bx, w.sloc, w.spos, w.off,
+    const unsigned blocks = seg_blocks(hl, n, 32, 4, 6 * (int64_t)(w.ncu > 0 ? w.ncu : 1));
+    hipLaunchKernelGGL(k_cand_search, dim3(blocks), dim3(kBlock), 0, s, hl, bx, w.sloc, w.spos, w.off,
                        w.cnt, w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of, w.gccnt,
                        w.counters + kCntHard);
     const int64_t tiles = scan_tiles(n);  // of the groups: at most one per particle
@@ -610,7 +557,7 @@ void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
 
 void launch_candidate_lists(int64_t n, Work &w, hipStream_t s) {
     // grids that stride over counts known on the device
-    const HardList hl = hard_list(n, w);
+    const SegList hl = seg_list(n, w);
     auto cap = [](int64_t want, int64_t most) { return (unsigned)(want < most ? want : most); };
     const unsigned per = cap((int64_t)hl.cap / (16 * kBlock) + 1, 16);
     hipLaunchKernelGGL(k_cand_scatter, dim3(hl.nseg * per), dim3(kBlock), 0, s, hl, w.gid_of, w.gcoff, w.gcfill,

@@ -6,13 +6,17 @@
 //   phase A  a sub-cell's diagonal is below l, so all members of a sub-cell are
 //            friends: in dense cells every member points at the first member of
 //            its sub-cell;
+//   cells    a head start for the dense cells: sub-cells next to each other
+//            whose first members are friends are joined, inside a cell without
+//            atomics, then across cell faces, edges and corners; a cell whose
+//            members are all in one set then carries that set's root;
 //   dense    one wavefront per dense chunk gathers the neighbour members within
 //            reach 64 at a time and tests them against its lanes (FP32
 //            prefilter on the cell-local coordinates, canonical FP64 distance
 //            for the undecided band); it joins sets in its own view of the
 //            forest and applies the resulting hooks in bulk;
-//   sparse   members of sparse cells link to the later members of sparse
-//            neighbour cells;
+//   sparse   members of sparse cells link to the members of sparse neighbour
+//            cells in the forward half of the stencil;
 //   labels   compression, then 1 + the smallest ORIGINAL index of each set.
 // Hooks always attach the larger root under the smaller one, so the sets, and
 // therefore the labels, do not depend on thread scheduling.
@@ -204,7 +208,8 @@ __device__ __forceinline__ void test_candidates(int32_t *parent, Hooks &h, const
 // or equal sorted index).  The first particle of every dense sub-cell also
 // records the sub-cell's first member (-1 if none) in submem, laid out like
 // the sub-cell table.  The smallest index and the member count of every
-// particle's set start here too.
+// particle's set start here too, and the members of sparse cells (about one in
+// ten of their particles) are listed.
 __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, const float4 *__restrict__ sloc,
                                                         const uint32_t *__restrict__ f_sparse,
                                                         const uint16_t *__restrict__ ssub,
@@ -214,14 +219,17 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
                                                         int32_t *__restrict__ parent,
                                                         int32_t *__restrict__ submem,
                                                         int32_t *__restrict__ minorig,
-                                                        uint32_t *__restrict__ gcnt) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+                                                        uint32_t *__restrict__ gcnt, SegList sl) {
+    const int64_t i = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
+    const bool in = i < n;
+    const Geo &g = bx.geo[in ? box_of(bx, (uint32_t)i) : 0];
+    const bool mem = in && is_member(dens_s, i, g.dl0);
+    const bool sp = in && f_sparse[i] != 0u;
+    seg_append(sl, sp && mem, (int32_t)i);
+    if (!in) return;
     minorig[i] = 0x7fffffff;
     gcnt[i] = 0u;
-    const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
-    const bool mem = is_member(dens_s, i, g.dl0);
-    if (f_sparse[i]) {
+    if (sp) {
         parent[i] = mem ? (int32_t)i : -1;
         return;
     }
@@ -243,6 +251,167 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
     }
 }
 
+// ------------------------------------------------------------ dense cells
+// The chunk kernel below starts from a forest in which every sub-cell is a set
+// of its own, and all chunks run at once: on a small box each of them tested
+// its whole neighbourhood before another one's joins could save it the work
+// (99 us on the 64^3 box, the longest chunk's chain), and on a large one two
+// thirds of the tests joined what a neighbour had joined meanwhile (1.72 ms on
+// the 256^3 box, 22.4 ms on the 512^3 one).  Three short kernels make the links that cost next to nothing to find: between
+// the first members of sub-cells that touch.
+
+// The first member of the sub-cell in this row of the table, -1 for none
+// (phase A writes submem for sub-cells that hold particles only).
+__device__ __forceinline__ int32_t sub_first(const uint32_t *__restrict__ subtab,
+                                             const int32_t *__restrict__ submem, int64_t row) {
+    const uint32_t u0 = subtab[row], u1 = subtab[row + 1];
+    const int32_t f = submem[row];
+    return u1 > u0 ? f : -1;
+}
+
+// Inside a cell, half a wavefront per cell, a lane per sub-cell: every sub-cell
+// is attached to the first of the sub-cells before it that touch it and whose
+// first member is a friend of its own (13 offsets).  Parents come earlier in
+// the order, so this is a forest, and nothing else touches the roots of this
+// cell's sub-cells yet: plain stores.  Sub-cells of one set may be left in two
+// trees here, which the later kernels join.  (Exact components by a search on
+// 64-bit link masks, a wavefront per cell, took 234 us on the 256^3 box, bound
+// by the scalar unit.)
+constexpr int kHalves = kBlock / 32;
+__global__ __launch_bounds__(kBlock) void k_fof_cells(int64_t ndc, Boxes bx,
+                                                      const uint32_t *__restrict__ dcells,
+                                                      const uint32_t *__restrict__ off,
+                                                      const float4 *__restrict__ sloc,
+                                                      const uint32_t *__restrict__ subtab,
+                                                      const int32_t *__restrict__ submem,
+                                                      int32_t *__restrict__ parent) {
+    extern __shared__ float4 s_first[];  // [kHalves][nsub_max]: first member's position, its index in w
+    const int hw = threadIdx.x >> 5, ln = threadIdx.x & 31;
+    const int64_t d = (int64_t)xcd_block() * kHalves + hw;
+    if (d >= ndc) return;
+    float4 *sp = s_first + hw * bx.nsub_max;
+    const Geo &g = bx.geo[box_of(bx, off[dcells[d]])];
+    const int k = g.ksub, nsub = g.nsub;
+    const int64_t row = d * (bx.nsub_max + 1);
+    for (int s = ln; s < nsub; s += 32) {
+        const int32_t fm = sub_first(subtab, submem, row + s);
+        float4 p = make_float4(1e8f, 0.0f, 0.0f, 0.0f);  // empty: far from everything
+        if (fm >= 0) p = sloc[fm];
+        p.w = __int_as_float(fm);
+        sp[s] = p;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    const float inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)(k * k);
+    for (int s = ln; s < nsub; s += 32) {
+        const float4 p = sp[s];
+        const int32_t fm = __float_as_int(p.w);
+        if (fm < 0) continue;
+        const int sz = div_small(s, inv_k2), syx = s - sz * k * k, sy = div_small(syx, inv_k), sx = syx - sy * k;
+        int32_t to = fm;
+#pragma unroll
+        for (int e = 0; e < 13; e++) {
+            // backward offsets: stencil indices 0..12
+            const int dx = e % 3 - 1, dy = (e / 3) % 3 - 1, dz = e / 9 - 1;
+            const bool ok = sx + dx >= 0 && sx + dx < k && sy + dy >= 0 && sy + dy < k && sz + dz >= 0;
+            const float4 q = sp[ok ? s + (dz * k + dy) * k + dx : s];
+            if (ok && d2_f32(q.x - p.x, q.y - p.y, q.z - p.z) < g.l2b_lo) to = min(to, __float_as_int(q.w));
+        }
+        if (to != fm) parent[fm] = to;
+    }
+}
+
+// Across cells, half a wavefront per cell: the pairs of sub-cells that touch
+// through the cell's three forward faces, one per lane (27 for k = 3).  Of the
+// pairs that would join the same two sets one lane joins them.
+__global__ __launch_bounds__(kBlock) void k_fof_faces(int64_t ndc, Boxes bx,
+                                                      const uint32_t *__restrict__ dcells,
+                                                      const uint32_t *__restrict__ off,
+                                                      const uint32_t *__restrict__ cellmap,
+                                                      const float4 *__restrict__ sloc,
+                                                      const uint32_t *__restrict__ subtab,
+                                                      const int32_t *__restrict__ submem,
+                                                      int32_t *parent) {
+    const int hw = threadIdx.x >> 5, ln = threadIdx.x & 31, hsh = threadIdx.x & 32;
+    const int64_t d = (int64_t)xcd_block() * kHalves + hw;
+    if (d >= ndc) return;
+    auto hballot = [&](bool p) { return (uint32_t)(__ballot(p) >> hsh); };
+    const uint32_t c = dcells[d];
+    const Geo &g = bx.geo[box_of(bx, off[c])];
+    const int k = g.ksub, k2 = k * k, tstride = bx.nsub_max + 1;
+    const float inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)k2;
+    int cx, cy, cz;
+    cell_xyz(g, c, cx, cy, cz);
+    for (int t0 = 0; t0 < 3 * k2; t0 += 32) {
+        const int t = t0 + ln;
+        int32_t r1 = -1, r2 = -1;
+        if (t < 3 * k2) {
+            const int ax = div_small(t, inv_k2), r = t - ax * k2, v = div_small(r, inv_k), u = r - v * k;
+            const uint32_t nb = cell_id(g, cx + (ax == 0), cy + (ax == 1), cz + (ax == 2));
+            const uint32_t na = off[nb], ne = off[nb + 1];
+            if (ne - na >= (uint32_t)kDenseMin) {
+                // the last layer of sub-cells here, the first one there
+                const int st = ax == 0 ? 1 : (ax == 1 ? k : k2);
+                const int s2 = ax == 0 ? v * k2 + u * k : (ax == 1 ? v * k2 + u : v * k + u);
+                const int32_t f1 = sub_first(subtab, submem, d * tstride + s2 + (k - 1) * st);
+                const int32_t f2 = sub_first(subtab, submem, (int64_t)cellmap[nb] * tstride + s2);
+                if (f1 >= 0 && f2 >= 0) {
+                    const float4 p = sloc[f1], q = sloc[f2];
+                    const float dx = q.x + (ax == 0 ? g.cellb : 0.0f) - p.x,
+                                dy = q.y + (ax == 1 ? g.cellb : 0.0f) - p.y,
+                                dz = q.z + (ax == 2 ? g.cellb : 0.0f) - p.z;
+                    if (d2_f32(dx, dy, dz) < g.l2b_lo) {
+                        r1 = uf_find_hint(parent, f1);
+                        r2 = uf_find_hint(parent, f2);
+                    }
+                }
+            }
+        }
+        bool join = false;
+        for (uint32_t m = hballot(r1 != r2); m;) {
+            const int L = __ffs(m) - 1;
+            const int x = __shfl(r1, L, 32), y = __shfl(r2, L, 32);
+            if (ln == L) join = true;
+            m &= ~hballot(r1 == x && r2 == y);
+        }
+        if (join) uf_unite(parent, r1, r2);
+    }
+}
+
+// The first members' roots, stored as their parents (the forest does not
+// change here), and per cell, in entry nsub_max of its row: the root when all
+// its members are in one set, -1 when they are not, -2 when it has none.
+__global__ __launch_bounds__(kBlock) void k_fof_cell_roots(int64_t ndc, Boxes bx,
+                                                           const uint32_t *__restrict__ dcells,
+                                                           const uint32_t *__restrict__ off,
+                                                           const uint32_t *__restrict__ subtab,
+                                                           int32_t *__restrict__ submem, int32_t *parent) {
+    const int hw = threadIdx.x >> 5, ln = threadIdx.x & 31, hsh = threadIdx.x & 32;
+    const int64_t d = (int64_t)xcd_block() * kHalves + hw;
+    if (d >= ndc) return;
+    const int nsub = bx.geo[box_of(bx, off[dcells[d]])].nsub;
+    const int64_t row = d * (bx.nsub_max + 1);
+    int32_t one = -2;
+    for (int s0 = 0; s0 < nsub; s0 += 32) {
+        const int32_t fm = s0 + ln < nsub ? sub_first(subtab, submem, row + s0 + ln) : -1;
+        int32_t r = -1;
+        if (fm >= 0) {
+            r = fm;
+            for (int p = ld(parent + r); p != r; p = ld(parent + r)) r = p;
+            st(parent + fm, r);
+        }
+        const uint32_t m = (uint32_t)(__ballot(fm >= 0) >> hsh);
+        if (!m) continue;
+        const int32_t f = __shfl(r, __ffs(m) - 1, 32);
+        const bool split = (uint32_t)(__ballot(fm >= 0 && r != f) >> hsh) != 0u;
+        one = split || (one != -2 && one != f) ? -1 : f;
+    }
+    if (ln == 0) submem[row + bx.nsub_max] = one;
+}
+
+// Sub-cells examined at a time by the dense kernel.
+constexpr int kTaskTile = 384;
+
 // Dense chunks, one wavefront each (lanes = the chunk's particles).  The wave
 // visits the neighbour cells that come within l of some lane: sparse cells in
 // all 26 directions, dense cells only in the forward half (the backward ones
@@ -255,12 +424,21 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
 // sub-cells and at the end (root hints read meanwhile are moved through the
 // queued hooks):
 //   sparse cells  all their particles, each member with its root;
-//   dense cells   their sub-cells, 64 at a time (one per lane): range, first
-//                 member (recorded by phase A) and that member's root.  A
-//                 sub-cell already in the set of every lane is passed over
-//                 (its members are one set); the particles of the others are
-//                 gathered in lane order.
-__global__ __launch_bounds__(kBlock, 8) void k_fof_dense(int64_t nchunks, Boxes bx,
+//   dense cells   their sub-cells, kTaskTile at a time: range and first member
+//                 (recorded by phase A); those with members within reach are
+//                 listed in LDS and taken 64 at a time (one per lane) with
+//                 that member's root.  A sub-cell already in the set of every
+//                 lane is passed over (its members are one set); the
+//                 particles of the others are gathered in lane order.  (Most
+//                 of the up to 378 sub-cells are empty or out of reach: taken
+//                 64 at a time unlisted, each round refreshed the forest and
+//                 the roots for a few of them.)
+// A dense cell that carries the root common to all lanes has nothing to join
+// and is not visited.
+// With nparts = 2 a chunk is two wavefronts, one for the sparse cells and one
+// for the dense ones: for inputs whose chunks do not fill the chip, where the
+// longest chain is the time.
+__global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts, Boxes bx,
                                                       const int32_t *__restrict__ chunks,
                                                       const float4 *__restrict__ sloc,
                                                       const float4 *__restrict__ spos,
@@ -270,11 +448,15 @@ __global__ __launch_bounds__(kBlock, 8) void k_fof_dense(int64_t nchunks, Boxes 
                                                       const int32_t *__restrict__ submem,
                                                       const float *__restrict__ dens_s,
                                                       int32_t *parent) {
-    __shared__ int64_t dbase[kBlock / 64][27];  // visited dense cells: sub-table base
-    __shared__ int8_t doff[kBlock / 64][27];    // and stencil index
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t q = (int64_t)xcd_block() * (int64_t)(blockDim.x >> 6) + wave;
+    __shared__ int64_t dbase[27];  // visited dense cells: sub-table base
+    __shared__ int8_t doff[27];    // and stencil index
+    __shared__ int32_t s_fs[kTaskTile];   // sub-cells to look at: first member to gather,
+    __shared__ uint32_t s_u1[kTaskTile];  // end,
+    __shared__ int8_t s_st[kTaskTile];    // stencil index
+    const unsigned wq = xcd_block();
+    const int64_t q = nparts == 2 ? wq >> 1 : wq;
     if (q >= nchunks) return;
+    const bool do_sparse = nparts != 2 || (wq & 1u) == 0u, do_dense = nparts != 2 || (wq & 1u) != 0u;
     const int lane = threadIdx.x & 63;
     const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane(chunks[q]);
     const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, h))];
@@ -325,12 +507,20 @@ __global__ __launch_bounds__(kBlock, 8) void k_fof_dense(int64_t nchunks, Boxes 
     }
     const bool ldense = lb - la >= (uint32_t)kDenseMin;
     const bool lforward = lz > 0 || (lz == 0 && (ly > 0 || (ly == 0 && lx >= 0)));  // own cell included
-    const bool lvisit = lreach && ldense && lforward;
+    const int wfirst = lane_get(wr, (int)__builtin_ctzll(__ballot(active)));
+    const bool wsame = !__ballot(active && wr != wfirst);
+    bool lvisit = do_dense && lreach && ldense && lforward;
+    int64_t lbase = 0;
+    if (lvisit) {
+        lbase = (int64_t)cellmap[nbl] * tstride;
+        const int32_t cr = submem[lbase + bx.nsub_max];
+        lvisit = cr != -2 && !(wsame && cr == wfirst);
+    }
     if (lvisit) {
         const uint64_t vm = __ballot(lvisit);
         const int slot = __popcll(vm & ((1ull << lane) - 1ull));
-        dbase[wave][slot] = (int64_t)cellmap[nbl] * tstride;
-        doff[wave][slot] = (int8_t)lane;
+        dbase[slot] = lbase;
+        doff[slot] = (int8_t)lane;
     }
     const int nvisit = __popcll(__ballot(lvisit));
     Hooks hk;
@@ -339,7 +529,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_fof_dense(int64_t nchunks, Boxes 
     // the cell sizes; lane p finds the cell of particle p by one walk over the
     // cells that hold particles (their starts are scalars)
     {
-        const int cntl = lreach && !ldense ? (int)(lb - la) : 0;
+        const int cntl = do_sparse && lreach && !ldense ? (int)(lb - la) : 0;
         int incl = cntl;
         for (int d = 1; d < 64; d <<= 1) {
             const int y = __shfl_up(incl, d, 64);
@@ -378,49 +568,80 @@ __global__ __launch_bounds__(kBlock, 8) void k_fof_dense(int64_t nchunks, Boxes 
         const int a0 = (int)__builtin_ctzll(__ballot(active));
         const int ntask = nvisit * nsub;
         const float inv_nsub = 1.0f / (float)nsub, inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)(k * k);
-        // (visited dense cell, sub-cell) pairs, 64 at a time
-        for (int t0 = 0; t0 < ntask; t0 += 64) {
+        for (int tb = 0; tb < ntask; tb += kTaskTile) {
+        int listed = 0;
+        constexpr int kTb = 3;  // 64-task rounds whose loads are issued together
+        for (int r0 = tb; r0 < tb + kTaskTile && r0 < ntask; r0 += 64 * kTb) {
+            uint32_t u0[kTb], u1[kTb];
+            int32_t fm[kTb];
+            int stv[kTb], sl[kTb];
+#pragma unroll
+            for (int r = 0; r < kTb; r++) {
+                const int tq = r0 + 64 * r + lane;
+                u0[r] = u1[r] = 0u;
+                fm[r] = -1;
+                stv[r] = sl[r] = 0;
+                if (tq < ntask) {
+                    const int cell = div_small(tq, inv_nsub);
+                    sl[r] = tq - cell * nsub;
+                    stv[r] = doff[cell];
+                    const int64_t row = dbase[cell] + sl[r];
+                    u0[r] = subtab[row];
+                    u1[r] = subtab[row + 1];
+                    fm[r] = submem[row];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kTb; r++) {
+                int fs = -1;
+                if (u1[r] > u0[r]) {
+                    const bool cut = stv[r] == 13 && u0[r] < h;  // own cell: from the chunk start on
+                    const int ox = stv[r] % 3 - 1, oy = (stv[r] / 3) % 3 - 1, oz = stv[r] / 9 - 1;
+                    const int sz = div_small(sl[r], inv_k2), syx = sl[r] - sz * k * k, sy = div_small(syx, inv_k),
+                              sx = syx - sy * k;
+                    // sub-cell box (neighbour frame) shifted into the chunk's frame
+                    const float ex = fmaxf(fmaxf(sx * subb + (float)ox * g.cellb - bx1,
+                                                 bx0 - ((sx + 1) * subb + (float)ox * g.cellb)), 0.0f);
+                    const float ey = fmaxf(fmaxf(sy * subb + (float)oy * g.cellb - by1,
+                                                 by0 - ((sy + 1) * subb + (float)oy * g.cellb)), 0.0f);
+                    const float ez = fmaxf(fmaxf(sz * subb + (float)oz * g.cellb - bz1,
+                                                 bz0 - ((sz + 1) * subb + (float)oz * g.cellb)), 0.0f);
+                    if (ex * ex + ey * ey + ez * ez < g.l2b_hi + 1e-4f) {
+                        // first member: recorded by phase A, searched where the
+                        // own cell's sub-cell is cut at the chunk start
+                        if (!cut) {
+                            fs = fm[r];
+                        } else {
+                            for (uint32_t j = h; j < u1[r]; j++)
+                                if (is_member(dens_s, j, g.dl0)) {
+                                    fs = (int)j;
+                                    break;
+                                }
+                        }
+                    }
+                }
+                const uint64_t km = __ballot(fs >= 0);
+                if (fs >= 0) {
+                    const int at = listed + __popcll(km & ((1ull << lane) - 1ull));
+                    s_fs[at] = fs;
+                    s_u1[at] = u1[r];
+                    s_st[at] = (int8_t)stv[r];
+                }
+                listed += __popcll(km);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        // the listed sub-cells, 64 at a time
+        for (int t0 = 0; t0 < listed; t0 += 64) {
             // the forest learns this chunk's joins so far, the lanes their
             // current roots (a sub-cell joined meanwhile, by any chunk, is
             // then passed over)
             hooks_apply(parent, hk);
             if (active) wr = uf_find_hint(parent, wr);
-            const int tq = t0 + lane;
-            uint32_t u1 = 0;
-            int fs = -1, st = 0;
-            if (tq < ntask) {
-                const int r = div_small(tq, inv_nsub), sl = tq - r * nsub;
-                st = doff[wave][r];
-                const int64_t base = dbase[wave][r];
-                const int ox = st % 3 - 1, oy = (st / 3) % 3 - 1, oz = st / 9 - 1;
-                uint32_t u0 = subtab[base + sl];
-                u1 = subtab[base + sl + 1];
-                const int32_t fm = submem[base + sl];
-                const bool cut = st == 13 && u0 < h;
-                if (cut) u0 = h;  // own cell: from the chunk start on
-                const int sz = div_small(sl, inv_k2), syx = sl - sz * k * k, sy = div_small(syx, inv_k),
-                          sx = syx - sy * k;
-                // sub-cell box (neighbour frame) shifted into the chunk's frame
-                const float ex = fmaxf(fmaxf(sx * subb + (float)ox * g.cellb - bx1,
-                                             bx0 - ((sx + 1) * subb + (float)ox * g.cellb)), 0.0f);
-                const float ey = fmaxf(fmaxf(sy * subb + (float)oy * g.cellb - by1,
-                                             by0 - ((sy + 1) * subb + (float)oy * g.cellb)), 0.0f);
-                const float ez = fmaxf(fmaxf(sz * subb + (float)oz * g.cellb - bz1,
-                                             bz0 - ((sz + 1) * subb + (float)oz * g.cellb)), 0.0f);
-                if (ex * ex + ey * ey + ez * ez < g.l2b_hi + 1e-4f && u1 > u0) {
-                    // first member: recorded by phase A, searched where the
-                    // own cell's sub-cell is cut at the chunk start
-                    if (!cut) {
-                        fs = fm;
-                    } else {
-                        for (uint32_t j = u0; j < u1; j++)
-                            if (is_member(dens_s, j, g.dl0)) {
-                                fs = (int)j;
-                                break;
-                            }
-                    }
-                }
-            }
+            const bool has = t0 + lane < listed;
+            const int fs = has ? s_fs[t0 + lane] : -1, st = has ? (int)s_st[t0 + lane] : 0;
+            const uint32_t u1 = has ? s_u1[t0 + lane] : 0u;
             int rt = fs >= 0 ? hooks_map(hk, uf_find_hint(parent, fs)) : -1;
             uint32_t pos = fs >= 0 ? (uint32_t)fs : 0u;  // next particle of the sub-cell to gather
             for (int gr = 0;; gr++) {
@@ -474,128 +695,105 @@ __global__ __launch_bounds__(kBlock, 8) void k_fof_dense(int64_t nchunks, Boxes 
                 test_candidates(parent, hk, spos, g, active, li, h, wr, cmem, qx, qy, qz, jt, rc, rt);
             }
         }
+        __builtin_amdgcn_wave_barrier();
+        }
     }
     hooks_apply(parent, hk);
 }
 
-// Members among the sparse-cell particles (about one in ten), compacted so
-// that the linking kernel runs without idle lanes.
-__global__ __launch_bounds__(kBlock) void k_fof_sparse_flags(int64_t nsparse, Boxes bx,
-                                                             const int32_t *__restrict__ sparse,
-                                                             const float *__restrict__ dens_s,
-                                                             uint32_t *__restrict__ flag) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nsparse) return;
-    const int i = sparse[t];
-    flag[t] = is_member(dens_s, i, bx.geo[box_of(bx, (uint32_t)i)].dl0) ? 1u : 0u;
-}
-
-// Four entries per thread (t0, t0 + kBlock, ...), their flags loaded
-// together (the kernel streams the flags).
-constexpr int kSparseListIlp = 4;
-__global__ __launch_bounds__(kBlock) void k_fof_sparse_list(int64_t nsparse, const int32_t *__restrict__ sparse,
-                                                            const uint32_t *__restrict__ flag,
-                                                            const uint32_t *__restrict__ at,
-                                                            int32_t *__restrict__ list) {
-    const int64_t t0 = (int64_t)blockIdx.x * (kBlock * kSparseListIlp) + threadIdx.x;
-    uint32_t f[kSparseListIlp];
-#pragma unroll
-    for (int u = 0; u < kSparseListIlp; u++) {
-        const int64_t t = t0 + (int64_t)u * kBlock;
-        f[u] = t < nsparse ? flag[t] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < kSparseListIlp; u++) {
-        const int64_t t = t0 + (int64_t)u * kBlock;
-        if (f[u]) list[at[t]] = sparse[t];
-    }
-}
-
-// Members of sparse cells (the compacted list, its length on the device):
-// links to the later members of sparse neighbour cells (pairs with dense cells
-// are found by the dense chunks).  The offsets of a stencil plane are loaded
-// together, and the plane's particles are walked as one sequence.  The list fills only the first blocks of the grid, which the plain
-// block order spreads over all XCDs.  The kernel waits on memory: it is held
-// to 64 VGPRs (eight wavefronts per SIMD; the compiler fits it without
-// spilling).
-__global__ __launch_bounds__(kBlock, 8) void k_fof_sparse(const uint32_t *__restrict__ count_p, Boxes bx,
-                                                       const int32_t *__restrict__ sparse,
+// Members of sparse cells (listed by phase A): links to the members of the
+// sparse cells in the forward half of the stencil (own cell: the later ones),
+// so each pair is seen once; pairs with dense cells are found by the dense
+// chunks.  Sixteen lanes per member, one stencil cell each (14 of them): the
+// ranges, then all densities and positions of a cell (seven at most) are one
+// round of loads each.  The links (two or three per member) are queued in LDS
+// and joined 64 at a time, one per lane: a join is a chain of its own, and
+// joined where they were found the links of a lane ran one after the other
+// with most lanes idle (925 us on the 256^3 box).  One thread per member, the
+// 27 cells walked as a chain of dependent loads, took 76 us on the 64^3 box and
+// 333 us on the 256^3 one, with 20 us of flags, scan and list before it.
+constexpr int kLinkMost = (64 / 16) * 14 * (kDenseMin - 1);  // links of a round of a wavefront
+__global__ __launch_bounds__(kBlock) void k_fof_sparse(SegList sl, Boxes bx,
                                                        const float4 *__restrict__ sloc,
                                                        const float4 *__restrict__ spos,
                                                        const uint32_t *__restrict__ off,
                                                        const float *__restrict__ dens_s,
                                                        int32_t *parent) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)*count_p) return;
-    const int i = sparse[t];
-    const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
-    const float4 li = sloc[i];
-    const float4 pi = spos[i];
-    const uint32_t c = __float_as_uint(li.w);
-    const int nc = g.nc;
-    int cx, cy, cz;
-    cell_xyz(g, c, cx, cy, cz);
-    const uint32_t x0 = (uint32_t)wrapc(cx - 1, nc), x1 = (uint32_t)cx, x2 = (uint32_t)wrapc(cx + 1, nc);
-    int ri = uf_find_hint(parent, i);
-#pragma unroll 1
-    for (int oz = -1; oz <= 1; oz++) {
-        const float gz = oz < 0 ? li.z : (oz > 0 ? g.cellb - li.z : 0.0f);
-        if (gz * gz >= g.l2b_hi) continue;
-        const int z = wrapc(cz + oz, nc);
-        // the plane's later particles in sparse cells within reach: per cell
-        // its first one and, packed three bits each, their count
-        uint32_t ra[9], cnts = 0;
-#pragma unroll
-        for (int oy = -1; oy <= 1; oy++) {
-            const uint32_t row =
-                g.cell_base + ((uint32_t)z * (uint32_t)nc + (uint32_t)wrapc(cy + oy, nc)) * (uint32_t)nc;
-            const uint32_t o[6] = {off[row + x0], off[row + x0 + 1], off[row + x1],
-                                   off[row + x1 + 1], off[row + x2], off[row + x2 + 1]};
+    __shared__ int2 s_link[kBlock / 64][64 + kLinkMost];
+    __shared__ uint32_t s_n[kBlock / 64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = threadIdx.x & 15;
+    // the forward half: stencil cells 13 (own) .. 26
+    const int ox = (ln + 13) % 3 - 1, oy = ((ln + 13) / 3) % 3 - 1, oz = (ln + 13) / 9 - 1;
+    const SegShare sh = seg_share<16>(sl);
+    uint32_t queued = 0;
+    auto join = [&](uint32_t cnt) {
+        queued -= cnt;
+        if ((uint32_t)lane < cnt) {
+            const int2 l = s_link[w][queued + (uint32_t)lane];
+            // most links are inside a set by now: plain loads tell
+            const int x = uf_find_hint(parent, l.x), y = uf_find_hint(parent, l.y);
+            if (x != y) uf_unite(parent, x, y);
+        }
+    };
+    for (uint32_t k = sh.k; __ballot(k < sh.n) != 0ull; k += sh.step) {
+        uint32_t links = 0, a = 0;
+        int i = 0;
+        if (k < sh.n && ln < 14) {
+            i = sl.list[(int64_t)sh.seg * sl.cap + k];
+            const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
+            const float4 li = sloc[i];
+            const float gx = ox < 0 ? li.x : (ox > 0 ? g.cellb - li.x : 0.0f);
             const float gy = oy < 0 ? li.y : (oy > 0 ? g.cellb - li.y : 0.0f);
+            const float gz = oz > 0 ? g.cellb - li.z : 0.0f;
+            if (gx * gx + gy * gy + gz * gz < g.l2b_hi) {
+                int cx, cy, cz;
+                cell_xyz(g, __float_as_uint(li.w), cx, cy, cz);
+                const uint32_t nb = cell_id(g, cx + ox, cy + oy, cz + oz);
+                a = off[nb];
+                uint32_t b = off[nb + 1];
+                if (b - a >= (uint32_t)kDenseMin) b = a;
+                if (ln == 0) a = (uint32_t)i + 1u;
+                const float xs = li.x - (float)ox * g.cellb, ys = li.y - (float)oy * g.cellb,
+                            zs = li.z - (float)oz * g.cellb;
+                float dj[kDenseMin - 1];
+                float3 lj[kDenseMin - 1];
 #pragma unroll
-            for (int ox = -1; ox <= 1; ox++) {
-                const int r = (oy + 1) * 3 + (ox + 1);
-                uint32_t a = o[2 * (ox + 1)];
-                const uint32_t b = o[2 * (ox + 1) + 1];
-                const float gx = ox < 0 ? li.x : (ox > 0 ? g.cellb - li.x : 0.0f);
-                const bool use = b - a < (uint32_t)kDenseMin && gx * gx + gy * gy + gz * gz < g.l2b_hi;
-                if (a <= (uint32_t)i) a = (uint32_t)i + 1;
-                ra[r] = a;
-                cnts |= (use && b > a ? b - a : 0u) << (3 * r);
+                for (uint32_t v = 0; v < kDenseMin - 1; v++) {
+                    const float *const p = reinterpret_cast<const float *>(sloc + (a + v));
+                    dj[v] = 0.0f;
+                    lj[v] = make_float3(0.0f, 0.0f, 0.0f);
+                    if (a + v < b) {
+                        dj[v] = dens_s[a + v];
+                        lj[v] = make_float3(p[0], p[1], p[2]);
+                    }
+                }
+#pragma unroll
+                for (uint32_t v = 0; v < kDenseMin - 1; v++) {
+                    const uint32_t j = a + v;
+                    if (j >= b || !((double)dj[v] > g.dl0)) continue;
+                    const float d2f = d2_f32(lj[v].x - xs, lj[v].y - ys, lj[v].z - zs);
+                    if (d2f >= g.l2b_hi) continue;
+                    if (!(d2f < g.l2b_lo) && !(d2_exact(spos[i], spos[j], g.L, g.half) < g.l2)) continue;
+                    links |= 1u << v;
+                }
             }
         }
-        // walked as one sequence (cell after cell): the wavefront waits on the
-        // longest lane's count for the plane, not on the longest of each cell
-        uint32_t j = 0, e = 0;
-        float xs = 0.0f, ys = 0.0f, zs = 0.0f;
-        for (;;) {
-            if (j == e) {
-                if (cnts == 0u) break;
-                const int r = __builtin_ctz(cnts) / 3;
-                const uint32_t cnt = (cnts >> (3 * r)) & 7u;
-                cnts &= ~(7u << (3 * r));
-                uint32_t a = ra[0];
-#pragma unroll
-                for (int u = 1; u < 9; u++) a = r == u ? ra[u] : a;
-                j = a;
-                e = a + cnt;
-                // the lane's coordinates in this cell's frame
-                xs = li.x - (float)(r % 3 - 1) * g.cellb;
-                ys = li.y - (float)(r / 3 - 1) * g.cellb;
-                zs = li.z - (float)oz * g.cellb;
-            }
-            const uint32_t jj = j++;
-            const float dj = dens_s[jj];
-            const float4 lj = sloc[jj];
-            if (!((double)dj > g.dl0)) continue;
-            const float d2f = d2_f32(lj.x - xs, lj.y - ys, lj.z - zs);
-            if (d2f >= g.l2b_hi) continue;
-            if (!(d2f < g.l2b_lo) && !(d2_exact(pi, spos[jj], g.L, g.half) < g.l2)) continue;
-            if (uf_find_hint(parent, (int)jj) == ri) continue;
-            uf_unite(parent, i, (int)jj);
-            ri = uf_find_hint(parent, i);
+        const uint64_t lm = __ballot(links != 0u);
+        if (!lm) continue;
+        // queue the links (any order)
+        if (lane == 0) s_n[w] = queued;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        if (links) {
+            uint32_t at = atomicAdd(&s_n[w], (uint32_t)__popc(links));
+            for (uint32_t m = links; m; m &= m - 1) s_link[w][at++] = make_int2(i, (int)(a + (uint32_t)__ffs(m) - 1u));
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        queued = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_n[w]);
+        while (queued >= 64u) join(64u);
     }
+    if (queued) join(queued);
 }
 
 // Roots of all members, read-only: nothing writes the forest in this pass, so
@@ -710,27 +908,32 @@ __global__ __launch_bounds__(kBlock) void k_keys_from_labels(int64_t n, Boxes bx
 }  // namespace
 
 void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
+    const SegList sl = seg_list(n, w);
     // the first members of the dense sub-cells go to the sub-cell maxima's
     // argument table (free until the candidate stage)
     hipLaunchKernelGGL(k_fof_phase_a, grid(n), dim3(kBlock), 0, s, n, bx, w.sloc, w.f_sparse, w.ssub, w.cnt,
-                       w.subtab, w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt);
-    if (w.nchunks > 0)
+                       w.subtab, w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt, sl);
+    if (w.ndcells > 0) {
+        const dim3 cells((unsigned)((w.ndcells + kHalves - 1) / kHalves));
+        hipLaunchKernelGGL(k_fof_cells, cells, dim3(kBlock), kHalves * bx.nsub_max * sizeof(float4), s, w.ndcells, bx,
+                           w.dcells, w.off, w.sloc, w.subtab, w.subarg, w.parent);
+        hipLaunchKernelGGL(k_fof_faces, cells, dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.cnt, w.sloc,
+                           w.subtab, w.subarg, w.parent);
+        hipLaunchKernelGGL(k_fof_cell_roots, cells, dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.subtab,
+                           w.subarg, w.parent);
+    }
+    if (w.nchunks > 0) {
         // one wavefront per workgroup: chunk costs differ widely, and a
         // finished wavefront's slot is free at once
-        hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, bx,
+        const int parts = w.nchunks <= 16 * (int64_t)(w.ncu > 0 ? w.ncu : 1) ? 2 : 1;
+        hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)(w.nchunks * parts)), dim3(64), 0, s, w.nchunks, parts, bx,
                            w.chunks, w.sloc, w.spos, w.off, w.cnt, w.subtab, w.subarg, w.dens_s, w.parent);
-    if (w.nsparse > 0) {
-        // sparse members: flags, positions and list in arrays that are free
-        // during this stage (chunk flags of the binning, the hard-case list)
-        hipLaunchKernelGGL(k_fof_sparse_flags, grid(w.nsparse), dim3(kBlock), 0, s, w.nsparse, bx, w.sparse,
-                           w.dens_s, w.f_chunk);
-        scan_u32(w.f_chunk, w.s_chunk, w.nsparse, w.scan_tmp, s);
-        hipLaunchKernelGGL(k_fof_sparse_list, grid((w.nsparse + kSparseListIlp - 1) / kSparseListIlp), dim3(kBlock),
-                           0, s, w.nsparse, w.sparse,
-                           w.f_chunk, w.s_chunk, w.hardlist);
-        hipLaunchKernelGGL(k_fof_sparse, grid(w.nsparse), dim3(kBlock), 0, s, w.s_chunk + w.nsparse, bx,
-                           w.hardlist, w.sloc, w.spos, w.off, w.dens_s, w.parent);
     }
+    if (w.nsparse > 0)
+        // one member in ten sparse particles: sixteen lanes per 8 particles at
+        // most, and no more than fit the chip
+        hipLaunchKernelGGL(k_fof_sparse, dim3(seg_blocks(sl, w.nsparse, 16, 8, 6 * (int64_t)(w.ncu > 0 ? w.ncu : 1))),
+                           dim3(kBlock), 0, s, sl, bx, w.sloc, w.spos, w.off, w.dens_s, w.parent);
     // roots go to the owner array (free until the assignment stage)
     hipLaunchKernelGGL(k_fof_roots, grid(n), dim3(kBlock), 0, s, n, w.parent, w.spos, w.owner, w.minorig);
 }

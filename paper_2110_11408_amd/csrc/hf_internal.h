@@ -270,6 +270,60 @@ struct Work {
     uint32_t *host;                                    // the lane's pinned host words (read_words)
 };
 
+// A list that one kernel fills for the next, in nseg segments of `cap` entries:
+// workgroup b appends to segment b mod nseg with one atomic, so no address
+// sees more than a 64th of the workgroups (a flag per particle, a scan and a
+// list kernel took 60 us on the 256^3 box, a count read back by the host
+// another 25 us of an idle device).  Counters lie kSegStride words apart.
+constexpr uint32_t kSegs = 64, kSegStride = 16;
+struct SegList {
+    int32_t *list;
+    uint32_t *count;
+    uint32_t nseg, cap;
+};
+
+// Appends i of the lanes with `take` (every thread of the kBlock takes part).
+__device__ __forceinline__ void seg_append(const SegList &sl, bool take, int32_t i) {
+    __shared__ uint32_t s_cnt[kBlock / 64], s_base;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t m = __ballot(take);
+    if (lane == 0) s_cnt[w] = (uint32_t)__popcll(m);
+    __syncthreads();
+    const uint32_t seg = blockIdx.x % sl.nseg;
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int x = 0; x < kBlock / 64; x++) t += s_cnt[x];
+        s_base = t ? atomicAdd(sl.count + seg * kSegStride, t) : 0u;
+    }
+    __syncthreads();
+    if (take) {
+        uint32_t at = s_base;
+        for (int x = 0; x < w; x++) at += s_cnt[x];
+        sl.list[(int64_t)seg * sl.cap + at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = i;
+    }
+}
+
+// The share of one of kBlock / W lane groups per workgroup in a list: entries
+// k, k + step, ... of segment seg (none when k >= n).  The groups of a
+// workgroup take consecutive entries of one segment: particles near each other,
+// whose neighbourhoods overlap.  With all kSegs segments the grid is a multiple
+// of kSegs workgroups and a workgroup serves a segment that the workgroups of
+// its own XCD filled.
+struct SegShare {
+    uint32_t seg, k, step, n;
+};
+template <int W>
+__device__ __forceinline__ SegShare seg_share(const SegList &sl) {
+    constexpr uint32_t kGroups = kBlock / W;
+    const uint32_t q = threadIdx.x / W;
+    SegShare s;
+    s.seg = blockIdx.x % sl.nseg;
+    s.k = blockIdx.x / sl.nseg * kGroups + q;
+    s.step = gridDim.x / sl.nseg * kGroups;
+    s.n = sl.count[s.seg * kSegStride];
+    return s;
+}
+
 // Words of Work::counters that several stages use (zero when a call begins).
 enum {
     kCntHard = 8,       // hard cases of the candidate stage
@@ -285,6 +339,31 @@ struct SegClear {
     uint32_t *p[kRuns];
     int len[kRuns];
 };
+
+// The segmented list over n particles.  Its entries lie in the chunk and
+// dense-cell flag and scan arrays (4 n words in one run, free once the lists of
+// the binning are written; the segments hold at most 2 (n + 255) words, and a
+// single segment at most n), its counts in the radix counts (at least n / 8
+// words, of which n / 16 + 16 are used).
+inline SegList seg_list(int64_t n, const Work &w) {
+    const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    SegList sl;
+    sl.list = reinterpret_cast<int32_t *>(w.f_chunk);
+    sl.count = w.rhist;
+    sl.nseg = nb < kSegs ? nb : kSegs;
+    sl.cap = (nb + sl.nseg - 1) / sl.nseg * kBlock;
+    return sl;
+}
+// Workgroups whose lane groups of W share a segmented list of n particles'
+// entries: about `most` of them, no more than one group per `per` particles, and
+// a multiple of the segment count (at least one workgroup per segment).
+inline unsigned seg_blocks(const SegList &sl, int64_t n, int W, int64_t per, int64_t most) {
+    const int groups = kBlock / W;
+    int64_t b = (n / per + groups - 1) / groups;
+    if (b > most) b = most;
+    const int64_t each = b / sl.nseg;
+    return (unsigned)(sl.nseg * (each > 0 ? each : 1));
+}
 
 // ------------------------------------------------------------------ launchers
 // Device words to read back to the host in one go.
