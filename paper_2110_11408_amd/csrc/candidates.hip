@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, co
     for (uint32_t k = sh.k; k < sh.n; k += sh.step) {
         int32_t *const entry = hl.list + (int64_t)sh.seg * hl.cap + k;
         const int i = *entry;
-        const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
+        per_box(bx, box_of(bx, (uint32_t)i), [&](const Geo &g) {
         const int key = gkey[i];
         const float di = dens_s[i];
         const float4 li = sloc[i];
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, co
                 }
             }
         }
-        if (hballot(found)) continue;
+        if (hballot(found)) return;
         bool open = false;
         int64_t base = 0;
         if (dense) {
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, co
             open = mx > mykey;
             if (open) found = denser_within_b(top, dens_s, gkey, spos, key, di, oi, pi, g);
         }
-        if (hballot(found)) continue;
+        if (hballot(found)) return;
         const uint32_t om = hballot(open);
         if (open) {
             const int slot = __popc(om & ((1u << ln) - 1u));
@@ -378,6 +378,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, co
             *entry = ~i;
             atomicAdd(&gccnt[gid_of[i]], 1u);
         }
+        });
     }
 }
 

@@ -290,9 +290,9 @@ __global__ __launch_bounds__(kBlock) void k_fof_cells(int64_t ndc, Boxes bx,
     const int64_t d = (int64_t)xcd_block() * kHalves + hw;
     if (d >= ndc) return;
     float4 *sp = s_first + hw * bx.nsub_max;
-    const Geo &g = bx.geo[box_of(bx, off[dcells[d]])];
-    const int k = g.ksub, nsub = g.nsub;
     const int64_t row = d * (bx.nsub_max + 1);
+    per_box(bx, box_of(bx, off[dcells[d]]), [&](const Geo &g) {
+    const int k = g.ksub, nsub = g.nsub;
     for (int s = ln; s < nsub; s += 32) {
         const int32_t fm = sub_first(subtab, submem, row + s);
         float4 p = make_float4(1e8f, 0.0f, 0.0f, 0.0f);  // empty: far from everything
@@ -319,6 +319,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_cells(int64_t ndc, Boxes bx,
         }
         if (to != fm) parent[fm] = to;
     }
+    });
 }
 
 // Across cells, half a wavefront per cell: the pairs of sub-cells that touch
@@ -337,8 +338,9 @@ __global__ __launch_bounds__(kBlock) void k_fof_faces(int64_t ndc, Boxes bx,
     if (d >= ndc) return;
     auto hballot = [&](bool p) { return (uint32_t)(__ballot(p) >> hsh); };
     const uint32_t c = dcells[d];
-    const Geo &g = bx.geo[box_of(bx, off[c])];
-    const int k = g.ksub, k2 = k * k, tstride = bx.nsub_max + 1;
+    const int tstride = bx.nsub_max + 1;
+    per_box(bx, box_of(bx, off[c]), [&](const Geo &g) {
+    const int k = g.ksub, k2 = k * k;
     const float inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)k2;
     int cx, cy, cz;
     cell_xyz(g, c, cx, cy, cz);
@@ -376,6 +378,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_faces(int64_t ndc, Boxes bx,
         }
         if (join) uf_unite(parent, r1, r2);
     }
+    });
 }
 
 // The first members' roots, stored as their parents (the forest does not
@@ -389,7 +392,8 @@ __global__ __launch_bounds__(kBlock) void k_fof_cell_roots(int64_t ndc, Boxes bx
     const int hw = threadIdx.x >> 5, ln = threadIdx.x & 31, hsh = threadIdx.x & 32;
     const int64_t d = (int64_t)xcd_block() * kHalves + hw;
     if (d >= ndc) return;
-    const int nsub = bx.geo[box_of(bx, off[dcells[d]])].nsub;
+    int nsub = 0;
+    per_box(bx, box_of(bx, off[dcells[d]]), [&](const Geo &g) { nsub = g.nsub; });
     const int64_t row = d * (bx.nsub_max + 1);
     int32_t one = -2;
     for (int s0 = 0; s0 < nsub; s0 += 32) {
@@ -713,7 +717,7 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
 // 27 cells walked as a chain of dependent loads, took 76 us on the 64^3 box and
 // 333 us on the 256^3 one, with 20 us of flags, scan and list before it.
 constexpr int kLinkMost = (64 / 16) * 14 * (kDenseMin - 1);  // links of a round of a wavefront
-__global__ __launch_bounds__(kBlock) void k_fof_sparse(SegList sl, Boxes bx,
+__global__ __launch_bounds__(kBlock, 8) void k_fof_sparse(SegList sl, Boxes bx,
                                                        const float4 *__restrict__ sloc,
                                                        const float4 *__restrict__ spos,
                                                        const uint32_t *__restrict__ off,
@@ -740,8 +744,8 @@ __global__ __launch_bounds__(kBlock) void k_fof_sparse(SegList sl, Boxes bx,
         int i = 0;
         if (k < sh.n && ln < 14) {
             i = sl.list[(int64_t)sh.seg * sl.cap + k];
-            const Geo &g = bx.geo[box_of(bx, (uint32_t)i)];
             const float4 li = sloc[i];
+            per_box(bx, box_of(bx, (uint32_t)i), [&](const Geo &g) {
             const float gx = ox < 0 ? li.x : (ox > 0 ? g.cellb - li.x : 0.0f);
             const float gy = oy < 0 ? li.y : (oy > 0 ? g.cellb - li.y : 0.0f);
             const float gz = oz > 0 ? g.cellb - li.z : 0.0f;
@@ -767,16 +771,20 @@ __global__ __launch_bounds__(kBlock) void k_fof_sparse(SegList sl, Boxes bx,
                         lj[v] = make_float3(p[0], p[1], p[2]);
                     }
                 }
+                uint32_t open = 0;
 #pragma unroll
                 for (uint32_t v = 0; v < kDenseMin - 1; v++) {
-                    const uint32_t j = a + v;
-                    if (j >= b || !((double)dj[v] > g.dl0)) continue;
                     const float d2f = d2_f32(lj[v].x - xs, lj[v].y - ys, lj[v].z - zs);
-                    if (d2f >= g.l2b_hi) continue;
-                    if (!(d2f < g.l2b_lo) && !(d2_exact(spos[i], spos[j], g.L, g.half) < g.l2)) continue;
-                    links |= 1u << v;
+                    const bool near = a + v < b && (double)dj[v] > g.dl0 && d2f < g.l2b_hi;
+                    if (near) (d2f < g.l2b_lo ? links : open) |= 1u << v;
+                }
+                // the undecided band, by the canonical distance
+                for (; open; open &= open - 1) {
+                    const uint32_t v = (uint32_t)__ffs(open) - 1u;
+                    if (d2_exact(spos[i], spos[a + v], g.L, g.half) < g.l2) links |= 1u << v;
                 }
             }
+            });
         }
         const uint64_t lm = __ballot(links != 0u);
         if (!lm) continue;
@@ -932,7 +940,7 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     if (w.nsparse > 0)
         // one member in ten sparse particles: sixteen lanes per 8 particles at
         // most, and no more than fit the chip
-        hipLaunchKernelGGL(k_fof_sparse, dim3(seg_blocks(sl, w.nsparse, 16, 8, 6 * (int64_t)(w.ncu > 0 ? w.ncu : 1))),
+        hipLaunchKernelGGL(k_fof_sparse, dim3(seg_blocks(sl, w.nsparse, 16, 8, 8 * (int64_t)(w.ncu > 0 ? w.ncu : 1))),
                            dim3(kBlock), 0, s, sl, bx, w.sloc, w.spos, w.off, w.dens_s, w.parent);
     // roots go to the owner array (free until the assignment stage)
     hipLaunchKernelGGL(k_fof_roots, grid(n), dim3(kBlock), 0, s, n, w.parent, w.spos, w.owner, w.minorig);

@@ -74,6 +74,37 @@ __device__ __forceinline__ int box_of(const Boxes &bx, uint32_t i) {
     return b;
 }
 
+// f(constants of box b) for every lane, one box of the wavefront at a time
+// (nearly always one in all), with the box index in a scalar register, so that
+// the constants come with scalar loads.  With an index per lane every constant
+// is a vector load of its own, again in every loop that uses it.  The empty asm
+// hides that the scalar index equals the lane's, which the compiler would put
+// back in its place.
+template <class F>
+__device__ __forceinline__ void per_box(const Boxes &bx, int b, F f) {
+    for (uint64_t todo = __ballot(true); todo;) {
+        const int b1 = __builtin_amdgcn_readlane(b, (int)__builtin_ctzll(todo));
+        int b0 = b1;
+        asm volatile("" : "+s"(b0));
+        const bool mine = b == b1;
+        if (mine) {
+            // word by word through the constant address space: scalar loads
+            // also where stores of the kernel could lie in between (nothing
+            // writes the tables while kernels run); unused words are dropped
+            typedef const __attribute__((address_space(4))) uint32_t *Words;
+            const Words p = (Words)(uintptr_t)(bx.geo + b0);
+            static_assert(sizeof(Geo) % 4 == 0, "Geo is a run of words");
+            uint32_t words[sizeof(Geo) / 4];
+#pragma unroll
+            for (size_t k = 0; k < sizeof(Geo) / 4; k++) words[k] = p[k];
+            Geo g;
+            __builtin_memcpy(&g, words, sizeof(Geo));
+            f(g);
+        }
+        todo &= ~__ballot(mine);
+    }
+}
+
 // ---------------------------------------------------------------- predicates
 // Canonical minimum-image squared distance in FP64: the same sequence of IEEE
 // operations as the definition (differences of the float32 inputs promoted to
