@@ -4,15 +4,22 @@
 // The paper's host code receives particles already ordered by cell from the
 // N-body engine (Sec. 2.3.4); here the caller hands over an unordered float32
 // [n][3] array, so the library builds the order itself:
-//   1. key = cell * k^3 + sub-cell per particle (range check of the input);
-//   2. least-significant-digit radix sort of (key, original index), digits of
-//      at most 8 bits; key and index share one 64-bit word when they fit.
-//      Each pass: a block counts the digits of its tile of 2048 consecutive
-//      elements; an exclusive scan of the digit-major [digit][tile] counts
-//      gives every (digit, tile) its output offset; the tile is then walked
-//      again in order, each element's rank among equal digits coming from the
-//      ballots of its digit bits (lower lanes first), so the pass is stable,
-//      and written out through LDS in digit order (coalesced runs).
+//   1. key = cell * k^3 + sub-cell per particle (range check of the input), and
+//      the digit counts of the first pass on the way;
+//   2. the keys are put into buckets by their top bits, and a workgroup per
+//      bucket sorts it by the other bits in LDS and writes the sorted records.
+//      Up to kPartitionMost particles one pass over (key, index) words makes
+//      up to 1024 buckets; beyond, two passes make up to 2^18, and carry the
+//      positions with them, so that nothing is gathered from the unordered
+//      input.  (A least-significant-digit radix sort over all digits remains
+//      for keys and indices that need more than 64 bits, for sub-cells too few
+//      to lend their tables as a buffer, and for the later stages' lists.)
+//      A pass over a digit: a block counts the digits of its tile of 2048
+//      consecutive elements; an exclusive scan of the digit-major [digit][tile]
+//      counts gives every (digit, tile) its output offset; the tile is then
+//      walked again in order, each element's rank among equal digits coming
+//      from the ballots of its digit bits (lower lanes first), so the pass is
+//      stable, and written out through LDS in digit order (coalesced runs).
 //      Consecutive tiles run on one XCD, so the runs that consecutive tiles
 //      write for a digit (adjacent in the output) meet in one L2;
 //   3. the sorted order writes two float4 streams per particle:
@@ -55,54 +62,85 @@ __device__ __forceinline__ int sub_coord(float x, int c, const Geo &g) {
     return s < 0 ? 0 : (s >= g.ksub ? g.ksub - 1 : s);
 }
 
+// Cell and sub-cell of a position of box g, and the sort key made of them.
+struct Spot {
+    int cx, cy, cz;
+    uint32_t c, sub;  // cell in the call's numbering, sub-cell
+    uint64_t key;     // c * nsub_max + sub
+};
+__device__ __forceinline__ Spot spot_of(const Geo &g, int nsub_max, float x, float y, float z) {
+    Spot p;
+    p.cx = cell_coord(x, g);
+    p.cy = cell_coord(y, g);
+    p.cz = cell_coord(z, g);
+    p.c = g.cell_base + ((uint32_t)p.cz * (uint32_t)g.nc + (uint32_t)p.cy) * (uint32_t)g.nc + (uint32_t)p.cx;
+    const int k = g.ksub;
+    p.sub = (uint32_t)((sub_coord(z, p.cz, g) * k + sub_coord(y, p.cy, g)) * k + sub_coord(x, p.cx, g));
+    p.key = (uint64_t)p.c * (uint64_t)nsub_max + p.sub;
+    return p;
+}
+
+__device__ __forceinline__ bool inside(const Geo &g, float x, float y, float z) {
+    const float Lf = (float)g.L;
+    return x >= 0.0f && x < Lf && y >= 0.0f && y < Lf && z >= 0.0f && z < Lf;
+}
+
 // Sort key of particle i: cell * nsub_max + sub-cell, the cell numbered in the
 // call's numbering (box after box).  Packed mode stores (key << ib) | i in one
 // word (ib bits hold the index); otherwise the index travels in a separate
 // payload array.
-// A thread keys kKeyIlp particles (i0, i0 + kBlock, ...), their positions
-// loaded together (one load in flight per thread leaves most of the
-// bandwidth unused).
-constexpr int kKeyIlp = 4;
-__global__ __launch_bounds__(kBlock) void k_bin_key(const float *__restrict__ pos, int64_t n, Boxes bx, int ib,
-                                                    uint64_t *__restrict__ key,
-                                                    int32_t *__restrict__ err) {
-    const int64_t i0 = (int64_t)blockIdx.x * (kBlock * kKeyIlp) + threadIdx.x;
-    float px[kKeyIlp], py[kKeyIlp], pz[kKeyIlp];
-#pragma unroll
-    for (int u = 0; u < kKeyIlp; u++) {
-        const int64_t i = i0 + (int64_t)u * kBlock;
-        px[u] = i < n ? pos[3 * i + 0] : 0.0f;
-        py[u] = i < n ? pos[3 * i + 1] : 0.0f;
-        pz[u] = i < n ? pos[3 * i + 2] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < kKeyIlp; u++) {
-        const int64_t i = i0 + (int64_t)u * kBlock;
-        if (i >= n) break;
-        const int box = box_of(bx, (uint32_t)i);
-        const Geo &g = bx.geo[box];
-        const float x = px[u], y = py[u], z = pz[u];
-        const float Lf = (float)g.L;
-        const bool ok = x >= 0.0f && x < Lf && y >= 0.0f && y < Lf && z >= 0.0f && z < Lf;
-        if (!ok) flag_error(err, 1, box);
-        const int cx = cell_coord(x, g), cy = cell_coord(y, g), cz = cell_coord(z, g);
-        const uint32_t c =
-            g.cell_base + ((uint32_t)cz * (uint32_t)g.nc + (uint32_t)cy) * (uint32_t)g.nc + (uint32_t)cx;
-        const int k = g.ksub;
-        const uint32_t sub = (uint32_t)((sub_coord(z, cz, g) * k + sub_coord(y, cy, g)) * k + sub_coord(x, cx, g));
-        const uint64_t kk = (uint64_t)c * (uint64_t)bx.nsub_max + sub;
-        key[i] = ib > 0 ? (kk << ib) | (uint64_t)i : kk;
-    }
-}
-
-constexpr int kRadixMaxBits = 8;
-// k_radix_scatter scans the digit counts with one digit per thread of its 256
-static_assert((1 << kRadixMaxBits) <= 256, "at most 256 digits per radix pass");
+constexpr int kRadixMaxBits = 8;                    // digits of a pass of the radix sort
+constexpr int kPartBits = 10;                       // digits of the partition pass
 constexpr int kRadixWaves = 4;                      // wavefronts per tile
 constexpr int kRadixIters = 8;                      // 64-element steps per wavefront
 // 2048 elements per tile: the scatter's LDS tile (16 KB of keys) then lets
 // seven blocks share a CU, twice as many as with 4096
 constexpr int64_t kTile = 64 * kRadixWaves * kRadixIters;
+
+// Digit counts of a tile, stored digit-major ([digit][tile]), with one LDS
+// atomic per element: equal digits in a wavefront cost an LDS cycle each, fewer
+// than the ballots of the digit bits that find them (the counts were bound by
+// the vector ALU, 38 us a pass on 1.7e7 keys).
+__device__ __forceinline__ void counts_out(const uint32_t *h, int nd, int64_t t, int64_t ntiles,
+                                           uint32_t *__restrict__ hist) {
+    __syncthreads();
+    for (int d = threadIdx.x; d < nd; d += 256) hist[(int64_t)d * ntiles + t] = h[d];
+}
+
+// A workgroup keys one tile (eight particles per thread, their positions loaded
+// together: one load in flight per thread leaves most of the bandwidth unused)
+// and counts its digits [shift, shift + D) for the first pass.
+__global__ __launch_bounds__(256) void k_bin_key(const float *__restrict__ pos, int64_t n, Boxes bx, int ib,
+                                                 uint64_t *__restrict__ key, int shift, int D, int64_t ntiles,
+                                                 uint32_t *__restrict__ hist, int32_t *__restrict__ err) {
+    __shared__ uint32_t h[1 << kPartBits];
+    const int64_t t = xcd_block();
+    const int nd = 1 << D;
+    for (int d = threadIdx.x; d < nd; d += 256) h[d] = 0u;
+    const int64_t i0 = t * kTile + threadIdx.x;
+    float px[kRadixIters], py[kRadixIters], pz[kRadixIters];
+#pragma unroll
+    for (int u = 0; u < kRadixIters; u++) {
+        const int64_t i = i0 + (int64_t)u * 256;
+        px[u] = i < n ? pos[3 * i + 0] : 0.0f;
+        py[u] = i < n ? pos[3 * i + 1] : 0.0f;
+        pz[u] = i < n ? pos[3 * i + 2] : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRadixIters; u++) {
+        const int64_t i = i0 + (int64_t)u * 256;
+        if (i >= n) break;
+        const int box = box_of(bx, (uint32_t)i);
+        const Geo &g = bx.geo[box];
+        if (!inside(g, px[u], py[u], pz[u])) flag_error(err, 1, box);
+        const uint64_t kk = spot_of(g, bx.nsub_max, px[u], py[u], pz[u]).key;
+        const uint64_t kw = ib > 0 ? (kk << ib) | (uint64_t)i : kk;
+        key[i] = kw;
+        atomicAdd(&h[(uint32_t)(kw >> shift) & (uint32_t)(nd - 1)], 1u);
+    }
+    counts_out(h, nd, t, ntiles, hist);
+}
 
 // Lanes holding the same D-bit digit as this lane (within `active`).
 __device__ __forceinline__ uint64_t digit_peers(uint32_t d, int D, uint64_t active) {
@@ -118,36 +156,29 @@ __device__ __forceinline__ uint64_t lanes_below(int lane) {
     return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// Digit counts of one tile, stored digit-major ([digit][tile]).  Wavefront w
-// of the tile owns elements [w * 512, (w + 1) * 512) of it and loads all 8 of
-// its steps before counting.
+// Digit counts of one tile, all its elements loaded before counting.
 __global__ __launch_bounds__(256) void k_radix_count(const uint64_t *__restrict__ key, int64_t n, int shift,
                                                      int D, int64_t ntiles, uint32_t *__restrict__ hist) {
     __shared__ uint32_t h[1 << kRadixMaxBits];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t t = xcd_block();
     const int nd = 1 << D;
     for (int d = threadIdx.x; d < nd; d += 256) h[d] = 0u;
-    const int64_t base = t * kTile + (int64_t)w * (64 * kRadixIters) + lane;
+    const int64_t base = t * kTile + threadIdx.x;
     uint64_t k[kRadixIters];
 #pragma unroll
     for (int it = 0; it < kRadixIters; it++) {
-        const int64_t e = base + it * 64;
+        const int64_t e = base + it * 256;
         k[it] = e < n ? key[e] : 0ull;
     }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kRadixIters; it++) {
-        const bool act = base + it * 64 < n;
-        const uint32_t d = (uint32_t)(k[it] >> shift) & (uint32_t)(nd - 1);
-        const uint64_t m = digit_peers(d, D, __ballot(act));
-        if (act && (m & lanes_below(lane)) == 0ull) atomicAdd(&h[d], (uint32_t)__popcll(m));
-    }
-    __syncthreads();
-    for (int d = threadIdx.x; d < nd; d += 256) hist[(int64_t)d * ntiles + t] = h[d];
+    for (int it = 0; it < kRadixIters; it++)
+        if (base + it * 256 < n) atomicAdd(&h[(uint32_t)(k[it] >> shift) & (uint32_t)(nd - 1)], 1u);
+    counts_out(h, nd, t, ntiles, hist);
 }
 
-// Block-wide exclusive scan of one value per thread (256 threads).
+// Block-wide exclusive scan of one value per thread (NW wavefronts).
+template <int NW = kRadixWaves>
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *s_tot) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint32_t inc = v;
@@ -158,8 +189,49 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *s_tot)
     if (lane == 63) s_tot[w] = inc;
     __syncthreads();
     uint32_t pre = 0;
-    for (int x = 0; x < w; x++) pre += s_tot[x];
+#pragma unroll
+    for (int x = 0; x < NW; x++) pre += x < w ? s_tot[x] : 0u;
     return pre + inc - v;
+}
+
+// An element's place among the equal digits of its 64-element step: how many
+// before it (bits 0-7), how many in all (8-15), whether it is the first (16).
+// Kept from the counting walk for the ranking one: finding the peers again
+// made the scatter bound by the vector ALU (78 us a pass on 1.7e7 keys).
+__device__ __forceinline__ uint32_t step_place(uint32_t d, int D, bool act) {
+    const uint64_t m = digit_peers(d, D, __ballot(act));
+    const uint32_t before = (uint32_t)__popcll(m & lanes_below((int)(threadIdx.x & 63)));
+    return before | ((uint32_t)__popcll(m) << 8) | (before == 0u ? 1u << 16 : 0u);
+}
+
+// Counts per wavefront and digit (o[w][d]) to the first place of each in the
+// digit order of the tile, which starts at 0; lstart[d] receives the digit's
+// start.  nd <= threads * PER digits, PER consecutive ones each.
+template <int PER, int NW = kRadixWaves, class Row>
+__device__ __forceinline__ void digit_starts(Row o, int nd, uint32_t *lstart, uint32_t *s_tot) {
+    const int d0 = (int)threadIdx.x * PER;
+    uint32_t tot[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+        tot[q] = 0;
+        if (d0 + q < nd)
+            for (int x = 0; x < NW; x++) tot[q] += o[x][d0 + q];
+        sum += tot[q];
+    }
+    uint32_t at = block_scan_excl<NW>(sum, s_tot);
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+        if (d0 + q < nd) {
+            lstart[d0 + q] = at;
+            uint32_t b = at;
+            for (int x = 0; x < NW; x++) {
+                const uint32_t c = o[x][d0 + q];
+                o[x][d0 + q] = b;
+                b += c;
+            }
+        }
+        at += tot[q];
+    }
 }
 
 // Stable scatter of one tile.  Every element's position inside the tile's
@@ -168,13 +240,14 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *s_tot)
 // is first placed in LDS in that order and then written out in order, so
 // consecutive threads write consecutive addresses of one digit's run (the
 // digit's global offset for this tile comes from the scanned counts).
-template <bool kPacked>
+template <bool kPacked, int kBits>
 __global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restrict__ kin,
                                                        const uint32_t *__restrict__ vin, int64_t n, int shift,
                                                        int D, int64_t ntiles, const uint32_t *__restrict__ hscan,
                                                        uint64_t *__restrict__ kout, uint32_t *__restrict__ vout) {
-    __shared__ uint32_t o[kRadixWaves][1 << kRadixMaxBits];
-    __shared__ uint32_t lstart[1 << kRadixMaxBits], gbase[1 << kRadixMaxBits];
+    constexpr int kPer = (1 << kBits) > 256 ? (1 << kBits) / 256 : 1;
+    __shared__ uint32_t o[kRadixWaves][1 << kBits];
+    __shared__ uint32_t lstart[1 << kBits];
     __shared__ uint32_t s_tot[kRadixWaves];
     __shared__ uint64_t sk[kTile];
     __shared__ uint32_t sv[kPacked ? 1 : kTile];
@@ -193,91 +266,594 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restric
         if (!kPacked) v[it] = e < n ? (vin ? vin[e] : (uint32_t)e) : 0u;
     }
     // counts of this wavefront (its own LDS row; leaders only, in step order)
+    uint32_t place[kRadixIters];
 #pragma unroll
     for (int it = 0; it < kRadixIters; it++) {
         const bool act = base + it * 64 < n;
         const uint32_t d = (uint32_t)(k[it] >> shift) & dmask;
-        const uint64_t m = digit_peers(d, D, __ballot(act));
-        if (act && (m & lanes_below(lane)) == 0ull) o[w][d] += (uint32_t)__popcll(m);
+        place[it] = step_place(d, D, act);
+        if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
     }
     __syncthreads();
     // digit starts inside the tile, then every wavefront's start per digit
-    uint32_t tot = 0;
-    if (tid < nd)
-        for (int x = 0; x < kRadixWaves; x++) tot += o[x][tid];
-    const uint32_t ex = block_scan_excl(tot, s_tot);
-    if (tid < nd) {
-        lstart[tid] = ex;
-        gbase[tid] = hscan[(int64_t)tid * ntiles + t];
-        uint32_t b = ex;
-        for (int x = 0; x < kRadixWaves; x++) {
-            const uint32_t c = o[x][tid];
-            o[x][tid] = b;
-            b += c;
-        }
-    }
+    digit_starts<kPer>(o, nd, lstart, s_tot);
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < kRadixIters; it++) {
         const bool act = base + it * 64 < n;
         const uint32_t d = (uint32_t)(k[it] >> shift) & dmask;
-        const uint64_t m = digit_peers(d, D, __ballot(act));
         const uint32_t start = act ? o[w][d] : 0u;
         if (act) {
-            const uint32_t lp = start + (uint32_t)__popcll(m & lanes_below(lane));
+            const uint32_t lp = start + (place[it] & 0xffu);
             sk[lp] = k[it];
             if (!kPacked) sv[lp] = v[it];
         }
         // LDS operations of one wavefront complete in order: every lane of the
         // group has read `start` before the leader's update lands
-        if (act && (m & lanes_below(lane)) == 0ull) o[w][d] = start + (uint32_t)__popcll(m);
+        if (act && (place[it] >> 16)) o[w][d] = start + ((place[it] >> 8) & 0xffu);
     }
+    // lstart becomes the distance from a place in the tile to one in the output
+    __syncthreads();
+    for (int d = tid; d < nd; d += 256) lstart[d] = hscan[(int64_t)d * ntiles + t] - lstart[d];
     __syncthreads();
     const int64_t rem = n - t * kTile;
     const int cnt = rem < kTile ? (int)rem : (int)kTile;
     for (int lp = tid; lp < cnt; lp += 256) {
         const uint64_t key = sk[lp];
         const uint32_t d = (uint32_t)(key >> shift) & dmask;
-        const uint32_t dst = gbase[d] + ((uint32_t)lp - lstart[d]);
+        const uint32_t dst = lstart[d] + (uint32_t)lp;
         kout[dst] = key;
         if (!kPacked) vout[dst] = sv[lp];
     }
 }
 
-// Sorted slot s: the particle's two float4 records, its sub-cell and, when
-// densities follow, its density record.
-template <bool kPacked>
-__global__ __launch_bounds__(kBlock) void k_bin_place(const float *__restrict__ pos, int64_t n, Boxes bx, int ib,
-                                                      const uint64_t *__restrict__ key,
-                                                      const uint32_t *__restrict__ idx,
-                                                      float4 *__restrict__ spos, float4 *__restrict__ sloc,
-                                                      float4 *__restrict__ pq, uint16_t *__restrict__ ssub) {
-    const int64_t s = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
-    // pq's padding (read past a cell's end by the density kernel, never used)
-    if (pq && s < 32) pq[n + s] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (s >= n) return;
-    const uint64_t kw = key[s];
-    const uint64_t k = kPacked ? kw >> ib : kw;
-    const uint32_t o = kPacked ? (uint32_t)(kw & ((1ull << ib) - 1ull)) : idx[s];
+// Sorted slot s, key k (without index bits), original index o: the particle's
+// two float4 records, its sub-cell and, when densities follow, its density
+// record.
+struct Sorted {
+    float4 *__restrict__ spos, *__restrict__ sloc, *__restrict__ pq;
+    uint16_t *__restrict__ ssub;
+};
+__device__ __forceinline__ void place_particle(const float *__restrict__ pos, const Boxes &bx, int64_t s, uint64_t k,
+                                               uint32_t o, const Sorted &to) {
     const uint32_t nsub = (uint32_t)bx.nsub_max;
     const uint32_t c = (uint32_t)(k / nsub);
     const uint32_t sub = (uint32_t)(k - (uint64_t)c * nsub);
     const Geo &g = bx.geo[box_of(bx, (uint32_t)s)];
     const float x = pos[3 * (int64_t)o + 0], y = pos[3 * (int64_t)o + 1], z = pos[3 * (int64_t)o + 2];
-    spos[s] = make_float4(x, y, z, __uint_as_float(o));
+    to.spos[s] = make_float4(x, y, z, __uint_as_float(o));
     const uint32_t nc = (uint32_t)g.nc, lc = c - g.cell_base;
     const uint32_t cx = lc % nc, cy = (lc / nc) % nc, cz = lc / (nc * nc);
     const float xl = (float)(((double)x - (double)cx * g.cell) * g.inv_b);
     const float yl = (float)(((double)y - (double)cy * g.cell) * g.inv_b);
     const float zl = (float)(((double)z - (double)cz * g.cell) * g.inv_b);
-    sloc[s] = make_float4(xl, yl, zl, __uint_as_float(c));
-    if (pq) {
+    to.sloc[s] = make_float4(xl, yl, zl, __uint_as_float(c));
+    if (to.pq) {
         // coordinates about the cell centre and minus their squared norm
         const float c0 = 0.5f * g.cellb;
         const float xc = xl - c0, yc = yl - c0, zc = zl - c0;
-        pq[s] = make_float4(xc, yc, zc, -(xc * xc + yc * yc + zc * zc));
+        to.pq[s] = make_float4(xc, yc, zc, -(xc * xc + yc * yc + zc * zc));
     }
-    ssub[s] = (uint16_t)sub;
+    to.ssub[s] = (uint16_t)sub;
+}
+
+// pq's padding (read past a cell's end by the density kernel, never used).
+__device__ __forceinline__ void place_padding(int64_t n, int64_t s, const Sorted &to) {
+    if (to.pq && s < 32) to.pq[n + s] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+template <bool kPacked>
+__global__ __launch_bounds__(kBlock) void k_bin_place(const float *__restrict__ pos, int64_t n, Boxes bx, int ib,
+                                                      const uint64_t *__restrict__ key,
+                                                      const uint32_t *__restrict__ idx, Sorted to) {
+    const int64_t s = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
+    place_padding(n, s, to);
+    if (s >= n) return;
+    const uint64_t kw = key[s];
+    place_particle(pos, bx, s, kPacked ? kw >> ib : kw,
+                   kPacked ? (uint32_t)(kw & ((1ull << ib) - 1ull)) : idx[s], to);
+}
+
+// One stable pass of a workgroup over m words in memory, tile by tile, the
+// digits' places running on from one tile to the next.
+template <int NW = kRadixWaves, class Row>
+__device__ __forceinline__ void big_bucket_pass(const uint64_t *src, uint64_t *dst, int64_t m, int sh, int D,
+                                                uint32_t *run, Row o, uint32_t *s_tot) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x;
+    const int nd = 1 << D;
+    const uint32_t dmask = (uint32_t)(nd - 1);
+    for (int d = tid; d < nd; d += 64 * NW) run[d] = 0u;
+    __syncthreads();
+    for (int64_t e = tid; e < m; e += 64 * NW) atomicAdd(&run[(uint32_t)(src[e] >> sh) & dmask], 1u);
+    __syncthreads();
+    const uint32_t first = block_scan_excl<NW>(tid < nd ? run[tid] : 0u, s_tot);
+    __syncthreads();
+    if (tid < nd) run[tid] = first;
+    for (int64_t t0 = 0; t0 < m; t0 += 64 * NW * kRadixIters) {
+        const int64_t e0 = t0 + w * (64 * kRadixIters) + lane;
+        for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
+        uint64_t k[kRadixIters];
+#pragma unroll
+        for (int it = 0; it < kRadixIters; it++) k[it] = e0 + it * 64 < m ? src[e0 + it * 64] : 0ull;
+        uint32_t place[kRadixIters];
+#pragma unroll
+        for (int it = 0; it < kRadixIters; it++) {
+            const bool act = e0 + it * 64 < m;
+            const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
+            place[it] = step_place(d, D, act);
+            if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
+        }
+        __syncthreads();
+        if (tid < nd) {
+            uint32_t at = run[tid];
+            for (int x = 0; x < NW; x++) {
+                const uint32_t c = o[x][tid];
+                o[x][tid] = at;
+                at += c;
+            }
+            run[tid] = at;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kRadixIters; it++) {
+            const bool act = e0 + it * 64 < m;
+            const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
+            const uint32_t at = act ? o[w][d] : 0u;
+            if (act) dst[at + (place[it] & 0xffu)] = k[it];
+            if (act && (place[it] >> 16)) o[w][d] = at + ((place[it] >> 8) & 0xffu);
+        }
+        __syncthreads();
+    }
+}
+
+// One bucket of the partition pass (the keys with the same bits above shift +
+// bits), sorted by the bits [shift, shift + bits) with a stable radix sort of
+// its own, then its particles' sorted records.  Bucket b holds the elements
+// [start[b * stride], start[(b + 1) * stride]) (the whole input when start is
+// null).  Up to kLocal elements stay in registers and LDS: each pass counts the
+// digits of every wavefront's run of consecutive elements, places the elements
+// in LDS in digit order and reads them back.  A larger bucket (a halo's centre)
+// is sorted tile by tile between its ranges of kin and tmp.
+// On small inputs the passes are launch latency: four passes of count, two scan
+// launches and scatter (and k_bin_place) took 92 us on the 64^3 box.
+constexpr int kLocalIters = 16;
+constexpr int kLocal = 256 * kLocalIters;
+__global__ __launch_bounds__(256) void k_bucket_sort(uint64_t *kin, uint64_t *tmp, int64_t n,
+                                                     const uint32_t *__restrict__ start, int64_t stride, int shift,
+                                                     int bits, const float *__restrict__ pos, Boxes bx, int ib,
+                                                     Sorted to) {
+    __shared__ uint32_t o[kRadixWaves][1 << kRadixMaxBits];
+    __shared__ uint32_t lstart[1 << kRadixMaxBits], run[1 << kRadixMaxBits];
+    __shared__ uint32_t s_tot[kRadixWaves];
+    __shared__ uint64_t sk[kLocal];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x;
+    if (blockIdx.x == 0) place_padding(n, tid, to);
+    const int64_t b0 = start ? (int64_t)start[blockIdx.x * stride] : 0;
+    const int64_t m = (start ? (int64_t)start[(blockIdx.x + 1) * stride] : n) - b0;
+    if (m <= 0) return;
+    const int passes = (bits + kRadixMaxBits - 1) / kRadixMaxBits;
+    const int D = passes > 0 ? (bits + passes - 1) / passes : 0;
+    const int nd = 1 << D;
+    const uint32_t dmask = (uint32_t)(nd - 1);
+    uint64_t *src = kin + b0, *dst = tmp + b0;
+    if (m <= kLocal) {
+        const int iters = (int)((m + 255) / 256);  // elements per thread
+        const int e0 = w * 64 * iters + lane;
+        uint64_t k[kLocalIters];
+#pragma unroll
+        for (int it = 0; it < kLocalIters; it++) k[it] = it < iters && e0 + it * 64 < m ? src[e0 + it * 64] : 0ull;
+        for (int p = 0; p < passes; p++) {
+            const int sh = shift + p * D;
+            for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
+            uint32_t place[kLocalIters];
+#pragma unroll
+            for (int it = 0; it < kLocalIters; it++) {
+                place[it] = 0u;
+                if (it < iters) {
+                    const bool act = e0 + it * 64 < m;
+                    const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
+                    place[it] = step_place(d, D, act);
+                    if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
+                }
+            }
+            __syncthreads();
+            digit_starts<1>(o, nd, lstart, s_tot);
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < kLocalIters; it++) {
+                if (it < iters) {
+                    const bool act = e0 + it * 64 < m;
+                    const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
+                    const uint32_t at = act ? o[w][d] : 0u;
+                    if (act) sk[at + (place[it] & 0xffu)] = k[it];
+                    if (act && (place[it] >> 16)) o[w][d] = at + ((place[it] >> 8) & 0xffu);
+                }
+            }
+            __syncthreads();
+            if (p + 1 < passes) {
+#pragma unroll
+                for (int it = 0; it < kLocalIters; it++)
+                    if (it < iters && e0 + it * 64 < m) k[it] = sk[e0 + it * 64];
+                __syncthreads();
+            }
+        }
+        if (passes == 0) {
+#pragma unroll
+            for (int it = 0; it < kLocalIters; it++)
+                if (it < iters && e0 + it * 64 < m) sk[e0 + it * 64] = k[it];
+            __syncthreads();
+        }
+        for (int64_t s = tid; s < m; s += 256) {
+            const uint64_t kw = sk[s];
+            place_particle(pos, bx, b0 + s, kw >> ib, (uint32_t)(kw & ((1ull << ib) - 1ull)), to);
+        }
+        return;
+    }
+    for (int p = 0; p < passes; p++) {
+        big_bucket_pass(src, dst, m, shift + p * D, D, run, o, s_tot);
+        uint64_t *const t = src;
+        src = dst;
+        dst = t;
+    }
+    for (int64_t s = tid; s < m; s += 256) {
+        const uint64_t kw = src[s];
+        place_particle(pos, bx, b0 + s, kw >> ib, (uint32_t)(kw & ((1ull << ib) - 1ull)), to);
+    }
+}
+
+// ------------------------------------------------- the sort that carries positions
+// Two stable passes over digits of at most kRecBits bits, the low top bits and
+// then the high ones, move records (x, y, z, index) instead of key words: the
+// input positions are read in order twice and never gathered, where the gather
+// of 12 bytes per particle took a 128-byte line each (460 us on the 256^3 box,
+// 4.7 ms on the 512^3 one).  The key is computed again from the position
+// wherever it is needed; the second digit travels beside the record.
+constexpr int kRecBits = 9;
+
+struct RecPlan {
+    int low;     // key bits below the top ones, sorted within a bucket
+    int dl, dh;  // bits of the first (low) and second (high) digit
+};
+
+// Positions of the elements e0, e0 + step, ... of this thread in input order,
+// loaded together (past the end: the last one's).
+struct TilePos {
+    float x[kRadixIters], y[kRadixIters], z[kRadixIters];
+};
+__device__ __forceinline__ void tile_positions(const float *__restrict__ pos, int64_t n, int64_t e0, int step,
+                                               TilePos &p) {
+#pragma unroll
+    for (int u = 0; u < kRadixIters; u++) {
+        const int64_t i = e0 + (int64_t)u * step;
+        const int64_t q = i < n ? i : n - 1;
+        p.x[u] = pos[3 * q + 0];
+        p.y[u] = pos[3 * q + 1];
+        p.z[u] = pos[3 * q + 2];
+    }
+}
+
+// f(constants of the box of input particle i): of the only box (g0, loaded once
+// by the kernel), or through the box table.
+template <bool kOne, class F>
+__device__ __forceinline__ void with_box(const Boxes &bx, const Geo &g0, uint32_t i, F f) {
+    if constexpr (kOne) f(g0);
+    else per_box(bx, box_of(bx, i), f);
+}
+
+// The top key bits of the position of input particle i; *ok: it lies in its box.
+template <bool kOne>
+__device__ __forceinline__ uint32_t top_key(const Boxes &bx, const Geo &g0, uint32_t i, float x, float y, float z, int low, bool *ok) {
+    uint32_t top = 0;
+    bool in = true;
+    with_box<kOne>(bx, g0, i, [&](const Geo &g) {
+        in = inside(g, x, y, z);
+        top = (uint32_t)(spot_of(g, bx.nsub_max, x, y, z).key >> low);
+    });
+    *ok = in;
+    return top;
+}
+
+template <bool kOne>
+__global__ __launch_bounds__(256) void k_rec_count(const float *__restrict__ pos, int64_t n, Boxes bx, RecPlan rp,
+                                                   int64_t ntiles, uint32_t *__restrict__ hist,
+                                                   int32_t *__restrict__ err) {
+    __shared__ uint32_t h[1 << kRecBits];
+    const int64_t t = xcd_block();
+    const int nd = 1 << rp.dl;
+    for (int d = threadIdx.x; d < nd; d += 256) h[d] = 0u;
+    const Geo g0 = box_constants(bx, 0);
+    TilePos p;
+    tile_positions(pos, n, t * kTile + threadIdx.x, 256, p);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRadixIters; u++) {
+        const int64_t i = t * kTile + threadIdx.x + u * 256;
+        if (i < n) {
+            bool ok;
+            const uint32_t top = top_key<kOne>(bx, g0, (uint32_t)i, p.x[u], p.y[u], p.z[u], rp.low, &ok);
+            if (!ok) flag_error(err, 1, box_of(bx, (uint32_t)i));
+            atomicAdd(&h[top & (uint32_t)(nd - 1)], 1u);
+        }
+    }
+    counts_out(h, nd, t, ntiles, hist);
+}
+
+// Counts of the second digit (in the order the first pass left).
+__global__ __launch_bounds__(256) void k_rec_count2(const uint16_t *__restrict__ digit, int64_t n, int D,
+                                                    int64_t ntiles, uint32_t *__restrict__ hist) {
+    __shared__ uint32_t h[1 << kRecBits];
+    const int64_t t = xcd_block();
+    const int nd = 1 << D;
+    for (int d = threadIdx.x; d < nd; d += 256) h[d] = 0u;
+    const int64_t base = t * kTile + threadIdx.x;
+    uint16_t v[kRadixIters];
+#pragma unroll
+    for (int it = 0; it < kRadixIters; it++) v[it] = base + it * 256 < n ? digit[base + it * 256] : (uint16_t)0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kRadixIters; it++)
+        if (base + it * 256 < n) atomicAdd(&h[v[it]], 1u);
+    counts_out(h, nd, t, ntiles, hist);
+}
+
+// Stable scatter of one tile's records by a digit.  kFirst: the records come
+// from the input positions, by the first digit, with the second beside them;
+// else from the first pass's records, by the second digit.
+template <bool kFirst, bool kOne>
+__global__ __launch_bounds__(256) void k_rec_scatter(const float *__restrict__ pos, const float4 *__restrict__ rin,
+                                                     const uint16_t *__restrict__ din, int64_t n, Boxes bx,
+                                                     RecPlan rp, int64_t ntiles,
+                                                     const uint32_t *__restrict__ hscan, float4 *__restrict__ rout,
+                                                     uint16_t *__restrict__ dout) {
+    constexpr int kPer = (1 << kRecBits) / 256;
+    __shared__ uint32_t o[kRadixWaves][1 << kRecBits];
+    __shared__ uint32_t lstart[1 << kRecBits];
+    __shared__ uint32_t s_tot[kRadixWaves];
+    __shared__ float4 sr[kTile];
+    __shared__ uint32_t sd[kTile];  // digit of this pass, and the second digit above it
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x;
+    const int64_t t = xcd_block();
+    const int D = kFirst ? rp.dl : rp.dh, nd = 1 << D;
+    for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
+    const int64_t base = t * kTile + (int64_t)w * (64 * kRadixIters) + lane;
+    TilePos p;
+    uint32_t id[kRadixIters], dig[kRadixIters], place[kRadixIters];
+    if (kFirst) {
+        const Geo g0 = box_constants(bx, 0);
+        tile_positions(pos, n, base, 64, p);
+#pragma unroll
+        for (int it = 0; it < kRadixIters; it++) {
+            const int64_t e = base + it * 64;
+            id[it] = (uint32_t)(e < n ? e : n - 1);
+            bool ok;
+            const uint32_t top = top_key<kOne>(bx, g0, id[it], p.x[it], p.y[it], p.z[it], rp.low, &ok);
+            dig[it] = (top & (uint32_t)(nd - 1)) | ((top >> D) << 16);
+        }
+    } else {
+#pragma unroll
+        for (int it = 0; it < kRadixIters; it++) {
+            const int64_t e = base + it * 64;
+            const float4 r = rin[e < n ? e : n - 1];
+            p.x[it] = r.x;
+            p.y[it] = r.y;
+            p.z[it] = r.z;
+            id[it] = __float_as_uint(r.w);
+            dig[it] = din[e < n ? e : n - 1];
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < kRadixIters; it++) {
+        const bool act = base + it * 64 < n;
+        const uint32_t d = dig[it] & 0xffffu;
+        place[it] = step_place(d, D, act);
+        if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
+    }
+    __syncthreads();
+    digit_starts<kPer>(o, nd, lstart, s_tot);
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kRadixIters; it++) {
+        const bool act = base + it * 64 < n;
+        const uint32_t d = dig[it] & 0xffffu;
+        const uint32_t start = act ? o[w][d] : 0u;
+        if (act) {
+            sr[start + (place[it] & 0xffu)] = make_float4(p.x[it], p.y[it], p.z[it], __uint_as_float(id[it]));
+            sd[start + (place[it] & 0xffu)] = dig[it];
+        }
+        if (act && (place[it] >> 16)) o[w][d] = start + ((place[it] >> 8) & 0xffu);
+    }
+    __syncthreads();
+    for (int d = tid; d < nd; d += 256) lstart[d] = hscan[(int64_t)d * ntiles + t] - lstart[d];
+    __syncthreads();
+    const int64_t rem = n - t * kTile;
+    const int cnt = rem < kTile ? (int)rem : (int)kTile;
+    for (int lp = tid; lp < cnt; lp += 256) {
+        const uint32_t d = sd[lp];
+        const uint32_t dst = lstart[d & 0xffffu] + (uint32_t)lp;
+        rout[dst] = sr[lp];
+        if (kFirst) dout[dst] = (uint16_t)(d >> 16);
+    }
+}
+
+// First element of every bucket (high digit, low digit) after the second pass,
+// and the total at the end: with p the first element of the low digit after
+// the first pass, those of a high digit before p are the scanned count of p's
+// tile and the ones of the tile before p.  One workgroup per low digit.
+__global__ __launch_bounds__(256) void k_rec_starts(int64_t n, RecPlan rp, int64_t ntiles,
+                                                    const uint32_t *__restrict__ first,
+                                                    const uint32_t *__restrict__ hscan,
+                                                    const uint16_t *__restrict__ digit,
+                                                    uint32_t *__restrict__ starts) {
+    __shared__ uint32_t h[1 << kRecBits];
+    const int nh = 1 << rp.dh, nl = 1 << rp.dl;
+    const int64_t p = first[blockIdx.x];
+    const int64_t t = p < n ? p / kTile : ntiles - 1, t0 = t * kTile;
+    for (int d = threadIdx.x; d < nh; d += 256) h[d] = 0u;
+    __syncthreads();
+    for (int64_t e = t0 + threadIdx.x; e < p; e += 256) atomicAdd(&h[digit[e]], 1u);
+    __syncthreads();
+    for (int d = threadIdx.x; d < nh; d += 256)
+        starts[(int64_t)d * nl + blockIdx.x] = hscan[(int64_t)d * ntiles + t] + h[d];
+    if (blockIdx.x == 0 && threadIdx.x == 0) starts[(int64_t)nh * nl] = (uint32_t)n;
+}
+
+// The first elements of the low digits after the first pass, kept from its
+// scanned counts (the second pass's take their place), and after them the zero
+// that the list of large buckets starts from.
+__global__ __launch_bounds__(256) void k_rec_first(int nl, int64_t ntiles, const uint32_t *__restrict__ hscan,
+                                                   uint32_t *__restrict__ first) {
+    const int d = blockIdx.x * 256 + threadIdx.x;
+    if (d <= nl) first[d] = d < nl ? hscan[(int64_t)d * ntiles] : 0u;
+}
+
+// The sorted records of slot s from the particle's record and its key (the low
+// 32 bits: the sub-cell is what is left of it beyond the cell).
+template <bool kOne>
+__device__ __forceinline__ void place_record(const float4 &r, uint32_t key, const Boxes &bx, const Geo &g0, int64_t s,
+                                             const Sorted &to) {
+    with_box<kOne>(bx, g0, __float_as_uint(r.w), [&](const Geo &g) {
+        const int cx = cell_coord(r.x, g), cy = cell_coord(r.y, g), cz = cell_coord(r.z, g);
+        const uint32_t c =
+            g.cell_base + ((uint32_t)cz * (uint32_t)g.nc + (uint32_t)cy) * (uint32_t)g.nc + (uint32_t)cx;
+        to.spos[s] = r;
+        const float xl = (float)(((double)r.x - (double)cx * g.cell) * g.inv_b);
+        const float yl = (float)(((double)r.y - (double)cy * g.cell) * g.inv_b);
+        const float zl = (float)(((double)r.z - (double)cz * g.cell) * g.inv_b);
+        to.sloc[s] = make_float4(xl, yl, zl, __uint_as_float(c));
+        if (to.pq) {
+            // coordinates about the cell centre and minus their squared norm
+            const float c0 = 0.5f * g.cellb;
+            const float xc = xl - c0, yc = yl - c0, zc = zl - c0;
+            to.pq[s] = make_float4(xc, yc, zc, -(xc * xc + yc * yc + zc * zc));
+        }
+        to.ssub[s] = (uint16_t)(key - c * (uint32_t)bx.nsub_max);
+    });
+}
+
+// Buckets: their particles sorted by the low key bits (words of low bits and
+// place in the bucket, in registers and LDS) and their sorted records written.
+// A bucket is one workgroup's chain of dependent steps, so its length decides:
+// 256 threads take buckets of up to 8 elements each (2048 particles) and list
+// the larger ones (in `big`), which 1024 threads take with up to 16 each, one
+// workgroup per listed bucket (a grid striding over the list).  Beyond 16 384
+// particles a bucket is sorted tile by tile in its share of `work` (16 bytes
+// per particle, as two arrays of 64-bit words).  (256 threads with 16 elements
+// and the tile sort beyond 4096 had 2.8 wavefronts per SIMD on average on the
+// 256^3 box, most of the time a few long buckets: 563 us.)
+constexpr int kLowMost = 18;  // low key bits beside 14 bits of place
+template <int NW, int ITERS, bool kListed, bool kOne>
+__global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict__ rec, int64_t n,
+                                                        const uint32_t *__restrict__ starts, int low, Boxes bx,
+                                                        uint64_t *work, uint32_t *__restrict__ big,
+                                                        uint32_t *__restrict__ nbig, Sorted to) {
+    constexpr int NT = 64 * NW, kMost = NT * ITERS, kPlace = 14;
+    static_assert(kMost <= 1 << kPlace, "14 bits of place");
+    __shared__ uint32_t o[NW][1 << kRadixMaxBits];
+    __shared__ uint32_t lstart[1 << kRadixMaxBits], run[kListed ? 1 << kRadixMaxBits : 1];
+    __shared__ uint32_t s_tot[NW];
+    __shared__ uint32_t sk[kMost];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x;
+    const int passes = (low + kRadixMaxBits - 1) / kRadixMaxBits;
+    const int D = passes > 0 ? (low + passes - 1) / passes : 0;
+    const int nd = 1 << D;
+    const uint32_t dmask = (uint32_t)(nd - 1);
+    const uint64_t lmask = (1ull << low) - 1ull;
+    const Geo g0 = box_constants(bx, 0);
+    if (!kListed && blockIdx.x == 0) place_padding(n, tid, to);
+    const uint32_t nq = kListed ? *nbig : gridDim.x;
+    for (uint32_t q = blockIdx.x; q < nq; q += gridDim.x) {
+        const int64_t bucket = kListed ? big[q] : xcd_block();
+        const int64_t b0 = starts[bucket], m = (int64_t)starts[bucket + 1] - b0;
+        if (m <= 0) return;  // only unlisted buckets, one per workgroup, are empty
+        if (!kListed && m > kMost) {
+            if (tid == 0) big[atomicAdd(nbig, 1u)] = (uint32_t)bucket;
+            return;
+        }
+        auto low_key = [&](const float4 &r) -> uint32_t {
+            uint32_t k = 0;
+            with_box<kOne>(bx, g0, __float_as_uint(r.w), [&](const Geo &g) {
+                k = (uint32_t)(spot_of(g, bx.nsub_max, r.x, r.y, r.z).key & lmask);
+            });
+            return k;
+        };
+        const uint32_t high = (uint32_t)((uint64_t)bucket << low);  // of the keys' low 32 bits
+        if (m <= kMost) {
+            const int iters = (int)((m + NT - 1) / NT);  // elements per thread
+            const int e0 = w * 64 * iters + lane;
+            uint32_t k[ITERS];
+            // keys to LDS in order (two records in flight), then each thread's
+            // elements to registers: a rolled loop keeps the key arithmetic out
+            // of the unrolled passes
+            for (int it = 0; it < iters; it += 2) {
+                const int ea = e0 + it * 64, eb = ea + 64;
+                const bool ina = ea < m, inb = it + 1 < iters && eb < m;
+                const float4 ra = rec[b0 + (ina ? ea : 0)], rb = rec[b0 + (inb ? eb : 0)];
+                const uint32_t ka = low_key(ra), kb = low_key(rb);
+                if (ina) sk[ea] = (ka << kPlace) | (uint32_t)ea;
+                if (inb) sk[eb] = (kb << kPlace) | (uint32_t)eb;
+            }
+#pragma unroll
+            for (int it = 0; it < ITERS; it++) k[it] = it < iters && e0 + it * 64 < m ? sk[e0 + it * 64] : 0u;
+            __syncthreads();
+            for (int p = 0; p < passes; p++) {
+                const int sh = kPlace + p * D;
+                for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
+                uint32_t place[ITERS];
+#pragma unroll
+                for (int it = 0; it < ITERS; it++) {
+                    place[it] = 0u;
+                    if (it < iters) {
+                        const bool act = e0 + it * 64 < m;
+                        const uint32_t d = (k[it] >> sh) & dmask;
+                        place[it] = step_place(d, D, act);
+                        if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
+                    }
+                }
+                __syncthreads();
+                digit_starts<1, NW>(o, nd, lstart, s_tot);
+                __syncthreads();
+#pragma unroll
+                for (int it = 0; it < ITERS; it++) {
+                    if (it < iters) {
+                        const bool act = e0 + it * 64 < m;
+                        const uint32_t d = (k[it] >> sh) & dmask;
+                        const uint32_t at = act ? o[w][d] : 0u;
+                        if (act) sk[at + (place[it] & 0xffu)] = k[it];
+                        if (act && (place[it] >> 16)) o[w][d] = at + ((place[it] >> 8) & 0xffu);
+                    }
+                }
+                __syncthreads();
+                if (p + 1 < passes) {
+#pragma unroll
+                    for (int it = 0; it < ITERS; it++)
+                        if (it < iters && e0 + it * 64 < m) k[it] = sk[e0 + it * 64];
+                    __syncthreads();
+                }
+            }
+            for (int s = tid; s < m; s += 2 * NT) {
+                const bool two = s + NT < m;
+                const uint32_t wa = sk[s], wb = two ? sk[s + NT] : wa;
+                const float4 ra = rec[b0 + (wa & ((1u << kPlace) - 1u))], rb = rec[b0 + (wb & ((1u << kPlace) - 1u))];
+                place_record<kOne>(ra, high + (wa >> kPlace), bx, g0, b0 + s, to);
+                if (two) place_record<kOne>(rb, high + (wb >> kPlace), bx, g0, b0 + s + NT, to);
+            }
+        } else if constexpr (kListed) {
+            uint64_t *src = work + 2 * b0, *dst = src + m;
+            for (int64_t e = tid; e < m; e += NT) src[e] = ((uint64_t)low_key(rec[b0 + e]) << 32) | (uint64_t)e;
+            __syncthreads();
+            for (int p = 0; p < passes; p++) {
+                big_bucket_pass<NW>(src, dst, m, 32 + p * D, D, run, o, s_tot);
+                uint64_t *const t = src;
+                src = dst;
+                dst = t;
+            }
+            for (int64_t s = tid; s < m; s += NT)
+                place_record<kOne>(rec[b0 + (int64_t)(src[s] & 0xffffffffull)], high + (uint32_t)(src[s] >> 32), bx,
+                                   g0, b0 + s, to);
+        }
+        if (!kListed) return;
+        __syncthreads();  // LDS is free for the next listed bucket
+    }
 }
 
 // Cell offsets: off[c] = first sorted particle of cell c (the next cell's
@@ -498,31 +1074,66 @@ int bit_width(uint64_t x) {
     return b;
 }
 
-// Radix pass plan: key bits, index bits when packed (0 = separate payload).
-struct RadixPlan {
-    int passes, D, ib;
+// Particles up to which the sort is one partition pass over (key, index) words:
+// up to 1024 buckets of 512 particles on average.  One bucket is then the
+// longest chain: with 1300 on average (1.3e6 particles) the largest buckets
+// passed kLocal and the bucket sort took 140 us instead of 33 us on 2.6e5.
+constexpr int64_t kPartitionMost = (int64_t)1 << 19;
+
+// Sort plan: key bits; index bits when packed (0 = separate payload), and top
+// bits of the buckets of the partition pass (-1: none); the digits of the sort
+// that carries positions (dl < 0: none); the passes of D bits of the radix sort.
+struct SortPlan {
+    int bits, ib, top;
+    RecPlan rec;
+    int passes, D;
 };
 
-RadixPlan radix_plan(int64_t n, int64_t ncell, int nsub_max) {
+SortPlan sort_plan(int64_t n, int64_t ncell, int nsub_max) {
     const uint64_t nkeys = (uint64_t)ncell * (uint64_t)nsub_max;
-    int bits = bit_width(nkeys - 1);
-    if (bits < 1) bits = 1;
-    RadixPlan r;
-    r.passes = (bits + kRadixMaxBits - 1) / kRadixMaxBits;
-    r.D = (bits + r.passes - 1) / r.passes;
+    SortPlan r;
+    r.bits = bit_width(nkeys - 1);
+    if (r.bits < 1) r.bits = 1;
+    r.passes = (r.bits + kRadixMaxBits - 1) / kRadixMaxBits;
+    r.D = (r.bits + r.passes - 1) / r.passes;
     int ib = bit_width((uint64_t)(n > 1 ? n - 1 : 1));
-    r.ib = ib + bits <= 64 ? ib : 0;
-    // HF_RADIX_PAYLOAD=1 forces the separate-payload form (used by tests; it
-    // is otherwise taken only when key and index need more than 64 bits)
+    r.ib = ib + r.bits <= 64 ? ib : 0;
+    // HF_RADIX_PAYLOAD=1 forces the radix sort with a separate payload (used by
+    // tests; it is otherwise taken only when key and index need more than 64
+    // bits)
     const char *force = getenv("HF_RADIX_PAYLOAD");
-    if (force && force[0] == '1') r.ib = 0;
+    const bool radix = force && force[0] == '1';
+    if (radix) r.ib = 0;
+    r.top = -1;
+    r.rec = RecPlan{0, -1, -1};
+    if (radix) return r;
+    if (r.ib > 0 && n <= kPartitionMost) {
+        r.top = bit_width((uint64_t)((n - 1) / 256));
+        if (r.top > kPartBits) r.top = kPartBits;
+        if (r.top > r.bits) r.top = r.bits;
+        return r;
+    }
+    // the records' second buffer lies over the sub-cell tables (2 (nsub + 1)
+    // bytes per particle); buckets of 300 to 1000 particles on average, so many
+    // that the low bits fit beside the place in the bucket
+    int top = bit_width((uint64_t)((n - 1) / 1024));
+    if (top < r.bits - kLowMost) top = r.bits - kLowMost;
+    if (top > 2 * kRecBits) top = 2 * kRecBits;
+    if (top > r.bits) top = r.bits;
+    // (a grid of far more cells than particles would leave buckets of a few)
+    if (nsub_max + 1 >= 8 && top >= 2 && r.bits - top <= kLowMost && (n >> top) >= 128) {
+        r.rec.low = r.bits - top;
+        r.rec.dl = top / 2;
+        r.rec.dh = top - r.rec.dl;
+    }
     return r;
 }
 
 int64_t radix_hist_len(int64_t n) {
     // room for the widest digit, so that every sort of up to n keys fits
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    return ((int64_t)1 << kRadixMaxBits) * (ntiles > 0 ? ntiles : 1) + 1;
+    const int bits = n <= kPartitionMost ? kPartBits : kRecBits;
+    return ((int64_t)1 << bits) * (ntiles > 0 ? ntiles : 1) + 1;
 }
 
 uint64_t *radix_sort_keys(uint64_t *a, uint64_t *b, int64_t n, int lo, int bits, Work &w, hipStream_t s) {
@@ -537,8 +1148,8 @@ uint64_t *radix_sort_keys(uint64_t *a, uint64_t *b, int64_t n, int lo, int bits,
         hipLaunchKernelGGL(k_radix_count, dim3((unsigned)ntiles), dim3(256), 0, s, cur, n, shift, D, ntiles,
                            w.rhist);
         scan_u32(w.rhist, w.rscan, hl, w.scan_tmp, s);
-        hipLaunchKernelGGL(k_radix_scatter<true>, dim3((unsigned)ntiles), dim3(256), 0, s, cur, nullptr, n, shift,
-                           D, ntiles, w.rscan, nxt, nullptr);
+        hipLaunchKernelGGL((k_radix_scatter<true, kRadixMaxBits>), dim3((unsigned)ntiles), dim3(256), 0, s, cur,
+                           nullptr, n, shift, D, ntiles, w.rscan, nxt, nullptr);
         uint64_t *t = cur;
         cur = nxt;
         nxt = t;
@@ -547,33 +1158,84 @@ uint64_t *radix_sort_keys(uint64_t *a, uint64_t *b, int64_t n, int lo, int bits,
 }
 
 void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Work &w, hipStream_t s) {
-    const RadixPlan r = radix_plan(n, ncell, bx.nsub_max);
+    const SortPlan r = sort_plan(n, ncell, bx.nsub_max);
     const bool packed = r.ib > 0;
-    hipLaunchKernelGGL(k_bin_key, dim3(blocks((n + kKeyIlp - 1) / kKeyIlp)), dim3(kBlock), 0, s, pos, n, bx, r.ib,
-                       w.rkey[0], w.err);
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    const int64_t hl = ((int64_t)1 << r.D) * ntiles;
-    int cur = 0;
-    for (int p = 0; p < r.passes; p++) {
-        const int shift = r.ib + p * r.D;
-        hipLaunchKernelGGL(k_radix_count, dim3((unsigned)ntiles), dim3(256), 0, s, w.rkey[cur], n, shift, r.D,
-                           ntiles, w.rhist);
-        scan_u32(w.rhist, w.rscan, hl, w.scan_tmp, s);
+    const dim3 tiles((unsigned)ntiles);
+    const Sorted to{w.spos, w.sloc, w.pq, w.ssub};
+    if (r.top >= 0) {
+        const int low = r.bits - r.top, shift = r.ib + low;
+        hipLaunchKernelGGL(k_bin_key, tiles, dim3(256), 0, s, pos, n, bx, r.ib, w.rkey[0], shift, r.top, ntiles,
+                           w.rhist, w.err);
+        const uint32_t *start = nullptr;
+        int cur = 0;
+        if (r.top > 0) {
+            scan_u32(w.rhist, w.rscan, ((int64_t)1 << r.top) * ntiles, w.scan_tmp, s);
+            hipLaunchKernelGGL((k_radix_scatter<true, kPartBits>), tiles, dim3(256), 0, s, w.rkey[0], nullptr, n,
+                               shift, r.top, ntiles, w.rscan, w.rkey[1], nullptr);
+            start = w.rscan;
+            cur = 1;
+        }
+        hipLaunchKernelGGL(k_bucket_sort, dim3(1u << r.top), dim3(256), 0, s, w.rkey[cur], w.rkey[cur ^ 1], n, start,
+                           ntiles, r.ib, low, pos, bx, r.ib, to);
+    } else if (r.rec.dl >= 0) {
+        // first pass into the radix key block (16 bytes per particle), second
+        // into the sub-cell tables, which are written after the binning; the
+        // second digits lie in the sub-cell indices' array and the buckets'
+        // starts in the radix payload (both free until the buckets are sorted,
+        // which read neither after writing them)
+        float4 *ra = reinterpret_cast<float4 *>(w.rkey[0]), *rb = reinterpret_cast<float4 *>(w.subtab);
+        const int nl = 1 << r.rec.dl, nh = 1 << r.rec.dh;
+        const bool one = bx.nbox == 1;
+        hipLaunchKernelGGL(one ? k_rec_count<true> : k_rec_count<false>, tiles, dim3(256), 0, s, pos, n, bx, r.rec,
+                           ntiles, w.rhist, w.err);
+        scan_u32(w.rhist, w.rscan, (int64_t)nl * ntiles, w.scan_tmp, s);
+        hipLaunchKernelGGL((one ? k_rec_scatter<true, true> : k_rec_scatter<true, false>), tiles, dim3(256), 0, s, pos,
+                           nullptr, nullptr, n, bx, r.rec, ntiles, w.rscan, ra, w.ssub);
+        hipLaunchKernelGGL(k_rec_first, dim3((unsigned)(nl + 1 + 255) / 256), dim3(256), 0, s, nl, ntiles, w.rscan,
+                           w.rval[1]);
+        hipLaunchKernelGGL(k_rec_count2, tiles, dim3(256), 0, s, w.ssub, n, r.rec.dh, ntiles, w.rhist);
+        scan_u32(w.rhist, w.rscan, (int64_t)nh * ntiles, w.scan_tmp, s);
+        hipLaunchKernelGGL((k_rec_scatter<false, true>), tiles, dim3(256), 0, s, nullptr, ra, w.ssub, n, bx, r.rec,
+                           ntiles, w.rscan, rb, nullptr);
+        hipLaunchKernelGGL(k_rec_starts, dim3((unsigned)nl), dim3(256), 0, s, n, r.rec, ntiles, w.rval[1], w.rscan,
+                           w.ssub, w.rval[0]);
+        // the list of large buckets and its count after those first elements
+        uint32_t *nbig = w.rval[1] + nl, *big = nbig + 1;
+        hipLaunchKernelGGL((one ? k_rec_bucket<4, 8, false, true> : k_rec_bucket<4, 8, false, false>),
+                           dim3((unsigned)(nl * nh)), dim3(256), 0, s, rb, n, w.rval[0], r.rec.low, bx, w.rkey[0], big,
+                           nbig, to);
+        const int64_t most = n / 2048 + 1;  // more than 2048 particles each
+        hipLaunchKernelGGL((one ? k_rec_bucket<16, 16, true, true> : k_rec_bucket<16, 16, true, false>),
+                           dim3((unsigned)(most < 512 ? most : 512)), dim3(1024), 0, s, rb, n, w.rval[0], r.rec.low,
+                           bx, w.rkey[0], big, nbig, to);
+    } else {
+        hipLaunchKernelGGL(k_bin_key, tiles, dim3(256), 0, s, pos, n, bx, r.ib, w.rkey[0], r.ib, r.D, ntiles, w.rhist,
+                           w.err);
+        const int64_t hl = ((int64_t)1 << r.D) * ntiles;
+        int cur = 0;
+        for (int p = 0; p < r.passes; p++) {
+            const int shift = r.ib + p * r.D;
+            if (p > 0)
+                hipLaunchKernelGGL(k_radix_count, tiles, dim3(256), 0, s, w.rkey[cur], n, shift, r.D, ntiles,
+                                   w.rhist);
+            scan_u32(w.rhist, w.rscan, hl, w.scan_tmp, s);
+            if (packed)
+                hipLaunchKernelGGL((k_radix_scatter<true, kRadixMaxBits>), tiles, dim3(256), 0, s, w.rkey[cur],
+                                   nullptr, n, shift, r.D, ntiles, w.rscan, w.rkey[cur ^ 1], nullptr);
+            else
+                hipLaunchKernelGGL((k_radix_scatter<false, kRadixMaxBits>), tiles, dim3(256), 0, s, w.rkey[cur],
+                                   p == 0 ? nullptr : w.rval[cur], n, shift, r.D, ntiles, w.rscan,
+                                   w.rkey[cur ^ 1], w.rval[cur ^ 1]);
+            cur ^= 1;
+        }
         if (packed)
-            hipLaunchKernelGGL(k_radix_scatter<true>, dim3((unsigned)ntiles), dim3(256), 0, s, w.rkey[cur],
-                               nullptr, n, shift, r.D, ntiles, w.rscan, w.rkey[cur ^ 1], nullptr);
+            hipLaunchKernelGGL(k_bin_place<true>, dim3(blocks(n)), dim3(kBlock), 0, s, pos, n, bx, r.ib, w.rkey[cur],
+                               nullptr, to);
         else
-            hipLaunchKernelGGL(k_radix_scatter<false>, dim3((unsigned)ntiles), dim3(256), 0, s, w.rkey[cur],
-                               p == 0 ? nullptr : w.rval[cur], n, shift, r.D, ntiles, w.rscan,
-                               w.rkey[cur ^ 1], w.rval[cur ^ 1]);
-        cur ^= 1;
+            hipLaunchKernelGGL(k_bin_place<false>, dim3(blocks(n)), dim3(kBlock), 0, s, pos, n, bx, 0, w.rkey[cur],
+                               w.rval[cur], to);
     }
-    if (packed)
-        hipLaunchKernelGGL(k_bin_place<true>, dim3(blocks(n)), dim3(kBlock), 0, s, pos, n, bx, r.ib, w.rkey[cur],
-                           nullptr, w.spos, w.sloc, w.pq, w.ssub);
-    else
-        hipLaunchKernelGGL(k_bin_place<false>, dim3(blocks(n)), dim3(kBlock), 0, s, pos, n, bx, 0, w.rkey[cur],
-                           w.rval[cur], w.spos, w.sloc, w.pq, w.ssub);
     // slots 0..n (slot n closes the grid): one wavefront per 64
     hipLaunchKernelGGL(k_cell_offsets, dim3((unsigned)((n + 1 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n,
                        ncell, w.sloc, w.off);

@@ -74,6 +74,22 @@ __device__ __forceinline__ int box_of(const Boxes &bx, uint32_t i) {
     return b;
 }
 
+// The constants of box b (the same in every lane) in registers: word by word
+// through the constant address space, so scalar loads also where stores of the
+// kernel could lie in between (nothing writes the tables while kernels run);
+// words that are not used are not loaded.
+__device__ __forceinline__ Geo box_constants(const Boxes &bx, int b) {
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    const Words p = (Words)(uintptr_t)(bx.geo + b);
+    static_assert(sizeof(Geo) % 4 == 0, "Geo is a run of words");
+    uint32_t words[sizeof(Geo) / 4];
+#pragma unroll
+    for (size_t k = 0; k < sizeof(Geo) / 4; k++) words[k] = p[k];
+    Geo g;
+    __builtin_memcpy(&g, words, sizeof(Geo));
+    return g;
+}
+
 // f(constants of box b) for every lane, one box of the wavefront at a time
 // (nearly always one in all), with the box index in a scalar register, so that
 // the constants come with scalar loads.  With an index per lane every constant
@@ -87,20 +103,7 @@ __device__ __forceinline__ void per_box(const Boxes &bx, int b, F f) {
         int b0 = b1;
         asm volatile("" : "+s"(b0));
         const bool mine = b == b1;
-        if (mine) {
-            // word by word through the constant address space: scalar loads
-            // also where stores of the kernel could lie in between (nothing
-            // writes the tables while kernels run); unused words are dropped
-            typedef const __attribute__((address_space(4))) uint32_t *Words;
-            const Words p = (Words)(uintptr_t)(bx.geo + b0);
-            static_assert(sizeof(Geo) % 4 == 0, "Geo is a run of words");
-            uint32_t words[sizeof(Geo) / 4];
-#pragma unroll
-            for (size_t k = 0; k < sizeof(Geo) / 4; k++) words[k] = p[k];
-            Geo g;
-            __builtin_memcpy(&g, words, sizeof(Geo));
-            f(g);
-        }
+        if (mine) f(box_constants(bx, b0));
         todo &= ~__ballot(mine);
     }
 }

@@ -68,3 +68,77 @@ def test_fof_cell_links(ctx, n, side, kw):
     ref, _ = oracle.fof(pos, dens.cpu().numpy().astype(np.float64), box=side, **kw)
     np.testing.assert_array_equal(l0.cpu().numpy(), ref)
     assert groups == len(np.unique(ref[ref > 0]))
+
+
+# Binning: one partition pass and a sort per bucket up to 2^19 particles, two
+# passes that carry the positions beyond; a bucket is sorted in LDS up to 4096
+# particles.  HF_RADIX_PAYLOAD=1 takes the radix sort over all digits instead.
+# The sorted order is unique, so every output is the same.
+def _same_in_both_sorts(ctx, monkeypatch, pos, side, **kw):
+    print(f"[gpu] both sorts n={len(pos)} side={side} {kw}", file=sys.stderr, flush=True)
+    monkeypatch.delenv("HF_RADIX_PAYLOAD", raising=False)
+    a = gpu_find(ctx, pos, box=side, **kw)
+    monkeypatch.setenv("HF_RADIX_PAYLOAD", "1")
+    b = gpu_find(ctx, pos, box=side, **kw)
+    for key in ("density", "l0", "halo_id"):
+        np.testing.assert_array_equal(a[key], b[key])
+    for key in a["table"]:
+        np.testing.assert_array_equal(a["table"][key], b["table"][key])
+    return a
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 513, 2048, 2049, 4097, 65537, 131072])
+def test_bucket_sort_sizes(ctx, monkeypatch, n):
+    rng = np.random.default_rng(n)
+    side = max(float(n) ** (1.0 / 3.0), 1.5)
+    pos = (rng.random((n, 3)) * side).astype(np.float32)
+    pos[pos >= np.float32(side)] = 0.0
+    _same_in_both_sorts(ctx, monkeypatch, pos, side, mean_density=1.0)
+
+
+@pytest.mark.parametrize("background,clump,width", [
+    (5000, 4096, 0.3), (5000, 4097, 0.3), (5000, 9001, 0.3), (5000, 6000, 0.0),
+    (600000, 4096, 0.3), (600000, 9001, 0.3), (600000, 6000, 0.0),
+])
+def test_bucket_beyond_lds(ctx, monkeypatch, background, clump, width):
+    """A clump of one or two cells: a bucket of 4096 particles and more
+    (width 0: all at one point)."""
+    rng = np.random.default_rng(clump)
+    side = max(25.0, float(background) ** (1.0 / 3.0))
+    pos = np.concatenate([rng.random((background, 3)) * side, 12.0 + rng.random((clump, 3)) * width])
+    pos = pos.astype(np.float32)[rng.permutation(len(pos))]
+    pos[pos >= np.float32(side)] = 0.0
+    a = _same_in_both_sorts(ctx, monkeypatch, pos, side, mean_density=1.0)
+    assert a["n_halos"] >= 1
+    if width > 0.0:
+        assert len(density_violations(a["density"], oracle.density(pos, box=side, mean_density=1.0))) == 0
+
+
+@pytest.mark.parametrize("n,kw", [(2 ** 19, {}), (2 ** 19 + 1, {}), (2000003, {}), (2000003, {"l_fof": 0.13}),
+                                  (530000, {"mean_density": 64.0})])
+def test_sorts_agree(ctx, monkeypatch, n, kw):
+    """The last case has a grid of far more cells than particles."""
+    pos, side, _ = synth.small_box(n, seed=5, nmax=20000)
+    a = _same_in_both_sorts(ctx, monkeypatch, pos, side, **kw)
+    assert "mean_density" in kw or a["n_halos"] > 100
+
+
+def test_sort_over_box_boundaries(ctx, monkeypatch):
+    """Boxes whose particles share tiles and whose cells share buckets."""
+    import torch
+    from paper_2110_11408_amd import _lib
+    boxes = [synth.small_box(n, seed=n, nmax=n // 4 + 36) for n in
+             [1000, 300001, 4097, 200, 150000, 77777, 2047] + [600 + 7 * k for k in range(60)]]
+    pos = torch.from_numpy(np.concatenate([b[0] for b in boxes])).cuda()
+    offs = np.concatenate([[0], np.cumsum([len(b[0]) for b in boxes])])
+    params = [_lib.default_params(box=b[1]) for b in boxes]
+    print(f"[gpu] hf_find_batch boxes={len(boxes)} n={len(pos)}", file=sys.stderr, flush=True)
+    out = []
+    for force in (None, "1"):
+        if force:
+            monkeypatch.setenv("HF_RADIX_PAYLOAD", force)
+        r = ctx.find_batch(pos, offs, params, n_lanes=1)
+        out.append([r[k].cpu().numpy() for k in ("density", "l0_id", "halo_id")] +
+                   [torch.cat(r["halos"]).cpu().numpy()])
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
