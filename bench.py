@@ -60,7 +60,7 @@ STAGE_KEYS = ("ms_bin", "ms_density", "ms_fof", "ms_segment", "ms_candidates", "
 STAGE_KERNELS = {
     "density": ("k_density_dense", "k_density_sparse"),
     "bin": ("k_bin_key", "k_radix_count", "k_radix_scatter", "k_bucket_sort", "k_bin_place", "k_cell_offsets",
-            "k_bin_flags", "k_bin_lists", "k_sub_table"),
+            "k_bin_marks", "k_bin_lists", "k_sub_table"),
     "fof": ("k_fof_phase_a", "k_fof_cells", "k_fof_faces", "k_fof_cell_roots", "k_fof_dense", "k_fof_sparse",
             "k_fof_roots", "k_fof_keys"),
 }

@@ -45,6 +45,7 @@
 #include <stdlib.h>
 
 #include "hf_internal.h"
+#include "scan_tile.h"
 
 namespace hf {
 
@@ -309,10 +310,12 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restric
 
 // Sorted slot s, key k (without index bits), original index o: the particle's
 // two float4 records, its sub-cell and, when densities follow, its density
-// record.
+// record; and its cell once more on its own, for the kernels that only need
+// that.
 struct Sorted {
     float4 *__restrict__ spos, *__restrict__ sloc, *__restrict__ pq;
     uint16_t *__restrict__ ssub;
+    uint32_t *__restrict__ scell;
 };
 __device__ __forceinline__ void place_particle(const float *__restrict__ pos, const Boxes &bx, int64_t s, uint64_t k,
                                                uint32_t o, const Sorted &to) {
@@ -335,6 +338,7 @@ __device__ __forceinline__ void place_particle(const float *__restrict__ pos, co
         to.pq[s] = make_float4(xc, yc, zc, -(xc * xc + yc * yc + zc * zc));
     }
     to.ssub[s] = (uint16_t)sub;
+    to.scell[s] = c;
 }
 
 // pq's padding (read past a cell's end by the density kernel, never used).
@@ -727,6 +731,7 @@ __device__ __forceinline__ void place_record(const float4 &r, uint32_t key, cons
             to.pq[s] = make_float4(xc, yc, zc, -(xc * xc + yc * yc + zc * zc));
         }
         to.ssub[s] = (uint16_t)(key - c * (uint32_t)bx.nsub_max);
+        to.scell[s] = c;
     });
 }
 
@@ -865,7 +870,7 @@ __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict
 // it, found from a bitmask of the starts in each 256-cell window (a count of
 // set bits gives its rank among those slots) and a rank -> slot table.
 __global__ __launch_bounds__(kBlock) void k_cell_offsets(int64_t n, int64_t ncell,
-                                                         const float4 *__restrict__ sloc,
+                                                         const uint32_t *__restrict__ scell,
                                                          uint32_t *__restrict__ off) {
     __shared__ uint64_t s_bits[kBlock / 64][4];   // starts inside the current 256-cell window
     __shared__ uint8_t s_slot[kBlock / 64][64];   // slot of each rank
@@ -874,7 +879,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_offsets(int64_t n, int64_t ncel
     if (s0 > n) return;  // whole wavefront past slot n (uniform)
     const int64_t s = s0 + lane;
     auto C = [&](int64_t q) -> int64_t {
-        return q < 0 ? -1 : (q >= n ? ncell : (int64_t)__float_as_uint(sloc[q].w));
+        return q < 0 ? -1 : (q >= n ? ncell : (int64_t)scell[q]);
     };
     const int64_t hi = s <= n ? C(s) : ncell;
     const int64_t lo = s <= n ? C(s - 1) : ncell;
@@ -944,80 +949,129 @@ __global__ __launch_bounds__(kBlock) void k_cell_offsets(int64_t n, int64_t ncel
     }
 }
 
-// Flags per sorted particle: head of a dense chunk, head of a dense cell,
-// sparse.  A wavefront takes 64 consecutive particles and finds the bounds of
-// their cells from the cell ids of neighbouring particles (cell changes are
-// found by ballot); only a cell that starts before, or ends after, the
-// wavefront's particles reads its offset from the grid.
-__global__ __launch_bounds__(kBlock) void k_bin_flags(int64_t n, const float4 *__restrict__ sloc,
-                                                      const uint32_t *__restrict__ off,
-                                                      uint32_t *__restrict__ f_chunk,
-                                                      uint32_t *__restrict__ f_dcell,
-                                                      uint32_t *__restrict__ f_sparse) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    const int64_t s0 = i - lane;
-    const bool act = i < n;
-    // the cells beyond the wavefront's two ends are loaded with the lanes'
-    // own (lane 0: slot s0 - 1, lane 63: slot s0 + 64)
-    const int64_t e = lane == 0 ? s0 - 1 : (lane == 63 ? s0 + 64 : -1);
-    const uint32_t c = act ? __float_as_uint(sloc[i].w) : 0xffffffffu;
-    const uint32_t ce = e >= 0 && e < n ? __float_as_uint(sloc[e].w) : 0u;
-    uint32_t cprev = __shfl_up(c, 1, 64), cnext = __shfl_down(c, 1, 64);
-    if (lane == 0) cprev = s0 > 0 ? ce : 0xfffffffeu;
-    if (lane == 63) cnext = s0 + 64 < n ? ce : 0xfffffffdu;
-    const uint64_t heads = __ballot(act && c != cprev);
-    const uint64_t tails = __ballot(act && c != cnext);
-    if (!act) return;
-    const uint64_t le = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
-    const uint64_t h = heads & le, t = tails & ~(le >> 1);  // heads at or below, tails at or above
-    const uint32_t a = h ? (uint32_t)(s0 + 63 - __clzll((long long)h)) : off[c];
-    const uint32_t b = t ? (uint32_t)(s0 + __ffsll((unsigned long long)t)) : off[c + 1];
-    const bool dense = b - a >= (uint32_t)kDenseMin;
-    f_chunk[i] = dense && (((uint32_t)i - a) % 64u == 0u);
-    f_dcell[i] = dense && (uint32_t)i == a;
-    f_sparse[i] = !dense;
+// Marks of the sorted particles: head of a dense chunk, head of a dense cell,
+// sparse.  A wavefront takes 64 consecutive particles at a time and finds the
+// bounds of their cells from the cell ids of neighbouring particles (cell
+// changes are found by ballot); only a cell that starts before, or ends after,
+// the wavefront's particles reads its offset from the grid.  The marks are kept
+// as the ballots (a word per kind and particle, and its scan, moved 70 bytes
+// per particle and took eleven launches), and a workgroup's 4096 particles
+// leave the three counts for the scan of the lists.
+__global__ __launch_bounds__(kBlock) void k_bin_marks(int64_t n, const uint32_t *__restrict__ scell,
+                                                      const uint32_t *__restrict__ off, Marks marks,
+                                                      uint32_t *__restrict__ sums, int64_t tiles) {
+    __shared__ uint32_t s_cnt[kBlock / 64][3];
+    constexpr int kSteps = kScanTile / kBlock, kIlp = 4;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t t = xcd_block();
+    uint32_t nc = 0, nd = 0, ns = 0;
+    for (int k0 = 0; k0 < kSteps; k0 += kIlp) {
+        // each step's cells, and those beyond its two ends (lane 0: the slot
+        // before it, lane 63: the one after), all loaded together
+        uint32_t c[kIlp], ce[kIlp];
+#pragma unroll
+        for (int u = 0; u < kIlp; u++) {
+            const int64_t s0 = t * kScanTile + ((k0 + u) * (kBlock / 64) + w) * 64, i = s0 + lane;
+            const int64_t e = lane == 0 ? s0 - 1 : (lane == 63 ? s0 + 64 : -1);
+            c[u] = i < n ? scell[i] : 0xffffffffu;
+            ce[u] = e >= 0 && e < n ? scell[e] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kIlp; u++) {
+            const int64_t s0 = t * kScanTile + ((k0 + u) * (kBlock / 64) + w) * 64, i = s0 + lane;
+            if (s0 >= n) break;
+            const bool act = i < n;
+            uint32_t cprev = __shfl_up(c[u], 1, 64), cnext = __shfl_down(c[u], 1, 64);
+            if (lane == 0) cprev = s0 > 0 ? ce[u] : 0xfffffffeu;
+            if (lane == 63) cnext = s0 + 64 < n ? ce[u] : 0xfffffffdu;
+            const uint64_t heads = __ballot(act && c[u] != cprev);
+            const uint64_t tails = __ballot(act && c[u] != cnext);
+            bool dense = false, head = false, first = false;
+            if (act) {
+                const uint64_t le = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
+                const uint64_t h = heads & le, tl = tails & ~(le >> 1);  // heads at or below, tails at or above
+                const uint32_t a = h ? (uint32_t)(s0 + 63 - __clzll((long long)h)) : off[c[u]];
+                const uint32_t b = tl ? (uint32_t)(s0 + __ffsll((unsigned long long)tl)) : off[c[u] + 1];
+                dense = b - a >= (uint32_t)kDenseMin;
+                head = dense && (((uint32_t)i - a) % 64u == 0u);
+                first = dense && (uint32_t)i == a;
+            }
+            const uint64_t mc = __ballot(head), md = __ballot(first), ms = __ballot(act && !dense);
+            if (lane == 0) {
+                marks.chunk[s0 >> 6] = mc;
+                marks.dcell[s0 >> 6] = md;
+                marks.sparse[s0 >> 6] = ms;
+            }
+            nc += (uint32_t)__popcll(mc);
+            nd += (uint32_t)__popcll(md);
+            ns += (uint32_t)__popcll(ms);
+        }
+    }
+    if (lane == 0) {
+        s_cnt[w][0] = nc;
+        s_cnt[w][1] = nd;
+        s_cnt[w][2] = ns;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint32_t v = 0;
+        for (int x = 0; x < kBlock / 64; x++) v += s_cnt[x][threadIdx.x];
+        sums[threadIdx.x * tiles + t] = v;
+    }
 }
 
-constexpr int kListIlp = 4;
-__global__ __launch_bounds__(kBlock) void k_bin_lists(int64_t n, const uint32_t *__restrict__ f_chunk,
-                                                      const uint32_t *__restrict__ s_chunk,
-                                                      const uint32_t *__restrict__ f_dcell,
-                                                      const uint32_t *__restrict__ s_dcell,
-                                                      const uint32_t *__restrict__ f_sparse,
-                                                      const uint32_t *__restrict__ s_sparse,
-                                                      const float4 *__restrict__ sloc,
+// The lists of the marked particles, a workgroup per 4096 particles: dense
+// chunks, dense cells (and the map from cell to dense cell) and sparse
+// particles, with the zeros that the sparse particles' dense-neighbour sums
+// start from (dfx may be null).  The last workgroup leaves the three totals in
+// the counters.
+__global__ __launch_bounds__(kBlock) void k_bin_lists(int64_t n, Marks marks, const uint32_t *__restrict__ sums,
+                                                      int64_t tiles, bool scanned,
+                                                      const uint32_t *__restrict__ scell,
                                                       int32_t *__restrict__ chunks,
                                                       uint32_t *__restrict__ dcells,
                                                       int32_t *__restrict__ sparse,
-                                                      uint32_t *__restrict__ cellmap,
+                                                      uint32_t *__restrict__ cellmap, uint64_t *__restrict__ dfx,
+                                                      int32_t *__restrict__ counters,
                                                       uint32_t *__restrict__ zero, int nzero) {
+    constexpr int kWords = kScanTile / 64;
+    static_assert(kWords == 64, "one lane per word");
+    __shared__ uint64_t s_mark[3][kWords];
+    __shared__ uint32_t s_at[3][kWords];
+    const int64_t t = xcd_block();
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     // the counts of the next stage's segmented list start here
     if (blockIdx.x == 0)
-        for (int t = threadIdx.x; t < nzero; t += kBlock) zero[t] = 0u;
-    // kListIlp particles per thread (i0, i0 + kBlock, ...): their flags and
-    // list positions loaded together, the positions whatever the flags (one
-    // round of loads instead of two)
-    const int64_t i0 = (int64_t)blockIdx.x * (kBlock * kListIlp) + threadIdx.x;
-    uint32_t fc[kListIlp], sc[kListIlp], fs[kListIlp], ss[kListIlp], fd[kListIlp];
+        for (int q = threadIdx.x; q < nzero; q += kBlock) zero[q] = 0u;
+    uint32_t off[3];
 #pragma unroll
-    for (int u = 0; u < kListIlp; u++) {
-        const int64_t i = i0 + (int64_t)u * kBlock;
-        const bool in = i < n;
-        fc[u] = in ? f_chunk[i] : 0u;
-        sc[u] = in ? s_chunk[i] : 0u;
-        fs[u] = in ? f_sparse[i] : 0u;
-        ss[u] = in ? s_sparse[i] : 0u;
-        fd[u] = in ? f_dcell[i] : 0u;
+    for (int k = 0; k < 3; k++) off[k] = t > 0 ? tile_offset(sums + k * tiles, (uint32_t)t, scanned) : 0u;
+    if (w < 3) {
+        // wavefront w: the words of kind w and the marked particles before each
+        const int64_t word = t * kWords + lane;
+        const uint64_t *p = w == 0 ? marks.chunk : (w == 1 ? marks.dcell : marks.sparse);
+        const uint64_t m = word * 64 < n ? p[word] : 0ull;
+        const uint32_t cnt = (uint32_t)__popcll(m), incl = wave_incl_scan(cnt);
+        const uint32_t at = (w == 0 ? off[0] : (w == 1 ? off[1] : off[2])) + incl - cnt;
+        s_mark[w][lane] = m;
+        s_at[w][lane] = at;
+        if (w == 2 && word * 64 < n) marks.before[word] = at;
+        if (t == tiles - 1 && lane == 63)
+            counters[w == 0 ? kCntChunks : (w == 1 ? kCntDcells : kCntSparse)] = (int32_t)(at + cnt);
     }
-#pragma unroll
-    for (int u = 0; u < kListIlp; u++) {
-        const int64_t i = i0 + (int64_t)u * kBlock;
-        if (fc[u]) chunks[sc[u]] = (int32_t)i;
-        if (fs[u]) sparse[ss[u]] = (int32_t)i;
-        if (fd[u]) {
-            const uint32_t c = __float_as_uint(sloc[i].w);
-            const uint32_t d = s_dcell[i];
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (int k = w; k < kWords; k += kBlock / 64) {
+        const int64_t i = (t * kWords + k) * 64 + lane;
+        const uint64_t mc = s_mark[0][k], md = s_mark[1][k], ms = s_mark[2][k];
+        if ((mc >> lane) & 1ull) chunks[s_at[0][k] + (uint32_t)__popcll(mc & below)] = (int32_t)i;
+        if ((ms >> lane) & 1ull) {
+            const uint32_t at = s_at[2][k] + (uint32_t)__popcll(ms & below);
+            sparse[at] = (int32_t)i;
+            if (dfx) dfx[at] = 0ull;
+        }
+        if ((md >> lane) & 1ull) {
+            const uint32_t c = scell[i], d = s_at[1][k] + (uint32_t)__popcll(md & below);
             dcells[d] = c;
             cellmap[c] = d;  // the cell-count array is reused as cell -> dense-cell map
         }
@@ -1162,7 +1216,7 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
     const bool packed = r.ib > 0;
     const int64_t ntiles = (n + kTile - 1) / kTile;
     const dim3 tiles((unsigned)ntiles);
-    const Sorted to{w.spos, w.sloc, w.pq, w.ssub};
+    const Sorted to{w.spos, w.sloc, w.pq, w.ssub, w.scell};
     if (r.top >= 0) {
         const int low = r.bits - r.top, shift = r.ib + low;
         hipLaunchKernelGGL(k_bin_key, tiles, dim3(256), 0, s, pos, n, bx, r.ib, w.rkey[0], shift, r.top, ntiles,
@@ -1238,16 +1292,14 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
     }
     // slots 0..n (slot n closes the grid): one wavefront per 64
     hipLaunchKernelGGL(k_cell_offsets, dim3((unsigned)((n + 1 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n,
-                       ncell, w.sloc, w.off);
-    hipLaunchKernelGGL(k_bin_flags, dim3(blocks(n)), dim3(kBlock), 0, s, n, w.sloc, w.off, w.f_chunk,
-                       w.f_dcell, w.f_sparse);
-    scan_u32(w.f_chunk, w.s_chunk, n, w.scan_tmp, s);
-    scan_u32(w.f_dcell, w.s_dcell, n, w.scan_tmp, s);
-    scan_u32(w.f_sparse, w.s_sparse, n, w.scan_tmp, s);
-    hipLaunchKernelGGL(k_bin_lists, dim3(blocks((n + kListIlp - 1) / kListIlp)), dim3(kBlock), 0, s, n, w.f_chunk,
-                       w.s_chunk,
-                       w.f_dcell, w.s_dcell, w.f_sparse, w.s_sparse, w.sloc, w.chunks, w.dcells,
-                       w.sparse, w.cnt, w.rhist, (int)(seg_list(n, w).nseg * kSegStride));
+                       ncell, w.scell, w.off);
+    const int64_t lt = scan_tiles(n);
+    hipLaunchKernelGGL(k_bin_marks, dim3((unsigned)lt), dim3(kBlock), 0, s, n, w.scell, w.off, w.marks, w.scan_tmp,
+                       lt);
+    const bool scanned = scan_sums(w.scan_tmp, lt, lt, 3, s);
+    hipLaunchKernelGGL(k_bin_lists, dim3((unsigned)lt), dim3(kBlock), 0, s, n, w.marks, w.scan_tmp, lt, scanned,
+                       w.scell, w.chunks, w.dcells, w.sparse, w.cnt, w.pq ? w.rkey[0] : nullptr, w.counters, w.rhist,
+                       (int)(seg_list(n, w).nseg * kSegStride));
 }
 
 void launch_subtab(int64_t n, const uint32_t *ndc_p, const Boxes &bx, Work &w, hipStream_t s) {

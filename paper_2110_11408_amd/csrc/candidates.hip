@@ -140,9 +140,9 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
 // sub-cell of the same cell is denser and in its group, where such sub-cells
 // lie within b of each other entirely (s sqrt(6) < b).  Every other member at
 // or above the floor is listed as a hard case.
-__global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, const float4 *__restrict__ sloc,
+__global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
                                                        const float4 *__restrict__ spos,
-                                                       const uint32_t *__restrict__ f_sparse,
+                                                       const uint32_t *__restrict__ scell, Marks marks,
                                                        const uint16_t *__restrict__ ssub,
                                                        const uint32_t *__restrict__ cellmap,
                                                        const uint64_t *__restrict__ submax,
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx, cons
     if (key >= 0 && (double)di >= g.floor_nuc) {
         is_hard = true;
         // everything indexed by i in one round of loads
-        const uint32_t c = __float_as_uint(sloc[i].w);
-        const uint32_t sparse_i = f_sparse[i];
+        const uint32_t c = scell[i];
+        const bool sparse_i = is_sparse(marks, i);
         const int si = ssub[i];
         const float4 pi = spos[i];
         if (!sparse_i) {
@@ -539,8 +539,8 @@ void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
                            dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.ssub, w.dens_s, w.spos, w.submax,
                            w.subarg);
     const SegList hl = seg_list(n, w);
-    hipLaunchKernelGGL(k_cand_quick, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, bx, w.sloc,
-                       w.spos, w.f_sparse, w.ssub, w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, hl);
+    hipLaunchKernelGGL(k_cand_quick, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, bx,
+                       w.spos, w.scell, w.marks, w.ssub, w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, hl);
     // half-wavefronts striding over the segments: as many as fit the chip (six
     // wavefronts per SIMD at 79 VGPRs), and no more than one per four particles
     // (one particle in thirty is a hard case); their total goes to a counter

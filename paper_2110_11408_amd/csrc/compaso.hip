@@ -943,7 +943,7 @@ static int bits_for(int64_t x) {
 
 void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx, Work &w, hipStream_t s) {
     // groups with candidates (at most min(G, NC)), one wavefront each; the
-    // others are listed (in the free chunk-flag array, counts in counters[9]
+    // others are listed (in a scratch array, counts in counters[9]
     // and [11]) for one workgroup each: medium groups (at most M / kWaveHist
     // of kWaveHist particles or more, and NC / (kWaveNuc + 1) with more than
     // kWaveNuc candidates) and large ones (at most M / kHistMid), whose list
@@ -953,8 +953,8 @@ void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx,
     // zero since the call began.
     const int64_t bound = G < NC ? G : NC;
     if (bound <= 0) return;
-    int32_t *mid_list = reinterpret_cast<int32_t *>(w.f_chunk);
-    int32_t *big_list = reinterpret_cast<int32_t *>(w.f_chunk) + n / 2;
+    int32_t *mid_list = reinterpret_cast<int32_t *>(w.tmp_a);
+    int32_t *big_list = reinterpret_cast<int32_t *>(w.tmp_a) + n / 2;
     uint32_t *mid_count = reinterpret_cast<uint32_t *>(w.counters + 9);
     uint32_t *big_count = reinterpret_cast<uint32_t *>(w.counters + 11);
     const int64_t ncu = w.ncu > 0 ? w.ncu : 1;

@@ -101,7 +101,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
                                               const float *__restrict__ pq,
                                               const float4 *__restrict__ spos,
                                               const uint32_t *__restrict__ off,
-                                              const uint32_t *__restrict__ s_sparse,
+                                              const Marks &marks,
                                               uint64_t *__restrict__ dfx, float *__restrict__ dens_s,
                                               float *__restrict__ dens_out, float *__restrict__ cl,
                                               float4 *__restrict__ s_pk) {
@@ -159,7 +159,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
         rb = off[nb + 1];
         // a sparse cell's particles have consecutive sparse ordinals
         sp = rb > ra && rb - ra < (uint32_t)kDenseMin;
-        if (sp) sb = s_sparse[ra];
+        if (sp) sb = sparse_ordinal(marks, ra);
     }
     const uint32_t cend = (uint32_t)__builtin_amdgcn_readlane((int)rb, 13);
     const uint32_t tail = h + 16u * (uint32_t)R;
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, Boxes 
                                                       const float4 *__restrict__ pq,
                                                       const float4 *__restrict__ spos,
                                                       const uint32_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ s_sparse,
+                                                      Marks marks,
                                                       uint64_t *__restrict__ dfx,
                                                       float *__restrict__ dens_s,
                                                       float *__restrict__ dens_out) {
@@ -425,8 +425,8 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, Boxes 
     __shared__ float cl[16 * 64];
     __shared__ float4 s_pk[64];
 #define HF_DENSITY_CHUNK(RR)                                                                        \
-    (narrow ? density_chunk<RR, true>(g, h, c, end, p, spos, off, s_sparse, dfx, dens_s, dens_out, cl, s_pk) \
-            : density_chunk<RR, false>(g, h, c, end, p, spos, off, s_sparse, dfx, dens_s, dens_out, cl, s_pk))
+    (narrow ? density_chunk<RR, true>(g, h, c, end, p, spos, off, marks, dfx, dens_s, dens_out, cl, s_pk) \
+            : density_chunk<RR, false>(g, h, c, end, p, spos, off, marks, dfx, dens_s, dens_out, cl, s_pk))
     switch ((end - h + 15u) >> 4) {
     case 1: HF_DENSITY_CHUNK(1); break;
     case 2: HF_DENSITY_CHUNK(2); break;
@@ -623,9 +623,8 @@ __global__ __launch_bounds__(kBlock) void k_gather_density(int64_t n, const floa
 
 void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStream_t s) {
     // dfx: dense-neighbour sums of the sparse particles (fixed point), in the
-    // radix key array that binning no longer needs
+    // radix key array (zeroed with the list of the sparse particles)
     uint64_t *dfx = w.rkey[0];
-    if (w.nsparse > 0) fill_u32(reinterpret_cast<uint32_t *>(dfx), 0u, 2 * w.nsparse, s);
     if (w.nchunks > 0) {
         // one buffer descriptor for all record loads while the byte offsets
         // fit in 32 bits; HF_DENSITY_WIDE=1 forces the per-block descriptors
@@ -634,7 +633,7 @@ void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStr
         const char *force = getenv("HF_DENSITY_WIDE");
         if (force && force[0] == '1') narrow = false;
         hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, bx, narrow,
-                           w.chunks, w.sloc, w.pq, w.spos, w.off, w.s_sparse, dfx, w.dens_s, dens_out);
+                           w.chunks, w.sloc, w.pq, w.spos, w.off, w.marks, dfx, w.dens_s, dens_out);
     }
     if (w.nsparse > 0) {
         // the wavefronts that span a box boundary: at most nbox - 1, listed

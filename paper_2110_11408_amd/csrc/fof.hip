@@ -210,8 +210,8 @@ __device__ __forceinline__ void test_candidates(int32_t *parent, Hooks &h, const
 // the sub-cell table.  The smallest index and the member count of every
 // particle's set start here too, and the members of sparse cells (about one in
 // ten of their particles) are listed.
-__global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, const float4 *__restrict__ sloc,
-                                                        const uint32_t *__restrict__ f_sparse,
+__global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, const uint32_t *__restrict__ scell,
+                                                        Marks marks,
                                                         const uint16_t *__restrict__ ssub,
                                                         const uint32_t *__restrict__ cellmap,
                                                         const uint32_t *__restrict__ subtab,
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
     const bool in = i < n;
     const Geo &g = bx.geo[in ? box_of(bx, (uint32_t)i) : 0];
     const bool mem = in && is_member(dens_s, i, g.dl0);
-    const bool sp = in && f_sparse[i] != 0u;
+    const bool sp = in && is_sparse(marks, i);
     seg_append(sl, sp && mem, (int32_t)i);
     if (!in) return;
     minorig[i] = 0x7fffffff;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
         parent[i] = mem ? (int32_t)i : -1;
         return;
     }
-    const uint32_t c = __float_as_uint(sloc[i].w);
+    const uint32_t c = scell[i];
     const int64_t row = (int64_t)cellmap[c] * (bx.nsub_max + 1) + ssub[i];
     const uint32_t u0 = subtab[row];
     if (mem) {
@@ -919,7 +919,7 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     const SegList sl = seg_list(n, w);
     // the first members of the dense sub-cells go to the sub-cell maxima's
     // argument table (free until the candidate stage)
-    hipLaunchKernelGGL(k_fof_phase_a, grid(n), dim3(kBlock), 0, s, n, bx, w.sloc, w.f_sparse, w.ssub, w.cnt,
+    hipLaunchKernelGGL(k_fof_phase_a, grid(n), dim3(kBlock), 0, s, n, bx, w.scell, w.marks, w.ssub, w.cnt,
                        w.subtab, w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt, sl);
     if (w.ndcells > 0) {
         const dim3 cells((unsigned)((w.ndcells + kHalves - 1) / kHalves));

@@ -208,12 +208,15 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->spos = c.take<float4>(n);
     w->sloc = c.take<float4>(n);
     w->pq = c.take<float4>(n + 32);
-    w->f_chunk = c.take<uint32_t>(n1);
-    w->s_chunk = c.take<uint32_t>(n1);
-    w->f_dcell = c.take<uint32_t>(n1);
-    w->s_dcell = c.take<uint32_t>(n1);
-    w->f_sparse = c.take<uint32_t>(n1);
-    w->s_sparse = c.take<uint32_t>(n1);
+    w->scell = c.take<uint32_t>(n);
+    w->marks.chunk = c.take<uint64_t>(n / 64 + 1);
+    w->marks.dcell = c.take<uint64_t>(n / 64 + 1);
+    w->marks.sparse = c.take<uint64_t>(n / 64 + 1);
+    w->marks.before = c.take<uint32_t>(n / 64 + 1);
+    w->tmp_a = c.take<uint32_t>(n1);
+    w->tmp_b = c.take<uint32_t>(n1);
+    w->tmp_c = c.take<uint32_t>(n1);
+    w->tmp_d = c.take<uint32_t>(n1);
     w->chunks = c.take<int32_t>(n1);
     w->sparse = c.take<int32_t>(n1);
     w->dcells = c.take<uint32_t>(n1);
@@ -606,14 +609,15 @@ hf_status begin(Lane *c, const Plan &pl, const float *pos, hf::Boxes *bx, Work *
     // enqueued before the host waits for these words, so the device keeps
     // working while the host reads them and enqueues the next stage.
     hf::WordSrc src{};
-    src.p[0] = w->s_chunk + n;
-    src.p[1] = w->s_dcell + n;
-    src.p[2] = w->s_sparse + n;
+    const uint32_t *cnt = reinterpret_cast<const uint32_t *>(w->counters);
+    src.p[0] = cnt + hf::kCntChunks;
+    src.p[1] = cnt + hf::kCntDcells;
+    src.p[2] = cnt + hf::kCntSparse;
     src.p[3] = reinterpret_cast<const uint32_t *>(w->err);
     src.p[4] = reinterpret_cast<const uint32_t *>(w->err + 1);
     HIP_OK(c, hf::publish_words(src, 5, c->host, s));
     HIP_OK(c, hipEventRecord(c->pub, s));
-    hf::launch_subtab(n, w->s_dcell + n, *bx, *w, s);
+    hf::launch_subtab(n, cnt + hf::kCntDcells, *bx, *w, s);
     HIP_OK(c, hipEventSynchronize(c->pub));
     uint32_t counts[5];
     hf::collect_words(c->host, 5, counts);

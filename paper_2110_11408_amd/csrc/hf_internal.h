@@ -259,6 +259,18 @@ __device__ __forceinline__ int32_t wave_run_min(int32_t v, const WaveRun &r) {
 }
 
 // --------------------------------------------------------------- workspace
+// Bits of the sorted particles, 64 to a word: head of a dense chunk, head of a
+// dense cell, in a sparse cell; and the sparse particles before each word.
+struct Marks {
+    uint64_t *chunk, *dcell, *sparse;
+    uint32_t *before;
+};
+__device__ __forceinline__ bool is_sparse(const Marks &m, int64_t i) { return (m.sparse[i >> 6] >> (i & 63)) & 1ull; }
+// Place of sparse particle i in the sparse list.
+__device__ __forceinline__ uint32_t sparse_ordinal(const Marks &m, uint32_t i) {
+    return m.before[i >> 6] + (uint32_t)__popcll(m.sparse[i >> 6] & ((1ull << (i & 63u)) - 1ull));
+}
+
 struct Work {
     // binning
     uint32_t *cnt, *off;             // cnt: cell -> dense-cell ordinal (dense cells only)
@@ -269,7 +281,9 @@ struct Work {
     float4 *spos, *sloc;
     float4 *pq;                      // density only: cell-centred (x, y, z, -|x|^2), n + 32 entries
     // work decomposition (dense chunks, dense cells, sparse particles)
-    uint32_t *f_chunk, *s_chunk, *f_dcell, *s_dcell, *f_sparse, *s_sparse;
+    uint32_t *scell;                 // cell of every sorted particle
+    Marks marks;                     // dense chunk and cell heads, sparse particles
+    uint32_t *tmp_a, *tmp_b, *tmp_c, *tmp_d;  // scratch of n + 1 words each, in one run
     int32_t *chunks, *sparse;
     uint32_t *dcells, *subtab;
     uint64_t *submax;                                  // densest particle per dense sub-cell
@@ -360,6 +374,9 @@ __device__ __forceinline__ SegShare seg_share(const SegList &sl) {
 
 // Words of Work::counters that several stages use (zero when a call begins).
 enum {
+    kCntChunks = 0,     // dense chunks
+    kCntDcells = 1,     // dense cells
+    kCntSparse = 3,     // particles of sparse cells
     kCntHard = 8,       // hard cases of the candidate stage
     kCntListed = 10,    // groups with candidates in glist
     kCntCand = 13,      // candidates
@@ -374,15 +391,14 @@ struct SegClear {
     int len[kRuns];
 };
 
-// The segmented list over n particles.  Its entries lie in the chunk and
-// dense-cell flag and scan arrays (4 n words in one run, free once the lists of
-// the binning are written; the segments hold at most 2 (n + 255) words, and a
+// The segmented list over n particles.  Its entries lie in the scratch arrays
+// (4 n words in one run; the segments hold at most 2 (n + 255) words, and a
 // single segment at most n), its counts in the radix counts (at least n / 8
 // words, of which n / 16 + 16 are used).
 inline SegList seg_list(int64_t n, const Work &w) {
     const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
     SegList sl;
-    sl.list = reinterpret_cast<int32_t *>(w.f_chunk);
+    sl.list = reinterpret_cast<int32_t *>(w.tmp_a);
     sl.count = w.rhist;
     sl.nseg = nb < kSegs ? nb : kSegs;
     sl.cap = (nb + sl.nseg - 1) / sl.nseg * kBlock;

@@ -161,8 +161,8 @@ bool scan_sums(uint32_t *sums, int64_t tiles, int64_t stride, int arrays, hipStr
     return true;
 }
 
-// Two runs of tile sums (the segmentation scans two quantities at once).
-int64_t scan_tmp_words(int64_t n) { return 2 * scan_tiles(n) + 16; }
+// Three runs of tile sums (the binning scans three quantities at once).
+int64_t scan_tmp_words(int64_t n) { return 3 * scan_tiles(n) + 16; }
 
 template <bool kBits>
 static void scan_impl(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
