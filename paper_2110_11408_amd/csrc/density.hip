@@ -439,88 +439,110 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, Boxes 
 // Sparse cells: one particle per lane, sparse neighbour cells only; the pairs
 // with dense neighbour cells were summed by the dense kernel into dfx.  This
 // is particle i (entry t of the sparse list) of box g.
-__device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int64_t i,
+//
+// The kernel is bound by the vector ALU, so what a lane does besides its pairs
+// counts.  Per stencil plane the nine cells become runs of sorted particles:
+// cells of a row that follow each other (all but those across the periodic x
+// edges and beyond a dense cell) are one run, which the lane keeps in LDS; it
+// then walks all its runs as one sequence, so that the wavefront waits on its
+// longest lane's count for the plane.  (With a run per cell, in registers, a
+// change of cell was a chain of selects and FP64 image shifts that ran whenever
+// any lane changed: 2300 vector instructions per wavefront, 782 us on the 256^3
+// box.  Listing the pairs of all lanes in LDS and computing one pair per lane
+// took 911 us: there are about a dozen pairs per particle, and each cost a
+// list entry and the image of its own.)
+constexpr int kSparseWaves = kBlock / 64;
+__device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int64_t i, uint2 (*runs)[64],
                                                    const float4 *__restrict__ sloc,
                                                    const float4 *__restrict__ spos,
                                                    const uint32_t *__restrict__ off,
                                                    const uint64_t *__restrict__ dfx,
                                                    float *__restrict__ dens_s, float *__restrict__ dens_out) {
+    const int lane = threadIdx.x & 63;
     const float4 li = sloc[i];
     const float4 pi = spos[i];
-    const uint32_t c = __float_as_uint(li.w);
     const int nc = g.nc;
+    const uint32_t c = __float_as_uint(li.w), row1 = (uint32_t)nc, plane1 = row1 * row1;
     int cx, cy, cz;
     cell_xyz(g, c, cx, cy, cz);
-    const uint32_t x0 = (uint32_t)wrapc(cx - 1, nc), x1 = (uint32_t)cx, x2 = (uint32_t)wrapc(cx + 1, nc);
-    // away from the periodic x edges the three cells of a stencil row are
-    // consecutive: their four bounding offsets are one 16-byte load
-    const bool inner = cx > 0 && cx < nc - 1;
+    // neighbour cells by additions from the own cell
+    const bool x_lo = cx == 0, x_hi = cx == nc - 1, y_lo = cy == 0, y_hi = cy == nc - 1;
+    const uint32_t xm = x_lo ? c + row1 - 1u : c - 1u, xp = x_hi ? c + 1u - row1 : c + 1u;
+    const uint32_t ym = y_lo ? plane1 - row1 : 0u - row1, yp = y_hi ? row1 - plane1 : row1;
+    // a cell whose nearest face is b or more away (by a margin far above the
+    // rounding of the local coordinates) weighs nothing
+    const float hx = g.cellb - li.x, hy = g.cellb - li.y, hz = g.cellb - li.z;
+    const float most = 1.0f + 1e-5f;
+    // the position in the frames of the cells to both sides (the periodic image
+    // of a cell across a face of the box), and in its own
+    const double px = (double)pi.x, py = (double)pi.y, pz = (double)pi.z;
+    const double pxm = x_lo ? px + g.L : px, pxp = x_hi ? px - g.L : px;
+    const double pym = y_lo ? py + g.L : py, pyp = y_hi ? py - g.L : py;
     double acc = 0.0;
 #pragma unroll 1
     for (int oz = -1; oz <= 1; oz++) {
-        const int z = wrapc(cz + oz, nc);
-        const float gz = oz < 0 ? li.z : (oz > 0 ? g.cellb - li.z : 0.0f);
-        // the offsets of this plane are loaded together so their latencies
-        // overlap; the cells to visit are kept as their starts and, packed
-        // three bits each, their particle counts (0: dense, empty or out of
-        // reach)
-        uint32_t ra[9], cnts = 0;
+        const bool wraps = oz < 0 ? cz == 0 : (oz > 0 ? cz == nc - 1 : false);
+        const uint32_t dz = (uint32_t)oz * plane1 - (wraps ? (uint32_t)oz * plane1 * row1 : 0u);
+        const float gz = oz < 0 ? li.z : (oz > 0 ? hz : 0.0f);
+        const float gz2 = most - gz * gz;
+        Pos64 pim{px, py, wraps ? (oz < 0 ? pz + g.L : pz - g.L) : pz};
+        // the plane's offsets are loaded together so their latencies overlap
+        uint32_t a[9], b[9];
 #pragma unroll
-        for (int oy = -1; oy <= 1; oy++) {
-            const uint32_t row =
-                g.cell_base + ((uint32_t)z * (uint32_t)nc + (uint32_t)wrapc(cy + oy, nc)) * (uint32_t)nc;
-            const int r = (oy + 1) * 3;
-            uint32_t o[6];
-            if (inner) {
-                const uint32_t *p = off + row + x0;
-                o[0] = p[0];
-                o[1] = p[1];
-                o[2] = p[1];
-                o[3] = p[2];
-                o[4] = p[2];
-                o[5] = p[3];
-            } else {
-                o[0] = off[row + x0];
-                o[1] = off[row + x0 + 1];
-                o[2] = off[row + x1];
-                o[3] = off[row + x1 + 1];
-                o[4] = off[row + x2];
-                o[5] = off[row + x2 + 1];
+        for (int r = 0; r < 3; r++) {
+            const uint32_t d = dz + (r == 0 ? ym : (r == 2 ? yp : 0u));
+            const uint32_t *const pm = off + (xm + d), *const p0 = off + (c + d), *const pp = off + (xp + d);
+            a[3 * r] = pm[0];
+            b[3 * r] = pm[1];
+            a[3 * r + 1] = p0[0];
+            b[3 * r + 1] = p0[1];
+            a[3 * r + 2] = pp[0];
+            b[3 * r + 2] = pp[1];
+        }
+        uint32_t open = 0;  // runs that hold particles
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            const float gy = r == 0 ? li.y : (r == 2 ? hy : 0.0f);
+            const float left = gz2 - gy * gy;
+            // end of each cell's run, its start when the cell is left out
+            uint32_t e0 = b[3 * r] - a[3 * r] < (uint32_t)kDenseMin && li.x * li.x < left ? b[3 * r] : a[3 * r];
+            uint32_t e1 = b[3 * r + 1] - a[3 * r + 1] < (uint32_t)kDenseMin && 0.0f < left ? b[3 * r + 1] : a[3 * r + 1];
+            uint32_t e2 = b[3 * r + 2] - a[3 * r + 2] < (uint32_t)kDenseMin && hx * hx < left ? b[3 * r + 2] : a[3 * r + 2];
+            // runs that meet are one (a wrapped cell's never does: its particles
+            // lie elsewhere in the order, or the box is empty between them)
+            if (!x_hi && e1 == a[3 * r + 2]) {
+                e1 = e2;
+                e2 = a[3 * r + 2];
             }
-            const float gy = oy < 0 ? li.y : (oy > 0 ? g.cellb - li.y : 0.0f);
-#pragma unroll
-            for (int ox = -1; ox <= 1; ox++) {
-                const uint32_t a = o[2 * (ox + 1)], cnt = o[2 * (ox + 1) + 1] - a;
-                // a cell whose nearest face is b or more away (by a margin far
-                // above the rounding of the local coordinates) weighs nothing
-                const float gx = ox < 0 ? li.x : (ox > 0 ? g.cellb - li.x : 0.0f);
-                const bool use = cnt < (uint32_t)kDenseMin && gx * gx + gy * gy + gz * gz < 1.0f + 1e-5f;
-                ra[r + ox + 1] = a;
-                cnts |= (use ? cnt : 0u) << (3 * (r + ox + 1));
+            if (!x_lo && e0 == a[3 * r + 1]) {
+                e0 = e1;
+                e1 = a[3 * r + 1];
+            }
+            if (e0 > a[3 * r]) {
+                runs[3 * r][lane] = make_uint2(a[3 * r], e0);
+                open |= 1u << (3 * r);
+            }
+            if (e1 > a[3 * r + 1]) {
+                runs[3 * r + 1][lane] = make_uint2(a[3 * r + 1], e1);
+                open |= 2u << (3 * r);
+            }
+            if (e2 > a[3 * r + 2]) {
+                runs[3 * r + 2][lane] = make_uint2(a[3 * r + 2], e2);
+                open |= 4u << (3 * r);
             }
         }
-        // the plane's cells walked as one sequence of particles (cell after
-        // cell in stencil order, so the summation order is that of a loop per
-        // cell): every lane runs through its own particles, and the wavefront
-        // waits on the longest lane's count for the whole plane rather than on
-        // the longest count of each cell
         uint32_t j = 0, e = 0;
-        Pos64 pim{0.0, 0.0, 0.0};
         for (;;) {
             if (j == e) {
-                if (cnts == 0u) break;
-                const int r = __builtin_ctz(cnts) / 3;
-                const uint32_t cnt = (cnts >> (3 * r)) & 7u;
-                cnts &= ~(7u << (3 * r));
-                uint32_t a = ra[0];
-#pragma unroll
-                for (int u = 1; u < 9; u++) a = r == u ? ra[u] : a;
-                j = a;
-                e = a + cnt;
-                // i's position in this cell's frame
-                const int ox = r % 3 - 1, oy = r / 3 - 1;
-                pim = Pos64{(double)pi.x - image_shift(cx, ox, nc, g.L), (double)pi.y - image_shift(cy, oy, nc, g.L),
-                            (double)pi.z - image_shift(cz, oz, nc, g.L)};
+                if (open == 0u) break;
+                const int k = __builtin_ctz(open);
+                open &= open - 1u;
+                const uint2 run = runs[k][lane];
+                j = run.x;
+                e = run.y;
+                const int ry = (k * 11) >> 5, rx = k - 3 * ry;
+                pim.x = rx == 0 ? pxm : (rx == 2 ? pxp : px);
+                pim.y = ry == 0 ? pym : (ry == 2 ? pyp : py);
             }
             acc += weight64(pim, spos[j], g.inv_b2);
             j++;
@@ -530,12 +552,6 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
     write_density(i, acc, g, spos, dens_s, dens_out);
 }
 
-// The sparse-cell particles whose wavefront lies in one box (nearly all): the
-// box's constants are read with a box index uniform over the wavefront, so
-// they come with scalar loads into scalar registers.  A wavefront that spans
-// a box boundary (one per boundary at most) is listed in mixed[] and left to
-// k_density_sparse_mixed.  The kernel waits on memory, so it is held to 64
-// VGPRs (eight wavefronts per SIMD, the most a SIMD runs).
 __global__ __launch_bounds__(kBlock, 8) void k_density_sparse(int64_t nsparse, Boxes bx,
                                                            const int32_t *__restrict__ sparse,
                                                            const float4 *__restrict__ sloc,
@@ -543,40 +559,14 @@ __global__ __launch_bounds__(kBlock, 8) void k_density_sparse(int64_t nsparse, B
                                                            const uint32_t *__restrict__ off,
                                                            const uint64_t *__restrict__ dfx,
                                                            float *__restrict__ dens_s,
-                                                           float *__restrict__ dens_out,
-                                                           int32_t *__restrict__ mixed,
-                                                           uint32_t *__restrict__ nmixed) {
+                                                           float *__restrict__ dens_out) {
+    __shared__ uint2 s_runs[kSparseWaves][9][64];
     const int64_t t = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     if (t >= nsparse) return;
-    const int lane = threadIdx.x & 63;
     const int64_t i = sparse[t];
-    const int b = box_of(bx, (uint32_t)i);
-    const int b0 = __builtin_amdgcn_readfirstlane(b);
-    if (__ballot(b != b0) != 0ull) {
-        const uint64_t act = __ballot(true);
-        if (lane == __ffsll((unsigned long long)act) - 1) mixed[atomicAdd(nmixed, 1u)] = (int32_t)(t - lane);
-        return;
-    }
-    density_sparse_one(bx.geo[b0], t, i, sloc, spos, off, dfx, dens_s, dens_out);
-}
-
-// The wavefronts of the sparse list that span a box boundary: each lane reads
-// its own box's constants.
-__global__ __launch_bounds__(64) void k_density_sparse_mixed(int64_t nsparse, Boxes bx,
-                                                             const uint32_t *__restrict__ nmixed,
-                                                             const int32_t *__restrict__ mixed,
-                                                             const int32_t *__restrict__ sparse,
-                                                             const float4 *__restrict__ sloc,
-                                                             const float4 *__restrict__ spos,
-                                                             const uint32_t *__restrict__ off,
-                                                             const uint64_t *__restrict__ dfx,
-                                                             float *__restrict__ dens_s,
-                                                             float *__restrict__ dens_out) {
-    if (blockIdx.x >= *nmixed) return;
-    const int64_t t = (int64_t)mixed[blockIdx.x] + threadIdx.x;
-    if (t >= nsparse) return;
-    const int64_t i = sparse[t];
-    density_sparse_one(bx.geo[box_of(bx, (uint32_t)i)], t, i, sloc, spos, off, dfx, dens_s, dens_out);
+    per_box(bx, box_of(bx, (uint32_t)i), [&](const Geo &g) {
+        density_sparse_one(g, t, i, s_runs[threadIdx.x >> 6], sloc, spos, off, dfx, dens_s, dens_out);
+    });
 }
 
 // Number of ordered pairs (i, j != i) closer than b, for the roofline's
@@ -636,17 +626,9 @@ void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStr
                            w.chunks, w.sloc, w.pq, w.spos, w.off, w.marks, dfx, w.dens_s, dens_out);
     }
     if (w.nsparse > 0) {
-        // the wavefronts that span a box boundary: at most nbox - 1, listed
-        // in the table-flag array (free until the output stage), their count
-        // in counters[14] (zero since the call began)
-        int32_t *mixed = reinterpret_cast<int32_t *>(w.tflag);
-        uint32_t *nmixed = reinterpret_cast<uint32_t *>(w.counters + 14);
         hipLaunchKernelGGL(k_density_sparse, dim3((unsigned)((w.nsparse + kBlock - 1) / kBlock)),
                            dim3(kBlock), 0, s, w.nsparse, bx, w.sparse, w.sloc, w.spos, w.off, dfx, w.dens_s,
-                           dens_out, mixed, nmixed);
-        if (bx.nbox > 1)
-            hipLaunchKernelGGL(k_density_sparse_mixed, dim3((unsigned)bx.nbox), dim3(64), 0, s, w.nsparse, bx,
-                               nmixed, mixed, w.sparse, w.sloc, w.spos, w.off, dfx, w.dens_s, dens_out);
+                           dens_out);
     }
 }
 
