@@ -351,7 +351,7 @@ typedef struct {
     double t_submit;    /* seconds on the server clock (hf_server_now)         */
     double t_start;     /* taken by a slot                                     */
     double t_done;      /* results written to the host buffers                 */
-    float ms_gpu;       /* device time of its pass (first to last stage event) */
+    float ms_gpu;       /* device time of its pass (start of its first stage to its end) */
     char error[160];    /* error text when status != HF_OK                     */
 } hf_result;
 

@@ -63,7 +63,9 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
                                                         const float *__restrict__ dens_s,
                                                         const float4 *__restrict__ spos,
                                                         uint64_t *__restrict__ submax,
-                                                        int32_t *__restrict__ subarg) {
+                                                        int32_t *__restrict__ subarg,
+                                                        uint64_t *clock) {
+    stamp(clock);
     __shared__ uint64_t s_best[kBlock / 64][kSubMost];
     __shared__ int32_t s_arg[kBlock / 64][kSubMost];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -149,7 +151,9 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
                                                        const int32_t *__restrict__ subarg,
                                                        const float *__restrict__ dens_s,
                                                        const int32_t *__restrict__ gkey,
-                                                       SegList hl) {
+                                                       SegList hl,
+                                                       uint64_t *clock) {
+    stamp(clock);
     const int64_t i = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     const int64_t ic = i < n ? i : n - 1;
     const Geo &g = bx.geo[box_of(bx, (uint32_t)ic)];
@@ -537,10 +541,11 @@ void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     if (w.ndcells > 0)
         hipLaunchKernelGGL(k_submax_wave, dim3((unsigned)((w.ndcells + kBlock / 64 - 1) / (kBlock / 64))),
                            dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.ssub, w.dens_s, w.spos, w.submax,
-                           w.subarg);
+                           w.subarg, w.clock + kClockCand);
     const SegList hl = seg_list(n, w);
     hipLaunchKernelGGL(k_cand_quick, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, bx,
-                       w.spos, w.scell, w.marks, w.ssub, w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, hl);
+                       w.spos, w.scell, w.marks, w.ssub, w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, hl,
+                       w.ndcells > 0 ? nullptr : w.clock + kClockCand);
     // half-wavefronts striding over the segments: as many as fit the chip (six
     // wavefronts per SIMD at 79 VGPRs), and no more than one per four particles
     // (one particle in thirty is a hard case); their total goes to a counter

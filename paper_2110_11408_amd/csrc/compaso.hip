@@ -46,7 +46,9 @@ __device__ __forceinline__ void stu(uint32_t *p, uint32_t v) {
 // keys (gcnt[key], zero before).  Two prefix sums over the keys, of the counts
 // and of their non-zero ones, give every group its start and its ordinal.
 __global__ __launch_bounds__(kBlock) void k_seg_sums(int64_t n, const uint32_t *__restrict__ gcnt,
-                                                     uint32_t *__restrict__ msum, uint32_t *__restrict__ gsum) {
+                                                     uint32_t *__restrict__ msum, uint32_t *__restrict__ gsum,
+                                                     uint64_t *clock) {
+    stamp(clock);
     uint32_t m = 0, g = 0;
     tile_each(gcnt, (int64_t)blockIdx.x * kScanTile, n, [&](uint32_t c) {
         m += c;
@@ -345,8 +347,10 @@ __global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restr
                                                          int32_t *__restrict__ mid_list,
                                                          uint32_t *__restrict__ mid_count,
                                                          int32_t *__restrict__ big_list,
-                                                         uint32_t *__restrict__ big_count) {
+                                                         uint32_t *__restrict__ big_count,
+                                                         uint64_t *clock) {
 #pragma clang fp contract(off)
+    stamp(clock);
     __shared__ uint32_t s_hist[kBlock / 64][kWaveHist];
     __shared__ float4 s_hp[kBlock / 64][kWaveNuc];
     __shared__ int32_t s_hi[kBlock / 64][kWaveNuc];
@@ -691,8 +695,10 @@ __global__ __launch_bounds__(kBlock) void k_assign(int64_t n, Boxes bx, const in
                                                    const int32_t *__restrict__ h_ienc,
                                                    const float4 *__restrict__ spos,
                                                    int32_t *__restrict__ owner,
-                                                   uint32_t *__restrict__ h_count) {
+                                                   uint32_t *__restrict__ h_count,
+                                                   uint64_t *clock) {
 #pragma clang fp contract(off)
+    stamp(clock);
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int gi = i < n ? gid_of[i] : -1;
     int own = -1;
@@ -748,7 +754,9 @@ __global__ __launch_bounds__(kBlock) void k_out_flags(int64_t NC, Boxes bx, cons
                                                       const float4 *__restrict__ spos,
                                                       uint32_t *__restrict__ tflag,
                                                       int32_t *__restrict__ h_label,
-                                                      int32_t *__restrict__ counters) {
+                                                      int32_t *__restrict__ counters,
+                                                      uint64_t *clock) {
+    stamp(clock);
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int nuc = s < NC ? h_nuc[s] : -1;
     const uint64_t b = __ballot(nuc >= 0);
@@ -777,12 +785,18 @@ __device__ __forceinline__ uint32_t table_pos(const uint32_t *__restrict__ tflag
 
 // Rows of the halo table of every box: the kept halos are flagged at their
 // nucleus's original index, so a box's rows are the flags in its index range.
-__global__ __launch_bounds__(kBlock) void k_box_rows(Boxes bx, const uint32_t *__restrict__ tflag,
-                                                     const uint32_t *__restrict__ tpos,
-                                                     int64_t *__restrict__ box_rows) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= bx.nbox) return;
-    box_rows[b] = (int64_t)table_pos(tflag, tpos, bx.base[b + 1]) - (int64_t)table_pos(tflag, tpos, bx.base[b]);
+// One workgroup, with the last words that the host reads.
+__global__ __launch_bounds__(kBlock) void k_finish(Boxes bx, const uint32_t *__restrict__ tflag,
+                                                   const uint32_t *__restrict__ tpos, WordSrc src, int k,
+                                                   uint32_t *host, int64_t *rows, uint64_t *clock) {
+    stamp(clock);
+    for (int b = threadIdx.x; b < bx.nbox; b += blockDim.x)
+        __hip_atomic_store(rows + b,
+                           (int64_t)table_pos(tflag, tpos, bx.base[b + 1]) -
+                               (int64_t)table_pos(tflag, tpos, bx.base[b]),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const int t = threadIdx.x;
+    if (t < k) __hip_atomic_store(host + t, *src.p[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // A halo's row in its box's table (ascending id); a box whose rows exceed its
@@ -906,14 +920,16 @@ __global__ __launch_bounds__(kBlock) void k_order_out(int64_t n, int64_t nrows, 
 void launch_segment_totals(int64_t n, Work &w, hipStream_t s) {
     const int64_t tiles = scan_tiles(n);
     uint32_t *msum = w.scan_tmp, *gsum = w.scan_tmp + tiles;
-    hipLaunchKernelGGL(k_seg_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum);
+    hipLaunchKernelGGL(k_seg_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum,
+                       w.clock + kClockSegment);
     hipLaunchKernelGGL(k_seg_totals, dim3(1), dim3(kBlock), 0, s, tiles, msum, gsum, w.counters);
 }
 
 void launch_segment(int64_t n, Work &w, hipStream_t s) {
     const int64_t tiles = scan_tiles(n);
     uint32_t *msum = w.scan_tmp, *gsum = w.scan_tmp + tiles;
-    hipLaunchKernelGGL(k_seg_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum);
+    hipLaunchKernelGGL(k_seg_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum,
+                       w.clock + kClockSegment);
     const bool scanned = scan_sums(w.scan_tmp, tiles, tiles, 2, s);
     // flags of the extent check in h_ienc (free until the acceptance fills it)
     hipLaunchKernelGGL(k_seg_offsets, dim3((unsigned)tiles), dim3(kBlock), 0, s, n, w.gcnt, msum, gsum, scanned,
@@ -963,7 +979,8 @@ void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx,
     // six wavefronts per SIMD (its register use): 6 workgroups of 4 per CU
     hipLaunchKernelGGL(k_accept_small, dim3(cap((bound + kBlock / 64 - 1) / (kBlock / 64), 6 * ncu)), dim3(kBlock),
                        0, s, reinterpret_cast<const uint32_t *>(w.counters + kCntListed), bins, bx, w.glist, w.g_start, w.g_size, w.gcoff, w.cand_sorted,
-                       w.mem, w.spos, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh, mid_list, mid_count, big_list, big_count);
+                       w.mem, w.spos, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh, mid_list, mid_count, big_list, big_count,
+                       w.clock + kClockAccept);
     // with radial bins every group is listed: at most bound medium groups
     const int64_t nmid = bins ? bound : M / kWaveHist + NC / (kWaveNuc + 1) + 1;
     const dim3 gmid(cap(nmid, bound));
@@ -990,7 +1007,7 @@ void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx,
 
 void launch_assign(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     hipLaunchKernelGGL(k_assign, grid(n), dim3(kBlock), 0, s, n, bx, w.gid_of, w.gcoff, w.g_nh, w.h_nuc,
-                       w.h_ienc, w.spos, w.owner, w.h_count);
+                       w.h_ienc, w.spos, w.owner, w.h_count, w.clock + kClockAssign);
 }
 
 void launch_output_flags(int64_t n, int64_t NC, const Boxes &bx, Work &w, hipStream_t s) {
@@ -999,17 +1016,15 @@ void launch_output_flags(int64_t n, int64_t NC, const Boxes &bx, Work &w, hipStr
         // the candidates' member labels go to the hard-case list (free after
         // the candidate stage)
         hipLaunchKernelGGL(k_out_flags, grid(NC), dim3(kBlock), 0, s, NC, bx, w.h_nuc, w.h_count, w.spos,
-                           w.tflag, w.hardlist, w.counters);
+                           w.tflag, w.hardlist, w.counters, w.clock + kClockOutput);
     scan_bits_u32(w.tflag, w.tpos, n / 32 + 1, w.scan_tmp, s);
 }
 
 void launch_output(int64_t n, int64_t NC, const Boxes &bx, Work &w, int32_t *halo_id, int32_t *l0_out,
-                   float *dens_out, int64_t *box_rows, hipStream_t s) {
+                   float *dens_out, hipStream_t s) {
     if (NC > 0)
         hipLaunchKernelGGL(k_out_table, grid(NC), dim3(kBlock), 0, s, NC, bx, w.h_nuc, w.h_ienc, w.h_gid,
                            w.h_count, w.g_label, w.spos, w.tflag, w.tpos);
-    if (box_rows)
-        hipLaunchKernelGGL(k_box_rows, grid(bx.nbox), dim3(kBlock), 0, s, bx, w.tflag, w.tpos, box_rows);
     if (!l0_out && !dens_out) {
         fill_i32(halo_id, 0, n, s);
         hipLaunchKernelGGL(k_out_particles, grid(n), dim3(kBlock), 0, s, n, w.owner, w.hardlist, w.spos,
@@ -1021,6 +1036,11 @@ void launch_output(int64_t n, int64_t NC, const Boxes &bx, Work &w, int32_t *hal
     hipLaunchKernelGGL(k_out_records, grid(n), dim3(kBlock), 0, s, n, bx, w.owner, w.hardlist, w.gkey, w.spos,
                        w.dens_s, rec);
     hipLaunchKernelGGL(k_out_split, grid(n), dim3(kBlock), 0, s, n, rec, dens_out, l0_out, halo_id);
+}
+
+void launch_finish(const Boxes &bx, const WordSrc &src, int k, Work &w, int64_t *rows, hipStream_t s) {
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(kBlock), 0, s, bx, w.tflag, w.tpos, src, k, w.host, rows,
+                       w.clock + kClockEnd);
 }
 
 void launch_group_order(int64_t n, int64_t nrows, const int32_t *halo_id, Work &w, int32_t *members,

@@ -412,7 +412,9 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, Boxes 
                                                       Marks marks,
                                                       uint64_t *__restrict__ dfx,
                                                       float *__restrict__ dens_s,
-                                                      float *__restrict__ dens_out) {
+                                                      float *__restrict__ dens_out,
+                                                      uint64_t *clock) {
+    stamp(clock);
     const int64_t q = (int64_t)xcd_block();
     if (q >= nchunks) return;
     const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane(chunks[q]);
@@ -559,7 +561,9 @@ __global__ __launch_bounds__(kBlock, 8) void k_density_sparse(int64_t nsparse, B
                                                            const uint32_t *__restrict__ off,
                                                            const uint64_t *__restrict__ dfx,
                                                            float *__restrict__ dens_s,
-                                                           float *__restrict__ dens_out) {
+                                                           float *__restrict__ dens_out,
+                                                           uint64_t *clock) {
+    stamp(clock);
     __shared__ uint2 s_runs[kSparseWaves][9][64];
     const int64_t t = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     if (t >= nsparse) return;
@@ -603,7 +607,9 @@ __global__ __launch_bounds__(kBlock) void k_count_pairs(int64_t n, Boxes bx,
 
 __global__ __launch_bounds__(kBlock) void k_gather_density(int64_t n, const float4 *__restrict__ spos,
                                                            const float *__restrict__ dens_in,
-                                                           float *__restrict__ dens_s) {
+                                                           float *__restrict__ dens_s,
+                                                           uint64_t *clock) {
+    stamp(clock);
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     dens_s[i] = dens_in[orig_of(spos[i])];
@@ -623,12 +629,13 @@ void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStr
         const char *force = getenv("HF_DENSITY_WIDE");
         if (force && force[0] == '1') narrow = false;
         hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, bx, narrow,
-                           w.chunks, w.sloc, w.pq, w.spos, w.off, w.marks, dfx, w.dens_s, dens_out);
+                           w.chunks, w.sloc, w.pq, w.spos, w.off, w.marks, dfx, w.dens_s, dens_out,
+                           w.clock + kClockDensity);
     }
     if (w.nsparse > 0) {
         hipLaunchKernelGGL(k_density_sparse, dim3((unsigned)((w.nsparse + kBlock - 1) / kBlock)),
                            dim3(kBlock), 0, s, w.nsparse, bx, w.sparse, w.sloc, w.spos, w.off, dfx, w.dens_s,
-                           dens_out);
+                           dens_out, w.nchunks > 0 ? nullptr : w.clock + kClockDensity);
     }
 }
 
@@ -639,7 +646,7 @@ void launch_count_pairs(int64_t n, const Boxes &bx, Work &w, unsigned long long 
 
 void launch_gather_density(const float *dens_in, int64_t n, Work &w, hipStream_t s) {
     hipLaunchKernelGGL(k_gather_density, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, n,
-                       w.spos, dens_in, w.dens_s);
+                       w.spos, dens_in, w.dens_s, w.clock + kClockDensity);
 }
 
 }  // namespace hf

@@ -219,7 +219,9 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
                                                         int32_t *__restrict__ parent,
                                                         int32_t *__restrict__ submem,
                                                         int32_t *__restrict__ minorig,
-                                                        uint32_t *__restrict__ gcnt, SegList sl) {
+                                                        uint32_t *__restrict__ gcnt, SegList sl,
+                                                        uint64_t *clock) {
+    stamp(clock);
     const int64_t i = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     const bool in = i < n;
     const Geo &g = bx.geo[in ? box_of(bx, (uint32_t)i) : 0];
@@ -870,7 +872,9 @@ __global__ __launch_bounds__(kBlock) void k_fof_keys(int64_t n, Boxes bx, const 
 __global__ __launch_bounds__(kBlock) void k_pack_labels(int64_t n, const int32_t *__restrict__ l0_in,
                                                         const float *__restrict__ dens_in,
                                                         uint2 *__restrict__ packed,
-                                                        uint32_t *__restrict__ gcnt) {
+                                                        uint32_t *__restrict__ gcnt,
+                                                        uint64_t *clock) {
+    stamp(clock);
     const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (o >= n) return;
     packed[o] = make_uint2((uint32_t)l0_in[o], __float_as_uint(dens_in[o]));
@@ -920,7 +924,7 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     // the first members of the dense sub-cells go to the sub-cell maxima's
     // argument table (free until the candidate stage)
     hipLaunchKernelGGL(k_fof_phase_a, grid(n), dim3(kBlock), 0, s, n, bx, w.scell, w.marks, w.ssub, w.cnt,
-                       w.subtab, w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt, sl);
+                       w.subtab, w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt, sl, w.clock + kClockFof);
     if (w.ndcells > 0) {
         const dim3 cells((unsigned)((w.ndcells + kHalves - 1) / kHalves));
         hipLaunchKernelGGL(k_fof_cells, cells, dim3(kBlock), kHalves * bx.nsub_max * sizeof(float4), s, w.ndcells, bx,
@@ -955,7 +959,8 @@ void launch_keys_from_labels(const int32_t *l0_in, const float *dens_in, int64_t
                              hipStream_t s) {
     // the packed copy lives in the second radix key array (free after binning)
     uint2 *packed = reinterpret_cast<uint2 *>(w.rkey[1]);
-    hipLaunchKernelGGL(k_pack_labels, grid(n), dim3(kBlock), 0, s, n, l0_in, dens_in, packed, w.gcnt);
+    hipLaunchKernelGGL(k_pack_labels, grid(n), dim3(kBlock), 0, s, n, l0_in, dens_in, packed, w.gcnt,
+                       w.clock + kClockDensity);
     hipLaunchKernelGGL(k_keys_from_labels, grid(n), dim3(kBlock), 0, s, n, bx, packed, w.spos, w.gkey, w.dens_s,
                        w.gcnt, w.err);
 }

@@ -260,7 +260,6 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->geo2 = extra ? c.take<Geo>(nbox) : nullptr;
     w->base = c.take<uint32_t>(nbox + 1);
     w->btab = c.take<int32_t>(box_table_len(nbox));
-    w->box_rows = c.take<int64_t>(nbox);
     w->gcom = extra ? c.take<double>(6 * n1) : nullptr;
     w->ordk = extra ? c.take<int32_t>(n1) : nullptr;
     return c.off + 256;
@@ -369,7 +368,7 @@ hf_status ensure_stage(Lane *c, size_t bytes, bool may_grow) {
     c->stage = nullptr;
     c->stage_bytes = 0;
     const size_t want = bytes + bytes / 2;
-    if (hipHostMalloc(&c->stage, want, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&c->stage, want, hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
         c->stage = nullptr;
         return fail(c, HF_ERR_NOMEM, "hipHostMalloc of the box tables failed");
@@ -419,6 +418,9 @@ hf_status prepare(Lane *c, const Plan &pl, Work *w, bool extra, const hf::FixedA
         carve((char *)c->arena, pl.n, pl.ncell, pl.nsub_max, rhl, pl.nbox, extra, w);
     }
     w->host = c->host;
+    // the stage stamps take the upper half of the lane's pinned words
+    w->clock = reinterpret_cast<uint64_t *>(c->host + 32);
+    for (int k = 0; k < hf::kClocks; k++) w->clock[k] = 0;
     w->ncu = c->ncu;
     w->radius_bins = c->radius_bins;
     c->stats = hf_stats{};
@@ -431,11 +433,12 @@ hf_status prepare(Lane *c, const Plan &pl, Work *w, bool extra, const hf::FixedA
 
 // Device words read back in one dispatch and one wait (the lane's pinned host
 // words); out[i] = *src[i].
-hf_status read_dev(Lane *c, hipStream_t s, std::initializer_list<const void *> src, uint32_t *out) {
+hf_status read_dev(Lane *c, hipStream_t s, std::initializer_list<const void *> src, uint32_t *out,
+                   uint64_t *clock = nullptr) {
     hf::WordSrc w{};
     int k = 0;
     for (const void *p : src) w.p[k++] = static_cast<const uint32_t *>(p);
-    HIP_OK(c, hf::read_words(w, k, c->host, out, s));
+    HIP_OK(c, hf::read_words(w, k, c->host, out, s, clock));
     return HF_OK;
 }
 
@@ -456,18 +459,33 @@ hf_status err_status(Lane *c, uint32_t err, uint32_t box, const Plan *pl) {
 
 hf_status check_pos_flags(Lane *c, const Work &w, const Plan *pl, hipStream_t s) {
     uint32_t e[2] = {0, 0};
-    hf_status st = read_dev(c, s, {w.err, w.err + 1}, e);
+    hf_status st = read_dev(c, s, {w.err, w.err + 1}, e, w.clock + hf::kClockEnd);
     return st != HF_OK ? st : err_status(c, e[0], e[1], pl);
 }
 
-float elapsed(hipEvent_t a, hipEvent_t b) {
-    float ms = 0.0f;
-    if (hipEventElapsedTime(&ms, a, b) != hipSuccess) {
-        (void)hipGetLastError();
-        return 0.0f;
-    }
-    return ms;
+// Milliseconds from the start of stage a to that of stage b, once the stream has
+// drained.  A stage without a stamp starts with the next that has one.
+float stage_ms(const Lane *c, const Work &w, int a, int b) {
+    auto at = [&](int k) {
+        while (k < hf::kClockEnd && w.clock[k] == 0) k++;
+        return w.clock[k];
+    };
+    const uint64_t from = at(a), to = at(b);
+    return to > from && c->clock_khz > 0 ? (float)((double)(to - from) / c->clock_khz) : 0.0f;
 }
+
+// The times of the stages in `mask` (bit k: the stage that starts at stamp k),
+// and the total up to stamp `last`.
+void stage_times(Lane *c, const Work &w, uint32_t mask, int last = hf::kClockEnd) {
+    hf_stats &st = c->stats;
+    float *const ms[hf::kClockEnd] = {&st.ms_bin, &st.ms_density, &st.ms_fof, &st.ms_segment,
+                                      &st.ms_candidates, &st.ms_accept, &st.ms_assign, &st.ms_output};
+    for (int k = 0; k < hf::kClockEnd; k++)
+        if (mask >> k & 1u) *ms[k] = stage_ms(c, w, k, k + 1);
+    st.ms_total = stage_ms(c, w, hf::kClockBin, last);
+}
+constexpr uint32_t kAllStages = (1u << hf::kClockEnd) - 1u;
+constexpr uint32_t kCompasoStages = kAllStages & ~(1u << hf::kClockDensity) & ~(1u << hf::kClockFof);
 
 // The candidate stage on the segmented groups.  The counts that size the later
 // launches and the error flags of the steps so far (the kernels before this
@@ -506,7 +524,7 @@ hf_status candidates(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, Coun
 // CompaSO on the binned particles with group keys in w.gkey.  Fills halo_id,
 // l0_out and dens_out (either may be null; the densities from w.dens_s), every
 // box's table and its row count (n_halos, host,
-// nbox entries); records events ev[3..8].  CAPACITY when a table did not fit.
+// nbox entries).  CAPACITY when a table did not fit.
 // Optional output of a one-box pass: its members in group order (Sec. 2.3.5).
 struct GroupOut {
     int32_t *members = nullptr;     // device [n]
@@ -518,34 +536,29 @@ hf_status run_compaso(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, int
                       const GroupOut &go = GroupOut{}) {
     const int64_t n = pl.n;
     hf_status st = HF_OK;
-    HIP_OK(c, hipEventRecord(c->ev[3], s));
     hf::launch_segment(n, w, s);
     hf::launch_extent(n, bx, w, s);
-    HIP_OK(c, hipEventRecord(c->ev[4], s));
     Counts ct;
     st = candidates(c, pl, bx, w, &ct, s);
     if (st != HF_OK) return st;
     const int64_t G = ct.groups, NC = ct.candidates;
-    HIP_OK(c, hipEventRecord(c->ev[5], s));
     hf::launch_accept(n, G, NC, c->stats.n_members, bx, w, s);
-    HIP_OK(c, hipEventRecord(c->ev[6], s));
     hf::launch_assign(n, bx, w, s);
-    HIP_OK(c, hipEventRecord(c->ev[7], s));
     hf::launch_output_flags(n, NC, bx, w, s);
-    hf::launch_output(n, NC, bx, w, halo_id, l0_out, dens_out, w.box_rows, s);
-    HIP_OK(c, hipEventRecord(c->ev[8], s));
+    hf::launch_output(n, NC, bx, w, halo_id, l0_out, dens_out, s);
     // every box's rows, the nuclei accepted (counter 2) and the error flags
     int64_t *rows = reinterpret_cast<int64_t *>(c->stage);
-    HIP_OK(c, hipMemcpyAsync(rows, w.box_rows, sizeof(int64_t) * pl.nbox, hipMemcpyDeviceToHost, s));
+    hf::WordSrc last{};
+    last.p[0] = reinterpret_cast<const uint32_t *>(w.counters + 2);
+    last.p[1] = reinterpret_cast<const uint32_t *>(w.err);
+    last.p[2] = reinterpret_cast<const uint32_t *>(w.err + 1);
+    hf::launch_finish(bx, last, 3, w, rows, s);
+    HIP_OK(c, hipGetLastError());
+    HIP_OK(c, hipStreamSynchronize(s));
     uint32_t r2[3];
-    st = read_dev(c, s, {w.counters + 2, w.err, w.err + 1}, r2);
-    if (st == HF_OK) st = err_status(c, r2[1], r2[2], &pl);
+    hf::collect_words(c->host, 3, r2);
+    st = err_status(c, r2[1], r2[2], &pl);
     if (st != HF_OK) return st;
-    c->stats.ms_segment = elapsed(c->ev[3], c->ev[4]);
-    c->stats.ms_candidates = elapsed(c->ev[4], c->ev[5]);
-    c->stats.ms_accept = elapsed(c->ev[5], c->ev[6]);
-    c->stats.ms_assign = elapsed(c->ev[6], c->ev[7]);
-    c->stats.ms_output = elapsed(c->ev[7], c->ev[8]);
     c->stats.n_candidates = NC;
     c->stats.n_dense_cells = w.ndcells;
     c->stats.n_dense_chunks = w.nchunks;
@@ -567,41 +580,42 @@ hf_status run_compaso(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, int
         // the rows are known and fit: members by table row (the call ends
         // synchronized with its stream, as every call does)
         hf::launch_group_order(n, total, halo_id, w, go.members, go.halo_start, s);
-        HIP_OK(c, hipEventRecord(c->ev[8], s));
+        HIP_OK(c, hf::publish_words(last, 0, c->host, s, w.clock + hf::kClockEnd));
         HIP_OK(c, hipStreamSynchronize(s));
-        c->stats.ms_output = elapsed(c->ev[7], c->ev[8]);
     }
     return HF_OK;
 }
 
 // Uploads the box tables, bins all particles and reads the work counts.
 // dens: the call computes densities (binning also writes the records the
-// density kernel reads); extra: halo statistics buffers.  bx receives the
-// device view of the boxes.
+// density kernel reads); extra: halo statistics buffers; geo2: a second level's
+// constants (one box).  bx receives the device view of the boxes.
 hf_status begin(Lane *c, const Plan &pl, const float *pos, hf::Boxes *bx, Work *w, hipStream_t s, bool dens,
-                bool extra = false, const hf::FixedArena *fx = nullptr) {
+                bool extra = false, const hf::FixedArena *fx = nullptr, const Geo *geo2 = nullptr) {
     if (pl.n > 0 && !pos) return fail(c, HF_ERR_INVALID, "pos is NULL");
     hf_status st = prepare(c, pl, w, extra, fx);
     if (st != HF_OK) return st;
     if (!dens) w->pq = nullptr;
-    // the tables through pinned staging (the lane's previous call has ended)
+    // the tables through pinned staging (the lane's previous call has ended),
+    // read by the call's first kernel
     char *stg = reinterpret_cast<char *>(c->stage);
-    memcpy(stg, pl.geo.data(), sizeof(Geo) * pl.nbox);
-    memcpy(stg + sizeof(Geo) * pl.nbox, pl.base.data(), sizeof(uint32_t) * (pl.nbox + 1));
-    HIP_OK(c, hipMemcpyAsync(w->geo, stg, sizeof(Geo) * pl.nbox, hipMemcpyHostToDevice, s));
-    HIP_OK(c, hipMemcpyAsync(w->base, stg + sizeof(Geo) * pl.nbox, sizeof(uint32_t) * (pl.nbox + 1),
-                             hipMemcpyHostToDevice, s));
-    if (!pl.btab.empty()) {
-        char *tb = stg + sizeof(Geo) * pl.nbox + sizeof(uint32_t) * (pl.nbox + 1);
-        memcpy(tb, pl.btab.data(), sizeof(int32_t) * pl.btab.size());
-        HIP_OK(c, hipMemcpyAsync(w->btab, tb, sizeof(int32_t) * pl.btab.size(), hipMemcpyHostToDevice, s));
-    }
+    hf::BeginCopy bc{};
+    bc.src = reinterpret_cast<const uint32_t *>(stg);
+    int na = 0;
+    auto add = [&](const void *from, void *to, size_t bytes) {
+        memcpy(stg, from, bytes);
+        stg += bytes;
+        bc.dst[na] = static_cast<uint32_t *>(to);
+        bc.words[na++] = (uint32_t)(bytes / 4);
+    };
+    static_assert(sizeof(Geo) % 4 == 0, "tables are copied by words");
+    add(pl.geo.data(), w->geo, sizeof(Geo) * pl.nbox);
+    add(pl.base.data(), w->base, sizeof(uint32_t) * (pl.nbox + 1));
+    if (!pl.btab.empty()) add(pl.btab.data(), w->btab, sizeof(int32_t) * pl.btab.size());
+    if (geo2) add(geo2, w->geo2, sizeof(Geo));
     *bx = hf::Boxes{w->geo, w->base, pl.nbox, pl.nsub_max, w->btab, pl.bshift};
-    hf::fill_i32(w->counters, 0, 16, s);
-    hf::fill_i32(w->err, 0, 1, s);
-    hf::fill_i32(w->err + 1, 0x7fffffff, 1, s);
+    HIP_OK(c, hf::begin_call(bc, w->counters, w->err, w->clock + hf::kClockBin, s));
     const int64_t n = pl.n;
-    HIP_OK(c, hipEventRecord(c->ev[0], s));
     hf::launch_bin(pos, n, pl.ncell, *bx, *w, s);
     // dense chunks, dense cells, sparse particles, and the range flag of the
     // positions (binning clamps cells, so nothing it wrote is out of bounds).
@@ -632,7 +646,6 @@ hf_status begin(Lane *c, const Plan &pl, const float *pos, hf::Boxes *bx, Work *
     w->ndcells = counts[1];
     w->nsparse = counts[2];
     w->nhard = 0;
-    HIP_OK(c, hipEventRecord(c->ev[1], s));
     return HF_OK;
 }
 
@@ -677,15 +690,10 @@ hf_status find_boxes(Lane *c, const hf::BoxSet &bs, const float *pos, float *den
     // output stage only the halo labels (two words cost less than a record)
     float *dens_late = l0_id ? density : nullptr;
     hf::launch_density(pl.n, bx, w, l0_id ? nullptr : density, s);
-    HIP_OK(c, hipEventRecord(c->ev[2], s));
     hf::launch_fof(pl.n, bx, w, s);
     hf::launch_fof_labels(pl.n, bx, w, nullptr, s);
-    HIP_OK(c, hipEventRecord(c->ev[9], s));
     st = run_compaso(c, pl, bx, w, halo_id, l0_id, dens_late, n_halos, s, go);
-    c->stats.ms_bin = elapsed(c->ev[0], c->ev[1]);
-    c->stats.ms_density = elapsed(c->ev[1], c->ev[2]);
-    c->stats.ms_fof = elapsed(c->ev[2], c->ev[9]);
-    c->stats.ms_total = elapsed(c->ev[0], c->ev[8]);
+    stage_times(c, w, kAllStages);
     return st;
 }
 
@@ -705,13 +713,13 @@ hf_status lane_init(Lane *L, int device, bool own_stream) {
         return HF_ERR_DEVICE;
     }
     // room for the tables of a few hundred boxes; larger calls grow it
-    if (hipHostMalloc(&L->stage, 64 << 10, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&L->stage, 64 << 10, hipHostMallocCoherent) != hipSuccess) {
         L->stage = nullptr;
         return HF_ERR_DEVICE;
     }
     L->stage_bytes = 64 << 10;
-    for (auto &e : L->ev)
-        if (hipEventCreate(&e) != hipSuccess) return HF_ERR_DEVICE;
+    if (hipDeviceGetAttribute(&L->clock_khz, hipDeviceAttributeWallClockRate, device) != hipSuccess)
+        return HF_ERR_DEVICE;
     if (hipEventCreateWithFlags(&L->pub, hipEventDisableTiming) != hipSuccess) return HF_ERR_DEVICE;
     if (own_stream && hipStreamCreateWithFlags(&L->stream, hipStreamNonBlocking) != hipSuccess)
         return HF_ERR_DEVICE;
@@ -735,8 +743,6 @@ void lane_destroy(Lane *L) {
     if (L->stage) (void)hipHostFree(L->stage);
     L->stage = nullptr;
     L->stage_bytes = 0;
-    for (auto &e : L->ev)
-        if (e) (void)hipEventDestroy(e);
     if (L->pub) (void)hipEventDestroy(L->pub);
     L->pub = nullptr;
     if (L->stream) (void)hipStreamDestroy(L->stream);
@@ -901,11 +907,8 @@ hf_status hf_density(hf_ctx *ctx, const float *pos, int64_t n, const hf_params *
     st = begin(c, pl, pos, &bx, &w, s, true);
     if (st != HF_OK) return st;
     hf::launch_density(n, bx, w, density, s);
-    HIP_OK(c, hipEventRecord(c->ev[2], s));
     st = check_pos_flags(c, w, &pl, s);
-    c->stats.ms_bin = elapsed(c->ev[0], c->ev[1]);
-    c->stats.ms_density = elapsed(c->ev[1], c->ev[2]);
-    c->stats.ms_total = elapsed(c->ev[0], c->ev[2]);
+    stage_times(c, w, 1u << hf::kClockBin | 1u << hf::kClockDensity);
     return st;
 }
 
@@ -953,18 +956,15 @@ hf_status hf_l0_fof(hf_ctx *ctx, const float *pos, const float *density, int64_t
     st = begin(c, pl, pos, &bx, &w, s, false);
     if (st != HF_OK) return st;
     hf::launch_gather_density(density, n, w, s);
-    HIP_OK(c, hipEventRecord(c->ev[2], s));
     hf::launch_fof(n, bx, w, s);
     hf::launch_fof_labels(n, bx, w, l0_id, s);
-    HIP_OK(c, hipEventRecord(c->ev[3], s));
     hf::launch_segment_totals(n, w, s);
     uint32_t r[4] = {0, 0, 0, 0};
-    st = read_dev(c, s, {w.counters + hf::kCntGroups, w.counters + hf::kCntMembers, w.err, w.err + 1}, r);
+    st = read_dev(c, s, {w.counters + hf::kCntGroups, w.counters + hf::kCntMembers, w.err, w.err + 1}, r,
+                  w.clock + hf::kClockEnd);
     if (st == HF_OK) st = err_status(c, r[2], r[3], &pl);
     const uint32_t G32 = r[0], M32 = r[1];
-    c->stats.ms_bin = elapsed(c->ev[0], c->ev[1]);
-    c->stats.ms_fof = elapsed(c->ev[2], c->ev[3]);
-    c->stats.ms_total = elapsed(c->ev[0], c->ev[3]);
+    stage_times(c, w, 1u << hf::kClockBin | 1u << hf::kClockFof, hf::kClockSegment);
     c->stats.n_members = M32;
     c->stats.n_groups = G32;
     if (n_groups) *n_groups = G32;
@@ -995,12 +995,10 @@ hf_status hf_compaso(hf_ctx *ctx, const float *pos, const float *density, const 
     st = begin(c, pl, pos, &bx, &w, s, false);
     if (st != HF_OK) return st;
     hf::launch_keys_from_labels(l0_id, density, n, bx, w, s);  // also gathers the densities
-    HIP_OK(c, hipEventRecord(c->ev[2], s));
     int64_t nh = 0;
     st = run_compaso(c, pl, bx, w, halo_id, nullptr, nullptr, &nh, s);
     if (n_halos) *n_halos = nh;
-    c->stats.ms_bin = elapsed(c->ev[0], c->ev[1]);
-    c->stats.ms_total = elapsed(c->ev[0], c->ev[8]);
+    stage_times(c, w, kCompasoStages);
     return st;
 }
 
@@ -1031,19 +1029,13 @@ hf_status hf_halo_stats(hf_ctx *ctx, const float *pos, const float *density, con
     if (st != HF_OK) return st;
     hf::Boxes bx;
     Work w;
-    st = begin(c, pl, pos, &bx, &w, s, false, true);
-    if (st != HF_OK) return st;
     g2.cell_base = pl.geo[0].cell_base;
     g2.orig_base = 0;
-    char *stg = reinterpret_cast<char *>(c->stage) + sizeof(Geo) * 2 + 256;
-    memcpy(stg, &g2, sizeof(Geo));
-    HIP_OK(c, hipMemcpyAsync(w.geo2, stg, sizeof(Geo), hipMemcpyHostToDevice, s));
+    st = begin(c, pl, pos, &bx, &w, s, false, true, nullptr, &g2);
+    if (st != HF_OK) return st;
     const hf::Boxes bx2{w.geo2, w.base, 1, pl.nsub_max, nullptr, 0};
     hf::launch_keys_from_labels(halo_id, density, n, bx, w, s);  // also gathers the densities
-    HIP_OK(c, hipEventRecord(c->ev[2], s));
-    HIP_OK(c, hipEventRecord(c->ev[3], s));
     hf::launch_segment(n, w, s);
-    HIP_OK(c, hipEventRecord(c->ev[4], s));
     Counts ct;
     st = candidates(c, pl, bx2, w, &ct, s);
     if (st == HF_OK && ct.groups != n_halos) {
@@ -1052,22 +1044,13 @@ hf_status hf_halo_stats(hf_ctx *ctx, const float *pos, const float *density, con
     }
     if (st != HF_OK) return st;
     const int64_t G = ct.groups, M = c->stats.n_members, NC32 = ct.candidates;
-    HIP_OK(c, hipEventRecord(c->ev[5], s));
     hf::launch_accept(n, G, NC32, M, bx2, w, s);
-    HIP_OK(c, hipEventRecord(c->ev[6], s));
     hf::launch_assign(n, bx2, w, s);
-    HIP_OK(c, hipEventRecord(c->ev[7], s));
     hf::launch_halo_stats(n, G, M, g2, p->particle_mass, pos, halo_id, w, stats, group_start, group_members, s);
-    HIP_OK(c, hipEventRecord(c->ev[8], s));
+    HIP_OK(c, hf::publish_words(hf::WordSrc{}, 0, c->host, s, w.clock + hf::kClockEnd));
     HIP_OK(c, hipStreamSynchronize(s));
     c->stats.n_candidates = NC32;
-    c->stats.ms_bin = elapsed(c->ev[0], c->ev[1]);
-    c->stats.ms_segment = elapsed(c->ev[3], c->ev[4]);
-    c->stats.ms_candidates = elapsed(c->ev[4], c->ev[5]);
-    c->stats.ms_accept = elapsed(c->ev[5], c->ev[6]);
-    c->stats.ms_assign = elapsed(c->ev[6], c->ev[7]);
-    c->stats.ms_output = elapsed(c->ev[7], c->ev[8]);
-    c->stats.ms_total = elapsed(c->ev[0], c->ev[8]);
+    stage_times(c, w, kCompasoStages);
     return HF_OK;
 }
 

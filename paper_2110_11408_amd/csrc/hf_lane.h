@@ -37,7 +37,7 @@ struct Lane {
     Budget *budget = nullptr;      // the owning context's, or null (no accounting)
     void *arena = nullptr;
     size_t arena_bytes = 0;
-    hipEvent_t ev[10] = {};
+    int clock_khz = 0;             // rate of the device's wall clock (stage times)
     hf_stats stats = {};
     std::string err;
     hipStream_t stream = nullptr;  // owned; null for a context's main lane
@@ -69,12 +69,12 @@ struct FixedArena {
     size_t bytes;
 };
 
-// Create the events, the pinned host words (and a non-blocking stream of
+// Create the event, the pinned host words (and a non-blocking stream of
 // default priority when own_stream).  Returns HF_ERR_DEVICE on failure.
 hf_status lane_init(Lane *L, int device, bool own_stream);
 // Free the arena (the lane stays usable; the next call allocates again).
 void lane_release(Lane *L);
-// Release, destroy events, the host words and the owned stream.
+// Release, destroy the event, the host words and the owned stream.
 void lane_destroy(Lane *L);
 // Bytes of arena a call of n particles under p needs (0 if p or n is invalid).
 size_t lane_arena_bytes(const hf_params *p, int64_t n);

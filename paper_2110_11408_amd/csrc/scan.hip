@@ -108,9 +108,22 @@ __global__ __launch_bounds__(kBlock) void k_fill_u32x4(uint4 *p, uint32_t v, int
 
 // Copies k device words into pinned host memory with system-scope stores, so
 // the host sees them once the stream has drained.
-__global__ void k_publish(WordSrc src, int k, uint32_t *host) {
+__global__ void k_publish(WordSrc src, int k, uint32_t *host, uint64_t *clock) {
+    stamp(clock);
     const int t = threadIdx.x;
     if (t < k) __hip_atomic_store(host + t, *src.p[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ __launch_bounds__(kBlock) void k_begin(BeginCopy c, int32_t *counters, int32_t *err, uint64_t *clock) {
+    stamp(clock);
+    const uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    const uint32_t *src = c.src;
+    for (int a = 0; a < 4; a++) {
+        for (uint32_t i = t0; i < c.words[a]; i += step) c.dst[a][i] = src[i];
+        src += c.words[a];
+    }
+    if (t0 < 16) counters[t0] = 0;
+    if (t0 < 2) err[t0] = t0 ? 0x7fffffff : 0;
 }
 
 int64_t grid_for(int64_t n, int64_t cap = 1 << 20) {
@@ -136,9 +149,15 @@ void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
     fill_u32(reinterpret_cast<uint32_t *>(p), (uint32_t)v, n, s);
 }
 
-hipError_t publish_words(const WordSrc &src, int k, uint32_t *host, hipStream_t s) {
-    if (k < 1 || k > WordSrc::kMax) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, src, k, host);
+hipError_t begin_call(const BeginCopy &c, int32_t *counters, int32_t *err, uint64_t *clock, hipStream_t s) {
+    const int64_t words = (int64_t)c.words[0] + c.words[1] + c.words[2] + c.words[3];
+    hipLaunchKernelGGL(k_begin, dim3(grid_for(words, 64)), dim3(kBlock), 0, s, c, counters, err, clock);
+    return hipGetLastError();
+}
+
+hipError_t publish_words(const WordSrc &src, int k, uint32_t *host, hipStream_t s, uint64_t *clock) {
+    if (k < 0 || k > WordSrc::kMax) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, src, k, host, clock);
     return hipGetLastError();
 }
 
@@ -146,8 +165,8 @@ void collect_words(const uint32_t *host, int k, uint32_t *out) {
     for (int i = 0; i < k; i++) out[i] = __atomic_load_n(host + i, __ATOMIC_ACQUIRE);
 }
 
-hipError_t read_words(const WordSrc &src, int k, uint32_t *host, uint32_t *out, hipStream_t s) {
-    hipError_t e = publish_words(src, k, host, s);
+hipError_t read_words(const WordSrc &src, int k, uint32_t *host, uint32_t *out, hipStream_t s, uint64_t *clock) {
+    hipError_t e = publish_words(src, k, host, s, clock);
     if (e != hipSuccess) return e;
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;

@@ -57,8 +57,10 @@ __global__ __launch_bounds__(kBlock) void k_stats_centres(int G, Geo g, double p
                                                           const uint32_t *__restrict__ h_count,
                                                           double *__restrict__ gcom,
                                                           int32_t *__restrict__ ordk,
-                                                          hf_halo_summary *__restrict__ out) {
+                                                          hf_halo_summary *__restrict__ out,
+                                                          uint64_t *clock) {
 #pragma clang fp contract(off)
+    stamp(clock);
     __shared__ long long s_red[kBlock / 64];
     const int gi = blockIdx.x;
     const int64_t start = g_start[gi], m = g_size[gi];
@@ -255,7 +257,7 @@ void launch_halo_stats(int64_t n, int64_t G, int64_t M, const Geo &g, double par
     if (G <= 0) return;
     hipLaunchKernelGGL(k_stats_centres, dim3((unsigned)G), dim3(kBlock), 0, s, (int)G, g, particle_mass, pos,
                        w.g_start, w.g_size, w.g_label, w.mem, w.spos, w.owner, w.gcoff, w.g_nh, w.h_nuc,
-                       w.h_count, w.gcom, w.ordk, out);
+                       w.h_count, w.gcom, w.ordk, out, w.clock + kClockOutput);
     hipLaunchKernelGGL(k_stats_keys, grid(M), dim3(kBlock), 0, s, M, g, w.mem, w.gid_of, w.spos, w.gcom,
                        w.rkey[0]);
     const int gbits = bit_width64((uint64_t)(G - 1));
