@@ -59,8 +59,9 @@ STAGE_KEYS = ("ms_bin", "ms_density", "ms_fof", "ms_segment", "ms_candidates", "
               "ms_assign", "ms_output", "ms_total")
 STAGE_KERNELS = {
     "density": ("k_density_dense", "k_density_sparse"),
-    "bin": ("k_bin_key", "k_radix_count", "k_radix_scatter", "k_bucket_sort", "k_bin_place", "k_cell_offsets",
-            "k_bin_marks", "k_bin_lists", "k_sub_table"),
+    "bin": ("k_bin_key", "k_radix_count", "k_radix_scatter", "k_bucket_sort", "k_bin_place", "k_rec_count",
+            "k_rec_scatter", "k_rec_first", "k_rec_count2", "k_rec_starts", "k_rec_bucket", "k_bin_marks",
+            "k_bin_lists", "k_sub_table"),
     "fof": ("k_fof_phase_a", "k_fof_cells", "k_fof_faces", "k_fof_cell_roots", "k_fof_dense", "k_fof_sparse",
             "k_fof_roots", "k_fof_keys"),
 }
@@ -81,9 +82,9 @@ def stage_work(n, ncell, pairs):
         "density": ("alu", pairs * FLOPS_PER_PAIR / 1e12, FP32_PEAK_TFLOPS, "TFLOP/s"),
         # binning: read xyz 12 + sort key written and read once 16 + three
         # sorted float4 records (positions, cell-local, density operand) 48 +
-        # sub-cell index 2 = 78 B per particle, plus the cell offset 4 B per
-        # cell of the grid
-        "bin": ("hbm", (78.0 * n + 4.0 * ncell) / 1e9, HBM_PEAK_GBS, "GB/s"),
+        # sub-cell index 2 = 78 B per particle, plus the cell index's 8 B per
+        # 32 cells of the grid
+        "bin": ("hbm", (78.0 * n + 0.25 * ncell) / 1e9, HBM_PEAK_GBS, "GB/s"),
         # FoF: read float4 x2 + density for every particle (36 B), parent r/w 8 B
         "fof": ("hbm", 44.0 * n / 1e9, HBM_PEAK_GBS, "GB/s"),
     }

@@ -861,219 +861,235 @@ __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict
     }
 }
 
-// Cell offsets: off[c] = first sorted particle of cell c (the next cell's
-// start when c is empty), off[ncell] = n.  With C(s) = cell of slot s,
-// C(-1) = -1 and C(n) = ncell, slot s owns the cells (C(s-1), C(s)].  Each
-// wavefront takes 64 consecutive slots (the last one slot n) and writes the
-// cells they own with consecutive lanes on consecutive cells (16-byte stores);
-// the owner of a cell is the last slot that owns cells and starts at or before
-// it, found from a bitmask of the starts in each 256-cell window (a count of
-// set bits gives its rank among those slots) and a rank -> slot table.
-__global__ __launch_bounds__(kBlock) void k_cell_offsets(int64_t n, int64_t ncell,
-                                                         const uint32_t *__restrict__ scell,
-                                                         uint32_t *__restrict__ off) {
-    __shared__ uint64_t s_bits[kBlock / 64][4];   // starts inside the current 256-cell window
-    __shared__ uint8_t s_slot[kBlock / 64][64];   // slot of each rank
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t s0 = ((int64_t)blockIdx.x * (kBlock / 64) + w) * 64;
-    if (s0 > n) return;  // whole wavefront past slot n (uniform)
-    const int64_t s = s0 + lane;
-    auto C = [&](int64_t q) -> int64_t {
-        return q < 0 ? -1 : (q >= n ? ncell : (int64_t)scell[q]);
-    };
-    const int64_t hi = s <= n ? C(s) : ncell;
-    const int64_t lo = s <= n ? C(s - 1) : ncell;
-    // cells owned by this slot, and their exclusive prefix over the wavefront
-    // (32-bit: the grid has fewer than 2^32 cells)
-    const uint32_t g = (uint32_t)(hi - lo);
-    uint32_t incl = g;
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += y;
+// First sorted particle of the cell cc that holds particle s0 - 1, by a wavefront:
+// the 64 particles before that one, then steps back of doubling length, then
+// the interval between two of them cut 65-fold.
+__device__ __forceinline__ int64_t cell_start(const uint32_t *__restrict__ scell, int64_t s0, uint32_t cc) {
+    const int lane = threadIdx.x & 63;
+    int64_t hi = s0 - 1;  // in the cell
+    auto in = [&](int64_t p) { return p >= 0 && scell[p] == cc; };
+    uint64_t m = ~__ballot(in(hi - 1 - lane));
+    if (m) return hi - __builtin_ctzll(m);
+    hi -= 64;
+    // lane 63 would step back 2^69 particles: all past the first 33 miss
+    const int64_t back = (int64_t)64 << min(lane, 33);
+    m = ~__ballot(in(hi - back));
+    const int f = __builtin_ctzll(m);  // the first step out of the cell
+    int64_t lo = hi - ((int64_t)64 << f);
+    if (f > 0) hi -= (int64_t)64 << (f - 1);
+    if (lo < -1) lo = -1;
+    // lo is not in the cell, hi is
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + 64) / 65;
+        const int64_t p = lo + step * (lane + 1);
+        const uint64_t q = __ballot(p >= hi || in(p));
+        const int k = q ? __builtin_ctzll(q) : 64;  // the first probe in the cell
+        const int64_t top = lo + step * (k + 1);
+        lo += step * k;
+        if (k < 64 && top < hi) hi = top;
     }
-    const uint32_t pre = incl - g;
-    const uint32_t G = lane_get(incl, 63);
-    // first cell owned by the wavefront: one past the cell of the slot before
-    // it, which lane 0 holds as lo (a cell id below 2^32 when s0 > 0)
-    const int64_t first =
-        s0 == 0 ? 0 : (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)lo) + 1;
-    const int64_t end = first + (int64_t)G;
-    // the slots that own cells, in order: rank -> slot
-    const uint64_t owners = __ballot(g > 0);
-    if (g > 0) s_slot[w][__popcll(owners & lanes_below(lane))] = (uint8_t)lane;
-    // windows of 256 cells aligned to 4, four consecutive cells per lane; the
-    // owner of a cell is the slot of rank (number of owned starts at or before
-    // it) - 1, counted from a bitmask of the starts in the window
-    uint32_t before = 0;  // starts in earlier windows
-    for (int64_t w0 = first & ~(int64_t)3; w0 < end; w0 += 256) {
-        if (lane < 4) s_bits[w][lane] = 0ull;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        const int64_t st = first + (int64_t)pre;
-        if (g > 0 && st >= w0 && st < w0 + 256) {
-            const int r = (int)(st - w0);
-            atomicOr(reinterpret_cast<unsigned long long *>(&s_bits[w][r >> 6]), 1ull << (r & 63));
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        const uint64_t b0 = s_bits[w][0], b1 = s_bits[w][1], b2 = s_bits[w][2], b3 = s_bits[w][3];
-        const int p = 4 * lane, k = p >> 6;
-        const uint64_t wk = k == 0 ? b0 : (k == 1 ? b1 : (k == 2 ? b2 : b3));
-        const uint32_t lower = before + (k > 0 ? (uint32_t)__popcll(b0) : 0u) + (k > 1 ? (uint32_t)__popcll(b1) : 0u) +
-                               (k > 2 ? (uint32_t)__popcll(b2) : 0u);
-        uint32_t v[4];
-        bool all = true;
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int pu = (p + u) & 63;
-            const uint64_t upto = pu == 63 ? ~0ull : ((2ull << pu) - 1ull);
-            const uint32_t cnt = lower + (uint32_t)__popcll(wk & upto);
-            const int64_t cell = w0 + p + u;
-            const bool valid = cell >= first && cell < end;
-            all = all && valid;
-            // read for every cell (the rank is at most 64), so that the four
-            // reads are issued together
-            const uint32_t sl = s_slot[w][(cnt > 0u ? cnt - 1u : 0u) & 63u];
-            v[u] = valid ? (uint32_t)s0 + sl : 0u;
-        }
-        if (all) {
-            *reinterpret_cast<uint4 *>(off + w0 + p) = make_uint4(v[0], v[1], v[2], v[3]);
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int64_t cell = w0 + p + u;
-                if (cell >= first && cell < end) off[cell] = v[u];
-            }
-        }
-        before += (uint32_t)(__popcll(b0) + __popcll(b1) + __popcll(b2) + __popcll(b3));
-    }
+    return hi;
 }
 
+constexpr int kFineTile = 1024;
+constexpr int64_t kFineTilesMost = (int64_t)1 << 22;  // 4096 tiles
+
 // Marks of the sorted particles: head of a dense chunk, head of a dense cell,
-// sparse.  A wavefront takes 64 consecutive particles at a time and finds the
-// bounds of their cells from the cell ids of neighbouring particles (cell
-// changes are found by ballot); only a cell that starts before, or ends after,
-// the wavefront's particles reads its offset from the grid.  The marks are kept
-// as the ballots (a word per kind and particle, and its scan, moved 70 bytes
-// per particle and took eleven launches), and a workgroup's 4096 particles
-// leave the three counts for the scan of the lists.
-__global__ __launch_bounds__(kBlock) void k_bin_marks(int64_t n, const uint32_t *__restrict__ scell,
-                                                      const uint32_t *__restrict__ off, Marks marks,
-                                                      uint32_t *__restrict__ sums, int64_t tiles) {
-    __shared__ uint32_t s_cnt[kBlock / 64][3];
-    constexpr int kSteps = kScanTile / kBlock, kIlp = 4;
+// sparse, head of a cell.  A wavefront takes 64 consecutive particles at a time
+// and finds the bounds of their cells from the cell ids of neighbouring
+// particles (cell changes are found by ballot); only where a cell starts before
+// the wavefront's particles is its start searched for, and where one ends after
+// them one more id tells whether it is dense.  The marks are kept as the ballots
+// (a word per kind and particle, and its scan, moved 70 bytes per particle and
+// took eleven launches), and a workgroup's kTile particles leave the four counts
+// for the scan of the lists.  The words of the cell index are zeroed for the
+// next kernel (zero: nzero of them).
+template <int kTile>
+__global__ __launch_bounds__(kBlock) void k_bin_marks(int64_t n, const uint32_t *__restrict__ scell, Marks marks,
+                                                      uint32_t *__restrict__ sums, int64_t tiles,
+                                                      uint2 *__restrict__ zero, int64_t nzero) {
+    __shared__ uint32_t s_cnt[kBlock / 64][4];
+    constexpr int kSteps = kTile / kBlock, kIlp = 4;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int64_t z = (int64_t)blockIdx.x * kBlock + threadIdx.x; z < nzero; z += (int64_t)gridDim.x * kBlock)
+        zero[z] = make_uint2(0u, 0u);
     const int64_t t = xcd_block();
-    uint32_t nc = 0, nd = 0, ns = 0;
+    uint32_t nc = 0, nd = 0, ns = 0, nh = 0;
     for (int k0 = 0; k0 < kSteps; k0 += kIlp) {
         // each step's cells, and those beyond its two ends (lane 0: the slot
         // before it, lane 63: the one after), all loaded together
         uint32_t c[kIlp], ce[kIlp];
 #pragma unroll
         for (int u = 0; u < kIlp; u++) {
-            const int64_t s0 = t * kScanTile + ((k0 + u) * (kBlock / 64) + w) * 64, i = s0 + lane;
+            const int64_t s0 = t * kTile + ((k0 + u) * (kBlock / 64) + w) * 64, i = s0 + lane;
             const int64_t e = lane == 0 ? s0 - 1 : (lane == 63 ? s0 + 64 : -1);
             c[u] = i < n ? scell[i] : 0xffffffffu;
             ce[u] = e >= 0 && e < n ? scell[e] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < kIlp; u++) {
-            const int64_t s0 = t * kScanTile + ((k0 + u) * (kBlock / 64) + w) * 64, i = s0 + lane;
+            const int64_t s0 = t * kTile + ((k0 + u) * (kBlock / 64) + w) * 64, i = s0 + lane;
             if (s0 >= n) break;
             const bool act = i < n;
             uint32_t cprev = __shfl_up(c[u], 1, 64), cnext = __shfl_down(c[u], 1, 64);
-            if (lane == 0) cprev = s0 > 0 ? ce[u] : 0xfffffffeu;
-            if (lane == 63) cnext = s0 + 64 < n ? ce[u] : 0xfffffffdu;
+            if (lane == 0) cprev = s0 > 0 ? ce[u] : ~c[u];
+            if (lane == 63) cnext = s0 + 64 < n ? ce[u] : ~c[u];
+            if (i + 1 == n) cnext = ~c[u];
             const uint64_t heads = __ballot(act && c[u] != cprev);
             const uint64_t tails = __ballot(act && c[u] != cnext);
-            bool dense = false, head = false, first = false;
-            if (act) {
-                const uint64_t le = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
-                const uint64_t h = heads & le, tl = tails & ~(le >> 1);  // heads at or below, tails at or above
-                const uint32_t a = h ? (uint32_t)(s0 + 63 - __clzll((long long)h)) : off[c[u]];
-                const uint32_t b = tl ? (uint32_t)(s0 + __ffsll((unsigned long long)tl)) : off[c[u] + 1];
-                dense = b - a >= (uint32_t)kDenseMin;
-                head = dense && (((uint32_t)i - a) % 64u == 0u);
-                first = dense && (uint32_t)i == a;
-            }
+            const uint64_t le = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
+            const uint64_t h = heads & le, tl = tails & ~(le >> 1);  // heads at or below, tails at or above
+            // the start of the cell, for the first cell possibly before s0
+            int64_t before = s0;
+            if (!(heads & 1ull)) before = cell_start(scell, s0, lane_get(c[u], 0));
+            const int64_t a = h ? s0 + 63 - __clzll((long long)h) : before;
+            bool dense;
+            if (tl)
+                dense = s0 + __ffsll((unsigned long long)tl) - a >= kDenseMin;
+            else  // holds the particle after the wavefront's too
+                dense = a + kDenseMin - 1 <= s0 + 64 ||
+                        (a + kDenseMin - 1 < n && scell[a + kDenseMin - 1] == c[u]);
+            dense = dense && act;
+            const bool head = dense && ((i - a) & 63) == 0, first = dense && i == a;
             const uint64_t mc = __ballot(head), md = __ballot(first), ms = __ballot(act && !dense);
             if (lane == 0) {
                 marks.chunk[s0 >> 6] = mc;
                 marks.dcell[s0 >> 6] = md;
                 marks.sparse[s0 >> 6] = ms;
+                marks.head[s0 >> 6] = heads;
             }
             nc += (uint32_t)__popcll(mc);
             nd += (uint32_t)__popcll(md);
             ns += (uint32_t)__popcll(ms);
+            nh += (uint32_t)__popcll(heads);
         }
     }
     if (lane == 0) {
         s_cnt[w][0] = nc;
         s_cnt[w][1] = nd;
         s_cnt[w][2] = ns;
+        s_cnt[w][3] = nh;
     }
     __syncthreads();
-    if (threadIdx.x < 3) {
+    if (threadIdx.x < 4) {
         uint32_t v = 0;
         for (int x = 0; x < kBlock / 64; x++) v += s_cnt[x][threadIdx.x];
         sums[threadIdx.x * tiles + t] = v;
     }
 }
 
-// The lists of the marked particles, a workgroup per 4096 particles: dense
-// chunks, dense cells (and the map from cell to dense cell) and sparse
+// The lists of the marked particles, a workgroup per kTile particles: dense
+// chunks, dense cells (their cell and its number, and the map back) and sparse
 // particles, with the zeros that the sparse particles' dense-neighbour sums
-// start from (dfx may be null).  The last workgroup leaves the three totals in
-// the counters.
+// start from (dfx may be null), and the cell index: the cells that start in the
+// tile are gathered in LDS in order, and the first of each word writes it.  Only
+// a word shared with a neighbouring tile takes an atomic.  The last workgroup
+// leaves the totals in the counters.
+template <int kTile>
 __global__ __launch_bounds__(kBlock) void k_bin_lists(int64_t n, Marks marks, const uint32_t *__restrict__ sums,
                                                       int64_t tiles, bool scanned,
                                                       const uint32_t *__restrict__ scell,
                                                       int32_t *__restrict__ chunks,
                                                       uint32_t *__restrict__ dcells,
-                                                      int32_t *__restrict__ sparse,
-                                                      uint32_t *__restrict__ cellmap, uint64_t *__restrict__ dfx,
+                                                      uint32_t *__restrict__ dord,
+                                                      int32_t *__restrict__ sparse, Cells cells,
+                                                      uint64_t *__restrict__ dfx,
                                                       int32_t *__restrict__ counters,
                                                       uint32_t *__restrict__ zero, int nzero) {
-    constexpr int kWords = kScanTile / 64;
-    static_assert(kWords == 64, "one lane per word");
-    __shared__ uint64_t s_mark[3][kWords];
-    __shared__ uint32_t s_at[3][kWords];
+    constexpr int kWords = kTile / 64, kKinds = 4, kIlp = 4;
+    static_assert(kWords <= 64 && kBlock / 64 == kKinds, "one lane per word, one wavefront per kind");
+    static_assert(kWords % (kKinds * kIlp) == 0, "whole rounds");
+    __shared__ uint64_t s_mark[kKinds][kWords];
+    __shared__ uint32_t s_at[kKinds][kWords];
+    __shared__ uint32_t s_cell[kTile];
+    __shared__ uint32_t s_heads, s_first;
+    __shared__ bool s_shared;  // the tile's first cell shares its word with the cell before it
     const int64_t t = xcd_block();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     // the counts of the next stage's segmented list start here
     if (blockIdx.x == 0)
         for (int q = threadIdx.x; q < nzero; q += kBlock) zero[q] = 0u;
-    uint32_t off[3];
+    // wavefront w: the words of kind w and the marked particles before each
+    {
+        uint32_t off = 0;
+        if (t > 0 && scanned) off = sums[w * tiles + t];
+        else if (t > 0) {
+            for (int64_t q = lane; q < t; q += 4 * 64) {
 #pragma unroll
-    for (int k = 0; k < 3; k++) off[k] = t > 0 ? tile_offset(sums + k * tiles, (uint32_t)t, scanned) : 0u;
-    if (w < 3) {
-        // wavefront w: the words of kind w and the marked particles before each
+                for (int u = 0; u < 4; u++) off += q + 64 * u < t ? sums[w * tiles + q + 64 * u] : 0u;
+            }
+            for (int d = 32; d >= 1; d >>= 1) off += __shfl_xor(off, d, 64);
+        }
         const int64_t word = t * kWords + lane;
-        const uint64_t *p = w == 0 ? marks.chunk : (w == 1 ? marks.dcell : marks.sparse);
-        const uint64_t m = word * 64 < n ? p[word] : 0ull;
+        const bool in = lane < kWords && word * 64 < n;
+        const uint64_t *p = w == 0 ? marks.chunk : (w == 1 ? marks.dcell : (w == 2 ? marks.sparse : marks.head));
+        const uint64_t m = in ? p[word] : 0ull;
         const uint32_t cnt = (uint32_t)__popcll(m), incl = wave_incl_scan(cnt);
-        const uint32_t at = (w == 0 ? off[0] : (w == 1 ? off[1] : off[2])) + incl - cnt;
-        s_mark[w][lane] = m;
-        s_at[w][lane] = at;
-        if (w == 2 && word * 64 < n) marks.before[word] = at;
-        if (t == tiles - 1 && lane == 63)
-            counters[w == 0 ? kCntChunks : (w == 1 ? kCntDcells : kCntSparse)] = (int32_t)(at + cnt);
+        const uint32_t at = off + incl - cnt;
+        if (lane < kWords) {
+            s_mark[w][lane] = m;
+            s_at[w][lane] = at;
+        }
+        if (w == 1 && in) marks.dbefore[word] = at;
+        if (w == 2 && in) marks.before[word] = at;
+        if (w == 3 && lane == 63) {
+            s_heads = incl;
+            s_first = off;
+        }
+        if (t == tiles - 1 && lane == 63) {
+            if (w == 3) cells.start[at + cnt] = (uint32_t)n;
+            else counters[w == 0 ? kCntChunks : (w == 1 ? kCntDcells : kCntSparse)] = (int32_t)(at + cnt);
+        }
     }
     __syncthreads();
     const uint64_t below = (1ull << lane) - 1ull;
-    for (int k = w; k < kWords; k += kBlock / 64) {
-        const int64_t i = (t * kWords + k) * 64 + lane;
-        const uint64_t mc = s_mark[0][k], md = s_mark[1][k], ms = s_mark[2][k];
-        if ((mc >> lane) & 1ull) chunks[s_at[0][k] + (uint32_t)__popcll(mc & below)] = (int32_t)i;
-        if ((ms >> lane) & 1ull) {
-            const uint32_t at = s_at[2][k] + (uint32_t)__popcll(ms & below);
-            sparse[at] = (int32_t)i;
-            if (dfx) dfx[at] = 0ull;
+    const uint32_t ofirst = s_first;  // number of the tile's first cell
+    for (int k0 = w; k0 < kWords; k0 += kKinds * kIlp) {
+        uint32_t c[kIlp];
+#pragma unroll
+        for (int u = 0; u < kIlp; u++) {
+            const int64_t i = (t * kWords + k0 + kKinds * u) * 64 + lane;
+            c[u] = i < n ? scell[i] : 0u;
         }
-        if ((md >> lane) & 1ull) {
-            const uint32_t c = scell[i], d = s_at[1][k] + (uint32_t)__popcll(md & below);
-            dcells[d] = c;
-            cellmap[c] = d;  // the cell-count array is reused as cell -> dense-cell map
+#pragma unroll
+        for (int u = 0; u < kIlp; u++) {
+            const int k = k0 + kKinds * u;
+            const int64_t i = (t * kWords + k) * 64 + lane;
+            const uint64_t mc = s_mark[0][k], md = s_mark[1][k], ms = s_mark[2][k], mh = s_mark[3][k];
+            if ((mc >> lane) & 1ull) chunks[s_at[0][k] + (uint32_t)__popcll(mc & below)] = (int32_t)i;
+            if ((ms >> lane) & 1ull) {
+                const uint32_t at = s_at[2][k] + (uint32_t)__popcll(ms & below);
+                sparse[at] = (int32_t)i;
+                if (dfx) dfx[at] = 0ull;
+            }
+            if ((mh >> lane) & 1ull) {
+                const uint32_t o = s_at[3][k] + (uint32_t)__popcll(mh & below), q = o - ofirst;
+                cells.start[o] = (uint32_t)i;
+                s_cell[q] = c[u];
+                if (q == 0u) s_shared = i > 0 && scell[i - 1] / kOccCells == c[u] / kOccCells;
+                if ((md >> lane) & 1ull) {
+                    const uint32_t d = s_at[1][k] + (uint32_t)__popcll(md & below);
+                    dcells[d] = c[u];
+                    dord[d] = o;
+                    cells.dmap[o] = d;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const uint32_t heads = s_heads;
+    for (uint32_t q = threadIdx.x; q < heads; q += kBlock) {
+        const uint32_t word = s_cell[q] / kOccCells;
+        if (q > 0u && s_cell[q - 1u] / kOccCells == word) continue;
+        uint32_t bits = 0, r = q;
+        for (; r < heads && s_cell[r] / kOccCells == word; r++) bits |= 1u << (s_cell[r] % kOccCells);
+        uint2 *const e = cells.occ + word;
+        const bool joins = q == 0u && s_shared;
+        if (joins || r == heads) {
+            atomicOr(&e->x, bits);
+            if (!joins) e->y = ofirst + q;
+        } else {
+            *e = make_uint2(bits, ofirst + q);
         }
     }
 }
@@ -1084,14 +1100,14 @@ __global__ __launch_bounds__(kBlock) void k_bin_lists(int64_t n, Marks marks, co
 // cell's particles are sorted by sub-cell, so particle j writes the entries
 // after its predecessor's sub-cell up to its own, and the entries after the
 // last particle's sub-cell get the cell end; every entry is written once.
-__device__ __forceinline__ void sub_table_cell(int64_t d, const Boxes &bx, const uint32_t *__restrict__ dcells,
-                                               const uint32_t *__restrict__ off,
+__device__ __forceinline__ void sub_table_cell(int64_t d, const Boxes &bx, const uint32_t *__restrict__ dord,
+                                               const uint32_t *__restrict__ start,
                                                const uint16_t *__restrict__ ssub,
                                                uint32_t *__restrict__ subtab) {
     const int lane = threadIdx.x & 63;
-    const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane(dcells[d]);
-    const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane(off[c]);
-    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(off[c + 1]);
+    const uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane(dord[d]);
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane(start[o]);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(start[o + 1]);
     const int nsub = __builtin_amdgcn_readfirstlane(bx.geo[box_of(bx, a)].nsub);
     uint32_t *t = subtab + d * (bx.nsub_max + 1);
     for (uint32_t j0 = a; j0 < b; j0 += 64) {
@@ -1109,15 +1125,15 @@ __device__ __forceinline__ void sub_table_cell(int64_t d, const Boxes &bx, const
 // The sub-cell tables of all dense cells, one wavefront per cell over a grid
 // that strides the cells; the cell count *ndc_p is read on the device.
 __global__ __launch_bounds__(kBlock) void k_sub_table(const uint32_t *__restrict__ ndc_p, Boxes bx,
-                                                      const uint32_t *__restrict__ dcells,
-                                                      const uint32_t *__restrict__ off,
+                                                      const uint32_t *__restrict__ dord,
+                                                      const uint32_t *__restrict__ start,
                                                       const uint16_t *__restrict__ ssub,
                                                       uint32_t *__restrict__ subtab) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t ndc = *ndc_p;
     const int64_t stride = (int64_t)gridDim.x * (kBlock / 64);
     for (int64_t d = (int64_t)blockIdx.x * (kBlock / 64) + wave; d < ndc; d += stride)
-        sub_table_cell(d, bx, dcells, off, ssub, subtab);
+        sub_table_cell(d, bx, dord, start, ssub, subtab);
 }
 
 }  // namespace
@@ -1290,16 +1306,23 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
             hipLaunchKernelGGL(k_bin_place<false>, dim3(blocks(n)), dim3(kBlock), 0, s, pos, n, bx, 0, w.rkey[cur],
                                w.rval[cur], to);
     }
-    // slots 0..n (slot n closes the grid): one wavefront per 64
-    hipLaunchKernelGGL(k_cell_offsets, dim3((unsigned)((n + 1 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n,
-                       ncell, w.scell, w.off);
-    const int64_t lt = scan_tiles(n);
-    hipLaunchKernelGGL(k_bin_marks, dim3((unsigned)lt), dim3(kBlock), 0, s, n, w.scell, w.off, w.marks, w.scan_tmp,
-                       lt);
-    const bool scanned = scan_sums(w.scan_tmp, lt, lt, 3, s);
-    hipLaunchKernelGGL(k_bin_lists, dim3((unsigned)lt), dim3(kBlock), 0, s, n, w.marks, w.scan_tmp, lt, scanned,
-                       w.scell, w.chunks, w.dcells, w.sparse, w.cnt, w.pq ? w.rkey[0] : nullptr, w.counters, w.rhist,
-                       (int)(seg_list(n, w).nseg * kSegStride));
+    // tiles of 4096 particles, of 1024 where those would leave most of the chip
+    // idle and a workgroup's rounds be the time (20 000 particles: the two
+    // kernels took 14 and 17 us, 5 and 8 with the smaller tiles)
+    const bool fine = n <= kFineTilesMost;
+    const int64_t lt = fine ? (n + kFineTile - 1) / kFineTile : scan_tiles(n);
+    // the index words are zeroed by the marks' workgroups, by a launch of their
+    // own when there are too many for them (a nearly empty grid)
+    const int64_t words = occ_words(ncell);
+    const bool apart = words > 128 * kBlock * lt;
+    if (apart) fill_u32(reinterpret_cast<uint32_t *>(w.cells.occ), 0u, 2 * words, s);
+    hipLaunchKernelGGL(fine ? k_bin_marks<kFineTile> : k_bin_marks<kScanTile>, dim3((unsigned)lt), dim3(kBlock), 0, s, n,
+                       w.scell, w.marks, w.scan_tmp, lt, w.cells.occ, apart ? 0 : words);
+    const bool scanned = scan_sums(w.scan_tmp, lt, lt, 4, s);
+    // the dense cells' numbers in the radix sort's payload (free by now)
+    hipLaunchKernelGGL(fine ? k_bin_lists<kFineTile> : k_bin_lists<kScanTile>, dim3((unsigned)lt), dim3(kBlock), 0, s, n,
+                       w.marks, w.scan_tmp, lt, scanned, w.scell, w.chunks, w.dcells, w.rval[0], w.sparse, w.cells,
+                       w.pq ? w.rkey[0] : nullptr, w.counters, w.rhist, (int)(seg_list(n, w).nseg * kSegStride));
 }
 
 void launch_subtab(int64_t n, const uint32_t *ndc_p, const Boxes &bx, Work &w, hipStream_t s) {
@@ -1309,8 +1332,8 @@ void launch_subtab(int64_t n, const uint32_t *ndc_p, const Boxes &bx, Work &w, h
     const int64_t ub = n / kDenseMin + 1;
     int64_t blocks = (ub + kBlock / 64 - 1) / (kBlock / 64);
     if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(k_sub_table, dim3((unsigned)blocks), dim3(kBlock), 0, s, ndc_p, bx, w.dcells, w.off,
-                       w.ssub, w.subtab);
+    hipLaunchKernelGGL(k_sub_table, dim3((unsigned)blocks), dim3(kBlock), 0, s, ndc_p, bx, w.rval[0],
+                       w.cells.start, w.ssub, w.subtab);
 }
 
 }  // namespace hf

@@ -57,8 +57,7 @@ __device__ __forceinline__ uint64_t dkey(float d, uint32_t orig) {
 // the densest particle of the whole cell.
 constexpr int kSubMost = 216;  // 6^3 sub-cells at most
 __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
-                                                        const uint32_t *__restrict__ dcells,
-                                                        const uint32_t *__restrict__ off,
+                                                        const uint32_t *__restrict__ subtab,
                                                         const uint16_t *__restrict__ ssub,
                                                         const float *__restrict__ dens_s,
                                                         const float4 *__restrict__ spos,
@@ -72,11 +71,10 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
     const int64_t d = (int64_t)blockIdx.x * (kBlock / 64) + wave;
     if (d >= ndc) return;
     const int lane = threadIdx.x & 63;
-    const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane(dcells[d]);
-    const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane(off[c]);
-    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(off[c + 1]);
-    const int nsub = __builtin_amdgcn_readfirstlane(bx.geo[box_of(bx, a)].nsub);
     const int64_t row = d * (bx.nsub_max + 1);
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane(subtab[row]);
+    const int nsub = __builtin_amdgcn_readfirstlane(bx.geo[box_of(bx, a)].nsub);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(subtab[row + nsub]);
     for (int v = lane; v < nsub; v += 64) {
         s_best[wave][v] = 0ull;
         s_arg[wave][v] = -1;
@@ -144,9 +142,7 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
 // or above the floor is listed as a hard case.
 __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
                                                        const float4 *__restrict__ spos,
-                                                       const uint32_t *__restrict__ scell, Marks marks,
-                                                       const uint16_t *__restrict__ ssub,
-                                                       const uint32_t *__restrict__ cellmap,
+                                                       Marks marks, const uint16_t *__restrict__ ssub,
                                                        const uint64_t *__restrict__ submax,
                                                        const int32_t *__restrict__ subarg,
                                                        const float *__restrict__ dens_s,
@@ -163,12 +159,11 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
     if (key >= 0 && (double)di >= g.floor_nuc) {
         is_hard = true;
         // everything indexed by i in one round of loads
-        const uint32_t c = scell[i];
         const bool sparse_i = is_sparse(marks, i);
         const int si = ssub[i];
         const float4 pi = spos[i];
         if (!sparse_i) {
-            const int64_t base = (int64_t)cellmap[c] * (bx.nsub_max + 1);
+            const int64_t base = (int64_t)dense_ordinal(marks, (uint32_t)i) * (bx.nsub_max + 1);
             const int32_t top = subarg[base + si];
             const uint32_t oi = orig_of(pi);
             if (top != (int32_t)i) {
@@ -243,9 +238,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
 // 20 000 particles, 178 us on the 64^3 box and 455 us on the 256^3 one.
 __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, const float4 *__restrict__ sloc,
                                                         const float4 *__restrict__ spos,
-                                                        const uint32_t *__restrict__ off,
-                                                        const uint32_t *__restrict__ cellmap,
-                                                        const uint32_t *__restrict__ subtab,
+                                                        Cells cells, const uint32_t *__restrict__ subtab,
                                                         const uint64_t *__restrict__ submax,
                                                         const int32_t *__restrict__ subarg,
                                                         const float *__restrict__ dens_s,
@@ -278,7 +271,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, co
         int cx, cy, cz;
         cell_xyz(g, __float_as_uint(li.w), cx, cy, cz);
         bool found = false, dense = false;
-        uint32_t nb = 0;
+        uint32_t number = 0;
         if (ln < 27) {
             int ox, oy, oz;
             stencil_offset(ln, ox, oy, oz);
@@ -286,8 +279,8 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, co
             const float gy = oy < 0 ? li.y : (oy > 0 ? g.cellb - li.y : 0.0f);
             const float gz = oz < 0 ? li.z : (oz > 0 ? g.cellb - li.z : 0.0f);
             if (gx * gx + gy * gy + gz * gz < g.b2b_hi) {
-                nb = cell_id(g, cx + ox, cy + oy, cz + oz);
-                const uint32_t a = off[nb], b = off[nb + 1];
+                uint32_t a, b;
+                number = cell_range(cells, cell_id(g, cx + ox, cy + oy, cz + oz), a, b);
                 dense = b - a >= (uint32_t)kDenseMin;
                 if (!dense) {
                     float dj[kDenseMin - 1];
@@ -304,7 +297,7 @@ __global__ __launch_bounds__(kBlock) void k_cand_search(SegList hl, Boxes bx, co
         bool open = false;
         int64_t base = 0;
         if (dense) {
-            base = (int64_t)cellmap[nb] * tstride;
+            base = (int64_t)cells.dmap[number] * tstride;
             const uint64_t mx = submax[base + bx.nsub_max];
             const int32_t top = subarg[base + bx.nsub_max];
             open = mx > mykey;
@@ -540,18 +533,18 @@ SegClear candidates_clear(int64_t n, const Work &w) {
 void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     if (w.ndcells > 0)
         hipLaunchKernelGGL(k_submax_wave, dim3((unsigned)((w.ndcells + kBlock / 64 - 1) / (kBlock / 64))),
-                           dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.ssub, w.dens_s, w.spos, w.submax,
+                           dim3(kBlock), 0, s, w.ndcells, bx, w.subtab, w.ssub, w.dens_s, w.spos, w.submax,
                            w.subarg, w.clock + kClockCand);
     const SegList hl = seg_list(n, w);
     hipLaunchKernelGGL(k_cand_quick, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, bx,
-                       w.spos, w.scell, w.marks, w.ssub, w.cnt, w.submax, w.subarg, w.dens_s, w.gkey, hl,
+                       w.spos, w.marks, w.ssub, w.submax, w.subarg, w.dens_s, w.gkey, hl,
                        w.ndcells > 0 ? nullptr : w.clock + kClockCand);
     // half-wavefronts striding over the segments: as many as fit the chip (six
     // wavefronts per SIMD at 79 VGPRs), and no more than one per four particles
     // (one particle in thirty is a hard case); their total goes to a counter
     const unsigned blocks = seg_blocks(hl, n, 32, 4, 6 * (int64_t)(w.ncu > 0 ? w.ncu : 1));
-    hipLaunchKernelGGL(k_cand_search, dim3(blocks), dim3(kBlock), 0, s, hl, bx, w.sloc, w.spos, w.off,
-                       w.cnt, w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of, w.gccnt,
+    hipLaunchKernelGGL(k_cand_search, dim3(blocks), dim3(kBlock), 0, s, hl, bx, w.sloc, w.spos, w.cells,
+                       w.subtab, w.submax, w.subarg, w.dens_s, w.gkey, w.gid_of, w.gccnt,
                        w.counters + kCntHard);
     const int64_t tiles = scan_tiles(n);  // of the groups: at most one per particle
     hipLaunchKernelGGL(k_gc_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, w.counters + kCntGroups, w.gccnt,

@@ -100,8 +100,7 @@ template <int R, bool kNarrow>
 __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t c, uint32_t end,
                                               const float *__restrict__ pq,
                                               const float4 *__restrict__ spos,
-                                              const uint32_t *__restrict__ off,
-                                              const Marks &marks,
+                                              const Cells &cells, const Marks &marks,
                                               uint64_t *__restrict__ dfx, float *__restrict__ dens_s,
                                               float *__restrict__ dens_out, float *__restrict__ cl,
                                               float4 *__restrict__ s_pk) {
@@ -123,6 +122,11 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
     };
     int cx, cy, cz;
     cell_xyz(g, c, cx, cy, cz);
+    // one stencil cell per lane (lanes 0..26, lane 9 (oz+1) + 3 (oy+1) + ox+1);
+    // its index word, and further down its range, are loaded ahead of their use
+    const int sl = lane < 27 ? lane : 13;
+    const uint32_t nbl = cell_id(g, cx + sl % 3 - 1, cy + (sl / 3) % 3 - 1, cz + sl / 9 - 1);
+    const uint2 nbw = cells.occ[nbl / kOccCells];
     // the chunk's rows: A = (2 x_i, 1), accumulator input 1 - |x_i|^2; rows
     // past the chunk get A = (0, 0, 0, 1) and -1, so all their weights clamp
     // to exactly 0
@@ -147,20 +151,14 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
             cl[(4 * r + u) * 64 + lane] = iu < end ? 1.0f + q : -1.0f;
         }
     }
-    // neighbour ranges, one per lane: lanes 0..26 the stencil cells (lane
-    // 9 (oz+1) + 3 (oy+1) + ox+1); the chunk's own cell (lane 13) is cut
-    // around the chunk's diagonal blocks, its tail is range 27
     uint32_t ra = 0, rb = 0, sb = 0;
-    bool sp = false;
-    if (lane < 27) {
-        const int ox = lane % 3 - 1, oy = (lane / 3) % 3 - 1, oz = lane / 9 - 1;
-        const uint32_t nb = cell_id(g, cx + ox, cy + oy, cz + oz);
-        ra = off[nb];
-        rb = off[nb + 1];
-        // a sparse cell's particles have consecutive sparse ordinals
-        sp = rb > ra && rb - ra < (uint32_t)kDenseMin;
-        if (sp) sb = sparse_ordinal(marks, ra);
-    }
+    if (lane < 27) cell_range(cells, nbw, nbl, ra, rb);
+
+    // neighbour ranges, one per lane: the stencil cells; the chunk's own cell
+    // (lane 13) is cut around the chunk's diagonal blocks, its tail is range 27.
+    // A sparse cell's particles have consecutive sparse ordinals.
+    const bool sp = rb > ra && rb - ra < (uint32_t)kDenseMin;
+    if (sp) sb = sparse_ordinal(marks, ra);
     const uint32_t cend = (uint32_t)__builtin_amdgcn_readlane((int)rb, 13);
     const uint32_t tail = h + 16u * (uint32_t)R;
     if (lane == 13) rb = h;
@@ -215,7 +213,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
     for (int rd = 0; rd < R; rd++) {
         const uint32_t j0 = h + 16u * (uint32_t)rd;
         const float val = ld(j0);
-        const float bv = (grp == 3 && (uint32_t)col >= cend - j0) ? -1e30f : val;
+        const float bv = (grp == 3 && (uint32_t)col >= end - j0) ? -1e30f : val;
 #pragma unroll
         for (int r = 0; r < R; r++) {
             f32x4 cin = Cget(r);
@@ -403,13 +401,12 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
 
 // One wavefront per workgroup: chunk costs differ widely, and a finished
 // wavefront frees its slot at once.
-__global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, Boxes bx, bool narrow,
+__global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, int64_t n, Boxes bx, bool narrow,
                                                       const int32_t *__restrict__ chunks,
                                                       const float4 *__restrict__ sloc,
                                                       const float4 *__restrict__ pq,
                                                       const float4 *__restrict__ spos,
-                                                      const uint32_t *__restrict__ off,
-                                                      Marks marks,
+                                                      Cells cells, Marks marks,
                                                       uint64_t *__restrict__ dfx,
                                                       float *__restrict__ dens_s,
                                                       float *__restrict__ dens_out,
@@ -420,15 +417,14 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, Boxes 
     const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane(chunks[q]);
     const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, h))];
     const uint32_t c = __builtin_amdgcn_readfirstlane(__float_as_uint(sloc[h].w));
-    const uint32_t cend = __builtin_amdgcn_readfirstlane(off[c + 1]);
-    const uint32_t end = min(h + 64u, cend);
+    const uint32_t end = __builtin_amdgcn_readfirstlane(chunk_end(marks, h, n));
     const float *p = reinterpret_cast<const float *>(pq);
     // the rows' accumulator inputs, and the packed sparse neighbours
     __shared__ float cl[16 * 64];
     __shared__ float4 s_pk[64];
 #define HF_DENSITY_CHUNK(RR)                                                                        \
-    (narrow ? density_chunk<RR, true>(g, h, c, end, p, spos, off, marks, dfx, dens_s, dens_out, cl, s_pk) \
-            : density_chunk<RR, false>(g, h, c, end, p, spos, off, marks, dfx, dens_s, dens_out, cl, s_pk))
+    (narrow ? density_chunk<RR, true>(g, h, c, end, p, spos, cells, marks, dfx, dens_s, dens_out, cl, s_pk) \
+            : density_chunk<RR, false>(g, h, c, end, p, spos, cells, marks, dfx, dens_s, dens_out, cl, s_pk))
     switch ((end - h + 15u) >> 4) {
     case 1: HF_DENSITY_CHUNK(1); break;
     case 2: HF_DENSITY_CHUNK(2); break;
@@ -452,12 +448,12 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, Boxes 
 // any lane changed: 2300 vector instructions per wavefront, 782 us on the 256^3
 // box.  Listing the pairs of all lanes in LDS and computing one pair per lane
 // took 911 us: there are about a dozen pairs per particle, and each cost a
-// list entry and the image of its own.)
+// list entry and the image of its own.)  Seven wavefronts per SIMD: at eight the
+// registers spill, 727 us against 683.
 constexpr int kSparseWaves = kBlock / 64;
 __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int64_t i, uint2 (*runs)[64],
                                                    const float4 *__restrict__ sloc,
-                                                   const float4 *__restrict__ spos,
-                                                   const uint32_t *__restrict__ off,
+                                                   const float4 *__restrict__ spos, const Cells &cells,
                                                    const uint64_t *__restrict__ dfx,
                                                    float *__restrict__ dens_s, float *__restrict__ dens_out) {
     const int lane = threadIdx.x & 63;
@@ -470,6 +466,10 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
     // neighbour cells by additions from the own cell
     const bool x_lo = cx == 0, x_hi = cx == nc - 1, y_lo = cy == 0, y_hi = cy == nc - 1;
     const uint32_t xm = x_lo ? c + row1 - 1u : c - 1u, xp = x_hi ? c + 1u - row1 : c + 1u;
+    // the window of three cells of a row (two of them at an x edge of the box,
+    // the cell across the edge apart)
+    const bool edge = x_lo || x_hi;
+    const uint32_t wc = x_lo ? c : c - 1u, ec = x_lo ? xm : xp, wmask = edge ? 3u : 7u;
     const uint32_t ym = y_lo ? plane1 - row1 : 0u - row1, yp = y_hi ? row1 - plane1 : row1;
     // a cell whose nearest face is b or more away (by a margin far above the
     // rounding of the local coordinates) weighs nothing
@@ -488,18 +488,50 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
         const float gz = oz < 0 ? li.z : (oz > 0 ? hz : 0.0f);
         const float gz2 = most - gz * gz;
         Pos64 pim{px, py, wraps ? (oz < 0 ? pz + g.L : pz - g.L) : pz};
-        // the plane's offsets are loaded together so their latencies overlap
-        uint32_t a[9], b[9];
+        // the plane's index words, then the ranges of the rows that hold
+        // particles, are loaded together so their latencies overlap.  Three
+        // cells of a row lie in one word or two (one load), and the numbers of
+        // those that hold particles follow each other, so their ranges are one
+        // load too.  The cell across an x edge is looked up by itself, with the
+        // window moved to the two others.
+        Words4 wd[3], st[3];
+        uint2 we[3];
+        uint32_t has[3], ae[3], be[3];
 #pragma unroll
         for (int r = 0; r < 3; r++) {
             const uint32_t d = dz + (r == 0 ? ym : (r == 2 ? yp : 0u));
-            const uint32_t *const pm = off + (xm + d), *const p0 = off + (c + d), *const pp = off + (xp + d);
-            a[3 * r] = pm[0];
-            b[3 * r] = pm[1];
-            a[3 * r + 1] = p0[0];
-            b[3 * r + 1] = p0[1];
-            a[3 * r + 2] = pp[0];
-            b[3 * r + 2] = pp[1];
+            wd[r] = *reinterpret_cast<const Words4 *>(cells.occ + (wc + d) / kOccCells);
+            we[r] = make_uint2(0u, 0u);
+            if (edge) we[r] = cells.occ[(ec + d) / kOccCells];
+        }
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            const uint32_t d = dz + (r == 0 ? ym : (r == 2 ? yp : 0u));
+            const uint32_t sh = (wc + d) % kOccCells;
+            const uint64_t bits = ((uint64_t)wd[r].v[2] << 32 | wd[r].v[0]) >> sh;
+            has[r] = (uint32_t)bits & wmask;
+            const uint32_t o = wd[r].v[0] != 0u
+                                   ? wd[r].v[1] + (uint32_t)__popc(wd[r].v[0] & ((1u << sh) - 1u))
+                                   : wd[r].v[3];
+            if (has[r]) st[r] = *reinterpret_cast<const Words4 *>(cells.start + o);
+            else st[r] = Words4{};
+            cell_range(cells, we[r], ec + d, ae[r], be[r]);
+        }
+        uint32_t a[9], b[9];
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            // an empty cell starts and ends where the next one starts, so that
+            // runs meet across it
+            const uint32_t p1 = has[r] & 1u, p2 = (uint32_t)__popc(has[r] & 3u), p3 = (uint32_t)__popc(has[r]);
+            const uint32_t s0 = st[r].v[0], s1 = p1 ? st[r].v[1] : s0,
+                           s2 = p2 == 2u ? st[r].v[2] : (p2 == 1u ? st[r].v[1] : s0),
+                           s3 = p3 == 3u ? st[r].v[3] : (p3 == 2u ? st[r].v[2] : (p3 == 1u ? st[r].v[1] : s0));
+            a[3 * r] = x_lo ? ae[r] : s0;
+            b[3 * r] = x_lo ? be[r] : s1;
+            a[3 * r + 1] = x_lo ? s0 : s1;
+            b[3 * r + 1] = x_lo ? s1 : s2;
+            a[3 * r + 2] = x_lo ? s1 : (x_hi ? ae[r] : s2);
+            b[3 * r + 2] = x_lo ? s2 : (x_hi ? be[r] : s3);
         }
         uint32_t open = 0;  // runs that hold particles
 #pragma unroll
@@ -554,12 +586,11 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
     write_density(i, acc, g, spos, dens_s, dens_out);
 }
 
-__global__ __launch_bounds__(kBlock, 8) void k_density_sparse(int64_t nsparse, Boxes bx,
+__global__ __launch_bounds__(kBlock, 7) void k_density_sparse(int64_t nsparse, Boxes bx,
                                                            const int32_t *__restrict__ sparse,
                                                            const float4 *__restrict__ sloc,
                                                            const float4 *__restrict__ spos,
-                                                           const uint32_t *__restrict__ off,
-                                                           const uint64_t *__restrict__ dfx,
+                                                           Cells cells, const uint64_t *__restrict__ dfx,
                                                            float *__restrict__ dens_s,
                                                            float *__restrict__ dens_out,
                                                            uint64_t *clock) {
@@ -569,7 +600,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_density_sparse(int64_t nsparse, B
     if (t >= nsparse) return;
     const int64_t i = sparse[t];
     per_box(bx, box_of(bx, (uint32_t)i), [&](const Geo &g) {
-        density_sparse_one(g, t, i, s_runs[threadIdx.x >> 6], sloc, spos, off, dfx, dens_s, dens_out);
+        density_sparse_one(g, t, i, s_runs[threadIdx.x >> 6], sloc, spos, cells, dfx, dens_s, dens_out);
     });
 }
 
@@ -577,7 +608,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_density_sparse(int64_t nsparse, B
 // algorithmic pair count (evaluated in the same FP32 local coordinates).
 __global__ __launch_bounds__(kBlock) void k_count_pairs(int64_t n, Boxes bx,
                                                         const float4 *__restrict__ sloc,
-                                                        const uint32_t *__restrict__ off,
+                                                        Cells cells,
                                                         unsigned long long *__restrict__ total) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t cnt = 0;
@@ -593,7 +624,9 @@ __global__ __launch_bounds__(kBlock) void k_count_pairs(int64_t n, Boxes bx,
                     const uint32_t nb = cell_id(g, cx + ox, cy + oy, cz + oz);
                     const float xs = li.x - (float)ox * g.cellb, ys = li.y - (float)oy * g.cellb,
                                 zs = li.z - (float)oz * g.cellb;
-                    for (uint32_t j = off[nb]; j < off[nb + 1]; j++) {
+                    uint32_t a, e;
+                    cell_range(cells, nb, a, e);
+                    for (uint32_t j = a; j < e; j++) {
                         const float4 lj = sloc[j];
                         const float dx = lj.x - xs, dy = lj.y - ys, dz = lj.z - zs;
                         cnt += (dx * dx + dy * dy + dz * dz < 1.0f) ? 1u : 0u;
@@ -628,20 +661,20 @@ void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStr
         bool narrow = (n + 32) * 16 <= (int64_t)0xffffff00;
         const char *force = getenv("HF_DENSITY_WIDE");
         if (force && force[0] == '1') narrow = false;
-        hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, bx, narrow,
-                           w.chunks, w.sloc, w.pq, w.spos, w.off, w.marks, dfx, w.dens_s, dens_out,
+        hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, n, bx, narrow,
+                           w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s, dens_out,
                            w.clock + kClockDensity);
     }
     if (w.nsparse > 0) {
         hipLaunchKernelGGL(k_density_sparse, dim3((unsigned)((w.nsparse + kBlock - 1) / kBlock)),
-                           dim3(kBlock), 0, s, w.nsparse, bx, w.sparse, w.sloc, w.spos, w.off, dfx, w.dens_s,
+                           dim3(kBlock), 0, s, w.nsparse, bx, w.sparse, w.sloc, w.spos, w.cells, dfx, w.dens_s,
                            dens_out, w.nchunks > 0 ? nullptr : w.clock + kClockDensity);
     }
 }
 
 void launch_count_pairs(int64_t n, const Boxes &bx, Work &w, unsigned long long *total, hipStream_t s) {
     hipLaunchKernelGGL(k_count_pairs, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, n, bx, w.sloc,
-                       w.off, total);
+                       w.cells, total);
 }
 
 void launch_gather_density(const float *dens_in, int64_t n, Work &w, hipStream_t s) {

@@ -210,10 +210,8 @@ __device__ __forceinline__ void test_candidates(int32_t *parent, Hooks &h, const
 // the sub-cell table.  The smallest index and the member count of every
 // particle's set start here too, and the members of sparse cells (about one in
 // ten of their particles) are listed.
-__global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, const uint32_t *__restrict__ scell,
-                                                        Marks marks,
+__global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, Marks marks,
                                                         const uint16_t *__restrict__ ssub,
-                                                        const uint32_t *__restrict__ cellmap,
                                                         const uint32_t *__restrict__ subtab,
                                                         const float *__restrict__ dens_s,
                                                         int32_t *__restrict__ parent,
@@ -235,8 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, con
         parent[i] = mem ? (int32_t)i : -1;
         return;
     }
-    const uint32_t c = scell[i];
-    const int64_t row = (int64_t)cellmap[c] * (bx.nsub_max + 1) + ssub[i];
+    const int64_t row = (int64_t)dense_ordinal(marks, (uint32_t)i) * (bx.nsub_max + 1) + ssub[i];
     const uint32_t u0 = subtab[row];
     if (mem) {
         uint32_t f = u0;
@@ -281,8 +278,6 @@ __device__ __forceinline__ int32_t sub_first(const uint32_t *__restrict__ subtab
 // by the scalar unit.)
 constexpr int kHalves = kBlock / 32;
 __global__ __launch_bounds__(kBlock) void k_fof_cells(int64_t ndc, Boxes bx,
-                                                      const uint32_t *__restrict__ dcells,
-                                                      const uint32_t *__restrict__ off,
                                                       const float4 *__restrict__ sloc,
                                                       const uint32_t *__restrict__ subtab,
                                                       const int32_t *__restrict__ submem,
@@ -293,7 +288,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_cells(int64_t ndc, Boxes bx,
     if (d >= ndc) return;
     float4 *sp = s_first + hw * bx.nsub_max;
     const int64_t row = d * (bx.nsub_max + 1);
-    per_box(bx, box_of(bx, off[dcells[d]]), [&](const Geo &g) {
+    per_box(bx, box_of(bx, subtab[row]), [&](const Geo &g) {
     const int k = g.ksub, nsub = g.nsub;
     for (int s = ln; s < nsub; s += 32) {
         const int32_t fm = sub_first(subtab, submem, row + s);
@@ -329,9 +324,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_cells(int64_t ndc, Boxes bx,
 // pairs that would join the same two sets one lane joins them.
 __global__ __launch_bounds__(kBlock) void k_fof_faces(int64_t ndc, Boxes bx,
                                                       const uint32_t *__restrict__ dcells,
-                                                      const uint32_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ cellmap,
-                                                      const float4 *__restrict__ sloc,
+                                                      Cells cells, const float4 *__restrict__ sloc,
                                                       const uint32_t *__restrict__ subtab,
                                                       const int32_t *__restrict__ submem,
                                                       int32_t *parent) {
@@ -341,7 +334,7 @@ __global__ __launch_bounds__(kBlock) void k_fof_faces(int64_t ndc, Boxes bx,
     auto hballot = [&](bool p) { return (uint32_t)(__ballot(p) >> hsh); };
     const uint32_t c = dcells[d];
     const int tstride = bx.nsub_max + 1;
-    per_box(bx, box_of(bx, off[c]), [&](const Geo &g) {
+    per_box(bx, box_of(bx, subtab[d * tstride]), [&](const Geo &g) {
     const int k = g.ksub, k2 = k * k;
     const float inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)k2;
     int cx, cy, cz;
@@ -352,13 +345,14 @@ __global__ __launch_bounds__(kBlock) void k_fof_faces(int64_t ndc, Boxes bx,
         if (t < 3 * k2) {
             const int ax = div_small(t, inv_k2), r = t - ax * k2, v = div_small(r, inv_k), u = r - v * k;
             const uint32_t nb = cell_id(g, cx + (ax == 0), cy + (ax == 1), cz + (ax == 2));
-            const uint32_t na = off[nb], ne = off[nb + 1];
+            uint32_t na, ne;
+            const uint32_t o = cell_range(cells, nb, na, ne);
             if (ne - na >= (uint32_t)kDenseMin) {
                 // the last layer of sub-cells here, the first one there
                 const int st = ax == 0 ? 1 : (ax == 1 ? k : k2);
                 const int s2 = ax == 0 ? v * k2 + u * k : (ax == 1 ? v * k2 + u : v * k + u);
                 const int32_t f1 = sub_first(subtab, submem, d * tstride + s2 + (k - 1) * st);
-                const int32_t f2 = sub_first(subtab, submem, (int64_t)cellmap[nb] * tstride + s2);
+                const int32_t f2 = sub_first(subtab, submem, (int64_t)cells.dmap[o] * tstride + s2);
                 if (f1 >= 0 && f2 >= 0) {
                     const float4 p = sloc[f1], q = sloc[f2];
                     const float dx = q.x + (ax == 0 ? g.cellb : 0.0f) - p.x,
@@ -387,16 +381,14 @@ __global__ __launch_bounds__(kBlock) void k_fof_faces(int64_t ndc, Boxes bx,
 // change here), and per cell, in entry nsub_max of its row: the root when all
 // its members are in one set, -1 when they are not, -2 when it has none.
 __global__ __launch_bounds__(kBlock) void k_fof_cell_roots(int64_t ndc, Boxes bx,
-                                                           const uint32_t *__restrict__ dcells,
-                                                           const uint32_t *__restrict__ off,
                                                            const uint32_t *__restrict__ subtab,
                                                            int32_t *__restrict__ submem, int32_t *parent) {
     const int hw = threadIdx.x >> 5, ln = threadIdx.x & 31, hsh = threadIdx.x & 32;
     const int64_t d = (int64_t)xcd_block() * kHalves + hw;
     if (d >= ndc) return;
     int nsub = 0;
-    per_box(bx, box_of(bx, off[dcells[d]]), [&](const Geo &g) { nsub = g.nsub; });
     const int64_t row = d * (bx.nsub_max + 1);
+    per_box(bx, box_of(bx, subtab[row]), [&](const Geo &g) { nsub = g.nsub; });
     int32_t one = -2;
     for (int s0 = 0; s0 < nsub; s0 += 32) {
         const int32_t fm = s0 + ln < nsub ? sub_first(subtab, submem, row + s0 + ln) : -1;
@@ -444,12 +436,11 @@ constexpr int kTaskTile = 384;
 // With nparts = 2 a chunk is two wavefronts, one for the sparse cells and one
 // for the dense ones: for inputs whose chunks do not fill the chip, where the
 // longest chain is the time.
-__global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts, Boxes bx,
+__global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts, int64_t n, Boxes bx,
                                                       const int32_t *__restrict__ chunks,
                                                       const float4 *__restrict__ sloc,
                                                       const float4 *__restrict__ spos,
-                                                      const uint32_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ cellmap,
+                                                      Cells cells, Marks marks,
                                                       const uint32_t *__restrict__ subtab,
                                                       const int32_t *__restrict__ submem,
                                                       const float *__restrict__ dens_s,
@@ -467,8 +458,7 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane(chunks[q]);
     const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, h))];
     const uint32_t c = __builtin_amdgcn_readfirstlane(__float_as_uint(sloc[h].w));
-    const uint32_t cend = (uint32_t)__builtin_amdgcn_readfirstlane(off[c + 1]);
-    const uint32_t end = min(h + 64u, cend);
+    const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane(chunk_end(marks, h, n));
     const uint32_t i = h + (uint32_t)lane;
     const uint32_t ic = i < end ? i : h;
     const bool active = i < end && is_member(dens_s, ic, g.dl0);
@@ -479,6 +469,12 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     const float subb = g.cellb / (float)k;
     int cx, cy, cz;
     cell_xyz(g, c, cx, cy, cz);
+    // one stencil cell per lane (offset (t % 3 - 1, t / 3 % 3 - 1, t / 9 - 1)):
+    // its index word here, its range below if it comes within l of the chunk's box
+    const int tl = lane < 27 ? lane : 13;
+    const int lx = tl % 3 - 1, ly = (tl / 3) % 3 - 1, lz = tl / 9 - 1;
+    const uint32_t nbl = cell_id(g, cx + lx, cy + ly, cz + lz);
+    const uint2 nbw = cells.occ[nbl / kOccCells];
     // chunk bounding box (active lanes), for the reach tests of stencil cells
     // and sub-cells
     float bx0 = active ? li.x : 1e30f, by0 = active ? li.y : 1e30f, bz0 = active ? li.z : 1e30f;
@@ -497,20 +493,12 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     bx1 = uniform(bx1);
     by1 = uniform(by1);
     bz1 = uniform(bz1);
-    // one stencil cell per lane (offset (t % 3 - 1, t / 3 % 3 - 1, t / 9 - 1)):
-    // its range, if it comes within l of the chunk's box
-    const int tl = lane < 27 ? lane : 13;
-    const int lx = tl % 3 - 1, ly = (tl / 3) % 3 - 1, lz = tl / 9 - 1;
-    const uint32_t nbl = cell_id(g, cx + lx, cy + ly, cz + lz);
     const float gx = lx < 0 ? bx0 : (lx > 0 ? g.cellb - bx1 : 0.0f);
     const float gy = ly < 0 ? by0 : (ly > 0 ? g.cellb - by1 : 0.0f);
     const float gz = lz < 0 ? bz0 : (lz > 0 ? g.cellb - bz1 : 0.0f);
     const bool lreach = lane < 27 && gx * gx + gy * gy + gz * gz < g.l2b_hi;
-    uint32_t la = 0, lb = 0;
-    if (lreach) {
-        la = off[nbl];
-        lb = off[nbl + 1];
-    }
+    uint32_t la = 0, lb = 0, lo = 0;
+    if (lreach) lo = cell_range(cells, nbw, nbl, la, lb);
     const bool ldense = lb - la >= (uint32_t)kDenseMin;
     const bool lforward = lz > 0 || (lz == 0 && (ly > 0 || (ly == 0 && lx >= 0)));  // own cell included
     const int wfirst = lane_get(wr, (int)__builtin_ctzll(__ballot(active)));
@@ -518,7 +506,7 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     bool lvisit = do_dense && lreach && ldense && lforward;
     int64_t lbase = 0;
     if (lvisit) {
-        lbase = (int64_t)cellmap[nbl] * tstride;
+        lbase = (int64_t)cells.dmap[lo] * tstride;
         const int32_t cr = submem[lbase + bx.nsub_max];
         lvisit = cr != -2 && !(wsame && cr == wfirst);
     }
@@ -722,8 +710,7 @@ constexpr int kLinkMost = (64 / 16) * 14 * (kDenseMin - 1);  // links of a round
 __global__ __launch_bounds__(kBlock, 8) void k_fof_sparse(SegList sl, Boxes bx,
                                                        const float4 *__restrict__ sloc,
                                                        const float4 *__restrict__ spos,
-                                                       const uint32_t *__restrict__ off,
-                                                       const float *__restrict__ dens_s,
+                                                       Cells cells, const float *__restrict__ dens_s,
                                                        int32_t *parent) {
     __shared__ int2 s_link[kBlock / 64][64 + kLinkMost];
     __shared__ uint32_t s_n[kBlock / 64];
@@ -755,8 +742,8 @@ __global__ __launch_bounds__(kBlock, 8) void k_fof_sparse(SegList sl, Boxes bx,
                 int cx, cy, cz;
                 cell_xyz(g, __float_as_uint(li.w), cx, cy, cz);
                 const uint32_t nb = cell_id(g, cx + ox, cy + oy, cz + oz);
-                a = off[nb];
-                uint32_t b = off[nb + 1];
+                uint32_t b;
+                cell_range(cells, nb, a, b);
                 if (b - a >= (uint32_t)kDenseMin) b = a;
                 if (ln == 0) a = (uint32_t)i + 1u;
                 const float xs = li.x - (float)ox * g.cellb, ys = li.y - (float)oy * g.cellb,
@@ -923,29 +910,29 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     const SegList sl = seg_list(n, w);
     // the first members of the dense sub-cells go to the sub-cell maxima's
     // argument table (free until the candidate stage)
-    hipLaunchKernelGGL(k_fof_phase_a, grid(n), dim3(kBlock), 0, s, n, bx, w.scell, w.marks, w.ssub, w.cnt,
-                       w.subtab, w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt, sl, w.clock + kClockFof);
+    hipLaunchKernelGGL(k_fof_phase_a, grid(n), dim3(kBlock), 0, s, n, bx, w.marks, w.ssub, w.subtab,
+                       w.dens_s, w.parent, w.subarg, w.minorig, w.gcnt, sl, w.clock + kClockFof);
     if (w.ndcells > 0) {
         const dim3 cells((unsigned)((w.ndcells + kHalves - 1) / kHalves));
         hipLaunchKernelGGL(k_fof_cells, cells, dim3(kBlock), kHalves * bx.nsub_max * sizeof(float4), s, w.ndcells, bx,
-                           w.dcells, w.off, w.sloc, w.subtab, w.subarg, w.parent);
-        hipLaunchKernelGGL(k_fof_faces, cells, dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.cnt, w.sloc,
+                           w.sloc, w.subtab, w.subarg, w.parent);
+        hipLaunchKernelGGL(k_fof_faces, cells, dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.cells, w.sloc,
                            w.subtab, w.subarg, w.parent);
-        hipLaunchKernelGGL(k_fof_cell_roots, cells, dim3(kBlock), 0, s, w.ndcells, bx, w.dcells, w.off, w.subtab,
+        hipLaunchKernelGGL(k_fof_cell_roots, cells, dim3(kBlock), 0, s, w.ndcells, bx, w.subtab,
                            w.subarg, w.parent);
     }
     if (w.nchunks > 0) {
         // one wavefront per workgroup: chunk costs differ widely, and a
         // finished wavefront's slot is free at once
         const int parts = w.nchunks <= 16 * (int64_t)(w.ncu > 0 ? w.ncu : 1) ? 2 : 1;
-        hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)(w.nchunks * parts)), dim3(64), 0, s, w.nchunks, parts, bx,
-                           w.chunks, w.sloc, w.spos, w.off, w.cnt, w.subtab, w.subarg, w.dens_s, w.parent);
+        hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)(w.nchunks * parts)), dim3(64), 0, s, w.nchunks, parts, n, bx,
+                           w.chunks, w.sloc, w.spos, w.cells, w.marks, w.subtab, w.subarg, w.dens_s, w.parent);
     }
     if (w.nsparse > 0)
         // one member in ten sparse particles: sixteen lanes per 8 particles at
         // most, and no more than fit the chip
         hipLaunchKernelGGL(k_fof_sparse, dim3(seg_blocks(sl, w.nsparse, 16, 8, 8 * (int64_t)(w.ncu > 0 ? w.ncu : 1))),
-                           dim3(kBlock), 0, s, sl, bx, w.sloc, w.spos, w.off, w.dens_s, w.parent);
+                           dim3(kBlock), 0, s, sl, bx, w.sloc, w.spos, w.cells, w.dens_s, w.parent);
     // roots go to the owner array (free until the assignment stage)
     hipLaunchKernelGGL(k_fof_roots, grid(n), dim3(kBlock), 0, s, n, w.parent, w.spos, w.owner, w.minorig);
 }

@@ -195,8 +195,12 @@ int64_t box_table_len(int nbox) {
 size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nbox, bool extra, Work *w) {
     Carver c{base};
     int64_t n1 = n + 1;
-    w->cnt = c.take<uint32_t>(ncell + 1);
-    w->off = c.take<uint32_t>(ncell + 1);
+    // start and dmap hold an entry per cell that holds particles; a word and
+    // three entries more for loads of several
+    const int64_t nocc = n < ncell ? n : ncell;
+    w->cells.occ = c.take<uint2>(hf::occ_words(ncell) + 1);
+    w->cells.start = c.take<uint32_t>(nocc + 4);
+    w->cells.dmap = c.take<uint32_t>(nocc + 1);
     // one block: the output stage stores a 16-byte record per particle there
     w->rkey[0] = c.take<uint64_t>(2 * n);
     w->rkey[1] = w->rkey[0] ? w->rkey[0] + n : nullptr;
@@ -212,7 +216,9 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->marks.chunk = c.take<uint64_t>(n / 64 + 1);
     w->marks.dcell = c.take<uint64_t>(n / 64 + 1);
     w->marks.sparse = c.take<uint64_t>(n / 64 + 1);
+    w->marks.head = c.take<uint64_t>(n / 64 + 1);
     w->marks.before = c.take<uint32_t>(n / 64 + 1);
+    w->marks.dbefore = c.take<uint32_t>(n / 64 + 1);
     w->tmp_a = c.take<uint32_t>(n1);
     w->tmp_b = c.take<uint32_t>(n1);
     w->tmp_c = c.take<uint32_t>(n1);
@@ -248,8 +254,8 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->h_gid = c.take<int32_t>(n1);
     w->g_nh = c.take<int32_t>(n1);
     w->h_count = c.take<uint32_t>(n1);
-    w->tflag = c.take<uint32_t>(n1);
-    w->tpos = c.take<uint32_t>(n1);
+    w->tflag = c.take<uint32_t>(n / 32 + 2);
+    w->tpos = c.take<uint32_t>(n / 32 + 3);
     w->hist = c.take<uint32_t>(2 * n1);
     int64_t scan_len = ncell > n ? ncell : n;
     if (rhl > scan_len) scan_len = rhl;

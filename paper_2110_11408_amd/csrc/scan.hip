@@ -180,8 +180,9 @@ bool scan_sums(uint32_t *sums, int64_t tiles, int64_t stride, int arrays, hipStr
     return true;
 }
 
-// Three runs of tile sums (the binning scans three quantities at once).
-int64_t scan_tmp_words(int64_t n) { return 3 * scan_tiles(n) + 16; }
+// Four runs of tile sums (the binning scans four quantities at once, of up to
+// 4096 smaller tiles when there are few particles).
+int64_t scan_tmp_words(int64_t n) { return 4 * scan_tiles(n) + 4 * 4096 + 16; }
 
 template <bool kBits>
 static void scan_impl(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {

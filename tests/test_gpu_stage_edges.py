@@ -142,3 +142,30 @@ def test_sort_over_box_boundaries(ctx, monkeypatch):
                    [torch.cat(r["halos"]).cpu().numpy()])
     for a, b in zip(*out):
         np.testing.assert_array_equal(a, b)
+
+
+# The index of the cells: a bit per cell in words of 32, written per tile of 4096
+# particles; the start of a cell that began before a wavefront's 64 particles is
+# searched for.  Cells of 8, 64, 65 and more particles, one over several tiles
+# (reached by steps back of doubling length), next to sparse ones; and few
+# particles in a grid of very many cells, where the words are zeroed apart.
+@pytest.mark.parametrize("clumps,background,mean_density", [
+    ((7, 8, 9, 63, 64, 65, 66), 500, 1.0),
+    ((127, 128, 129, 400, 1100), 4096, 1.0),
+    ((12000, 3000, 4095), 2000, 1.0),
+    ((30, 20), 40, 700.0),
+    ((3, 2), 9000, 0.02),
+])
+def test_cell_index(ctx, clumps, background, mean_density):
+    rng = np.random.default_rng(len(clumps) + background)
+    side = 24.0
+    width = 0.05 * mean_density ** (-1.0 / 3.0)  # an eighth of a cell
+    pos = [rng.random((background, 3)) * side]
+    for k, m in enumerate(clumps):
+        pos.append(rng.random(3) * (side - 1.0) + rng.random((m, 3)) * width)
+    # one clump at the end of the grid, one at its start
+    pos.append(side - rng.random((70, 3)) * width)
+    pos.append(rng.random((9, 3)) * width)
+    pos = np.concatenate(pos).astype(np.float32)[rng.permutation(background + sum(clumps) + 79)]
+    pos[pos >= np.float32(side)] = 0.0
+    _check(ctx, pos, box=side, mean_density=mean_density)
