@@ -28,13 +28,6 @@ namespace {
 
 inline dim3 grid(int64_t n) { return dim3((unsigned)((n + kBlock - 1) / kBlock)); }
 
-// Particles of the dense sub-cells gathered per round of the dense kernel.
-// Half a wavefront: after each round with joins the forest and the roots are
-// refreshed, so more, smaller rounds pass over more of the sub-cells that the
-// joins made common (k_fof_dense 5.76 -> 5.53 ms on the 96-box batch against
-// 64; 16 was faster there but slower on the 256^3 box).
-constexpr int kGather = 32;
-
 __device__ __forceinline__ int ld(const int32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -64,6 +57,11 @@ __device__ __forceinline__ int uf_find_hint(const int32_t *parent, int x) {
         if (p == x) return x;
         x = p;
     }
+}
+
+// The same once parent p of x is known.
+__device__ __forceinline__ int uf_find_from(const int32_t *parent, int x, int p) {
+    return p == x ? x : uf_find_hint(parent, p);
 }
 
 __device__ void uf_unite(int32_t *parent, int a, int b) {
@@ -418,9 +416,11 @@ constexpr int kTaskTile = 384;
 // Neighbour particles are gathered 64 at a time (one per lane, shifted into
 // the chunk's cell frame) and tested one after the other against all lanes;
 // sets are joined in the wavefront's registers and the hooks applied to the
-// forest in bulk after every gather round with joins, before each round of
-// sub-cells and at the end (root hints read meanwhile are moved through the
-// queued hooks):
+// forest in bulk before each round of sub-cells and at the end (root hints read
+// meanwhile are moved through the queued hooks; applying them and reading the
+// roots again after every gather round with joins was a chain of round trips
+// for little: 852 us on the 256^3 box, 815 without, 795 gathering 64 instead of
+// 32 at a time):
 //   sparse cells  all their particles, each member with its root;
 //   dense cells   their sub-cells, kTaskTile at a time: range and first member
 //                 (recorded by phase A); those with members within reach are
@@ -433,9 +433,9 @@ constexpr int kTaskTile = 384;
 //                 the roots for a few of them.)
 // A dense cell that carries the root common to all lanes has nothing to join
 // and is not visited.
-// With nparts = 2 a chunk is two wavefronts, one for the sparse cells and one
-// for the dense ones: for inputs whose chunks do not fill the chip, where the
-// longest chain is the time.
+// With nparts > 1 a chunk is a wavefront for the sparse cells and nparts - 1 for
+// the sub-cells of the dense ones: for inputs whose chunks do not fill the chip,
+// where the longest chain is the time.
 __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts, int64_t n, Boxes bx,
                                                       const int32_t *__restrict__ chunks,
                                                       const float4 *__restrict__ sloc,
@@ -451,9 +451,13 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     __shared__ uint32_t s_u1[kTaskTile];  // end,
     __shared__ int8_t s_st[kTaskTile];    // stencil index
     const unsigned wq = xcd_block();
-    const int64_t q = nparts == 2 ? wq >> 1 : wq;
+    const int64_t q = wq / (unsigned)nparts;
     if (q >= nchunks) return;
-    const bool do_sparse = nparts != 2 || (wq & 1u) == 0u, do_dense = nparts != 2 || (wq & 1u) != 0u;
+    // wavefront 0 of several takes the sparse cells, the others every
+    // shares-th sub-cell of each dense one (which cells a wavefront visits
+    // depends on the joins it sees, so the shares are cut within the cells)
+    const int role = (int)(wq - (unsigned)q * (unsigned)nparts), shares = max(nparts - 1, 1), share = max(role - 1, 0);
+    const bool do_sparse = role == 0, do_dense = nparts == 1 || role > 0;
     const int lane = threadIdx.x & 63;
     const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane(chunks[q]);
     const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, h))];
@@ -461,10 +465,12 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane(chunk_end(marks, h, n));
     const uint32_t i = h + (uint32_t)lane;
     const uint32_t ic = i < end ? i : h;
-    const bool active = i < end && is_member(dens_s, ic, g.dl0);
+    // a particle is a member if it has a parent
+    const int up = parent[ic];
+    const bool active = i < end && up >= 0;
     if (!__ballot(active)) return;
     const float4 li = sloc[ic];
-    int wr = active ? uf_find_hint(parent, (int)ic) : -1;
+    int wr = active ? uf_find_from(parent, (int)ic, up) : -1;
     const int k = g.ksub, nsub = g.nsub, tstride = bx.nsub_max + 1;
     const float subb = g.cellb / (float)k;
     int cx, cy, cz;
@@ -479,20 +485,12 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     // and sub-cells
     float bx0 = active ? li.x : 1e30f, by0 = active ? li.y : 1e30f, bz0 = active ? li.z : 1e30f;
     float bx1 = active ? li.x : -1e30f, by1 = active ? li.y : -1e30f, bz1 = active ? li.z : -1e30f;
-    for (int d = 32; d >= 1; d >>= 1) {
-        bx0 = fminf(bx0, __shfl_xor(bx0, d, 64));
-        by0 = fminf(by0, __shfl_xor(by0, d, 64));
-        bz0 = fminf(bz0, __shfl_xor(bz0, d, 64));
-        bx1 = fmaxf(bx1, __shfl_xor(bx1, d, 64));
-        by1 = fmaxf(by1, __shfl_xor(by1, d, 64));
-        bz1 = fmaxf(bz1, __shfl_xor(bz1, d, 64));
-    }
-    bx0 = uniform(bx0);
-    by0 = uniform(by0);
-    bz0 = uniform(bz0);
-    bx1 = uniform(bx1);
-    by1 = uniform(by1);
-    bz1 = uniform(bz1);
+    bx0 = wave_min(bx0);
+    by0 = wave_min(by0);
+    bz0 = wave_min(bz0);
+    bx1 = wave_max(bx1);
+    by1 = wave_max(by1);
+    bz1 = wave_max(bz1);
     const float gx = lx < 0 ? bx0 : (lx > 0 ? g.cellb - bx1 : 0.0f);
     const float gy = ly < 0 ? by0 : (ly > 0 ? g.cellb - by1 : 0.0f);
     const float gz = lz < 0 ? bz0 : (lz > 0 ? g.cellb - bz1 : 0.0f);
@@ -524,11 +522,7 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     // cells that hold particles (their starts are scalars)
     {
         const int cntl = do_sparse && lreach && !ldense ? (int)(lb - la) : 0;
-        int incl = cntl;
-        for (int d = 1; d < 64; d <<= 1) {
-            const int y = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += y;
-        }
+        const int incl = (int)wave_incl_scan((uint32_t)cntl);
         const int P = lane_get(incl, 63);
         const uint64_t cells = __ballot(cntl > 0);
         for (int p0 = 0; p0 < P; p0 += 64) {
@@ -548,20 +542,23 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
             int rc = -1;
             if (p < P) {
                 const float4 lj = sloc[jt];
-                cmem = is_member(dens_s, jt, g.dl0);
+                const int upj = parent[jt];
+                cmem = upj >= 0;
+                rc = upj;
                 qx = lj.x + (float)(t % 3 - 1) * g.cellb;
                 qy = lj.y + (float)((t / 3) % 3 - 1) * g.cellb;
                 qz = lj.z + (float)(t / 9 - 1) * g.cellb;
             }
-            if (cmem) rc = hooks_map(hk, uf_find_hint(parent, (int)jt));
+            if (cmem) rc = hooks_map(hk, uf_find_from(parent, (int)jt, rc));
             test_candidates(parent, hk, spos, g, active, li, h, wr, cmem, qx, qy, qz, jt, rc, no_rt);
         }
     }
     if (nvisit > 0) {
         __builtin_amdgcn_wave_barrier();
         const int a0 = (int)__builtin_ctzll(__ballot(active));
-        const int ntask = nvisit * nsub;
-        const float inv_nsub = 1.0f / (float)nsub, inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)(k * k);
+        const int nmine = (nsub - share + shares - 1) / shares;  // sub-cells of this share per cell
+        const int ntask = nvisit * nmine;
+        const float inv_mine = 1.0f / (float)nmine, inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)(k * k);
         for (int tb = 0; tb < ntask; tb += kTaskTile) {
         int listed = 0;
         constexpr int kTb = 3;  // 64-task rounds whose loads are issued together
@@ -576,8 +573,8 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
                 fm[r] = -1;
                 stv[r] = sl[r] = 0;
                 if (tq < ntask) {
-                    const int cell = div_small(tq, inv_nsub);
-                    sl[r] = tq - cell * nsub;
+                    const int cell = div_small(tq, inv_mine);
+                    sl[r] = (tq - cell * nmine) * shares + share;
                     stv[r] = doff[cell];
                     const int64_t row = dbase[cell] + sl[r];
                     u0[r] = subtab[row];
@@ -638,34 +635,20 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
             const uint32_t u1 = has ? s_u1[t0 + lane] : 0u;
             int rt = fs >= 0 ? hooks_map(hk, uf_find_hint(parent, fs)) : -1;
             uint32_t pos = fs >= 0 ? (uint32_t)fs : 0u;  // next particle of the sub-cell to gather
-            for (int gr = 0;; gr++) {
-                // after the joins of a gather round the forest learns them
-                // and the lanes and sub-cells read their current roots, so
-                // that sub-cells joined meanwhile (by this chunk or another)
-                // are passed over
-                if (gr > 0 && hk.n > 0) {
-                    hooks_apply(parent, hk);
-                    if (active) wr = uf_find_hint(parent, wr);
-                    if (rt >= 0) rt = uf_find_hint(parent, rt);
-                }
+            for (;;) {
                 const int w0 = lane_get(wr, a0);
                 const int wcommon = __ballot(active && wr != w0) ? -2 : w0;
                 const uint32_t len = fs >= 0 && pos < u1 && rt != wcommon ? u1 - pos : 0u;
-                uint32_t incl = len;
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t y = __shfl_up(incl, d, 64);
-                    if (lane >= d) incl += y;
-                }
+                const uint32_t incl = wave_incl_scan(len);
                 const uint32_t T = lane_get(incl, 63);
                 if (T == 0) break;
-                // lane p < kGather takes particle p of the sub-cells' runs laid end
-                // to end
+                // lane p takes particle p of the sub-cells' runs laid end to end
                 int tst = 13, trt = -1;
                 uint32_t jt = 0;
                 for (uint64_t m = __ballot(len > 0); m; m &= m - 1) {
                     const int u = (int)__builtin_ctzll(m);
                     const uint32_t stu = lane_get(incl, u) - lane_get(len, u);
-                    if (stu >= (uint32_t)kGather) break;
+                    if (stu >= 64u) break;
                     if ((uint32_t)lane >= stu) {
                         tst = lane_get(st, u);
                         trt = lane_get(rt, u);
@@ -674,11 +657,11 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
                 }
                 // every sub-cell moves past what this round takes from it
                 const uint32_t mine = incl - len;
-                if (mine < (uint32_t)kGather) pos += min(len, (uint32_t)kGather - mine);
+                if (mine < 64u) pos += min(len, 64u - mine);
                 bool cmem = false;
                 float qx = 0.0f, qy = 0.0f, qz = 0.0f;
                 int rc = -1;
-                if ((uint32_t)lane < T && lane < kGather) {
+                if ((uint32_t)lane < T) {
                     const float4 lj = sloc[jt];
                     cmem = is_member(dens_s, jt, g.dl0);
                     qx = lj.x + (float)(tst % 3 - 1) * g.cellb;
@@ -923,8 +906,11 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
     }
     if (w.nchunks > 0) {
         // one wavefront per workgroup: chunk costs differ widely, and a
-        // finished wavefront's slot is free at once
-        const int parts = w.nchunks <= 16 * (int64_t)(w.ncu > 0 ? w.ncu : 1) ? 2 : 1;
+        // finished wavefront's slot is free at once.  Three per chunk up to
+        // three quarters of the wavefronts the chip holds: with 4209 chunks 66 us
+        // became 44 and with 332 30 became 23, but with 9699 68 became 87 (and,
+        // in 64 boxes with longer chains, 9082 went from 82 to 64).
+        const int parts = w.nchunks <= 24 * (int64_t)(w.ncu > 0 ? w.ncu : 1) ? 3 : 1;
         hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)(w.nchunks * parts)), dim3(64), 0, s, w.nchunks, parts, n, bx,
                            w.chunks, w.sloc, w.spos, w.cells, w.marks, w.subtab, w.subarg, w.dens_s, w.parent);
     }

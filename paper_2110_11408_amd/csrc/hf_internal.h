@@ -176,6 +176,39 @@ __device__ __forceinline__ float lane_get(float v, int L) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), L));
 }
 
+// Scans and reductions over the 64 lanes (all active) in data-parallel-primitive
+// moves: shifts by 1, 2, 4 and 8 lanes within the rows of 16, then the last lane
+// of row 0 (2) to row 1 (3), and of the lower half to the upper one.  A lane
+// without a source takes `none`.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int dpp_move(int none, int v) {
+    return __builtin_amdgcn_update_dpp(none, v, kCtrl, kRows, 0xf, false);
+}
+template <typename Op>
+__device__ __forceinline__ int dpp_scan(int v, Op op) {
+    v = op(v, [](int none, int x) { return dpp_move<0x111, 0xf>(none, x); });
+    v = op(v, [](int none, int x) { return dpp_move<0x112, 0xf>(none, x); });
+    v = op(v, [](int none, int x) { return dpp_move<0x114, 0xf>(none, x); });
+    v = op(v, [](int none, int x) { return dpp_move<0x118, 0xf>(none, x); });
+    v = op(v, [](int none, int x) { return dpp_move<0x142, 0xa>(none, x); });
+    return op(v, [](int none, int x) { return dpp_move<0x143, 0xc>(none, x); });
+}
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    return (uint32_t)dpp_scan((int)v, [](int x, auto from) { return x + from(0, x); });
+}
+__device__ __forceinline__ float wave_min(float v) {
+    const int m = dpp_scan(__float_as_int(v), [](int x, auto from) {
+        return __float_as_int(fminf(__int_as_float(x), __int_as_float(from(x, x))));
+    });
+    return lane_get(__int_as_float(m), 63);
+}
+__device__ __forceinline__ float wave_max(float v) {
+    const int m = dpp_scan(__float_as_int(v), [](int x, auto from) {
+        return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(from(x, x))));
+    });
+    return lane_get(__int_as_float(m), 63);
+}
+
 // a / d for 0 <= a < 2^16 and 1 <= d <= 256 from FP32, given inv_d = 1/d:
 // (a + 1/2) / d is at least 1/(2d) away from every integer and its FP32
 // product with inv_d is within a few ulps of it, far less, so the truncation

@@ -25,16 +25,6 @@ inline int64_t scan_tiles(int64_t n) { return n > 0 ? (n + kScanTile - 1) / kSca
 
 __device__ __forceinline__ int scan_pad(int i) { return i + (i >> 5); }
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
 // Exclusive scan of one value per thread across an NT-thread block; *total
 // receives the block sum.
 template <int NT = kBlock>
