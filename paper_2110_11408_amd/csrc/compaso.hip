@@ -880,6 +880,126 @@ __global__ __launch_bounds__(kBlock) void k_out_split(int64_t n, const uint4 *__
     halo_id[o] = (int32_t)r.z;
 }
 
+// On large inputs the records take the way of a sort instead: partitioned by
+// their original index into runs of kOutBucket, one or two passes, and then put
+// in place in LDS.  A bucket's start is known (every index comes once), so a
+// tile needs no counting pass: it takes its share of each bucket by an atomic.
+// Scattered 16-byte records go to memory as 32-byte sectors all over it: 410 us
+// and 98 for the split on the 256^3 box, 231 and 115 with the partition; 6.2 and
+// 0.67 ms on the 512^3 box, 2.2 (two passes) and 0.71.  Below about 3 million
+// particles the records stay in the memory-side cache and the scatter is faster
+// (2^21: the output stage 58 us against 65; 2^22: 127 against 106).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // a record in registers
+constexpr int kOutTile = 4096, kOutThreads = 512, kOutPer = kOutTile / kOutThreads;
+constexpr int kOutBits = 14, kOutBucket = 1 << kOutBits;
+constexpr int kOutBins = 1024;  // buckets of one pass at most
+constexpr int64_t kOutPartLeast = (int64_t)1 << 22;
+
+// One pass: records (density, L0 label, halo label, original index) of a tile
+// into the buckets of 2^shift indices (first pass: from the sorted arrays; else
+// from `in`, whose runs of 2^from indices hold whole tiles).
+template <bool kFirst>
+__global__ __launch_bounds__(kOutThreads, 4) void k_out_part(int64_t n, Boxes bx, const int32_t *__restrict__ owner,
+                                                          const int32_t *__restrict__ h_label,
+                                                          const int32_t *__restrict__ gkey,
+                                                          const float4 *__restrict__ spos,
+                                                          const float *__restrict__ dens_s,
+                                                          const u32x4 *__restrict__ in, int from, int shift,
+                                                          uint32_t *__restrict__ cursor, u32x4 *__restrict__ out) {
+    __shared__ u32x4 s_rec[kOutTile];
+    __shared__ uint32_t s_off[kOutBins], s_base[kOutBins];
+    static_assert(kOutBins == 2 * kOutThreads, "two buckets per thread");
+    const int64_t t0 = (int64_t)xcd_block() * kOutTile;
+    // the tile's first possible bucket
+    const uint32_t b0 = kFirst ? 0u : (uint32_t)(t0 >> from) << (from - shift);
+    s_off[2 * threadIdx.x] = 0u;
+    s_off[2 * threadIdx.x + 1] = 0u;
+    __syncthreads();
+    u32x4 rec[kOutPer];
+    if (kFirst) {
+        int32_t own[kOutPer], key[kOutPer];
+#pragma unroll
+        for (int k = 0; k < kOutPer; k++) {
+            const int64_t i = t0 + k * kOutThreads + threadIdx.x, ic = i < n ? i : n - 1;
+            own[k] = owner[ic];
+            key[k] = gkey[ic];
+            rec[k].x = __float_as_uint(dens_s[ic]);
+            rec[k].w = orig_of(spos[ic]);
+        }
+#pragma unroll
+        for (int k = 0; k < kOutPer; k++) {
+            rec[k].y = key[k] < 0 ? 0u : (uint32_t)key[k] + 1u;
+            rec[k].z = own[k] >= 0 ? (uint32_t)h_label[own[k]] : 0u;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kOutPer; k++) {
+            const int64_t i = t0 + k * kOutThreads + threadIdx.x;
+            rec[k] = in[i < n ? i : n - 1];
+        }
+    }
+    uint32_t rank[kOutPer];
+#pragma unroll
+    for (int k = 0; k < kOutPer; k++)
+        if (t0 + k * kOutThreads + threadIdx.x < n) rank[k] = atomicAdd(&s_off[(rec[k].w >> shift) - b0], 1u);
+    __syncthreads();
+    const uint32_t c0 = s_off[2 * threadIdx.x], c1 = s_off[2 * threadIdx.x + 1];
+    uint32_t total;
+    const uint32_t pre = block_excl_scan<kOutThreads>(c0 + c1, &total);
+    const uint32_t b = b0 + 2u * threadIdx.x;
+    s_off[2 * threadIdx.x] = pre;
+    s_off[2 * threadIdx.x + 1] = pre + c0;
+    if (c0) s_base[2 * threadIdx.x] = (b << shift) + atomicAdd(cursor + b, c0) - pre;
+    if (c1) s_base[2 * threadIdx.x + 1] = ((b + 1u) << shift) + atomicAdd(cursor + b + 1u, c1) - (pre + c0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kOutPer; k++)
+        if (t0 + k * kOutThreads + threadIdx.x < n) s_rec[s_off[(rec[k].w >> shift) - b0] + rank[k]] = rec[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kOutPer; k++) {
+        const uint32_t j = k * kOutThreads + threadIdx.x;
+        if (j < total) {
+            u32x4 q = s_rec[j];
+            // the L0 label in its box's numbering (a box holds the same indices
+            // in input and in sorted order)
+            if (kFirst && q.y) q.y -= (uint32_t)bx.geo[box_of(bx, q.w)].orig_base;
+            out[s_base[(q.w >> shift) - b0] + j] = q;
+        }
+    }
+}
+
+// The records of a bucket to the output arrays, each put in order in LDS.
+__global__ __launch_bounds__(1024) void k_out_place(int64_t n, const u32x4 *__restrict__ rec,
+                                                    float *__restrict__ dens_out, int32_t *__restrict__ l0_out,
+                                                    int32_t *__restrict__ halo_id) {
+    __shared__ uint32_t s_val[kOutBucket];
+    constexpr int kPer = kOutBucket / 1024;
+    const int64_t o0 = (int64_t)xcd_block() * kOutBucket;
+    const int m = (int)min((int64_t)kOutBucket, n - o0);
+    u32x4 q[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        const int j = k * 1024 + threadIdx.x;
+        q[k] = j < m ? rec[o0 + j] : u32x4{0u, 0u, 0u, 0u};
+    }
+    auto place = [&](auto pick, uint32_t *to) {
+#pragma unroll
+        for (int k = 0; k < kPer; k++)
+            if (k * 1024 + (int)threadIdx.x < m) s_val[q[k].w & (uint32_t)(kOutBucket - 1)] = pick(q[k]);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            const int j = k * 1024 + threadIdx.x;
+            if (j < m) to[o0 + j] = s_val[j];
+        }
+        __syncthreads();
+    };
+    if (dens_out) place([](const u32x4 &x) { return x.x; }, reinterpret_cast<uint32_t *>(dens_out));
+    if (l0_out) place([](const u32x4 &x) { return x.y; }, reinterpret_cast<uint32_t *>(l0_out));
+    place([](const u32x4 &x) { return x.z; }, reinterpret_cast<uint32_t *>(halo_id));
+}
+
 // ------------------------------------------------------------ group order
 // Members collected into group order (Sec. 2.3.5): the particles sorted by the
 // table row of their halo (particles of no halo after the last row), ascending
@@ -1031,7 +1151,32 @@ void launch_output(int64_t n, int64_t NC, const Boxes &bx, Work &w, int32_t *hal
                            halo_id);
         return;
     }
-    // records in the radix key block (2n words, free at this point)
+    // records in the radix key block (16 n bytes, free at this point)
+    if (n >= kOutPartLeast) {
+        u32x4 *rec = reinterpret_cast<u32x4 *>(w.rkey[0]);
+        const dim3 tiles((unsigned)((n + kOutTile - 1) / kOutTile));
+        const int64_t buckets = (n + kOutBucket - 1) / kOutBucket;
+        // the cursors in the radix sort's payload, those of a first pass behind
+        // the others'; its records in the scratch run of 4 (n + 1) words
+        uint32_t *cursor = w.rval[0];
+        if (buckets <= kOutBins) {
+            fill_u32(cursor, 0u, buckets, s);
+            hipLaunchKernelGGL(k_out_part<true>, tiles, dim3(kOutThreads), 0, s, n, bx, w.owner, w.hardlist, w.gkey,
+                               w.spos, w.dens_s, nullptr, 0, kOutBits, cursor, rec);
+        } else {
+            // two passes of about equally many bits
+            const int bits = bits_for(buckets - 1), from = kOutBits + bits / 2;
+            const int64_t coarse = ((n - 1) >> from) + 1;
+            u32x4 *half = reinterpret_cast<u32x4 *>(w.tmp_a);
+            fill_u32(cursor, 0u, buckets + coarse, s);
+            hipLaunchKernelGGL(k_out_part<true>, tiles, dim3(kOutThreads), 0, s, n, bx, w.owner, w.hardlist, w.gkey,
+                               w.spos, w.dens_s, nullptr, 0, from, cursor + buckets, half);
+            hipLaunchKernelGGL(k_out_part<false>, tiles, dim3(kOutThreads), 0, s, n, bx, nullptr, nullptr, nullptr,
+                               nullptr, nullptr, half, from, kOutBits, cursor, rec);
+        }
+        hipLaunchKernelGGL(k_out_place, dim3((unsigned)buckets), dim3(1024), 0, s, n, rec, dens_out, l0_out, halo_id);
+        return;
+    }
     uint4 *rec = reinterpret_cast<uint4 *>(w.rkey[0]);
     hipLaunchKernelGGL(k_out_records, grid(n), dim3(kBlock), 0, s, n, bx, w.owner, w.hardlist, w.gkey, w.spos,
                        w.dens_s, rec);

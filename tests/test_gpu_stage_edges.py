@@ -169,3 +169,43 @@ def test_cell_index(ctx, clumps, background, mean_density):
     pos = np.concatenate(pos).astype(np.float32)[rng.permutation(background + sum(clumps) + 79)]
     pos[pos >= np.float32(side)] = 0.0
     _check(ctx, pos, box=side, mean_density=mean_density)
+
+
+# The three outputs of a find leave as records: scattered below 2^22 particles,
+# partitioned by original index beyond, in one pass up to 2^24 and two above.
+# The density and the L0 labels alone, and the halo labels alone, are written
+# without records.
+@pytest.mark.parametrize("n", [2 ** 22 - 1, 2 ** 22, 2 ** 22 + 4097, 2 ** 24, 2 ** 24 + 1])
+def test_output_records(ctx, n):
+    import torch
+    from paper_2110_11408_amd import _lib
+    pos, side, _ = synth.small_box(n, seed=11, nmax=20000)
+    p = _lib.default_params(box=side)
+    t = torch.from_numpy(np.ascontiguousarray(pos)).cuda()
+    print(f"[gpu] hf_find outputs n={n}", file=sys.stderr, flush=True)
+    a = ctx.find(t, p)
+    b = ctx.find(t, p, want_density=False, want_l0=False)
+    dens = ctx.density(t, p)
+    l0, _ = ctx.l0_fof(t, dens, p)
+    assert torch.equal(a["density"], dens) and torch.equal(a["l0_id"], l0)
+    assert torch.equal(a["halo_id"], b["halo_id"]) and torch.equal(a["halos"], b["halos"])
+    assert int((a["halo_id"] > 0).sum()) > n // 10
+    c = ctx.find(t, p, want_density=False)
+    assert torch.equal(c["l0_id"], l0) and torch.equal(c["halo_id"], a["halo_id"])
+
+
+def test_output_records_of_several_boxes(ctx):
+    """L0 labels count from the box's own first particle."""
+    import torch
+    from paper_2110_11408_amd import _lib
+    boxes = [synth.small_box(n, seed=n) for n in (2200003, 4095, 2100001)]
+    params = [_lib.default_params(box=b[1]) for b in boxes]
+    pos = torch.from_numpy(np.concatenate([b[0] for b in boxes])).cuda()
+    offs = np.concatenate([[0], np.cumsum([len(b[0]) for b in boxes])])
+    print(f"[gpu] hf_find_batch outputs n={len(pos)}", file=sys.stderr, flush=True)
+    r = ctx.find_batch(pos, offs, params, n_lanes=1)
+    for k in range(len(boxes)):
+        one = ctx.find(pos[offs[k]:offs[k + 1]].contiguous(), params[k])
+        for key in ("density", "l0_id", "halo_id"):
+            assert torch.equal(r[key][offs[k]:offs[k + 1]], one[key])
+        assert torch.equal(r["halos"][k], one["halos"])
