@@ -448,8 +448,10 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, int64_
 // any lane changed: 2300 vector instructions per wavefront, 782 us on the 256^3
 // box.  Listing the pairs of all lanes in LDS and computing one pair per lane
 // took 911 us: there are about a dozen pairs per particle, and each cost a
-// list entry and the image of its own.)  Seven wavefronts per SIMD: at eight the
-// registers spill, 727 us against 683.
+// list entry and the image of its own.  Seven wavefronts per SIMD: at eight the
+// registers spill, 727 us against 683.  With the image of a run told by two of its
+// bits it takes 658.  All planes' runs in one walk, with room for eleven runs a
+// lane: 708, at six wavefronts 682.)
 constexpr int kSparseWaves = kBlock / 64;
 __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int64_t i, uint2 (*runs)[64],
                                                    const float4 *__restrict__ sloc,
@@ -475,11 +477,12 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
     // rounding of the local coordinates) weighs nothing
     const float hx = g.cellb - li.x, hy = g.cellb - li.y, hz = g.cellb - li.z;
     const float most = 1.0f + 1e-5f;
-    // the position in the frames of the cells to both sides (the periodic image
-    // of a cell across a face of the box), and in its own
+    // the position in the frame of its own cell and of a cell across a face of
+    // the box (the periodic image; a run carries in its top bits whether it lies
+    // across an x or a y face)
     const double px = (double)pi.x, py = (double)pi.y, pz = (double)pi.z;
-    const double pxm = x_lo ? px + g.L : px, pxp = x_hi ? px - g.L : px;
-    const double pym = y_lo ? py + g.L : py, pyp = y_hi ? py - g.L : py;
+    const double pxw = x_lo ? px + g.L : px - g.L, pyw = y_lo ? py + g.L : py - g.L;
+    const uint32_t x_lo31 = x_lo ? 1u << 31 : 0u, x_hi31 = x_hi ? 1u << 31 : 0u;
     double acc = 0.0;
 #pragma unroll 1
     for (int oz = -1; oz <= 1; oz++) {
@@ -538,6 +541,7 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
         for (int r = 0; r < 3; r++) {
             const float gy = r == 0 ? li.y : (r == 2 ? hy : 0.0f);
             const float left = gz2 - gy * gy;
+            const uint32_t yw31 = (r == 0 ? y_lo : (r == 2 ? y_hi : false)) ? 1u << 31 : 0u;
             // end of each cell's run, its start when the cell is left out
             uint32_t e0 = b[3 * r] - a[3 * r] < (uint32_t)kDenseMin && li.x * li.x < left ? b[3 * r] : a[3 * r];
             uint32_t e1 = b[3 * r + 1] - a[3 * r + 1] < (uint32_t)kDenseMin && 0.0f < left ? b[3 * r + 1] : a[3 * r + 1];
@@ -553,15 +557,15 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
                 e1 = a[3 * r + 1];
             }
             if (e0 > a[3 * r]) {
-                runs[3 * r][lane] = make_uint2(a[3 * r], e0);
+                runs[3 * r][lane] = make_uint2(a[3 * r] | x_lo31, e0 | yw31);
                 open |= 1u << (3 * r);
             }
             if (e1 > a[3 * r + 1]) {
-                runs[3 * r + 1][lane] = make_uint2(a[3 * r + 1], e1);
+                runs[3 * r + 1][lane] = make_uint2(a[3 * r + 1], e1 | yw31);
                 open |= 2u << (3 * r);
             }
             if (e2 > a[3 * r + 2]) {
-                runs[3 * r + 2][lane] = make_uint2(a[3 * r + 2], e2);
+                runs[3 * r + 2][lane] = make_uint2(a[3 * r + 2] | x_hi31, e2 | yw31);
                 open |= 4u << (3 * r);
             }
         }
@@ -572,11 +576,10 @@ __device__ __forceinline__ void density_sparse_one(const Geo &g, int64_t t, int6
                 const int k = __builtin_ctz(open);
                 open &= open - 1u;
                 const uint2 run = runs[k][lane];
-                j = run.x;
-                e = run.y;
-                const int ry = (k * 11) >> 5, rx = k - 3 * ry;
-                pim.x = rx == 0 ? pxm : (rx == 2 ? pxp : px);
-                pim.y = ry == 0 ? pym : (ry == 2 ? pyp : py);
+                j = run.x & 0x7fffffffu;
+                e = run.y & 0x7fffffffu;
+                pim.x = (int)run.x < 0 ? pxw : px;
+                pim.y = (int)run.y < 0 ? pyw : py;
             }
             acc += weight64(pim, spos[j], g.inv_b2);
             j++;
