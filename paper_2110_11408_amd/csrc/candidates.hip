@@ -136,10 +136,15 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
 // the densest particle of its sub-cell is decided at once when that densest
 // particle belongs to its group and lies within b (the usual case inside an L0
 // group, the sub-cell diagonal being below l).  A member that is its
-// sub-cell's densest is decided when the densest particle of a face-adjacent
-// sub-cell of the same cell is denser and in its group, where such sub-cells
-// lie within b of each other entirely (s sqrt(6) < b).  Every other member at
-// or above the floor is listed as a hard case.
+// sub-cell's densest is decided in the same way by the densest particle of its
+// cell, or when the densest particle of a face-adjacent sub-cell of the same
+// cell is denser and in its group, where such sub-cells lie within b of each
+// other entirely (s sqrt(6) < b).  Every other member at or above the floor is
+// listed as a hard case.  The kernel waits on rounds of dependent loads: with the
+// marks loaded next to the key, and the cell's densest particle tested in the
+// round that a sub-cell's densest had free, it takes 190 us on the 256^3 box
+// (248 before) and leaves 371 000 hard cases of 524 000 (k_cand_search 324 ->
+// 236 us).
 __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
                                                        const float4 *__restrict__ spos,
                                                        Marks marks, const uint16_t *__restrict__ ssub,
@@ -156,27 +161,31 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
     bool is_hard = false;
     const int key = i < n ? gkey[i] : -1;
     const float di = dens_s[ic];
+    // (with the key and the density, so that a member saves a round of loads)
+    const bool sparse_i = is_sparse(marks, ic);
+    const int si = ssub[ic];
+    const uint32_t cell = dense_ordinal(marks, (uint32_t)ic);
     if (key >= 0 && (double)di >= g.floor_nuc) {
         is_hard = true;
-        // everything indexed by i in one round of loads
-        const bool sparse_i = is_sparse(marks, i);
-        const int si = ssub[i];
         const float4 pi = spos[i];
         if (!sparse_i) {
-            const int64_t base = (int64_t)dense_ordinal(marks, (uint32_t)i) * (bx.nsub_max + 1);
-            const int32_t top = subarg[base + si];
+            const int64_t base = (int64_t)cell * (bx.nsub_max + 1);
+            const int32_t own = subarg[base + si], most = subarg[base + bx.nsub_max];
             const uint32_t oi = orig_of(pi);
+            // the maximum of i's sub-cell or, when that is i, of its cell, is
+            // denser than i (the bit order of the key matches the values for the
+            // non-negative densities the stage works on; checked anyway); its
+            // key, density and position are loaded together
+            const int32_t top = own != (int32_t)i ? own : most;
             if (top != (int32_t)i) {
-                // top, the maximum of i's sub-cell, is denser than i (the bit
-                // order of the key matches the values for the non-negative
-                // densities the stage works on; checked anyway); its key,
-                // density and position are loaded together
                 const int kt = gkey[top];
                 const float dt = dens_s[top];
                 const float4 pt = spos[top];
                 if (kt == key && denser(dt, orig_of(pt), di, oi) && d2_exact(pi, pt, g.L, g.half) < g.b2)
                     is_hard = false;
-            } else if (g.face_sub_in_b) {
+            }
+            // (the densest particle of the cell has no denser sub-cell next to it)
+            if (is_hard && own == (int32_t)i && most != (int32_t)i && g.face_sub_in_b) {
                 // the six face-adjacent sub-cells at once: their maxima, then
                 // the particles that hold them, then those particles' keys
                 const int k = g.ksub;
