@@ -145,6 +145,7 @@ __global__ __launch_bounds__(kBlock) void k_submax_wave(int64_t ndc, Boxes bx,
 // round that a sub-cell's densest had free, it takes 190 us on the 256^3 box
 // (248 before) and leaves 371 000 hard cases of 524 000 (k_cand_search 324 ->
 // 236 us).
+template <int kQuickPer>  // particles per thread
 __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
                                                        const float4 *__restrict__ spos,
                                                        Marks marks, const uint16_t *__restrict__ ssub,
@@ -155,43 +156,72 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
                                                        SegList hl,
                                                        uint64_t *clock) {
     stamp(clock);
-    const int64_t i = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
-    const int64_t ic = i < n ? i : n - 1;
-    const Geo &g = bx.geo[box_of(bx, (uint32_t)ic)];
-    bool is_hard = false;
-    const int key = i < n ? gkey[i] : -1;
-    const float di = dens_s[ic];
-    // (with the key and the density, so that a member saves a round of loads)
-    const bool sparse_i = is_sparse(marks, ic);
-    const int si = ssub[ic];
-    const uint32_t cell = dense_ordinal(marks, (uint32_t)ic);
-    if (key >= 0 && (double)di >= g.floor_nuc) {
-        is_hard = true;
-        const float4 pi = spos[i];
-        if (!sparse_i) {
-            const int64_t base = (int64_t)cell * (bx.nsub_max + 1);
-            const int32_t own = subarg[base + si], most = subarg[base + bx.nsub_max];
-            const uint32_t oi = orig_of(pi);
-            // the maximum of i's sub-cell or, when that is i, of its cell, is
-            // denser than i (the bit order of the key matches the values for the
-            // non-negative densities the stage works on; checked anyway); its
-            // key, density and position are loaded together
-            const int32_t top = own != (int32_t)i ? own : most;
-            if (top != (int32_t)i) {
-                const int kt = gkey[top];
-                const float dt = dens_s[top];
-                const float4 pt = spos[top];
-                if (kt == key && denser(dt, orig_of(pt), di, oi) && d2_exact(pi, pt, g.L, g.half) < g.b2)
-                    is_hard = false;
-            }
-            // (the densest particle of the cell has no denser sub-cell next to it)
-            if (is_hard && own == (int32_t)i && most != (int32_t)i && g.face_sub_in_b) {
+    const int64_t i0 = (int64_t)xcd_block() * (kQuickPer * kBlock) + threadIdx.x;
+    bool hard[kQuickPer], dense[kQuickPer];
+    int key[kQuickPer], si[kQuickPer];
+    int32_t idx[kQuickPer], own[kQuickPer], most[kQuickPer];
+    uint32_t cell[kQuickPer];
+    float di[kQuickPer];
+    float4 pi[kQuickPer];
+    // (the marks with the key and the density, so that a member saves a round of
+    // loads)
+#pragma unroll
+    for (int u = 0; u < kQuickPer; u++) {
+        const int64_t i = i0 + u * kBlock, ic = i < n ? i : n - 1;
+        idx[u] = (int32_t)i;
+        key[u] = i < n ? gkey[ic] : -1;
+        di[u] = dens_s[ic];
+        dense[u] = !is_sparse(marks, ic);
+        si[u] = ssub[ic];
+        cell[u] = dense_ordinal(marks, (uint32_t)ic);
+    }
+#pragma unroll
+    for (int u = 0; u < kQuickPer; u++) {
+        const int64_t i = i0 + u * kBlock, ic = i < n ? i : n - 1;
+        hard[u] = key[u] >= 0 && (double)di[u] >= bx.geo[box_of(bx, (uint32_t)ic)].floor_nuc;
+        dense[u] = dense[u] && hard[u];
+        own[u] = most[u] = idx[u];
+        if (dense[u]) {
+            const int64_t base = (int64_t)cell[u] * (bx.nsub_max + 1);
+            own[u] = subarg[base + si[u]];
+            most[u] = subarg[base + bx.nsub_max];
+            pi[u] = spos[i];
+        }
+    }
+    // the maximum of i's sub-cell or, when that is i, of its cell, is denser than
+    // i (the bit order of the key matches the values for the non-negative
+    // densities the stage works on; checked anyway); its key, density and
+    // position are loaded together
+    int kt1[kQuickPer];
+    float dt1[kQuickPer];
+    float4 pt1[kQuickPer];
+#pragma unroll
+    for (int u = 0; u < kQuickPer; u++) {
+        const int32_t top = own[u] != idx[u] ? own[u] : most[u];
+        kt1[u] = -1;
+        if (top != idx[u]) {
+            kt1[u] = gkey[top];
+            dt1[u] = dens_s[top];
+            pt1[u] = spos[top];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kQuickPer; u++) {
+        if (!dense[u]) continue;
+        const Geo &g = bx.geo[box_of(bx, (uint32_t)idx[u])];
+        const uint32_t oi = orig_of(pi[u]);
+        if (kt1[u] == key[u] && denser(dt1[u], orig_of(pt1[u]), di[u], oi) &&
+            d2_exact(pi[u], pt1[u], g.L, g.half) < g.b2)
+            hard[u] = false;
+        // (the densest particle of the cell has no denser sub-cell next to it)
+        if (hard[u] && own[u] == idx[u] && most[u] != idx[u] && g.face_sub_in_b) {
+            const int64_t base = (int64_t)cell[u] * (bx.nsub_max + 1);
                 // the six face-adjacent sub-cells at once: their maxima, then
                 // the particles that hold them, then those particles' keys
                 const int k = g.ksub;
-                const int sz = div_small(si, 1.0f / (float)(k * k)), syx = si - sz * k * k,
+                const int sz = div_small(si[u], 1.0f / (float)(k * k)), syx = si[u] - sz * k * k,
                           sy = div_small(syx, 1.0f / (float)k), sx = syx - sy * k;
-                const uint64_t mykey = dkey(di, oi);
+                const uint64_t mykey = dkey(di[u], oi);
                 int s2[6];
                 uint64_t mx[6];
 #pragma unroll
@@ -222,11 +252,10 @@ __global__ __launch_bounds__(kBlock) void k_cand_quick(int64_t n, Boxes bx,
                 }
 #pragma unroll
                 for (int f = 0; f < 6; f++)
-                    if (t2[f] >= 0 && kt[f] == key && denser(dt[f], ot[f], di, oi)) is_hard = false;
-            }
+                    if (t2[f] >= 0 && kt[f] == key[u] && denser(dt[f], ot[f], di[u], oi)) hard[u] = false;
         }
     }
-    seg_append(hl, is_hard, (int32_t)i);
+    seg_append<kQuickPer>(hl, hard, idx);
 }
 
 // Stage 2, half a wavefront per hard case: whether a denser particle of the
@@ -545,7 +574,9 @@ void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
                            dim3(kBlock), 0, s, w.ndcells, bx, w.subtab, w.ssub, w.dens_s, w.spos, w.submax,
                            w.subarg, w.clock + kClockCand);
     const SegList hl = seg_list(n, w);
-    hipLaunchKernelGGL(k_cand_quick, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, bx,
+    const int64_t per = list_per(n) * kBlock;
+    hipLaunchKernelGGL(list_per(n) == 2 ? k_cand_quick<2> : k_cand_quick<1>, dim3((unsigned)((n + per - 1) / per)),
+                       dim3(kBlock), 0, s, n, bx,
                        w.spos, w.marks, w.ssub, w.submax, w.subarg, w.dens_s, w.gkey, hl,
                        w.ndcells > 0 ? nullptr : w.clock + kClockCand);
     // half-wavefronts striding over the segments: as many as fit the chip (six

@@ -437,11 +437,19 @@ struct SegList {
 };
 
 // Appends i of the lanes with `take` (every thread of the kBlock takes part).
-__device__ __forceinline__ void seg_append(const SegList &sl, bool take, int32_t i) {
+// (K particles per thread: the workgroup waits once for its atomic.)
+template <int K>
+__device__ __forceinline__ void seg_append(const SegList &sl, const bool (&take)[K], const int32_t (&i)[K]) {
     __shared__ uint32_t s_cnt[kBlock / 64], s_base;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t m = __ballot(take);
-    if (lane == 0) s_cnt[w] = (uint32_t)__popcll(m);
+    uint64_t m[K];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < K; u++) {
+        m[u] = __ballot(take[u]);
+        mine += (uint32_t)__popcll(m[u]);
+    }
+    if (lane == 0) s_cnt[w] = mine;
     __syncthreads();
     const uint32_t seg = blockIdx.x % sl.nseg;
     if (threadIdx.x == 0) {
@@ -450,11 +458,18 @@ __device__ __forceinline__ void seg_append(const SegList &sl, bool take, int32_t
         s_base = t ? atomicAdd(sl.count + seg * kSegStride, t) : 0u;
     }
     __syncthreads();
-    if (take) {
-        uint32_t at = s_base;
-        for (int x = 0; x < w; x++) at += s_cnt[x];
-        sl.list[(int64_t)seg * sl.cap + at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = i;
+    uint32_t at = s_base;
+    for (int x = 0; x < w; x++) at += s_cnt[x];
+#pragma unroll
+    for (int u = 0; u < K; u++) {
+        if (take[u]) sl.list[(int64_t)seg * sl.cap + at + (uint32_t)__popcll(m[u] & ((1ull << lane) - 1ull))] = i[u];
+        at += (uint32_t)__popcll(m[u]);
     }
+}
+__device__ __forceinline__ void seg_append(const SegList &sl, bool take, int32_t i) {
+    const bool t[1] = {take};
+    const int32_t v[1] = {i};
+    seg_append<1>(sl, t, v);
 }
 
 // The share of one of kBlock / W lane groups per workgroup in a list: entries
@@ -497,17 +512,25 @@ struct SegClear {
     int len[kRuns];
 };
 
+// Particles per thread of the kernels that fill a segmented list: two on large
+// inputs, where twice the loads in flight hide their latency (k_cand_quick 191
+// -> 152 us on the 256^3 box, k_fof_phase_a 167 -> 148), one where a wavefront's
+// own chain is the time (20 000 particles: 4.7 us against 8.0; 2.6e5: 7.0 against
+// 8.6; equal at 1.3e6).
+inline int list_per(int64_t n) { return n > ((int64_t)1 << 20) ? 2 : 1; }
+
 // The segmented list over n particles.  Its entries lie in the scratch arrays
 // (4 n words in one run; the segments hold at most 2 (n + 255) words, and a
 // single segment at most n), its counts in the radix counts (at least n / 8
 // words, of which n / 16 + 16 are used).
 inline SegList seg_list(int64_t n, const Work &w) {
-    const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    const int per_thread = list_per(n);
+    const unsigned nb = (unsigned)((n + kBlock * per_thread - 1) / (kBlock * per_thread));
     SegList sl;
     sl.list = reinterpret_cast<int32_t *>(w.tmp_a);
     sl.count = w.rhist;
     sl.nseg = nb < kSegs ? nb : kSegs;
-    sl.cap = (nb + sl.nseg - 1) / sl.nseg * kBlock;
+    sl.cap = (nb + sl.nseg - 1) / sl.nseg * (unsigned)(kBlock * per_thread);
     return sl;
 }
 // Workgroups whose lane groups of W share a segmented list of n particles'
