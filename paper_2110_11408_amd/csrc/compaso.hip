@@ -33,10 +33,7 @@ inline dim3 grid(int64_t n) { return dim3((unsigned)((n + kBlock - 1) / kBlock))
 __device__ __forceinline__ int32_t ldi(const int32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint32_t ldu(const uint32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void stu(uint32_t *p, uint32_t v) {
+__device__ __forceinline__ void sti(int32_t *p, int32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -277,7 +274,7 @@ __device__ __forceinline__ int64_t bucket_of(double T, int64_t m) {
     return k;
 }
 
-constexpr int kHistMid = 12288;   // histogram buckets of a medium group counted in LDS (48 KB)
+constexpr int kHistMid = 2048;    // histogram buckets of a medium group, counted in LDS (8 KB)
 constexpr int kHistBig = 36864;   // histogram buckets of a large group counted in LDS (144 KB)
 constexpr int kScanIpt = 16;      // buckets per thread per scan step
 
@@ -314,8 +311,14 @@ __device__ __forceinline__ int block_min(int v, int *s_min) {
     return best;
 }
 
-constexpr int kWaveHist = 1024;   // groups below this size run one per wavefront
-constexpr int kWaveNuc = 64;      // ... when they have at most this many candidates
+// Candidates (their places in cand_sorted) of groups that are not small: each
+// group's densest from the front of the list, the others from its back.
+struct AcceptItems {
+    int32_t *list;
+    uint32_t *firsts, *rests, cap;
+};
+
+constexpr int kWaveHist = 1024;   // groups of one candidate below this size run one per wavefront
 
 // Groups with candidates (all boxes, largest first), one wavefront at a time
 // each: a persistent grid of W wavefronts in which wavefront w takes groups
@@ -323,15 +326,15 @@ constexpr int kWaveNuc = 64;      // ... when they have at most this many candid
 // every wavefront gets one group of each size tier.  (A shared counter that
 // every wavefront increments per group serialises on its one address: tens of
 // thousands of groups cost more in atomics than in work.)  Groups of fewer
-// than kWaveHist particles with at
-// most kWaveNuc candidates run here: the same walk as k_accept with the
-// histogram, the accepted nuclei and their positions in the wavefront's LDS
-// and wave-level scans instead of workgroup barriers, so that many small
-// groups run on a CU at once.  The other groups are appended to mid_list
-// (fewer than kHistMid particles) or big_list, with their counts in
-// *mid_count and *big_count, for k_accept (route_all: every group, when R is
-// searched by radial bins).
-__global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restrict__ ngc_p, bool route_all,
+// than kWaveHist particles with one candidate, most of all groups, are settled
+// here: the candidate is accepted, and its enclosed count found from a histogram
+// in the wavefront's LDS with wave-level scans, so that many small groups run on
+// a CU at once.  The candidates of the other groups go to the item lists of the
+// medium groups (fewer than mid_most particles) or the large ones, for
+// k_accept_eval (route_all: every group, when R is searched by radial bins).
+// (With groups of up to 64 candidates walked here, the longest walk was the
+// time: 17 us for 20 000 particles, 11 without.)
+__global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restrict__ ngc_p, bool route_all, int mid_most,
                                                          Boxes bx,
                                                          const int32_t *__restrict__ glist,
                                                          const int32_t *__restrict__ g_start,
@@ -344,16 +347,12 @@ __global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restr
                                                          int32_t *__restrict__ h_ienc,
                                                          int32_t *__restrict__ h_gid,
                                                          int32_t *__restrict__ g_nh,
-                                                         int32_t *__restrict__ mid_list,
-                                                         uint32_t *__restrict__ mid_count,
-                                                         int32_t *__restrict__ big_list,
-                                                         uint32_t *__restrict__ big_count,
+                                                         AcceptItems mid, AcceptItems big,
+                                                         int32_t *__restrict__ enc,
                                                          uint64_t *clock) {
 #pragma clang fp contract(off)
     stamp(clock);
     __shared__ uint32_t s_hist[kBlock / 64][kWaveHist];
-    __shared__ float4 s_hp[kBlock / 64][kWaveNuc];
-    __shared__ int32_t s_hi[kBlock / 64][kWaveNuc];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const uint32_t ngc = __builtin_amdgcn_readfirstlane(*ngc_p);
@@ -365,71 +364,58 @@ __global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restr
         const int64_t m = g_size[gi];
         const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, (uint32_t)mem[start]))];
         const uint32_t cs = gcoff[gi], ce = gcoff[gi + 1];
-        if (route_all || m + 1 > kWaveHist || ce - cs > (uint32_t)kWaveNuc) {
+        if (route_all || m + 1 > kWaveHist || ce - cs > 1u) {
+            const AcceptItems &to = m + 1 <= mid_most ? mid : big;
+            uint32_t at = 0;
             if (lane == 0) {
-                if (m + 1 <= kHistMid) mid_list[atomicAdd(mid_count, 1u)] = gi;
-                else big_list[atomicAdd(big_count, 1u)] = gi;
+                to.list[atomicAdd(to.firsts, 1u)] = (int32_t)cs;
+                enc[cs] = -1;  // not known yet
+                if (ce - cs > 1u) at = atomicAdd(to.rests, ce - cs - 1u);
             }
+            at = lane_get(at, 0);
+            for (uint32_t k = lane; k < ce - cs - 1u; k += 64)
+                to.list[to.cap - 1u - (at + k)] = (int32_t)(cs + 1u + k);
             continue;
         }
-        int nh = 0;
-        for (uint32_t r = cs; r < ce; r++) {
-            const int c = cand_sorted[r];
-            const float4 pc = spos[c];
-            // eligibility: not inside alpha R of any accepted nucleus (nh <= 64)
-            bool inel = false;
-            if (lane < nh) {
-                const double e = d2_exact(pc, s_hp[wave][lane], g.L, g.half);
-                inel = g.K2 * e3(e) < g.A6 * ii(s_hi[wave][lane]);
-            }
-            if (__ballot(inel)) continue;
-            // bucket histogram over all m particles of the group
-            for (int64_t k = lane; k <= m; k += 64) hist[k] = 0u;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            for (int64_t t = lane; t < m; t += 64) {
-                const double e = d2_exact(pc, spos[mem[start + t]], g.L, g.half);
-                atomicAdd(&hist[bucket_of(g.K2 * e3(e), m)], 1u);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            // first k in [1, m-1] with C(k) <= k, C(k) = sum of buckets 0..k;
-            // lane L covers buckets 16L .. 16L + 15 (m < 1024)
-            uint32_t v[16];
-            uint32_t sum = 0;
-    #pragma unroll
-            for (int u = 0; u < 16; u++) {
-                const int64_t k = (int64_t)lane * 16 + u;
-                v[u] = k < m ? hist[k] : 0u;
-                sum += v[u];
-            }
-            uint32_t incl = sum;
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t y = __shfl_up(incl, d, 64);
-                if (lane >= d) incl += y;
-            }
-            uint32_t C = incl - sum;
-            int hit = -1;
-    #pragma unroll
-            for (int u = 0; u < 16; u++) {
-                const int64_t k = (int64_t)lane * 16 + u;
-                C += v[u];
-                if (hit < 0 && k >= 1 && k < m && (int64_t)C <= k) hit = (int)k;
-            }
-            const uint64_t hm = __ballot(hit >= 0);
-            const int64_t found = hm ? (int64_t)lane_get(hit, __ffsll((unsigned long long)hm) - 1) : m;
-            if (lane == 0) {
-                h_nuc[cs + nh] = c;
-                h_ienc[cs + nh] = (int32_t)found;
-                h_gid[cs + nh] = gi;
-                s_hp[wave][nh] = pc;
-                s_hi[wave][nh] = (int32_t)found;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            nh++;
+        const int c = cand_sorted[cs];
+        const float4 pc = spos[c];
+        // bucket histogram over all m particles of the group
+        for (int64_t k = lane; k <= m; k += 64) hist[k] = 0u;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        for (int64_t t = lane; t < m; t += 64) {
+            const double e = d2_exact(pc, spos[mem[start + t]], g.L, g.half);
+            atomicAdd(&hist[bucket_of(g.K2 * e3(e), m)], 1u);
         }
-        if (lane == 0) g_nh[gi] = nh;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        // first k in [1, m-1] with C(k) <= k, C(k) = sum of buckets 0..k;
+        // lane L covers buckets 16L .. 16L + 15 (m < 1024)
+        uint32_t v[16];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int u = 0; u < 16; u++) {
+            const int64_t k = (int64_t)lane * 16 + u;
+            v[u] = k < m ? hist[k] : 0u;
+            sum += v[u];
+        }
+        uint32_t C = wave_incl_scan(sum) - sum;
+        int hit = -1;
+#pragma unroll
+        for (int u = 0; u < 16; u++) {
+            const int64_t k = (int64_t)lane * 16 + u;
+            C += v[u];
+            if (hit < 0 && k >= 1 && k < m && (int64_t)C <= k) hit = (int)k;
+        }
+        const uint64_t hm = __ballot(hit >= 0);
+        const int64_t found = hm ? (int64_t)lane_get(hit, __ffsll((unsigned long long)hm) - 1) : m;
+        if (lane == 0) {
+            h_nuc[cs] = c;
+            h_ienc[cs] = (int32_t)found;
+            h_gid[cs] = gi;
+            g_nh[gi] = 1;
+        }
+        __builtin_amdgcn_wave_barrier();  // the histogram is free for the next group
     }
 }
 
@@ -474,36 +460,21 @@ __device__ __forceinline__ void for_members(int64_t m, int64_t start, const int3
     }
 }
 
-// Zero hist[0..len]: LDS below HL, the group's global region gh beyond.
-template <int NT, int HL>
-__device__ __forceinline__ void hist_clear(uint32_t *s_hist, uint32_t *gh, int64_t len) {
-    for (int64_t k = threadIdx.x; k <= len && k < HL; k += NT) s_hist[k] = 0u;
-    if (len + 1 > HL) {
-        for (int64_t k = HL + threadIdx.x; k <= len; k += NT) stu(gh + k, 0u);
-        __threadfence();
-    }
-}
-
-__device__ __forceinline__ void hist_add(uint32_t *s_hist, uint32_t *gh, int64_t k, int hl) {
-    if (k < hl) atomicAdd(&s_hist[k], 1u);
-    else atomicAdd(gh + k, 1u);
-}
-
-// First t in [0, len) with C(t) <= t and 1 <= base + t <= m - 1, where
-// C(t) = hist[0] + ... + hist[t]; -1 when there is none.
-template <int NT, int HL>
-__device__ __forceinline__ int64_t first_crossing(const uint32_t *s_hist, const uint32_t *gh, int64_t len,
-                                                  int64_t base, int64_t m, uint32_t *s_red, int *s_min) {
+// First t in [w0, w1) with C(t) <= t and 1 <= base + t <= m - 1, where
+// C(t) = run + hist[0] + ... + hist[t - w0]; -1 when there is none (run then
+// includes the whole window).
+template <int NT>
+__device__ __forceinline__ int64_t first_crossing(const uint32_t *s_hist, int64_t w0, int64_t w1, int64_t base,
+                                                  int64_t m, uint32_t &run, uint32_t *s_red, int *s_min) {
     constexpr int SI = NT >= 1024 ? kScanIpt / 2 : kScanIpt;
-    uint32_t run = 0;
-    for (int64_t b0 = 0; b0 < len; b0 += (int64_t)NT * SI) {
+    for (int64_t b0 = w0; b0 < w1; b0 += (int64_t)NT * SI) {
         const int64_t k0 = b0 + (int64_t)threadIdx.x * SI;
         uint32_t v[SI];
         uint32_t sum = 0;
 #pragma unroll
         for (int u = 0; u < SI; u++) {
             const int64_t k = k0 + u;
-            v[u] = k < len ? (k < HL ? s_hist[k] : ldu(gh + k)) : 0u;
+            v[u] = k < w1 ? s_hist[k - w0] : 0u;
             sum += v[u];
         }
         uint32_t tot;
@@ -513,7 +484,7 @@ __device__ __forceinline__ int64_t first_crossing(const uint32_t *s_hist, const 
         for (int u = 0; u < SI; u++) {
             const int64_t k = k0 + u;
             C += v[u];
-            if (hit == 0x7fffffff && k < len && base + k >= 1 && base + k < m && (int64_t)C <= k)
+            if (hit == 0x7fffffff && k < w1 && base + k >= 1 && base + k < m && (int64_t)C <= k)
                 hit = (int)(k - b0);
         }
         const int best = block_min<NT>(hit, s_min);
@@ -523,15 +494,61 @@ __device__ __forceinline__ int64_t first_crossing(const uint32_t *s_hist, const 
     return -1;
 }
 
-// One workgroup per L0 group in `glist` (count on the device; the grid is an
-// upper bound).  No persistent loop here: a group index broadcast through LDS
-// by one thread, with a barrier inside a loop whose exit depends on it, is a
-// form the compiler may restructure so that the other threads pass the barrier
-// again before that thread has written the next index.  Walk the candidates
-// in descending density; a
-// candidate inside alpha R of an accepted nucleus is ineligible; an eligible
-// one is accepted and its enclosed count i found
-//   BINS = false: from the bucket histogram of all particles of the group;
+// First coarse bucket j in [j0, j1) of 2^sh buckets in which a crossing can lie:
+// C before it is at most its last bucket (C only grows).  run: C before j0, on
+// return C before the bucket found.
+template <int NT>
+__device__ __forceinline__ int64_t first_possible(const uint32_t *s_hist, int64_t j0, int64_t j1, int sh,
+                                                  uint32_t &run, uint32_t *s_red, int *s_min, uint32_t *s_c) {
+    constexpr int SI = NT >= 1024 ? kScanIpt / 2 : kScanIpt;
+    for (int64_t b0 = j0; b0 < j1; b0 += (int64_t)NT * SI) {
+        const int64_t k0 = b0 + (int64_t)threadIdx.x * SI;
+        uint32_t v[SI];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int u = 0; u < SI; u++) {
+            v[u] = k0 + u < j1 ? s_hist[k0 + u] : 0u;
+            sum += v[u];
+        }
+        uint32_t tot;
+        uint32_t C = run + block_excl<NT>(sum, s_red, &tot), Chit = 0;
+        int hit = 0x7fffffff;
+#pragma unroll
+        for (int u = 0; u < SI; u++) {
+            const int64_t k = k0 + u;
+            if (hit == 0x7fffffff && k < j1 && (int64_t)C <= ((k + 1) << sh) - 1) {
+                hit = (int)(k - b0);
+                Chit = C;
+            }
+            C += v[u];
+        }
+        const int best = block_min<NT>(hit, s_min);
+        if (best != 0x7fffffff) {
+            if (hit == best) *s_c = Chit;
+            __syncthreads();
+            run = *s_c;
+            __syncthreads();
+            return b0 + best;
+        }
+        run += tot;
+    }
+    return -1;
+}
+
+// The enclosed count i of every listed candidate, one workgroup at a time each.
+// A candidate is accepted unless it lies inside alpha R of a nucleus accepted
+// before it; i depends on the group and the candidate only.  Nearly every
+// candidate is accepted (28 072 of 28 141 on the 256^3 box), so i is found for
+// all of them at once instead of one after the other in the group's walk
+// (k_accept_walk), whose chain was the time of the stage (the three kernels took
+// 6.8 ms on the 512^3 box, 300 us on the 256^3 one and 152 us on 1.3e6 particles
+// at their labels; 3.8 ms, 195 us and 72 us now).  The groups'
+// densest candidates come first; a candidate that lies inside alpha R of that
+// one, if its i is known by then, is left out (its i is never asked for).
+//   BINS = false: i from the bucket histogram of all particles of the group, in
+//                 LDS; with more buckets than fit (HL), a first histogram of
+//                 coarse buckets tells where the crossing can lie, and a second
+//                 one holds the buckets from there on;
 //   BINS = true:  by the radial bins of Sec. 2.3.4.  Counts of the members per
 //                 radial bin (width g.rbin, in LDS) give C_j, the members
 //                 inside bin j's inner edge.  A bin whose C_j members, placed
@@ -541,69 +558,47 @@ __device__ __forceinline__ int64_t first_crossing(const uint32_t *s_hist, const 
 //                 bin that is not passed over is searched with the bucket
 //                 histogram of its own members (positions C_j .. C_j + c_j - 1
 //                 of the sorted order: the crossing is the first t with
-//                 #{bin members with bucket <= C_j + t} <= t), and the search
-//                 moves outwards while a bin holds no crossing.
+//                 #{bin members with bucket <= C_j + t} <= t), HL of them at a
+//                 time, and the search moves outwards while a bin holds no
+//                 crossing.
 template <int NT, int HL, bool BINS>
-__global__ __launch_bounds__(NT) void k_accept(const uint32_t *__restrict__ ngc_p,
-                                               Boxes bx,
-                                               const int32_t *__restrict__ glist,
-                                               const int32_t *__restrict__ g_start,
-                                               const int32_t *__restrict__ g_size,
-                                               const uint32_t *__restrict__ gcoff,
-                                               const int32_t *__restrict__ cand_sorted,
-                                               const int32_t *__restrict__ mem,
-                                               const float4 *__restrict__ spos,
-                                               uint32_t *__restrict__ hist_all,
-                                               int32_t *__restrict__ h_nuc,
-                                               int32_t *__restrict__ h_ienc,
-                                               int32_t *__restrict__ h_gid,
-                                               int32_t *__restrict__ g_nh) {
+__global__ __launch_bounds__(NT) void k_accept_eval(AcceptItems items, Boxes bx,
+                                                    const int32_t *__restrict__ gid_of,
+                                                    const int32_t *__restrict__ g_start,
+                                                    const int32_t *__restrict__ g_size,
+                                                    const uint32_t *__restrict__ gcoff,
+                                                    const int32_t *__restrict__ cand_sorted,
+                                                    const int32_t *__restrict__ mem,
+                                                    const float4 *__restrict__ spos,
+                                                    int32_t *enc,
+                                                    int32_t *__restrict__ h_nuc,
+                                                    int32_t *__restrict__ h_ienc,
+                                                    int32_t *__restrict__ h_gid,
+                                                    int32_t *__restrict__ g_nh) {
 #pragma clang fp contract(off)
-    __shared__ uint32_t s_hist[HL + 1];
+    __shared__ uint32_t s_hist[HL];
     __shared__ uint32_t s_rb[BINS ? kRadBins : 1];
-    __shared__ int s_nh;
-    __shared__ uint32_t s_red[NT / 64];
+    __shared__ uint32_t s_red[NT / 64], s_c;
     __shared__ int s_min[NT / 64];
-    if (blockIdx.x >= *ngc_p) return;
     const int tid = threadIdx.x;
-    const int gi = glist[blockIdx.x];
-    const int64_t start = g_start[gi];
-    const int64_t m = g_size[gi];
-    const uint32_t cs = gcoff[gi], ce = gcoff[gi + 1];
-    const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, (uint32_t)mem[start]))];
-    // buckets below HL live in LDS; a group with more buckets keeps the
-    // rest in its own global region (m + 1 words, disjoint per group).  The
-    // small buckets are where the particles of a dense core pile up, so the
-    // global atomics are only the sparse outer ones.
-    uint32_t *ghist = hist_all + start + gi;
-    if (tid == 0) s_nh = 0;
-    __syncthreads();
-    for (uint32_t r = cs; r < ce; r++) {
-        const int nh = s_nh;
-        // the next candidate from r on that is eligible (not inside alpha R of
-        // any nucleus accepted so far), NT candidates tested at once, one per
-        // thread: the ones passed over are ineligible in the serial order too,
-        // since the nuclei change only when a candidate is accepted
-        int next = 0x7fffffff;
-        for (uint32_t r0 = r; r0 < ce; r0 += NT) {
-            const uint32_t q = r0 + (uint32_t)tid;
-            int hit = 0x7fffffff;
-            if (q < ce) {
-                const float4 pq = spos[cand_sorted[q]];
-                bool el = true;
-                for (int h = 0; h < nh && el; h++) {
-                    const double e = d2_exact(pq, spos[ldi(h_nuc + cs + h)], g.L, g.half);
-                    el = !(g.K2 * e3(e) < g.A6 * ii(ldi(h_ienc + cs + h)));
-                }
-                if (el) hit = (int)(q - r);
-            }
-            next = block_min<NT>(hit, s_min);
-            if (next != 0x7fffffff) break;
-        }
-        if (next == 0x7fffffff) break;
-        r += (uint32_t)next;
-        const int c = cand_sorted[r];
+    const uint32_t firsts = *items.firsts, count = firsts + *items.rests;
+    for (uint32_t q = blockIdx.x; q < count; q += gridDim.x) {
+        const uint32_t cr = (uint32_t)items.list[q < firsts ? q : items.cap - 1u - (q - firsts)];
+        const int c = cand_sorted[cr];
+        const int gi = gid_of[c];
+        const int64_t start = g_start[gi];
+        const int64_t m = g_size[gi];
+        const uint32_t cs = gcoff[gi], ce = gcoff[gi + 1];
+        const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, (uint32_t)c))];
         const float4 pc = spos[c];
+        if (cr != cs) {
+            // one answer for the workgroup: another one may write it meanwhile
+            if (tid == 0) s_c = (uint32_t)ldi(enc + cs);
+            __syncthreads();
+            const int32_t i0 = (int32_t)s_c;
+            __syncthreads();
+            if (i0 >= 0 && g.K2 * e3(d2_exact(pc, spos[cand_sorted[cs]], g.L, g.half)) < g.A6 * ii(i0)) continue;
+        }
         int64_t found = m;
         if constexpr (BINS) {
             // members per radial bin, then their inclusive prefix in place
@@ -628,7 +623,7 @@ __global__ __launch_bounds__(NT) void k_accept(const uint32_t *__restrict__ ngc_
                 s_rb[tid * BI + u] = P;
             }
             __syncthreads();
-            for (int j0 = 0;;) {
+            for (int j0 = 0; found == m;) {
                 // the innermost occupied bin from j0 on that is not passed over
                 int jb = 0x7fffffff;
                 for (int j = j0 + tid; j < kRadBins; j += NT) {
@@ -643,45 +638,118 @@ __global__ __launch_bounds__(NT) void k_accept(const uint32_t *__restrict__ ngc_
                 const int64_t C = js ? s_rb[js - 1] : 0u;
                 const int64_t cnt = (int64_t)s_rb[js] - C;
                 const double lo = js ? rbin_edge2(js - 1, g.rbin) : -1.0, hi = rbin_edge2(js, g.rbin);
-                hist_clear<NT, HL>(s_hist, ghist, cnt);
-                __syncthreads();
-                for_members<NT>(m, start, mem, spos, pc, g, [&](double e) {
-                    if (e >= lo && e < hi) {
-                        int64_t k = bucket_of(g.K2 * e3(e), m) - C;
-                        k = k < 0 ? 0 : (k > cnt ? cnt : k);
-                        hist_add(s_hist, ghist, k, HL);
-                    }
-                });
-                if (cnt + 1 > HL) __threadfence();
-                __syncthreads();
-                const int64_t t = first_crossing<NT, HL>(s_hist, ghist, cnt, C, m, s_red, s_min);
-                if (t >= 0) {
-                    found = C + t;
-                    break;
+                uint32_t run = 0;
+                for (int64_t w0 = 0; w0 < cnt && found == m; w0 += HL) {
+                    const int64_t w1 = w0 + HL < cnt ? w0 + HL : cnt;
+                    for (int64_t k = tid; k < w1 - w0; k += NT) s_hist[k] = 0u;
+                    __syncthreads();
+                    for_members<NT>(m, start, mem, spos, pc, g, [&](double e) {
+                        if (e >= lo && e < hi) {
+                            int64_t k = bucket_of(g.K2 * e3(e), m) - C;
+                            k = k < 0 ? 0 : k;
+                            if (k >= w0 && k < w1) atomicAdd(&s_hist[k - w0], 1u);
+                        }
+                    });
+                    __syncthreads();
+                    const int64_t t = first_crossing<NT>(s_hist, w0, w1, C, m, run, s_red, s_min);
+                    if (t >= 0) found = C + t;
                 }
                 j0 = js + 1;
             }
         } else {
-            // histogram of buckets over all particles of the group
-            hist_clear<NT, HL>(s_hist, ghist, m);
-            __syncthreads();
-            for_members<NT>(m, start, mem, spos, pc, g,
-                            [&](double e) { hist_add(s_hist, ghist, bucket_of(g.K2 * e3(e), m), HL); });
-            if (m + 1 > HL) __threadfence();
-            __syncthreads();
-            // first k in [1, m-1] with C(k) <= k, C(k) = sum of buckets 0..k
-            const int64_t t = first_crossing<NT, HL>(s_hist, ghist, m, 0, m, s_red, s_min);
-            if (t >= 0) found = t;
+            int64_t w0 = 0;
+            uint32_t run = 0;
+            if (m > HL) {
+                int sh = 1;
+                while (m > (int64_t)HL << sh) sh++;
+                const int64_t nj = ((m - 1) >> sh) + 1;
+                for (int64_t k = tid; k < nj; k += NT) s_hist[k] = 0u;
+                __syncthreads();
+                for_members<NT>(m, start, mem, spos, pc, g, [&](double e) {
+                    const int64_t k = bucket_of(g.K2 * e3(e), m);
+                    if (k < m) atomicAdd(&s_hist[k >> sh], 1u);
+                });
+                __syncthreads();
+                const int64_t j = first_possible<NT>(s_hist, 0, nj, sh, run, s_red, s_min, &s_c);
+                w0 = j < 0 ? m : j << sh;
+            }
+            for (; w0 < m && found == m; w0 += HL) {
+                // the buckets [w0, w1), and C before them
+                const int64_t w1 = w0 + HL < m ? w0 + HL : m;
+                for (int64_t k = tid; k < w1 - w0; k += NT) s_hist[k] = 0u;
+                __syncthreads();
+                const double Tlo = w0 > 0 ? ii(w0 - 1) : -1.0, Thi = ii(w1 - 1);
+                for_members<NT>(m, start, mem, spos, pc, g, [&](double e) {
+                    const double T = g.K2 * e3(e);
+                    if (T > Tlo && T <= Thi) atomicAdd(&s_hist[bucket_of(T, m) - w0], 1u);
+                });
+                __syncthreads();
+                const int64_t t = first_crossing<NT>(s_hist, w0, w1, 0, m, run, s_red, s_min);
+                if (t >= 0) found = t;
+            }
         }
         if (tid == 0) {
-            h_nuc[cs + nh] = c;
-            h_ienc[cs + nh] = (int32_t)found;
-            h_gid[cs + nh] = gi;
-            s_nh = nh + 1;
+            sti(enc + cr, (int32_t)found);
+            if (ce - cs == 1u) {  // nothing to walk
+                h_nuc[cs] = c;
+                h_ienc[cs] = (int32_t)found;
+                h_gid[cs] = gi;
+                g_nh[gi] = 1;
+            }
         }
-        __syncthreads();
+        __syncthreads();  // the histogram and s_c are free for the next item
     }
-    if (tid == 0) g_nh[gi] = s_nh;
+}
+
+// The walk over a group's candidates in descending density, a wavefront per
+// group: 64 candidates at a time, one per lane, tested against the nuclei of the
+// earlier ones; then the first lane left is accepted and the lanes after it are
+// tested against it, until none is left.
+__global__ __launch_bounds__(kBlock) void k_accept_walk(AcceptItems mid, AcceptItems big, Boxes bx,
+                                                        const int32_t *__restrict__ gid_of,
+                                                        const uint32_t *__restrict__ gcoff,
+                                                        const int32_t *__restrict__ cand_sorted,
+                                                        const float4 *__restrict__ spos,
+                                                        const int32_t *__restrict__ enc, int32_t *h_nuc,
+                                                        int32_t *h_ienc, int32_t *__restrict__ h_gid,
+                                                        int32_t *__restrict__ g_nh) {
+#pragma clang fp contract(off)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t nmid = *mid.firsts, count = nmid + *big.firsts;
+    const uint32_t nw = gridDim.x * (kBlock / 64);
+    for (uint32_t q = blockIdx.x * (kBlock / 64) + (uint32_t)wave; q < count; q += nw) {
+        const uint32_t cs = (uint32_t)(q < nmid ? mid.list[q] : big.list[q - nmid]);
+        const int c0 = cand_sorted[cs], gi = gid_of[c0];
+        const uint32_t ce = gcoff[gi + 1];
+        if (ce - cs == 1u) continue;  // settled with its candidate
+        const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, (uint32_t)c0))];
+        uint32_t nh = 0;
+        for (uint32_t b = cs; b < ce; b += 64) {
+            const bool in = b + (uint32_t)lane < ce;
+            const int c = in ? cand_sorted[b + (uint32_t)lane] : c0;
+            const int32_t ic = in ? enc[b + (uint32_t)lane] : 0;
+            const float4 pc = spos[c];
+            bool el = in;
+            for (uint32_t h = 0; h < nh; h++) {
+                const double e = d2_exact(pc, spos[ldi(h_nuc + cs + h)], g.L, g.half);
+                el = el && !(g.K2 * e3(e) < g.A6 * ii(ldi(h_ienc + cs + h)));
+            }
+            for (uint64_t left; (left = __ballot(el)) != 0ull; nh++) {
+                const int L = (int)__builtin_ctzll(left);
+                const int32_t in1 = lane_get(ic, L);
+                const float4 pn = make_float4(lane_get(pc.x, L), lane_get(pc.y, L), lane_get(pc.z, L), 0.0f);
+                if (lane == L) {
+                    sti(h_nuc + cs + nh, c);
+                    sti(h_ienc + cs + nh, ic);
+                    h_gid[cs + nh] = gi;
+                    el = false;
+                }
+                el = el && !(g.K2 * e3(d2_exact(pc, pn, g.L, g.half)) < g.A6 * ii(in1));
+            }
+            if (b + 64 < ce) __threadfence();  // the nuclei are read by the next 64
+        }
+        if (lane == 0) g_nh[gi] = (int32_t)nh;
+    }
 }
 
 // --------------------------------------------------------------- assignment
@@ -1078,51 +1146,41 @@ static int bits_for(int64_t x) {
 }
 
 void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx, Work &w, hipStream_t s) {
-    // groups with candidates (at most min(G, NC)), one wavefront each; the
-    // others are listed (in a scratch array, counts in counters[9]
-    // and [11]) for one workgroup each: medium groups (at most M / kWaveHist
-    // of kWaveHist particles or more, and NC / (kWaveNuc + 1) with more than
-    // kWaveNuc candidates) and large ones (at most M / kHistMid), whose list
-    // starts halfway through the array.  The first kernel is a persistent
-    // grid (as many wavefronts as fit on the chip at once) striding over the
-    // list; the others run one workgroup per listed group.  The counts are
-    // zero since the call began.
+    // groups with candidates (at most min(G, NC)): those of one candidate and few
+    // particles one wavefront each; the candidates of the others are listed (in
+    // scratch arrays, which hold an entry per particle), evaluated by one workgroup
+    // each and walked by one wavefront per group.  Persistent grids that stride over the lists: as many wavefronts
+    // (six per SIMD) or workgroups (their LDS) as fit on the chip, and no more
+    // than there are entries.  A group of kHistMid particles needs as many
+    // members.  The counts are zero since the call began.
     const int64_t bound = G < NC ? G : NC;
     if (bound <= 0) return;
-    int32_t *mid_list = reinterpret_cast<int32_t *>(w.tmp_a);
-    int32_t *big_list = reinterpret_cast<int32_t *>(w.tmp_a) + n / 2;
-    uint32_t *mid_count = reinterpret_cast<uint32_t *>(w.counters + 9);
-    uint32_t *big_count = reinterpret_cast<uint32_t *>(w.counters + 11);
+    auto counter = [&](int k) { return reinterpret_cast<uint32_t *>(w.counters + k); };
+    const AcceptItems mid{reinterpret_cast<int32_t *>(w.tmp_a), counter(kCntMidFirst), counter(kCntMidRest), (uint32_t)n};
+    const AcceptItems big{reinterpret_cast<int32_t *>(w.tmp_b), counter(kCntBigFirst), counter(kCntBigRest), (uint32_t)n};
+    int32_t *enc = reinterpret_cast<int32_t *>(w.tmp_c);
     const int64_t ncu = w.ncu > 0 ? w.ncu : 1;
     auto cap = [](int64_t a, int64_t b) { return (unsigned)(a < b ? a : b); };
     const bool bins = w.radius_bins;
-    // six wavefronts per SIMD (its register use): 6 workgroups of 4 per CU
+    // with few candidates every one gets 1024 threads, and a launch less (20 000
+    // particles, 53 candidates: the second launch cost 5 us)
+    const bool few = NC <= 4 * ncu;
     hipLaunchKernelGGL(k_accept_small, dim3(cap((bound + kBlock / 64 - 1) / (kBlock / 64), 6 * ncu)), dim3(kBlock),
-                       0, s, reinterpret_cast<const uint32_t *>(w.counters + kCntListed), bins, bx, w.glist, w.g_start, w.g_size, w.gcoff, w.cand_sorted,
-                       w.mem, w.spos, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh, mid_list, mid_count, big_list, big_count,
-                       w.clock + kClockAccept);
-    // with radial bins every group is listed: at most bound medium groups
-    const int64_t nmid = bins ? bound : M / kWaveHist + NC / (kWaveNuc + 1) + 1;
-    const dim3 gmid(cap(nmid, bound));
-    // the large groups are few and each is a serial walk: 1024 threads and a
-    // 144 KB LDS histogram each (one workgroup per CU)
-    const int64_t nbig = M / kHistMid + 1;
-    const dim3 gbig(cap(nbig, bound));
-    if (bins) {
-        hipLaunchKernelGGL((k_accept<kBlock, kHistMid, true>), gmid, dim3(kBlock), 0, s, mid_count, bx,
-                           mid_list, w.g_start, w.g_size, w.gcoff, w.cand_sorted, w.mem, w.spos, w.hist, w.h_nuc,
-                           w.h_ienc, w.h_gid, w.g_nh);
-        hipLaunchKernelGGL((k_accept<1024, kHistBig, true>), gbig, dim3(1024), 0, s, big_count, bx,
-                           big_list, w.g_start, w.g_size, w.gcoff, w.cand_sorted, w.mem, w.spos, w.hist, w.h_nuc,
-                           w.h_ienc, w.h_gid, w.g_nh);
-    } else {
-        hipLaunchKernelGGL((k_accept<kBlock, kHistMid, false>), gmid, dim3(kBlock), 0, s, mid_count, bx,
-                           mid_list, w.g_start, w.g_size, w.gcoff, w.cand_sorted, w.mem, w.spos, w.hist, w.h_nuc,
-                           w.h_ienc, w.h_gid, w.g_nh);
-        hipLaunchKernelGGL((k_accept<1024, kHistBig, false>), gbig, dim3(1024), 0, s, big_count, bx,
-                           big_list, w.g_start, w.g_size, w.gcoff, w.cand_sorted, w.mem, w.spos, w.hist, w.h_nuc,
-                           w.h_ienc, w.h_gid, w.g_nh);
-    }
+                       0, s, counter(kCntListed), bins, few ? 0 : kHistMid, bx, w.glist, w.g_start, w.g_size, w.gcoff, w.cand_sorted,
+                       w.mem, w.spos, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh, mid, big, enc, w.clock + kClockAccept);
+    if (!few)
+        hipLaunchKernelGGL((bins ? k_accept_eval<kBlock, kHistMid, true> : k_accept_eval<kBlock, kHistMid, false>),
+                           dim3(cap(NC, 4 * ncu)), dim3(kBlock), 0, s, mid, bx, w.gid_of, w.g_start, w.g_size, w.gcoff,
+                           w.cand_sorted, w.mem, w.spos, enc, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh);
+    if (few || M >= kHistMid)
+        hipLaunchKernelGGL((bins ? k_accept_eval<1024, kHistBig, true> : k_accept_eval<1024, kHistBig, false>),
+                           dim3(cap(NC, ncu)), dim3(1024), 0, s, big, bx, w.gid_of, w.g_start, w.g_size, w.gcoff,
+                           w.cand_sorted, w.mem, w.spos, enc, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh);
+    // groups of two candidates at least
+    if (NC > 1)
+        hipLaunchKernelGGL(k_accept_walk, dim3(cap((bound + kBlock / 64 - 1) / (kBlock / 64), 6 * ncu)), dim3(kBlock), 0,
+                           s, mid, big, bx, w.gid_of, w.gcoff, w.cand_sorted, w.spos, enc, w.h_nuc, w.h_ienc, w.h_gid,
+                           w.g_nh);
 }
 
 void launch_assign(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {

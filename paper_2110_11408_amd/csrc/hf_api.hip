@@ -256,7 +256,6 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->h_count = c.take<uint32_t>(n1);
     w->tflag = c.take<uint32_t>(n / 32 + 2);
     w->tpos = c.take<uint32_t>(n / 32 + 3);
-    w->hist = c.take<uint32_t>(2 * n1);
     int64_t scan_len = ncell > n ? ncell : n;
     if (rhl > scan_len) scan_len = rhl;
     w->scan_tmp = c.take<uint32_t>(hf::scan_tmp_words(scan_len + 1));

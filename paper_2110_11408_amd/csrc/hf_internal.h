@@ -397,7 +397,6 @@ struct Work {
     uint32_t *h_count;
     uint32_t *tflag, *tpos;                            // table rows: a bit per original index, and the
                                                        // prefix sum of the words' set bits
-    uint32_t *hist;                                    // R search histograms
     uint32_t *scan_tmp;
     double *gcom;                    // halo statistics only: centres per group (6 doubles)
     int32_t *ordk;                   // halo statistics only: group ordinal per key
@@ -498,6 +497,10 @@ enum {
     kCntChunks = 0,     // dense chunks
     kCntDcells = 1,     // dense cells
     kCntSparse = 3,     // particles of sparse cells
+    kCntMidRest = 4,    // candidates of medium and of large groups to evaluate:
+    kCntBigRest = 5,    // the groups' densest, and the others
+    kCntMidFirst = 9,
+    kCntBigFirst = 11,
     kCntHard = 8,       // hard cases of the candidate stage
     kCntListed = 10,    // groups with candidates in glist
     kCntCand = 13,      // candidates

@@ -209,3 +209,40 @@ def test_output_records_of_several_boxes(ctx):
         for key in ("density", "l0_id", "halo_id"):
             assert torch.equal(r[key][offs[k]:offs[k + 1]], one[key])
         assert torch.equal(r["halos"][k], one["halos"])
+
+
+# Acceptance: groups of one candidate below 1024 members are settled by a
+# wavefront; else every candidate's enclosed count is found by itself, below 2048
+# members and beyond with a histogram in LDS, above 36 864 from a coarse one first,
+# and the candidates are then walked.  A ball of density ~ r^-2, with or without a
+# second one in its group, at a mean density of 88 (the threshold radius lies
+# inside, with more than 36 864 members in the largest case) or 400 (it does not,
+# and nearly all particles of the ball are in the group).
+@pytest.mark.parametrize("radius_search", ["histogram", "bins"])
+@pytest.mark.parametrize("m,mean,second", [
+    (1016, 400, 0.0), (1022, 400, 0.0), (1500, 88, 0.3), (2040, 400, 0.0), (2047, 400, 0.0), (3400, 88, 0.3),
+    (36700, 400, 0.0), (37100, 400, 0.0), (80000, 88, 0.0), (80000, 88, 0.2), (80000, 400, 0.0)])
+def test_acceptance_sizes(m, mean, second, radius_search):
+    from paper_2110_11408_amd.api import Context
+    rng = np.random.default_rng(m + mean)
+    R = (m / mean / 4.19) ** (1.0 / 3.0)
+    side = max(6.5 * R, 12.0)
+
+    def ball(k, at, r):
+        u = rng.normal(size=(k, 3))
+        return at + u / np.linalg.norm(u, axis=1)[:, None] * (r * rng.random((k, 1)))
+    k2 = int(second * m)
+    at = np.full(3, 0.3 * side)
+    pos = [rng.random((4000, 3)) * side, ball(m - k2, at, R)]
+    if k2:
+        pos.append(ball(k2, at + np.array([0.9 * R, 0.0, 0.0]), 0.5 * R))
+    pos = np.concatenate(pos).astype(np.float32)
+    pos = pos[rng.permutation(len(pos))]
+    c = Context(0)
+    c.set_radius_search(radius_search)
+    print(f"[gpu] acceptance m={m} mean={mean} second={second} {radius_search}", file=sys.stderr, flush=True)
+    g = gpu_find(c, pos, box=side, mean_density=1.0)
+    ref = oracle.find(pos, box=side, mean_density=1.0, density_override=g["density"].astype(np.float64))
+    assert_same_labels(g, ref)
+    assert np.bincount(g["l0"])[1:].max() > 0.5 * m
+    assert not (m == 80000 and mean == 88 and second == 0.0) or ref["found"]["ienc"].max() > 36864
