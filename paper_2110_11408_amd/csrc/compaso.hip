@@ -383,9 +383,17 @@ __global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restr
         for (int64_t k = lane; k <= m; k += 64) hist[k] = 0u;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
-        for (int64_t t = lane; t < m; t += 64) {
-            const double e = d2_exact(pc, spos[mem[start + t]], g.L, g.half);
-            atomicAdd(&hist[bucket_of(g.K2 * e3(e), m)], 1u);
+        // four members per lane and round of loads
+        for (int64_t t0 = lane; t0 < m; t0 += 4 * 64) {
+            int32_t id[4];
+            float4 pm[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) id[u] = t0 + 64 * u < m ? mem[start + t0 + 64 * u] : c;
+#pragma unroll
+            for (int u = 0; u < 4; u++) pm[u] = spos[id[u]];
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+                if (t0 + 64 * u < m) atomicAdd(&hist[bucket_of(g.K2 * e3(d2_exact(pc, pm[u], g.L, g.half)), m)], 1u);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         __builtin_amdgcn_wave_barrier();
