@@ -401,7 +401,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
 
 // One wavefront per workgroup: chunk costs differ widely, and a finished
 // wavefront frees its slot at once.
-__global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, int64_t n, Boxes bx, bool narrow,
+__global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, unsigned tile, int64_t n, Boxes bx, bool narrow,
                                                       const int32_t *__restrict__ chunks,
                                                       const float4 *__restrict__ sloc,
                                                       const float4 *__restrict__ pq,
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, int64_
                                                       float *__restrict__ dens_out,
                                                       uint64_t *clock) {
     stamp(clock);
-    const int64_t q = (int64_t)xcd_block();
+    const int64_t q = (int64_t)xcd_tile_block(tile);
     if (q >= nchunks) return;
     const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane(chunks[q]);
     const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, h))];
@@ -664,7 +664,7 @@ void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStr
         bool narrow = (n + 32) * 16 <= (int64_t)0xffffff00;
         const char *force = getenv("HF_DENSITY_WIDE");
         if (force && force[0] == '1') narrow = false;
-        hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, n, bx, narrow,
+        hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, xcd_tile(bx), n, bx, narrow,
                            w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s, dens_out,
                            w.clock + kClockDensity);
     }

@@ -455,7 +455,7 @@ constexpr int kTaskTile = 384;
 // With nparts > 1 a chunk is a wavefront for the sparse cells and nparts - 1 for
 // the sub-cells of the dense ones: for inputs whose chunks do not fill the chip,
 // where the longest chain is the time.
-__global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts, int64_t n, Boxes bx,
+__global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, unsigned tile, int nparts, int64_t n, Boxes bx,
                                                       const int32_t *__restrict__ chunks,
                                                       const float4 *__restrict__ sloc,
                                                       const float4 *__restrict__ spos,
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(64, 8) void k_fof_dense(int64_t nchunks, int nparts
     __shared__ int32_t s_fs[kTaskTile];   // sub-cells to look at: first member to gather,
     __shared__ uint32_t s_u1[kTaskTile];  // end,
     __shared__ int8_t s_st[kTaskTile];    // stencil index
-    const unsigned wq = xcd_block();
+    const unsigned wq = xcd_tile_block(tile);
     const int64_t q = wq / (unsigned)nparts;
     if (q >= nchunks) return;
     // wavefront 0 of several takes the sparse cells, the others every
@@ -945,7 +945,7 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
         // became 44 and with 332 30 became 23, but with 9699 68 became 87 (and,
         // in 64 boxes with longer chains, 9082 went from 82 to 64).
         const int parts = w.nchunks <= 24 * (int64_t)(w.ncu > 0 ? w.ncu : 1) ? 3 : 1;
-        hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)(w.nchunks * parts)), dim3(64), 0, s, w.nchunks, parts, n, bx,
+        hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)(w.nchunks * parts)), dim3(64), 0, s, w.nchunks, xcd_tile(bx), parts, n, bx,
                            w.chunks, w.sloc, w.spos, w.cells, w.marks, w.subtab, w.subarg, w.dens_s, w.parent);
     }
     if (w.nsparse > 0)
