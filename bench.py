@@ -58,7 +58,7 @@ WORKLOADS = {
 STAGE_KEYS = ("ms_bin", "ms_density", "ms_fof", "ms_segment", "ms_candidates", "ms_accept",
               "ms_assign", "ms_output", "ms_total")
 STAGE_KERNELS = {
-    "density": ("k_density_dense", "k_density_sparse"),
+    "density": ("k_density_dense", "k_density_rows", "k_density_sparse"),
     "bin": ("k_bin_key", "k_radix_count", "k_radix_scatter", "k_bucket_sort", "k_bin_place", "k_rec_count",
             "k_rec_scatter", "k_rec_first", "k_rec_count2", "k_rec_starts", "k_rec_bucket", "k_bin_marks",
             "k_bin_lists", "k_sub_table"),

@@ -96,15 +96,21 @@ __device__ __forceinline__ float clamp0(float x) { return __int_as_float(max(__f
 // end gets B = (., ., ., -1e30) and weighs 0 (pq is padded so that the load
 // stays in bounds).  The particles of the sparse neighbour cells (fewer than
 // 8 each) share blocks instead, with the shift on their side.
-template <int R, bool kNarrow>
+//
+// kSplit (R = 1): one of the chunk's row blocks, number `part` of `rows`, with the
+// same blocks in the same order; part `rows` computes the sparse particles'
+// shares instead.
+template <int R, bool kNarrow, bool kSplit = false>
 __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t c, uint32_t end,
                                               const float *__restrict__ pq,
                                               const float4 *__restrict__ spos,
                                               const Cells &cells, const Marks &marks,
                                               uint64_t *__restrict__ dfx, float *__restrict__ dens_s,
                                               float *__restrict__ dens_out, float *__restrict__ cl,
-                                              float4 *__restrict__ s_pk) {
+                                              float4 *__restrict__ s_pk, int part = 0, int rows = R) {
     const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+    const bool blocks = !kSplit || part < rows, shares = !kSplit || part == rows;
+    const uint32_t hr = kSplit ? h + 16u * (uint32_t)part : h;  // first row
     const int loff = 4 * col + grp;  // this lane's word of a block of 16 pq records
     // this lane's word of the block of 16 records from j0, as a buffer load
     // (scalar address arithmetic only; the lane offset is a constant VGPR):
@@ -141,12 +147,12 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
     };
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        const uint32_t ir = h + 16u * (uint32_t)r + (uint32_t)col;
+        const uint32_t ir = hr + 16u * (uint32_t)r + (uint32_t)col;
         const float v = pq[4 * (size_t)min(ir, end - 1u) + grp];
         A[r] = grp == 3 ? 1.0f : (ir < end ? v + v : 0.0f);
 #pragma unroll
         for (int u = 0; u < 4; u++) {
-            const uint32_t iu = h + 16u * (uint32_t)r + 4u * (uint32_t)grp + (uint32_t)u;
+            const uint32_t iu = hr + 16u * (uint32_t)r + 4u * (uint32_t)grp + (uint32_t)u;
             const float q = pq[4 * (size_t)min(iu, end - 1u) + 3];
             cl[(4 * r + u) * 64 + lane] = iu < end ? 1.0f + q : -1.0f;
         }
@@ -160,7 +166,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
     const bool sp = rb > ra && rb - ra < (uint32_t)kDenseMin;
     if (sp) sb = sparse_ordinal(marks, ra);
     const uint32_t cend = (uint32_t)__builtin_amdgcn_readlane((int)rb, 13);
-    const uint32_t tail = h + 16u * (uint32_t)R;
+    const uint32_t tail = h + 16u * (uint32_t)(kSplit ? rows : R);
     if (lane == 13) rb = h;
     if (lane == 27) {
         ra = tail;
@@ -210,14 +216,15 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
     // r = rd; their accumulator input is -1e30 so they weigh 0
     const int dv = col - 4 * grp;
 #pragma unroll
-    for (int rd = 0; rd < R; rd++) {
+    for (int rd = 0; rd < (kSplit ? 4 : R); rd++) {
+        if (kSplit && (!blocks || rd >= rows)) break;
         const uint32_t j0 = h + 16u * (uint32_t)rd;
         const float val = ld(j0);
-        const float bv = (grp == 3 && (uint32_t)col >= end - j0) ? -1e30f : val;
+        const float bv = (grp == 3 && (uint32_t)col >= cend - j0) ? -1e30f : val;
 #pragma unroll
         for (int r = 0; r < R; r++) {
             f32x4 cin = Cget(r);
-            if (r == rd) {
+            if (kSplit ? rd == part : r == rd) {
 #pragma unroll
                 for (int u = 0; u < 4; u++) cin[u] = dv == u ? -1e30f : cin[u];
             }
@@ -228,7 +235,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
         flush();
     }
 
-    if (todo) {
+    if (blocks && todo) {
         float As[R];
         f32x4 Cs[R];
         int k = __builtin_ctzll(todo);
@@ -356,7 +363,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
         // per lane), A and the accumulator input are the rows' unshifted ones.
         // For the pairs that count the terms stay below about 4 in magnitude,
         // as in the blocks above.
-        {
+        if (blocks) {
             const float4 qj = reinterpret_cast<const float4 *>(pq)[js];
             const float x = qj.x + (float)(kc % 3 - 1) * g.cellb, y = qj.y + (float)((kc / 3) % 3 - 1) * g.cellb,
                         z = qj.z + (float)(kc / 9 - 1) * g.cellb;
@@ -377,6 +384,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
             }
             __builtin_amdgcn_wave_barrier();
         }
+        if (!shares) continue;
         // the sparse particle's image in the chunk's frame
         const float4 pj = spos[js];
         const Pos64 pjm{(double)pj.x + image_shift(cx, kc % 3 - 1, g.nc, g.L),
@@ -388,9 +396,10 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
             atomicAdd(reinterpret_cast<unsigned long long *>(&dfx[dst]),
                       (unsigned long long)__double2ll_rn(v * kFixScale));
     }
+    if (!blocks) return;
     reduce();
-    const uint32_t ii = h + 16u * (uint32_t)(col >> 2) + 4u * (uint32_t)grp + (uint32_t)(col & 3);
-    if (ii < end) {
+    const uint32_t ii = hr + 16u * (uint32_t)(col >> 2) + 4u * (uint32_t)grp + (uint32_t)(col & 3);
+    if (ii < end && (!kSplit || col < 4)) {
         // the self pair weighs exactly 1 when it counts
         const double S = acc + (g.self_count ? 1.0 : 0.0);
         const float dd = (float)(g.norm * S);
@@ -432,6 +441,38 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, unsign
     default: HF_DENSITY_CHUNK(4); break;
     }
 #undef HF_DENSITY_CHUNK
+}
+
+// A wavefront per row block of 16 and one for the sparse particles' shares, for
+// inputs that do not fill the chip, where the longest chunk is the time: a lone
+// wavefront issues an instruction every few cycles, and a quarter of the rows
+// halves those of a block of neighbours (332 chunks: 37 us became 21; 4209: 83
+// became 67; 9699: 135 became 125; but about 40 000, which fill the chip: 330
+// became 385).
+constexpr int kRowParts = 5;
+__global__ __launch_bounds__(64, 4) void k_density_rows(int64_t nchunks, unsigned tile, int64_t n, Boxes bx,
+                                                        const int32_t *__restrict__ chunks,
+                                                        const float4 *__restrict__ sloc,
+                                                        const float4 *__restrict__ pq,
+                                                        const float4 *__restrict__ spos, Cells cells, Marks marks,
+                                                        uint64_t *__restrict__ dfx, float *__restrict__ dens_s,
+                                                        float *__restrict__ dens_out, uint64_t *clock) {
+    stamp(clock);
+    const unsigned wq = xcd_tile_block(tile);
+    const int64_t q = wq / kRowParts;
+    const int part = (int)(wq % kRowParts);
+    if (q >= nchunks) return;
+    const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane(chunks[q]);
+    const uint32_t end = __builtin_amdgcn_readfirstlane(chunk_end(marks, h, n));
+    const int rows = (int)((end - h + 15u) >> 4);
+    // the parts past the rows of a short chunk; the last one takes the shares
+    if (part >= rows && part != kRowParts - 1) return;
+    const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, h))];
+    const uint32_t c = __builtin_amdgcn_readfirstlane(__float_as_uint(sloc[h].w));
+    __shared__ float cl[4 * 64];
+    __shared__ float4 s_pk[64];
+    density_chunk<1, true, true>(g, h, c, end, reinterpret_cast<const float *>(pq), spos, cells, marks, dfx, dens_s,
+                                 dens_out, cl, s_pk, min(part, rows), rows);
 }
 
 // Sparse cells: one particle per lane, sparse neighbour cells only; the pairs
@@ -664,9 +705,14 @@ void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStr
         bool narrow = (n + 32) * 16 <= (int64_t)0xffffff00;
         const char *force = getenv("HF_DENSITY_WIDE");
         if (force && force[0] == '1') narrow = false;
-        hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, xcd_tile(bx), n, bx, narrow,
-                           w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s, dens_out,
-                           w.clock + kClockDensity);
+        if (narrow && w.nchunks <= 40 * (int64_t)(w.ncu > 0 ? w.ncu : 1))
+            hipLaunchKernelGGL(k_density_rows, dim3((unsigned)(w.nchunks * kRowParts)), dim3(64), 0, s, w.nchunks,
+                               xcd_tile(bx), n, bx, w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s,
+                               dens_out, w.clock + kClockDensity);
+        else
+            hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, xcd_tile(bx), n,
+                               bx, narrow, w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s, dens_out,
+                               w.clock + kClockDensity);
     }
     if (w.nsparse > 0) {
         hipLaunchKernelGGL(k_density_sparse, dim3((unsigned)((w.nsparse + kBlock - 1) / kBlock)),
