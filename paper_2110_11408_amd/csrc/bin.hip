@@ -28,8 +28,9 @@
 //        sloc = (x, y, z relative to the cell corner, in units of b; cell id
 //               bits) -- FP32 coordinates whose differences across a periodic
 //               face stay exact, used by the density loop and prefilters;
-//   4. cell offsets for every cell of the grid, written by the sorted
-//      particles that end each run of cells (coalesced, one wavefront per 64).
+//   4. the cell index: a bit per cell that holds particles, the number of the
+//      first one per 32 cells, and every such cell's first particle, written with
+//      the lists of the dense chunks and sparse particles.
 // Cells are at least max(b, l) wide; each is split into k^3 sub-cells whose
 // diagonal is below l, so all particles of one sub-cell are friends.  The
 // boxes of one call are binned together: their cells are numbered box after

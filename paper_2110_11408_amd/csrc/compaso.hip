@@ -8,10 +8,10 @@
 //     earlier assignments (steps 1-2);
 //   - eligibility depends only on earlier nuclei and their R (step 1);
 //   - a particle's reassignment depends only on its current halo (step 3).
-// Hence: candidates are found in parallel; one workgroup per group walks its
-// candidates in descending density, rejects those inside alpha R of an
-// accepted nucleus and computes R for the accepted ones; finally every
-// particle folds over its group's accepted halos in creation order.
+// Hence: candidates are found in parallel; R is computed for all of them in
+// parallel; a wavefront per group walks its candidates in descending density and
+// rejects those inside alpha R of an accepted nucleus; finally every particle
+// folds over its group's accepted halos in creation order.
 //
 // R without sorting (Sec. 2.3.3: the enclosed mass at sorted position k is k,
 // R_L1 is where the enclosed density first drops below Delta_L1).  With

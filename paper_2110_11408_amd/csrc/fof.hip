@@ -273,8 +273,9 @@ __global__ __launch_bounds__(kBlock) void k_fof_phase_a(int64_t n, Boxes bx, Mar
 // its whole neighbourhood before another one's joins could save it the work
 // (99 us on the 64^3 box, the longest chunk's chain), and on a large one two
 // thirds of the tests joined what a neighbour had joined meanwhile (1.72 ms on
-// the 256^3 box, 22.4 ms on the 512^3 one).  Three short kernels make the links that cost next to nothing to find: between
-// the first members of sub-cells that touch.
+// the 256^3 box, 22.4 ms on the 512^3 one).  Three short kernels make the links
+// that cost next to nothing to find: between the first members of sub-cells that
+// touch.
 
 // The first member of the sub-cell in this row of the table, -1 for none
 // (phase A writes submem for sub-cells that hold particles only).

@@ -355,7 +355,7 @@ hf_status plan_boxes(Lane *c, const hf::BoxSet &bs, Plan *pl) {
             pl->btab[k] = b;
         }
     }
-    // cells with nothing to bin still end the offset grid: at least one
+    // the cell index has at least one cell
     if (pl->ncell == 0) pl->ncell = 1;
     return HF_OK;
 }
