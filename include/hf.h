@@ -234,7 +234,7 @@ hf_status hf_find(hf_ctx *ctx, const float *pos, int64_t n, const hf_params *p,
  * static device array of 256 MiB that every GPU the library runs on holds until
  * the process ends (hf_create takes its address).  It calls no hipMalloc,
  * hipFree or allocating library routine.  A box needing more scratch than that
- * (about 6e5 particles at mean density 1 with the default parameters; the need
+ * (about 9e5 particles at mean density 1 with the default parameters; the need
  * grows with n and with the cell grid box^3 / max(b, l)^3) is refused with
  * HF_ERR_INVALID before anything is enqueued.  Every context on one GPU shares
  * that array, which keeps the last call's contents: calls that overlap on one
