@@ -707,10 +707,10 @@ void launch_density(int64_t n, const Boxes &bx, Work &w, float *dens_out, hipStr
         if (force && force[0] == '1') narrow = false;
         if (narrow && w.nchunks <= 40 * (int64_t)(w.ncu > 0 ? w.ncu : 1))
             hipLaunchKernelGGL(k_density_rows, dim3((unsigned)(w.nchunks * kRowParts)), dim3(64), 0, s, w.nchunks,
-                               xcd_tile(bx), n, bx, w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s,
+                               kXcdTile, n, bx, w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s,
                                dens_out, w.clock + kClockDensity);
         else
-            hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, xcd_tile(bx), n,
+            hipLaunchKernelGGL(k_density_dense, dim3((unsigned)w.nchunks), dim3(64), 0, s, w.nchunks, kXcdTile, n,
                                bx, narrow, w.chunks, w.sloc, w.pq, w.spos, w.cells, w.marks, dfx, w.dens_s, dens_out,
                                w.clock + kClockDensity);
     }
