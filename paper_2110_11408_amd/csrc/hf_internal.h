@@ -162,14 +162,15 @@ __device__ __forceinline__ unsigned xcd_block() {
 
 // The same with slices of `tile` blocks dealt to the XCDs in turn, for lists whose
 // parts differ in cost: one contiguous part per XCD leaves some XCDs with the
-// chunks of the largest haloes.  The density kernels take slices of 64 (3.1M
-// particles: k_density_dense 330 -> 290 us; 1.0M: k_density_rows 125 -> 117; 96
-// boxes: 6.70 -> 6.54 ms; 512^3: 29.6 -> 28.2; 256^3: 1.73 and 1.72), the FoF chunks in a batch
-// only (96 boxes: k_fof_dense 3.42 -> 3.03 ms): in one box their links run along the
-// slices, and contiguous ones are better (64^3: 44 us against 58; 512^3: 8.21 ms
-// against 8.55).
-constexpr unsigned kXcdTile = 64;
-inline unsigned xcd_tile(const Boxes &bx) { return bx.nbox > 1 ? kXcdTile : 0u; }
+// chunks of the largest haloes.  The density kernels and the record buckets take
+// slices of 16 (3.1M particles: k_density_dense 330 us contiguous, 297 in slices of
+// 64, 282 of 4 or 16; 1.0M: k_density_rows 125, 117, 114; 512^3: 29.6, 28.2, 28.2
+// ms; 256^3: 1.73, 1.73, 1.73), the FoF chunks slices of 64 and in a batch only (96
+// boxes: k_fof_dense 3.42 -> 3.03 ms): in one box their links run along the slices,
+// and contiguous ones are better (64^3: 44 us against 58; 512^3: 8.21 ms against
+// 8.55).
+constexpr unsigned kXcdTile = 16;
+inline unsigned xcd_tile(const Boxes &bx) { return bx.nbox > 1 ? 64u : 0u; }
 __device__ __forceinline__ unsigned xcd_tile_block(unsigned tile) {
     if (tile == 0u) return xcd_block();
     const unsigned b = blockIdx.x, whole = gridDim.x / (kXcds * tile) * (kXcds * tile);
