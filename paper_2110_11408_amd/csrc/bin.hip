@@ -411,97 +411,240 @@ __device__ __forceinline__ void big_bucket_pass(const uint64_t *src, uint64_t *d
     }
 }
 
+// ---------------------------------------------------------- long buckets
+// A bucket is a range of keys, part of a plane of cells, so a sheet of particles
+// fills a few of them, and a workgroup per bucket is then the whole sort.  A
+// bucket too long for LDS is therefore shared by several workgroups, each with a
+// range of its keys: every one counts the bucket's particles in bins of
+// consecutive keys, takes the bins that start in its share of the sorted order,
+// gathers their particles in order and sorts them as a bucket of their own.
+// Nobody waits for another workgroup.  (Half of the particles in one plane of
+// cells, the whole binning: 5.0e5 particles 537 us with a workgroup per bucket,
+// 139 with shares; 6.0e5 424 and 192; 2.0e6 609 and 292.)
+
+// Share `part` of `parts` of the m particles counted in hist (PER bins per
+// thread): the bins [lo, hi), the particles before them, and those in them.
+struct Share {
+    uint32_t lo, hi;
+    int64_t first, cnt;
+};
+template <int PER, int NW>
+__device__ __forceinline__ Share bin_share(const uint32_t *hist, int64_t m, int64_t part, int64_t parts,
+                                           uint32_t *s_tot, uint32_t *s_sel) {
+    const int64_t each = (m + parts - 1) / parts, from = part * each, to = from + each;
+    const uint32_t bin0 = threadIdx.x * PER;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+        c[q] = hist[bin0 + q];
+        sum += c[q];
+    }
+    if (threadIdx.x < 2) {  // of a bound that no bin starts at or after
+        s_sel[threadIdx.x] = 64 * NW * PER;
+        s_sel[2 + threadIdx.x] = (uint32_t)m;
+    }
+    int64_t at = block_scan_excl<NW>(sum, s_tot);  // (with a barrier)
+    int64_t prev = threadIdx.x > 0 ? at - (int64_t)hist[bin0 - 1] : -1;  // start of the bin before
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+        if (prev < from && at >= from) {
+            s_sel[0] = bin0 + q;
+            s_sel[2] = (uint32_t)at;
+        }
+        if (prev < to && at >= to) {
+            s_sel[1] = bin0 + q;
+            s_sel[3] = (uint32_t)at;
+        }
+        prev = at;
+        at += c[q];
+    }
+    __syncthreads();
+    const Share r{s_sel[0], s_sel[1], (int64_t)s_sel[2], (int64_t)s_sel[3] - (int64_t)s_sel[2]};
+    __syncthreads();  // hist and s_tot are free
+    return r;
+}
+
+// Some of the elements [0, m) gathered in order: load(u, e) fetches element e as
+// the lane's u-th of a round of kGather, take(u) tells whether it is one of them,
+// and put(u, place, e) stores it.
+constexpr int kGather = 4;
+template <int NW, class Load, class Take, class Put>
+__device__ __forceinline__ void gather_share(int64_t m, uint32_t *s_tot, Load load, Take take, Put put) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t run = 0;
+    for (int64_t t0 = 0; t0 < m; t0 += 64 * NW * kGather) {
+        const int64_t e0 = t0 + w * (64 * kGather) + lane;
+#pragma unroll
+        for (int u = 0; u < kGather; u++)
+            if (e0 + u * 64 < m) load(u, e0 + u * 64);
+        uint64_t mask[kGather];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int u = 0; u < kGather; u++) {
+            mask[u] = __ballot(e0 + u * 64 < m && take(u));
+            mine += (uint32_t)__popcll(mask[u]);
+        }
+        if (lane == 0) s_tot[w] = mine;
+        __syncthreads();
+        uint32_t at = run;
+#pragma unroll
+        for (int x = 0; x < NW; x++) {
+            at += x < w ? s_tot[x] : 0u;
+            run += s_tot[x];
+        }
+#pragma unroll
+        for (int u = 0; u < kGather; u++) {
+            if ((mask[u] >> lane) & 1ull) put(u, at + (uint32_t)__popcll(mask[u] & lanes_below(lane)), e0 + u * 64);
+            at += (uint32_t)__popcll(mask[u]);
+        }
+        __syncthreads();
+    }
+}
+
 // One bucket of the partition pass (the keys with the same bits above shift +
 // bits), sorted by the bits [shift, shift + bits) with a stable radix sort of
 // its own, then its particles' sorted records.  Bucket b holds the elements
 // [start[b * stride], start[(b + 1) * stride]) (the whole input when start is
 // null).  Up to kLocal elements stay in registers and LDS: each pass counts the
 // digits of every wavefront's run of consecutive elements, places the elements
-// in LDS in digit order and reads them back.  A larger bucket (a halo's centre)
-// is sorted tile by tile between its ranges of kin and tmp.
+// in LDS in digit order and reads them back.  A longer bucket is shared by the
+// workgroups past the buckets' own: one for every kShareStep-th element of the
+// partitioned order, which exits unless that element lies in such a bucket (at
+// least two do in each).  A share that is still too long (many particles in one
+// bin) is sorted tile by tile in `work` (16 bytes per particle).
 // On small inputs the passes are launch latency: four passes of count, two scan
 // launches and scatter (and k_bin_place) took 92 us on the 64^3 box.
 constexpr int kLocalIters = 16;
 constexpr int kLocal = 256 * kLocalIters;
-__global__ __launch_bounds__(256) void k_bucket_sort(uint64_t *kin, uint64_t *tmp, int64_t n,
-                                                     const uint32_t *__restrict__ start, int64_t stride, int shift,
-                                                     int bits, const float *__restrict__ pos, Boxes bx, int ib,
-                                                     Sorted to) {
+constexpr int kShareStep = 2048;
+__global__ __launch_bounds__(256) void k_bucket_sort(const uint64_t *__restrict__ kin, uint64_t *work, int64_t n,
+                                                     const uint32_t *__restrict__ start, int64_t stride,
+                                                     int nbuckets, int shift, int bits,
+                                                     const float *__restrict__ pos, Boxes bx, int ib, Sorted to) {
+    constexpr int kPer = 8, kBinBits = 11;  // bins of a long bucket
+    static_assert(256 * kPer == 1 << kBinBits, "bins of a long bucket");
     __shared__ uint32_t o[kRadixWaves][1 << kRadixMaxBits];
     __shared__ uint32_t lstart[1 << kRadixMaxBits], run[1 << kRadixMaxBits];
-    __shared__ uint32_t s_tot[kRadixWaves];
+    __shared__ uint32_t s_tot[kRadixWaves], s_sel[4];
     __shared__ uint64_t sk[kLocal];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x;
     if (blockIdx.x == 0) place_padding(n, tid, to);
-    const int64_t b0 = start ? (int64_t)start[blockIdx.x * stride] : 0;
-    const int64_t m = (start ? (int64_t)start[(blockIdx.x + 1) * stride] : n) - b0;
-    if (m <= 0) return;
     const int passes = (bits + kRadixMaxBits - 1) / kRadixMaxBits;
     const int D = passes > 0 ? (bits + passes - 1) / passes : 0;
     const int nd = 1 << D;
     const uint32_t dmask = (uint32_t)(nd - 1);
-    uint64_t *src = kin + b0, *dst = tmp + b0;
-    if (m <= kLocal) {
-        const int iters = (int)((m + 255) / 256);  // elements per thread
-        const int e0 = w * 64 * iters + lane;
-        uint64_t k[kLocalIters];
+    int64_t b0, m;  // the workgroup's elements: [b0, b0 + m) of the output
+    uint64_t k[kLocalIters];
+    if ((int)blockIdx.x < nbuckets) {
+        b0 = start ? (int64_t)start[blockIdx.x * stride] : 0;
+        m = (start ? (int64_t)start[(blockIdx.x + 1) * stride] : n) - b0;
+        if (m <= 0 || m > kLocal) return;
+        const int iters = (int)((m + 255) / 256), e0 = w * 64 * iters + lane;
 #pragma unroll
-        for (int it = 0; it < kLocalIters; it++) k[it] = it < iters && e0 + it * 64 < m ? src[e0 + it * 64] : 0ull;
-        for (int p = 0; p < passes; p++) {
-            const int sh = shift + p * D;
-            for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
-            uint32_t place[kLocalIters];
+        for (int it = 0; it < kLocalIters; it++)
+            k[it] = it < iters && e0 + it * 64 < m ? kin[b0 + e0 + it * 64] : 0ull;
+    } else {
+        // the bucket of element p: its start is the last at or before p (256
+        // starts probed at once, then those between two of them)
+        const int64_t e = (int64_t)blockIdx.x - nbuckets, p = e * kShareStep;
+        const int per = (nbuckets + 255) / 256;
+        const int g = __syncthreads_count(tid * per < nbuckets && (int64_t)start[tid * per * stride] <= p) - 1;
+        const int b = g * per - 1 +
+                      __syncthreads_count(tid < per && g * per + tid < nbuckets &&
+                                          (int64_t)start[(g * per + tid) * stride] <= p);
+        b0 = start[b * stride];
+        m = (int64_t)start[(b + 1) * stride] - b0;
+        if (m <= kLocal) return;
+        const int64_t e0 = (b0 + kShareStep - 1) / kShareStep, e1 = (b0 + m + kShareStep - 1) / kShareStep;
+        // bins of the top bits of those to sort by
+        const int bsh = shift + (bits > kBinBits ? bits - kBinBits : 0);
+        auto bin = [&](uint64_t x) { return (uint32_t)((x & ((1ull << (shift + bits)) - 1ull)) >> bsh); };
+        uint32_t *const hist = reinterpret_cast<uint32_t *>(sk);
+        for (int q = tid; q < 256 * kPer; q += 256) hist[q] = 0u;
+        __syncthreads();
+        for (int64_t t = tid; t < m; t += 256 * kGather) {
+            uint64_t x[kGather];
 #pragma unroll
-            for (int it = 0; it < kLocalIters; it++) {
-                place[it] = 0u;
-                if (it < iters) {
-                    const bool act = e0 + it * 64 < m;
-                    const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
-                    place[it] = step_place(d, D, act);
-                    if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
-                }
+            for (int u = 0; u < kGather; u++) x[u] = t + u * 256 < m ? kin[b0 + t + u * 256] : 0ull;
+#pragma unroll
+            for (int u = 0; u < kGather; u++)
+                if (t + u * 256 < m) atomicAdd(&hist[bin(x[u])], 1u);
+        }
+        __syncthreads();
+        const Share sh = bin_share<kPer, kRadixWaves>(hist, m, e - e0, e1 - e0, s_tot, s_sel);
+        if (sh.cnt <= 0) return;
+        uint64_t *src = work + 2 * (b0 + sh.first), *dst = src + sh.cnt;
+        uint64_t *const at = sh.cnt <= kLocal ? sk : src;
+        uint64_t x[kGather];
+        gather_share<kRadixWaves>(
+            m, s_tot, [&](int u, int64_t i) { x[u] = kin[b0 + i]; },
+            [&](int u) { return bin(x[u]) >= sh.lo && bin(x[u]) < sh.hi; },
+            [&](int u, uint32_t place, int64_t) { at[place] = x[u]; });
+        b0 += sh.first;
+        m = sh.cnt;
+        if (m > kLocal) {
+            for (int q = 0; q < passes; q++) {
+                big_bucket_pass(src, dst, m, shift + q * D, D, run, o, s_tot);
+                uint64_t *const t = src;
+                src = dst;
+                dst = t;
             }
-            __syncthreads();
-            digit_starts<1>(o, nd, lstart, s_tot);
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < kLocalIters; it++) {
-                if (it < iters) {
-                    const bool act = e0 + it * 64 < m;
-                    const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
-                    const uint32_t at = act ? o[w][d] : 0u;
-                    if (act) sk[at + (place[it] & 0xffu)] = k[it];
-                    if (act && (place[it] >> 16)) o[w][d] = at + ((place[it] >> 8) & 0xffu);
-                }
+            for (int64_t s = tid; s < m; s += 256) {
+                const uint64_t kw = src[s];
+                place_particle(pos, bx, b0 + s, kw >> ib, (uint32_t)(kw & ((1ull << ib) - 1ull)), to);
             }
-            __syncthreads();
-            if (p + 1 < passes) {
+            return;
+        }
+        const int iters = (int)((m + 255) / 256), i0 = w * 64 * iters + lane;
 #pragma unroll
-                for (int it = 0; it < kLocalIters; it++)
-                    if (it < iters && e0 + it * 64 < m) k[it] = sk[e0 + it * 64];
-                __syncthreads();
+        for (int it = 0; it < kLocalIters; it++) k[it] = it < iters && i0 + it * 64 < m ? sk[i0 + it * 64] : 0ull;
+        __syncthreads();
+    }
+    const int iters = (int)((m + 255) / 256);  // elements per thread
+    const int e0 = w * 64 * iters + lane;
+    for (int p = 0; p < passes; p++) {
+        const int sh = shift + p * D;
+        for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
+        uint32_t place[kLocalIters];
+#pragma unroll
+        for (int it = 0; it < kLocalIters; it++) {
+            place[it] = 0u;
+            if (it < iters) {
+                const bool act = e0 + it * 64 < m;
+                const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
+                place[it] = step_place(d, D, act);
+                if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
             }
         }
-        if (passes == 0) {
+        __syncthreads();
+        digit_starts<1>(o, nd, lstart, s_tot);
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kLocalIters; it++) {
+            if (it < iters) {
+                const bool act = e0 + it * 64 < m;
+                const uint32_t d = (uint32_t)(k[it] >> sh) & dmask;
+                const uint32_t at = act ? o[w][d] : 0u;
+                if (act) sk[at + (place[it] & 0xffu)] = k[it];
+                if (act && (place[it] >> 16)) o[w][d] = at + ((place[it] >> 8) & 0xffu);
+            }
+        }
+        __syncthreads();
+        if (p + 1 < passes) {
 #pragma unroll
             for (int it = 0; it < kLocalIters; it++)
-                if (it < iters && e0 + it * 64 < m) sk[e0 + it * 64] = k[it];
+                if (it < iters && e0 + it * 64 < m) k[it] = sk[e0 + it * 64];
             __syncthreads();
         }
-        for (int64_t s = tid; s < m; s += 256) {
-            const uint64_t kw = sk[s];
-            place_particle(pos, bx, b0 + s, kw >> ib, (uint32_t)(kw & ((1ull << ib) - 1ull)), to);
-        }
-        return;
     }
-    for (int p = 0; p < passes; p++) {
-        big_bucket_pass(src, dst, m, shift + p * D, D, run, o, s_tot);
-        uint64_t *const t = src;
-        src = dst;
-        dst = t;
+    if (passes == 0) {
+#pragma unroll
+        for (int it = 0; it < kLocalIters; it++)
+            if (it < iters && e0 + it * 64 < m) sk[e0 + it * 64] = k[it];
+        __syncthreads();
     }
     for (int64_t s = tid; s < m; s += 256) {
-        const uint64_t kw = src[s];
+        const uint64_t kw = sk[s];
         place_particle(pos, bx, b0 + s, kw >> ib, (uint32_t)(kw & ((1ull << ib) - 1ull)), to);
     }
 }
@@ -740,25 +883,34 @@ __device__ __forceinline__ void place_record(const float4 &r, uint32_t key, cons
 // place in the bucket, in registers and LDS) and their sorted records written.
 // A bucket is one workgroup's chain of dependent steps, so its length decides:
 // 256 threads take buckets of up to 8 elements each (2048 particles) and list
-// the larger ones (in `big`), which 1024 threads take with up to 16 each, one
-// workgroup per listed bucket (a grid striding over the list).  Beyond 16 384
-// particles a bucket is sorted tile by tile in its share of `work` (16 bytes
-// per particle, as two arrays of 64-bit words).  (256 threads with 16 elements
-// and the tile sort beyond 4096 had 2.8 wavefronts per SIMD on average on the
-// 256^3 box, most of the time a few long buckets: 563 us.)  The buckets are dealt
-// to the XCDs in slices, since long ones lie together: 3.1M particles 82 -> 64 us,
-// the 256^3 box 332 -> 279, the 512^3 box 2250 -> 1917 for 256 threads.
+// the longer ones (in `big`, pairs of bucket and share), which 1024 threads take
+// with up to 16 each, one workgroup per listed share (a grid striding over the
+// list).  A bucket beyond kRecMost particles is listed as several shares
+// (rec_shares), found by bins of consecutive cells; a share beyond half of
+// kRecMost (a cell of so many) is sorted tile by tile in its part of `work` (16
+// bytes per particle, as two arrays of 64-bit words).  (256 threads with 16
+// elements and the tile sort beyond 4096 had 2.8 wavefronts per SIMD on average
+// on the 256^3 box, most of the time a few long buckets: 563 us.)  The buckets are
+// dealt to the XCDs in slices, since long ones lie together: 3.1M particles 82 ->
+// 64 us, the 256^3 box 332 -> 279, the 512^3 box 2250 -> 1917 for 256 threads.
 constexpr int kLowMost = 18;  // low key bits beside 14 bits of place
+constexpr int kRecMost = 1 << 14;
+// Shares of a bucket of m particles: each reads the whole bucket twice, so no
+// more than there are compute units to run them at once.
+__device__ __forceinline__ int64_t rec_shares(int64_t m) {
+    return m <= kRecMost ? 1 : min((m + kRecMost / 4 - 1) / (kRecMost / 4), (int64_t)256);
+}
 template <int NW, int ITERS, bool kListed, bool kOne>
 __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict__ rec, int64_t n,
                                                         const uint32_t *__restrict__ starts, int low, Boxes bx,
                                                         uint64_t *work, uint32_t *__restrict__ big,
                                                         uint32_t *__restrict__ nbig, Sorted to) {
     constexpr int NT = 64 * NW, kMost = NT * ITERS, kPlace = 14;
-    static_assert(kMost <= 1 << kPlace, "14 bits of place");
+    constexpr uint32_t kPlaces = (1u << kPlace) - 1u;
+    static_assert(kMost <= 1 << kPlace && (!kListed || kMost == kRecMost), "14 bits of place");
     __shared__ uint32_t o[NW][1 << kRadixMaxBits];
     __shared__ uint32_t lstart[1 << kRadixMaxBits], run[kListed ? 1 << kRadixMaxBits : 1];
-    __shared__ uint32_t s_tot[NW];
+    __shared__ uint32_t s_tot[NW], s_sel[4];
     __shared__ uint32_t sk[kMost];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x;
     const int passes = (low + kRadixMaxBits - 1) / kRadixMaxBits;
@@ -770,11 +922,18 @@ __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict
     if (!kListed && blockIdx.x == 0) place_padding(n, tid, to);
     const uint32_t nq = kListed ? *nbig : gridDim.x;
     for (uint32_t q = blockIdx.x; q < nq; q += gridDim.x) {
-        const int64_t bucket = kListed ? big[q] : xcd_tile_block(kXcdTile);
-        const int64_t b0 = starts[bucket], m = (int64_t)starts[bucket + 1] - b0;
-        if (m <= 0) return;  // only unlisted buckets, one per workgroup, are empty
-        if (!kListed && m > kMost) {
-            if (tid == 0) big[atomicAdd(nbig, 1u)] = (uint32_t)bucket;
+        const int64_t bucket = kListed ? big[2 * q] : xcd_tile_block(kXcdTile);
+        const int64_t r0 = starts[bucket], rm = (int64_t)starts[bucket + 1] - r0;
+        if (rm <= 0) return;  // only unlisted buckets, one per workgroup, are empty
+        if (!kListed && rm > kMost) {
+            const uint32_t parts = (uint32_t)rec_shares(rm);
+            if (tid == 0) s_sel[0] = atomicAdd(nbig, parts);
+            __syncthreads();
+            const uint32_t at = s_sel[0];
+            for (uint32_t p = tid; p < parts; p += NT) {
+                big[2 * (at + p)] = (uint32_t)bucket;
+                big[2 * (at + p) + 1] = p;
+            }
             return;
         }
         auto low_key = [&](const float4 &r) -> uint32_t {
@@ -785,82 +944,143 @@ __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict
             return k;
         };
         const uint32_t high = (uint32_t)((uint64_t)bucket << low);  // of the keys' low 32 bits
-        if (m <= kMost) {
-            const int iters = (int)((m + NT - 1) / NT);  // elements per thread
-            const int e0 = w * 64 * iters + lane;
-            uint32_t k[ITERS];
+        int64_t b0 = r0, m = rm;  // the particles to sort: [b0, b0 + m) of the output
+        const bool shared = kListed && rm > kMost;
+        uint32_t *const sidx = sk + kMost / 2;  // a share's places in the bucket, by place in the share
+        if constexpr (kListed) {
+            if (shared) {
+                // bins of consecutive cells (no sub-cells: an eighth of the key's arithmetic)
+                constexpr int kPer = 4;
+                constexpr uint32_t kBins = NT * kPer;
+                const uint64_t key0 = (uint64_t)bucket << low;
+                const uint32_t c0 = (uint32_t)(key0 / (uint64_t)bx.nsub_max);
+                const uint32_t span = (uint32_t)((key0 + lmask) / (uint64_t)bx.nsub_max - c0);
+                int bsh = 0;
+                while (span >> bsh >= kBins) bsh++;
+                auto bin = [&](const float4 &r) -> uint32_t {
+                    uint32_t c = 0;
+                    with_box<kOne>(bx, g0, __float_as_uint(r.w), [&](const Geo &g) {
+                        const int cx = cell_coord(r.x, g), cy = cell_coord(r.y, g), cz = cell_coord(r.z, g);
+                        c = g.cell_base + ((uint32_t)cz * (uint32_t)g.nc + (uint32_t)cy) * (uint32_t)g.nc +
+                            (uint32_t)cx;
+                    });
+                    return (c - c0) >> bsh;
+                };
+                for (uint32_t d = tid; d < kBins; d += NT) sk[d] = 0u;
+                __syncthreads();
+                for (int64_t t = tid; t < rm; t += NT * kGather) {
+                    float4 r[kGather];
+#pragma unroll
+                    for (int u = 0; u < kGather; u++) r[u] = rec[r0 + (t + u * NT < rm ? t + u * NT : 0)];
+#pragma unroll
+                    for (int u = 0; u < kGather; u++)
+                        if (t + u * NT < rm) atomicAdd(&sk[bin(r[u])], 1u);
+                }
+                __syncthreads();
+                const Share sh = bin_share<kPer, NW>(sk, rm, big[2 * q + 1], rec_shares(rm), s_tot, s_sel);
+                if (sh.cnt <= 0) continue;
+                b0 += sh.first;
+                m = sh.cnt;
+                uint64_t *src = work + 2 * b0, *dst = src + m;
+                const bool fits = m <= kMost / 2;
+                float4 r[kGather];
+                gather_share<NW>(
+                    rm, s_tot, [&](int u, int64_t i) { r[u] = rec[r0 + i]; },
+                    [&](int u) {
+                        const uint32_t d = bin(r[u]);
+                        return d >= sh.lo && d < sh.hi;
+                    },
+                    [&](int u, uint32_t place, int64_t i) {
+                        const uint32_t key = low_key(r[u]);
+                        if (fits) {
+                            sk[place] = (key << kPlace) | place;
+                            sidx[place] = (uint32_t)i;
+                        } else {
+                            src[place] = ((uint64_t)key << 32) | (uint64_t)i;
+                        }
+                    });
+                if (!fits) {
+                    for (int p = 0; p < passes; p++) {
+                        big_bucket_pass<NW>(src, dst, m, 32 + p * D, D, run, o, s_tot);
+                        uint64_t *const t = src;
+                        src = dst;
+                        dst = t;
+                    }
+                    for (int64_t s = tid; s < m; s += NT)
+                        place_record<kOne>(rec[r0 + (int64_t)(src[s] & 0xffffffffull)],
+                                           high + (uint32_t)(src[s] >> 32), bx, g0, b0 + s, to);
+                    __syncthreads();  // LDS is free for the next listed share
+                    continue;
+                }
+            }
+        }
+        const int iters = (int)((m + NT - 1) / NT);  // elements per thread
+        const int e0 = w * 64 * iters + lane;
+        uint32_t k[ITERS];
+        if (!shared) {
             // keys to LDS in order (two records in flight), then each thread's
             // elements to registers: a rolled loop keeps the key arithmetic out
             // of the unrolled passes
             for (int it = 0; it < iters; it += 2) {
                 const int ea = e0 + it * 64, eb = ea + 64;
                 const bool ina = ea < m, inb = it + 1 < iters && eb < m;
-                const float4 ra = rec[b0 + (ina ? ea : 0)], rb = rec[b0 + (inb ? eb : 0)];
+                const float4 ra = rec[r0 + (ina ? ea : 0)], rb = rec[r0 + (inb ? eb : 0)];
                 const uint32_t ka = low_key(ra), kb = low_key(rb);
                 if (ina) sk[ea] = (ka << kPlace) | (uint32_t)ea;
                 if (inb) sk[eb] = (kb << kPlace) | (uint32_t)eb;
             }
+        }
 #pragma unroll
-            for (int it = 0; it < ITERS; it++) k[it] = it < iters && e0 + it * 64 < m ? sk[e0 + it * 64] : 0u;
+        for (int it = 0; it < ITERS; it++) k[it] = it < iters && e0 + it * 64 < m ? sk[e0 + it * 64] : 0u;
+        __syncthreads();
+        for (int p = 0; p < passes; p++) {
+            const int sh = kPlace + p * D;
+            for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
+            uint32_t place[ITERS];
+#pragma unroll
+            for (int it = 0; it < ITERS; it++) {
+                place[it] = 0u;
+                if (it < iters) {
+                    const bool act = e0 + it * 64 < m;
+                    const uint32_t d = (k[it] >> sh) & dmask;
+                    place[it] = step_place(d, D, act);
+                    if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
+                }
+            }
             __syncthreads();
-            for (int p = 0; p < passes; p++) {
-                const int sh = kPlace + p * D;
-                for (int d = lane; d < nd; d += 64) o[w][d] = 0u;
-                uint32_t place[ITERS];
-#pragma unroll
-                for (int it = 0; it < ITERS; it++) {
-                    place[it] = 0u;
-                    if (it < iters) {
-                        const bool act = e0 + it * 64 < m;
-                        const uint32_t d = (k[it] >> sh) & dmask;
-                        place[it] = step_place(d, D, act);
-                        if (act && (place[it] >> 16)) o[w][d] += (place[it] >> 8) & 0xffu;
-                    }
-                }
-                __syncthreads();
-                digit_starts<1, NW>(o, nd, lstart, s_tot);
-                __syncthreads();
-#pragma unroll
-                for (int it = 0; it < ITERS; it++) {
-                    if (it < iters) {
-                        const bool act = e0 + it * 64 < m;
-                        const uint32_t d = (k[it] >> sh) & dmask;
-                        const uint32_t at = act ? o[w][d] : 0u;
-                        if (act) sk[at + (place[it] & 0xffu)] = k[it];
-                        if (act && (place[it] >> 16)) o[w][d] = at + ((place[it] >> 8) & 0xffu);
-                    }
-                }
-                __syncthreads();
-                if (p + 1 < passes) {
-#pragma unroll
-                    for (int it = 0; it < ITERS; it++)
-                        if (it < iters && e0 + it * 64 < m) k[it] = sk[e0 + it * 64];
-                    __syncthreads();
-                }
-            }
-            for (int s = tid; s < m; s += 2 * NT) {
-                const bool two = s + NT < m;
-                const uint32_t wa = sk[s], wb = two ? sk[s + NT] : wa;
-                const float4 ra = rec[b0 + (wa & ((1u << kPlace) - 1u))], rb = rec[b0 + (wb & ((1u << kPlace) - 1u))];
-                place_record<kOne>(ra, high + (wa >> kPlace), bx, g0, b0 + s, to);
-                if (two) place_record<kOne>(rb, high + (wb >> kPlace), bx, g0, b0 + s + NT, to);
-            }
-        } else if constexpr (kListed) {
-            uint64_t *src = work + 2 * b0, *dst = src + m;
-            for (int64_t e = tid; e < m; e += NT) src[e] = ((uint64_t)low_key(rec[b0 + e]) << 32) | (uint64_t)e;
+            digit_starts<1, NW>(o, nd, lstart, s_tot);
             __syncthreads();
-            for (int p = 0; p < passes; p++) {
-                big_bucket_pass<NW>(src, dst, m, 32 + p * D, D, run, o, s_tot);
-                uint64_t *const t = src;
-                src = dst;
-                dst = t;
+#pragma unroll
+            for (int it = 0; it < ITERS; it++) {
+                if (it < iters) {
+                    const bool act = e0 + it * 64 < m;
+                    const uint32_t d = (k[it] >> sh) & dmask;
+                    const uint32_t at = act ? o[w][d] : 0u;
+                    if (act) sk[at + (place[it] & 0xffu)] = k[it];
+                    if (act && (place[it] >> 16)) o[w][d] = at + ((place[it] >> 8) & 0xffu);
+                }
             }
-            for (int64_t s = tid; s < m; s += NT)
-                place_record<kOne>(rec[b0 + (int64_t)(src[s] & 0xffffffffull)], high + (uint32_t)(src[s] >> 32), bx,
-                                   g0, b0 + s, to);
+            __syncthreads();
+            if (p + 1 < passes) {
+#pragma unroll
+                for (int it = 0; it < ITERS; it++)
+                    if (it < iters && e0 + it * 64 < m) k[it] = sk[e0 + it * 64];
+                __syncthreads();
+            }
+        }
+        auto record = [&](uint32_t word) {
+            const uint32_t at = word & kPlaces;
+            return rec[r0 + (shared ? sidx[at] : at)];
+        };
+        for (int s = tid; s < m; s += 2 * NT) {
+            const bool two = s + NT < m;
+            const uint32_t wa = sk[s], wb = two ? sk[s + NT] : wa;
+            const float4 ra = record(wa), rb = record(wb);
+            place_record<kOne>(ra, high + (wa >> kPlace), bx, g0, b0 + s, to);
+            if (two) place_record<kOne>(rb, high + (wb >> kPlace), bx, g0, b0 + s + NT, to);
         }
         if (!kListed) return;
-        __syncthreads();  // LDS is free for the next listed bucket
+        __syncthreads();  // LDS is free for the next listed share
     }
 }
 
@@ -1249,8 +1469,12 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
             start = w.rscan;
             cur = 1;
         }
-        hipLaunchKernelGGL(k_bucket_sort, dim3(1u << r.top), dim3(256), 0, s, w.rkey[cur], w.rkey[cur ^ 1], n, start,
-                           ntiles, r.ib, low, pos, bx, r.ib, to);
+        // long buckets: a workgroup for every kShareStep particles, and their
+        // tile sorts in the scratch run (16 bytes per particle)
+        const int64_t shares = n > kLocal ? (n + kShareStep - 1) / kShareStep : 0;
+        hipLaunchKernelGGL(k_bucket_sort, dim3((1u << r.top) + (unsigned)shares), dim3(256), 0, s, w.rkey[cur],
+                           reinterpret_cast<uint64_t *>(w.tmp_a), n, start, ntiles, 1 << r.top, r.ib, low, pos, bx,
+                           r.ib, to);
     } else if (r.rec.dl >= 0) {
         // first pass into the radix key block (16 bytes per particle), second
         // into the sub-cell tables, which are written after the binning; the
@@ -1273,7 +1497,7 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
                            ntiles, w.rscan, rb, nullptr);
         hipLaunchKernelGGL(k_rec_starts, dim3((unsigned)nl), dim3(256), 0, s, n, r.rec, ntiles, w.rval[1], w.rscan,
                            w.ssub, w.rval[0]);
-        // the list of large buckets and its count after those first elements
+        // the list of long buckets' shares and its count after those first elements
         uint32_t *nbig = w.rval[1] + nl, *big = nbig + 1;
         hipLaunchKernelGGL((one ? k_rec_bucket<4, 8, false, true> : k_rec_bucket<4, 8, false, false>),
                            dim3((unsigned)(nl * nh)), dim3(256), 0, s, rb, n, w.rval[0], r.rec.low, bx, w.rkey[0], big,

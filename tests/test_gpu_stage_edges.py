@@ -71,9 +71,12 @@ def test_fof_cell_links(ctx, n, side, kw):
 
 
 # Binning: one partition pass and a sort per bucket up to 2^19 particles, two
-# passes that carry the positions beyond; a bucket is sorted in LDS up to 4096
-# particles.  HF_RADIX_PAYLOAD=1 takes the radix sort over all digits instead.
-# The sorted order is unique, so every output is the same.
+# passes that carry the positions beyond.  A bucket of the first is sorted in LDS
+# up to 4096 particles; one of the second by 256 threads up to 2048, by 1024 up to
+# 16 384.  A longer bucket is shared by several workgroups, which sort up to 4096
+# and 8192 particles each in LDS and more tile by tile.  HF_RADIX_PAYLOAD=1 takes
+# the radix sort over all digits instead.  The sorted order is unique, so every
+# output is the same.
 def _same_in_both_sorts(ctx, monkeypatch, pos, side, **kw):
     print(f"[gpu] both sorts n={len(pos)} side={side} {kw}", file=sys.stderr, flush=True)
     monkeypatch.delenv("HF_RADIX_PAYLOAD", raising=False)
@@ -112,6 +115,91 @@ def test_bucket_beyond_lds(ctx, monkeypatch, background, clump, width):
     assert a["n_halos"] >= 1
     if width > 0.0:
         assert len(density_violations(a["density"], oracle.density(pos, box=side, mean_density=1.0))) == 0
+
+
+def _clump_in_empty_planes(background, clump, width, seed):
+    """A clump in one cell, whose bucket it has for itself: the planes of cells
+    around it hold nothing else (the cells are 0.4 wide or a little more)."""
+    rng = np.random.default_rng(seed)
+    side = max(25.0, float(background) ** (1.0 / 3.0))
+    cell = side / int(side / (0.4 * (1.0 + 1e-6)))
+    at = (np.floor(12.0 / cell) + 0.3) * cell
+    back = rng.random((background, 3)) * side
+    back[:, 2] = (at + 1.0 + back[:, 2] * (side - 2.0) / side) % side
+    pos = np.concatenate([back, at + rng.random((clump, 3)) * width])
+    pos = pos.astype(np.float32)[rng.permutation(len(pos))]
+    pos[pos >= np.float32(side)] = 0.0
+    return pos, side
+
+
+# (width 0: one point, so one bin of a long bucket; 0.1 lies in one cell, which is
+# a bin of the second sort and several of the first)
+@pytest.mark.parametrize("background,clump,width", [
+    (20000, 4095, 0.1), (20000, 4096, 0.1), (20000, 4097, 0.1), (20000, 4097, 0.0), (20000, 40000, 0.1),
+    (600000, 2048, 0.1), (600000, 2049, 0.1), (600000, 16384, 0.1), (600000, 16385, 0.1), (600000, 16385, 0.0),
+    (600000, 40000, 0.1)])
+def test_long_bucket_of_one_cell(ctx, monkeypatch, background, clump, width):
+    pos, side = _clump_in_empty_planes(background, clump, width, clump)
+    a = _same_in_both_sorts(ctx, monkeypatch, pos, side, mean_density=1.0)
+    assert a["table"]["n"].max() >= clump // 2
+
+
+def test_long_buckets_of_several_boxes(ctx, monkeypatch):
+    """The same in one fused pass over boxes, in both sorts."""
+    import torch
+    from paper_2110_11408_amd import _lib
+    for big in (20000, 600000):
+        boxes = [_clump_in_empty_planes(b, c, w, b + c) for b, c, w in
+                 [(3000, 500, 0.1), (big, 17000, 0.1), (4097, 0, 0.0), (9000, 40000, 0.0), (5000, 4200, 0.1)]]
+        pos = torch.from_numpy(np.concatenate([b[0] for b in boxes])).cuda()
+        offs = np.concatenate([[0], np.cumsum([len(b[0]) for b in boxes])])
+        params = [_lib.default_params(box=b[1], mean_density=1.0) for b in boxes]
+        print(f"[gpu] hf_find_batch long buckets n={len(pos)}", file=sys.stderr, flush=True)
+        monkeypatch.delenv("HF_RADIX_PAYLOAD", raising=False)
+        a = ctx.find_batch(pos, offs, params, n_lanes=1)
+        monkeypatch.setenv("HF_RADIX_PAYLOAD", "1")
+        b = ctx.find_batch(pos, offs, params, n_lanes=1)
+        for key in ("density", "l0_id", "halo_id"):
+            assert torch.equal(a[key], b[key])
+        assert torch.equal(torch.cat(a["halos"]), torch.cat(b["halos"]))
+
+
+def _sheet(n, planes, seed):
+    """Half of the particles in a few planes of cells, half all over the box."""
+    rng = np.random.default_rng(seed)
+    side = float(n) ** (1.0 / 3.0)
+    pos = rng.random((n, 3)) * side
+    pos[: n // 2, 2] = 0.37 * side + rng.random(n // 2) * 0.4 * planes
+    pos = pos.astype(np.float32)[rng.permutation(n)]
+    pos[pos >= np.float32(side)] = 0.0
+    return pos, side
+
+
+@pytest.mark.parametrize("n", [20000, 262144, 2 ** 19, 600000, 2000003])
+def test_buckets_of_a_sheet(ctx, monkeypatch, n):
+    """Long buckets of many cells: the sorted order is that of the radix sort, and
+    the binning takes no more than twice its time (a workgroup per bucket took
+    2.8 to 4.7 times from 2.6e5 particles on, the shares take 1.0 to 1.4)."""
+    import torch
+    from paper_2110_11408_amd import _lib
+    pos, side = _sheet(n, 1, n)
+    p = _lib.default_params(box=side)
+    t = torch.from_numpy(pos).cuda()
+    out, ms = [], []
+    for force in (None, "1"):
+        monkeypatch.setenv("HF_RADIX_PAYLOAD", force or "0")
+        print(f"[gpu] sheet n={n} radix={force}", file=sys.stderr, flush=True)
+        best = 1e9
+        for _ in range(6):
+            dens = ctx.density(t, p)
+            best = min(best, ctx.stats()["ms_bin"])
+        l0, groups = ctx.l0_fof(t, dens, p)
+        out.append((dens, l0))
+        ms.append(best)
+        assert groups > 0
+    print(f"[gpu] sheet n={n} ms_bin {ms}", file=sys.stderr, flush=True)
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert ms[0] <= 2.0 * ms[1]
 
 
 @pytest.mark.parametrize("n,kw", [(2 ** 19, {}), (2 ** 19 + 1, {}), (2000003, {}), (2000003, {"l_fof": 0.13}),
