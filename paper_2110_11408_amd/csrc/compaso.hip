@@ -502,20 +502,20 @@ __device__ __forceinline__ int64_t first_crossing(const uint32_t *s_hist, int64_
     return -1;
 }
 
-// First coarse bucket j in [j0, j1) of 2^sh buckets in which a crossing can lie:
-// C before it is at most its last bucket (C only grows).  run: C before j0, on
-// return C before the bucket found.
+// First coarse bucket j < nj, of the 2^sh buckets from w0 + (j << sh) on, in which
+// a crossing can lie: C before it is at most its last bucket (C only grows).
+// run: C before w0, on return C before the bucket found.
 template <int NT>
-__device__ __forceinline__ int64_t first_possible(const uint32_t *s_hist, int64_t j0, int64_t j1, int sh,
+__device__ __forceinline__ int64_t first_possible(const uint32_t *s_hist, int64_t w0, int64_t nj, int sh,
                                                   uint32_t &run, uint32_t *s_red, int *s_min, uint32_t *s_c) {
     constexpr int SI = NT >= 1024 ? kScanIpt / 2 : kScanIpt;
-    for (int64_t b0 = j0; b0 < j1; b0 += (int64_t)NT * SI) {
+    for (int64_t b0 = 0; b0 < nj; b0 += (int64_t)NT * SI) {
         const int64_t k0 = b0 + (int64_t)threadIdx.x * SI;
         uint32_t v[SI];
         uint32_t sum = 0;
 #pragma unroll
         for (int u = 0; u < SI; u++) {
-            v[u] = k0 + u < j1 ? s_hist[k0 + u] : 0u;
+            v[u] = k0 + u < nj ? s_hist[k0 + u] : 0u;
             sum += v[u];
         }
         uint32_t tot;
@@ -524,7 +524,7 @@ __device__ __forceinline__ int64_t first_possible(const uint32_t *s_hist, int64_
 #pragma unroll
         for (int u = 0; u < SI; u++) {
             const int64_t k = k0 + u;
-            if (hit == 0x7fffffff && k < j1 && (int64_t)C <= ((k + 1) << sh) - 1) {
+            if (hit == 0x7fffffff && k < nj && (int64_t)C <= w0 + ((k + 1) << sh) - 1) {
                 hit = (int)(k - b0);
                 Chit = C;
             }
@@ -554,9 +554,13 @@ __device__ __forceinline__ int64_t first_possible(const uint32_t *s_hist, int64_
 // densest candidates come first; a candidate that lies inside alpha R of that
 // one, if its i is known by then, is left out (its i is never asked for).
 //   BINS = false: i from the bucket histogram of all particles of the group, in
-//                 LDS; with more buckets than fit (HL), a first histogram of
-//                 coarse buckets tells where the crossing can lie, and a second
-//                 one holds the buckets from there on;
+//                 LDS; with more buckets than fit (HL), half of it holds the
+//                 first ones and the other half the rest in coarse ones, which
+//                 tell from where on the buckets are looked at next (mostly one
+//                 such step: few coarse buckets have C before them as low as
+//                 their numbers, but the very first ones always do, so they
+//                 must not be coarse: a group of 500 000 members took 8.0 ms in
+//                 windows from the first bucket on, 1.17 so);
 //   BINS = true:  by the radial bins of Sec. 2.3.4.  Counts of the members per
 //                 radial bin (width g.rbin, in LDS) give C_j, the members
 //                 inside bin j's inner edge.  A bin whose C_j members, placed
@@ -665,35 +669,27 @@ __global__ __launch_bounds__(NT) void k_accept_eval(AcceptItems items, Boxes bx,
                 j0 = js + 1;
             }
         } else {
-            int64_t w0 = 0;
-            uint32_t run = 0;
-            if (m > HL) {
-                int sh = 1;
-                while (m > (int64_t)HL << sh) sh++;
-                const int64_t nj = ((m - 1) >> sh) + 1;
-                for (int64_t k = tid; k < nj; k += NT) s_hist[k] = 0u;
+            // the buckets [w0, w1) each, and those beyond, 2^sh together
+            uint32_t run = 0;  // C before w0
+            for (int64_t w0 = 0; w0 < m && found == m;) {
+                const int64_t w1 = m - w0 <= HL ? m : w0 + HL / 2;
+                int sh = 0;
+                while (m - w1 > (int64_t)(HL / 2) << sh) sh++;
+                const int64_t nj = (m - w1 + (1ll << sh) - 1) >> sh;
+                for (int64_t k = tid; k < w1 - w0 + nj; k += NT) s_hist[k] = 0u;
                 __syncthreads();
-                for_members<NT>(m, start, mem, spos, pc, g, [&](double e) {
-                    const int64_t k = bucket_of(g.K2 * e3(e), m);
-                    if (k < m) atomicAdd(&s_hist[k >> sh], 1u);
-                });
-                __syncthreads();
-                const int64_t j = first_possible<NT>(s_hist, 0, nj, sh, run, s_red, s_min, &s_c);
-                w0 = j < 0 ? m : j << sh;
-            }
-            for (; w0 < m && found == m; w0 += HL) {
-                // the buckets [w0, w1), and C before them
-                const int64_t w1 = w0 + HL < m ? w0 + HL : m;
-                for (int64_t k = tid; k < w1 - w0; k += NT) s_hist[k] = 0u;
-                __syncthreads();
-                const double Tlo = w0 > 0 ? ii(w0 - 1) : -1.0, Thi = ii(w1 - 1);
+                const double Tlo = w0 > 0 ? ii(w0 - 1) : -1.0, Thi = ii(m - 1);
                 for_members<NT>(m, start, mem, spos, pc, g, [&](double e) {
                     const double T = g.K2 * e3(e);
-                    if (T > Tlo && T <= Thi) atomicAdd(&s_hist[bucket_of(T, m) - w0], 1u);
+                    if (!(T > Tlo && T <= Thi)) return;
+                    const int64_t k = bucket_of(T, m);
+                    atomicAdd(&s_hist[k < w1 ? k - w0 : w1 - w0 + ((k - w1) >> sh)], 1u);
                 });
                 __syncthreads();
                 const int64_t t = first_crossing<NT>(s_hist, w0, w1, 0, m, run, s_red, s_min);
                 if (t >= 0) found = t;
+                const int64_t j = t >= 0 ? -1 : first_possible<NT>(s_hist + (w1 - w0), w1, nj, sh, run, s_red, s_min, &s_c);
+                w0 = j < 0 ? m : w1 + (j << sh);
             }
         }
         if (tid == 0) {

@@ -334,3 +334,67 @@ def test_acceptance_sizes(m, mean, second, radius_search):
     assert_same_labels(g, ref)
     assert np.bincount(g["l0"])[1:].max() > 0.5 * m
     assert not (m == 80000 and mean == 88 and second == 0.0) or ref["found"]["ienc"].max() > 36864
+
+
+def _smooth_ball(m, mean, power):
+    """A ball of m particles of mean density `mean` whose density falls as
+    r^(1/power - 3), without noise, so that it has one candidate, in 4000 others."""
+    rng = np.random.default_rng(m)
+    R = (m / mean / 4.19) ** (1.0 / 3.0)
+    side = 6.5 * R
+    i = np.arange(m) + 0.5
+    z, phi = 1.0 - 2.0 * ((i * 0.7548776662466927) % 1.0), 2.0 * np.pi * ((i * 0.5698402909980532) % 1.0)
+    rho = np.sqrt(1.0 - z * z)
+    ball = 0.4 * side + np.stack([rho * np.cos(phi), rho * np.sin(phi), z], 1) * (R * (i / m) ** power)[:, None]
+    pos = np.concatenate([rng.random((4000, 3)) * side, ball]).astype(np.float32)
+    return pos[rng.permutation(len(pos))], side
+
+
+def _accept_ms(c, t, dens, l0, p):
+    best = 1e9
+    for _ in range(6):
+        r = c.compaso(t, dens, l0, p)
+        best = min(best, c.stats()["ms_accept"])
+    return r, best
+
+
+# Groups of many times 36 864 members: the buckets beyond the first half of the
+# histogram are counted together and looked at again from where a crossing can
+# lie.  Threshold radius inside the ball (mean 88), outside (400), and density
+# falling so slowly that the enclosed count stays close to the bucket number.
+@pytest.mark.parametrize("m,mean,power", [(300007, 88, 1.0), (300007, 400, 1.0), (300007, 230, 0.36)])
+def test_radius_of_a_huge_group(ctx, m, mean, power):
+    import torch
+    from paper_2110_11408_amd import _lib
+    from paper_2110_11408_amd.api import Context
+    pos, side = _smooth_ball(m, mean, power)
+    p = _lib.default_params(box=side, mean_density=1.0)
+    t = torch.from_numpy(pos).cuda()
+    print(f"[gpu] huge group m={m} mean={mean} power={power}", file=sys.stderr, flush=True)
+    a = ctx.find(t, p)
+    bins = Context(0)
+    bins.set_radius_search("bins")
+    b = bins.find(t, p)
+    assert torch.equal(a["halo_id"], b["halo_id"]) and torch.equal(a["halos"], b["halos"])
+    assert int(a["halos"][:, 4].max()) > 36864  # members enclosed
+
+
+def test_radius_of_a_huge_group_takes_few_passes():
+    """The time of the acceptance grows with the group as a fixed number of passes
+    over it does (8.6 times from 60 000 to 500 000 members; 40 times with a pass
+    per 36 864 buckets)."""
+    import torch
+    from paper_2110_11408_amd import _lib
+    from paper_2110_11408_amd.api import Context
+    c, ms = Context(0), []
+    for m in (60000, 500000):
+        pos, side = _smooth_ball(m, 400, 1.0)
+        p = _lib.default_params(box=side, mean_density=1.0)
+        t = torch.from_numpy(pos).cuda()
+        print(f"[gpu] acceptance time m={m}", file=sys.stderr, flush=True)
+        dens = c.density(t, p)
+        l0, _ = c.l0_fof(t, dens, p)
+        ms.append(_accept_ms(c, t, dens, l0, p)[1])
+        assert c.stats()["n_candidates"] < 10
+    print(f"[gpu] ms_accept {ms}", file=sys.stderr, flush=True)
+    assert ms[1] < 16.0 * ms[0]
