@@ -435,19 +435,21 @@ __global__ __launch_bounds__(kBlock) void k_gc_sums(const int32_t *__restrict__ 
 }
 
 // First candidate of every group (gcoff[G] and counters[kCntCand]: their
-// total), and the number of groups with candidates per size class.  The group
-// count is read on the device.
+// total), the number of groups with candidates per size class, and how many
+// candidates of groups above `late` members are not their group's first.  The
+// group count is read on the device.
 __global__ __launch_bounds__(kBlock) void k_gc_offsets(const uint32_t *__restrict__ gccnt,
                                                        const int32_t *__restrict__ g_size,
-                                                       const uint32_t *__restrict__ sums, bool scanned,
+                                                       const uint32_t *__restrict__ sums, bool scanned, int late,
                                                        uint32_t *__restrict__ gcoff,
                                                        uint32_t *__restrict__ nclass,
                                                        int32_t *__restrict__ counters) {
     __shared__ uint32_t buf[kScanLds];
-    __shared__ uint32_t s_class[kClasses];
+    __shared__ uint32_t s_class[kClasses], s_late;
     const int64_t G = counters[kCntGroups], base = (int64_t)blockIdx.x * kScanTile;
     if (base >= G && blockIdx.x > 0) return;
     if (threadIdx.x < kClasses) s_class[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) s_late = 0u;
     uint32_t v[kScanItems];
     tile_load(gccnt, base, G, buf, v, [](uint32_t x) { return x; });
     uint32_t s = 0;
@@ -463,10 +465,14 @@ __global__ __launch_bounds__(kBlock) void k_gc_offsets(const uint32_t *__restric
         if (g >= G) break;
         gcoff[g] = run;
         run += v[k];
-        if (v[k]) atomicAdd(&s_class[size_class((uint32_t)g_size[g])], 1u);
+        if (v[k] == 0u) continue;
+        const int32_t m = g_size[g];
+        atomicAdd(&s_class[size_class((uint32_t)m)], 1u);
+        if (m > late && v[k] > 1u) atomicAdd(&s_late, v[k] - 1u);
     }
     __syncthreads();
     if (threadIdx.x < kClasses && s_class[threadIdx.x]) atomicAdd(&nclass[threadIdx.x], s_class[threadIdx.x]);
+    if (threadIdx.x == 0 && s_late) atomicAdd(&counters[kCntLate], (int32_t)s_late);
     if (base + kScanTile >= G && threadIdx.x == 0) {
         gcoff[G] = toff + tot;
         counters[kCntCand] = (int32_t)(toff + tot);
@@ -591,7 +597,7 @@ void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
                        w.scan_tmp);
     const bool scanned = scan_sums(w.scan_tmp, tiles, tiles, 1, s);
     hipLaunchKernelGGL(k_gc_offsets, dim3((unsigned)tiles), dim3(kBlock), 0, s, w.gccnt, w.g_size, w.scan_tmp,
-                       scanned, w.gcoff, w.rscan, w.counters);
+                       scanned, accept_late(w), w.gcoff, w.rscan, w.counters);
 }
 
 void launch_candidate_lists(int64_t n, Work &w, hipStream_t s) {

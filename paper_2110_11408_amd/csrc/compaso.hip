@@ -312,7 +312,8 @@ __device__ __forceinline__ int block_min(int v, int *s_min) {
 }
 
 // Candidates (their places in cand_sorted) of groups that are not small: each
-// group's densest from the front of the list, the others from its back.
+// group's densest from the front of the list, the others from its back (the
+// list of the late ones has those at its front, and rests null).
 struct AcceptItems {
     int32_t *list;
     uint32_t *firsts, *rests, cap;
@@ -347,8 +348,8 @@ __global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restr
                                                          int32_t *__restrict__ h_ienc,
                                                          int32_t *__restrict__ h_gid,
                                                          int32_t *__restrict__ g_nh,
-                                                         AcceptItems mid, AcceptItems big,
-                                                         int32_t *__restrict__ enc,
+                                                         AcceptItems mid, AcceptItems big, AcceptItems late,
+                                                         int late_most, int32_t *__restrict__ enc,
                                                          uint64_t *clock) {
 #pragma clang fp contract(off)
     stamp(clock);
@@ -366,15 +367,19 @@ __global__ __launch_bounds__(kBlock) void k_accept_small(const uint32_t *__restr
         const uint32_t cs = gcoff[gi], ce = gcoff[gi + 1];
         if (route_all || m + 1 > kWaveHist || ce - cs > 1u) {
             const AcceptItems &to = m + 1 <= mid_most ? mid : big;
+            const bool wait = m > late_most;
             uint32_t at = 0;
             if (lane == 0) {
                 to.list[atomicAdd(to.firsts, 1u)] = (int32_t)cs;
                 enc[cs] = -1;  // not known yet
-                if (ce - cs > 1u) at = atomicAdd(to.rests, ce - cs - 1u);
+                if (ce - cs > 1u) at = atomicAdd(wait ? late.firsts : to.rests, ce - cs - 1u);
             }
             at = lane_get(at, 0);
-            for (uint32_t k = lane; k < ce - cs - 1u; k += 64)
-                to.list[to.cap - 1u - (at + k)] = (int32_t)(cs + 1u + k);
+            for (uint32_t k = lane; k < ce - cs - 1u; k += 64) {
+                const int32_t item = (int32_t)(cs + 1u + k);
+                if (wait) late.list[at + k] = item;
+                else to.list[to.cap - 1u - (at + k)] = item;
+            }
             continue;
         }
         const int c = cand_sorted[cs];
@@ -552,7 +557,9 @@ __device__ __forceinline__ int64_t first_possible(const uint32_t *s_hist, int64_
 // 6.8 ms on the 512^3 box, 300 us on the 256^3 one and 152 us on 1.3e6 particles
 // at their labels; 3.8 ms, 195 us and 72 us now).  The groups'
 // densest candidates come first; a candidate that lies inside alpha R of that
-// one, if its i is known by then, is left out (its i is never asked for).
+// one, if its i is known by then, is left out (its i is never asked for).  In
+// large groups (accept_late) the others are a list and a launch of their own, so
+// that it is.
 //   BINS = false: i from the bucket histogram of all particles of the group, in
 //                 LDS; with more buckets than fit (HL), half of it holds the
 //                 first ones and the other half the rest in coarse ones, which
@@ -593,7 +600,7 @@ __global__ __launch_bounds__(NT) void k_accept_eval(AcceptItems items, Boxes bx,
     __shared__ uint32_t s_red[NT / 64], s_c;
     __shared__ int s_min[NT / 64];
     const int tid = threadIdx.x;
-    const uint32_t firsts = *items.firsts, count = firsts + *items.rests;
+    const uint32_t firsts = *items.firsts, count = firsts + (items.rests ? *items.rests : 0u);
     for (uint32_t q = blockIdx.x; q < count; q += gridDim.x) {
         const uint32_t cr = (uint32_t)items.list[q < firsts ? q : items.cap - 1u - (q - firsts)];
         const int c = cand_sorted[cr];
@@ -1149,6 +1156,19 @@ static int bits_for(int64_t x) {
     return b;
 }
 
+// A group's other candidates are evaluated beside its densest one, which costs
+// nothing but idle compute units while they are few, and halves the time where
+// they are nuclei of their own (groups of 40 000 in pairs: 121 us, 216 one after
+// the other); but those inside its radius, nearly all in a large group with one
+// centre, are evaluated for nothing.  By the histogram that is two passes over the
+// group each: 250 000 members with 152 such candidates 534 us together and 604
+// after it, 500 000 with 429 of them 1652 and 1187.  By the radial bins it is a
+// pass for every bin out to a far crossing: 15 000 members in merging balls 103 us
+// together and 163 after it, 30 000 with four such candidates 353 and 80, 500 000
+// with 429 9.53 ms and 1.19.
+constexpr int kLateHist = 4 * kHistBig, kLateBins = 16384;
+int accept_late(const Work &w) { return w.radius_bins ? kLateBins : kLateHist; }
+
 void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx, Work &w, hipStream_t s) {
     // groups with candidates (at most min(G, NC)): those of one candidate and few
     // particles one wavefront each; the candidates of the others are listed (in
@@ -1162,6 +1182,7 @@ void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx,
     auto counter = [&](int k) { return reinterpret_cast<uint32_t *>(w.counters + k); };
     const AcceptItems mid{reinterpret_cast<int32_t *>(w.tmp_a), counter(kCntMidFirst), counter(kCntMidRest), (uint32_t)n};
     const AcceptItems big{reinterpret_cast<int32_t *>(w.tmp_b), counter(kCntBigFirst), counter(kCntBigRest), (uint32_t)n};
+    const AcceptItems late{reinterpret_cast<int32_t *>(w.tmp_d), counter(kCntLateListed), nullptr, (uint32_t)n};
     int32_t *enc = reinterpret_cast<int32_t *>(w.tmp_c);
     const int64_t ncu = w.ncu > 0 ? w.ncu : 1;
     auto cap = [](int64_t a, int64_t b) { return (unsigned)(a < b ? a : b); };
@@ -1171,7 +1192,8 @@ void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx,
     const bool few = NC <= 4 * ncu;
     hipLaunchKernelGGL(k_accept_small, dim3(cap((bound + kBlock / 64 - 1) / (kBlock / 64), 6 * ncu)), dim3(kBlock),
                        0, s, counter(kCntListed), bins, few ? 0 : kHistMid, bx, w.glist, w.g_start, w.g_size, w.gcoff, w.cand_sorted,
-                       w.mem, w.spos, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh, mid, big, enc, w.clock + kClockAccept);
+                       w.mem, w.spos, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh, mid, big, late, accept_late(w), enc,
+                       w.clock + kClockAccept);
     if (!few)
         hipLaunchKernelGGL((bins ? k_accept_eval<kBlock, kHistMid, true> : k_accept_eval<kBlock, kHistMid, false>),
                            dim3(cap(NC, 4 * ncu)), dim3(kBlock), 0, s, mid, bx, w.gid_of, w.g_start, w.g_size, w.gcoff,
@@ -1179,6 +1201,10 @@ void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx,
     if (few || M >= kHistMid)
         hipLaunchKernelGGL((bins ? k_accept_eval<1024, kHistBig, true> : k_accept_eval<1024, kHistBig, false>),
                            dim3(cap(NC, ncu)), dim3(1024), 0, s, big, bx, w.gid_of, w.g_start, w.g_size, w.gcoff,
+                           w.cand_sorted, w.mem, w.spos, enc, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh);
+    if (w.nlate > 0)
+        hipLaunchKernelGGL((bins ? k_accept_eval<1024, kHistBig, true> : k_accept_eval<1024, kHistBig, false>),
+                           dim3(cap(w.nlate, ncu)), dim3(1024), 0, s, late, bx, w.gid_of, w.g_start, w.g_size, w.gcoff,
                            w.cand_sorted, w.mem, w.spos, enc, w.h_nuc, w.h_ienc, w.h_gid, w.g_nh);
     // groups of two candidates at least
     if (NC > 1)

@@ -504,14 +504,15 @@ hf_status candidates(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, Coun
     hf::launch_candidates(pl.n, bx, w, s);
     hf::WordSrc src{};
     const int32_t *words[] = {w.counters + hf::kCntGroups, w.counters + hf::kCntMembers,
-                              w.counters + hf::kCntCand, w.counters + hf::kCntHard, w.err, w.err + 1};
-    for (int k = 0; k < 6; k++) src.p[k] = reinterpret_cast<const uint32_t *>(words[k]);
-    HIP_OK(c, hf::publish_words(src, 6, c->host, s));
+                              w.counters + hf::kCntCand, w.counters + hf::kCntHard, w.err, w.err + 1,
+                              w.counters + hf::kCntLate};
+    for (int k = 0; k < 7; k++) src.p[k] = reinterpret_cast<const uint32_t *>(words[k]);
+    HIP_OK(c, hf::publish_words(src, 7, c->host, s));
     HIP_OK(c, hipEventRecord(c->pub, s));
     hf::launch_candidate_lists(pl.n, w, s);
     HIP_OK(c, hipEventSynchronize(c->pub));
-    uint32_t r[6];
-    hf::collect_words(c->host, 6, r);
+    uint32_t r[7];
+    hf::collect_words(c->host, 7, r);
     const hf_status st = err_status(c, r[4], r[5], &pl);
     if (st != HF_OK) {
         // a failed call also ends synchronized with its stream
@@ -521,6 +522,7 @@ hf_status candidates(Lane *c, const Plan &pl, const hf::Boxes &bx, Work &w, Coun
     ct->groups = r[0];
     ct->candidates = r[2];
     w.nhard = r[3];
+    w.nlate = r[6];
     c->stats.n_groups = r[0];
     c->stats.n_members = r[1];
     return HF_OK;
@@ -651,6 +653,7 @@ hf_status begin(Lane *c, const Plan &pl, const float *pos, hf::Boxes *bx, Work *
     w->ndcells = counts[1];
     w->nsparse = counts[2];
     w->nhard = 0;
+    w->nlate = 0;
     return HF_OK;
 }
 

@@ -400,7 +400,7 @@ struct Work {
     uint64_t *submax;                                  // densest particle per dense sub-cell
     int32_t *subarg;
     int32_t *hardlist;                                 // candidate tests left after stage 1
-    int64_t nchunks, ndcells, nsparse, nhard;
+    int64_t nchunks, ndcells, nsparse, nhard, nlate;
     int ncu;                         // compute units (grids of the persistent kernels)
     bool radius_bins;                // R_L1 by radial bins instead of the whole-group histogram
     // density / FoF / groups (sorted order unless noted)
@@ -518,6 +518,8 @@ enum {
     kCntSparse = 3,     // particles of sparse cells
     kCntMidRest = 4,    // candidates of medium and of large groups to evaluate:
     kCntBigRest = 5,    // the groups' densest, and the others
+    kCntLate = 6,       // the others of groups above accept_late members,
+    kCntLateListed = 7, // and those of them listed
     kCntMidFirst = 9,
     kCntBigFirst = 11,
     kCntHard = 8,       // hard cases of the candidate stage
@@ -636,6 +638,9 @@ void launch_extent(int64_t n, const Boxes &bx, Work &w, hipStream_t s);
 // with candidates in descending size (the largest first, over all boxes).
 void launch_candidates(int64_t n, const Boxes &bx, Work &w, hipStream_t s);
 void launch_candidate_lists(int64_t n, Work &w, hipStream_t s);
+// Members from which on a group's other candidates wait for the densest one's
+// enclosed count (k_accept_eval).
+int accept_late(const Work &w);
 // Groups with candidates (their count is read on the device; grid bound
 // min(G, NC)); M = members of all groups, n = particles.
 void launch_accept(int64_t n, int64_t G, int64_t NC, int64_t M, const Boxes &bx, Work &w, hipStream_t s);

@@ -398,3 +398,32 @@ def test_radius_of_a_huge_group_takes_few_passes():
         assert c.stats()["n_candidates"] < 10
     print(f"[gpu] ms_accept {ms}", file=sys.stderr, flush=True)
     assert ms[1] < 16.0 * ms[0]
+
+
+@pytest.mark.parametrize("m", [30000, 500000])
+def test_candidates_inside_the_first_nucleus_cost_little(m):
+    """A ball with many candidates inside its centre's radius, against a smooth
+    one of the same size with one candidate, by the radial bins (2.5 and 8 times
+    the time when they are evaluated all the same)."""
+    import torch
+    from paper_2110_11408_amd import _lib
+    from paper_2110_11408_amd.api import Context
+    c, ms = Context(0), []
+    c.set_radius_search("bins")
+    for noisy in (False, True):
+        pos, side = _smooth_ball(m, 400, 1.0)
+        if noisy:
+            rng = np.random.default_rng(3)
+            u = rng.normal(size=(m, 3))
+            u *= rng.random((m, 1)) * side / 6.5 / np.linalg.norm(u, axis=1)[:, None]
+            pos = np.concatenate([rng.random((4000, 3)) * side, 0.4 * side + u]).astype(np.float32)
+        p = _lib.default_params(box=side, mean_density=1.0)
+        t = torch.from_numpy(pos).cuda()
+        print(f"[gpu] acceptance time m={m} noisy={noisy}", file=sys.stderr, flush=True)
+        dens = c.density(t, p)
+        l0, _ = c.l0_fof(t, dens, p)
+        r, best = _accept_ms(c, t, dens, l0, p)
+        ms.append(best)
+        assert r["n_halos"] >= 1 and (c.stats()["n_candidates"] > 1) == noisy
+    print(f"[gpu] ms_accept {ms}", file=sys.stderr, flush=True)
+    assert ms[1] < 2.0 * ms[0]
