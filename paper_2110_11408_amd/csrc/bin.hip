@@ -1373,6 +1373,12 @@ int bit_width(uint64_t x) {
 // passed kLocal and the bucket sort took 140 us instead of 33 us on 2.6e5.
 constexpr int64_t kPartitionMost = (int64_t)1 << 19;
 
+// Top bits of the partition pass: buckets of 256 to 512 particles on average.
+int partition_bits(int64_t n) {
+    const int top = bit_width((uint64_t)((n - 1) / 256));
+    return top < kPartBits ? top : kPartBits;
+}
+
 // Sort plan: key bits; index bits when packed (0 = separate payload), and top
 // bits of the buckets of the partition pass (-1: none); the digits of the sort
 // that carries positions (dl < 0: none); the passes of D bits of the radix sort.
@@ -1401,8 +1407,7 @@ SortPlan sort_plan(int64_t n, int64_t ncell, int nsub_max) {
     r.rec = RecPlan{0, -1, -1};
     if (radix) return r;
     if (r.ib > 0 && n <= kPartitionMost) {
-        r.top = bit_width((uint64_t)((n - 1) / 256));
-        if (r.top > kPartBits) r.top = kPartBits;
+        r.top = partition_bits(n);
         if (r.top > r.bits) r.top = r.bits;
         return r;
     }
@@ -1423,11 +1428,14 @@ SortPlan sort_plan(int64_t n, int64_t ncell, int nsub_max) {
 }
 
 int64_t radix_hist_len(int64_t n) {
-    // room for the widest digit, so that every sort of up to n keys fits
+    // the widest digit of a sort of n particles, and of every radix sort of up to
+    // n keys
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    const int bits = n <= kPartitionMost ? kPartBits : kRecBits;
-    return ((int64_t)1 << bits) * (ntiles > 0 ? ntiles : 1) + 1;
+    const int first = n > kPartitionMost ? kRecBits : (n > 0 ? partition_bits(n) : 0);
+    return ((int64_t)1 << (first > kRadixMaxBits ? first : kRadixMaxBits)) * (ntiles > 0 ? ntiles : 1) + 1;
 }
+
+int64_t bin_tiles(int64_t n) { return n <= kFineTilesMost ? (n + kFineTile - 1) / kFineTile : scan_tiles(n); }
 
 uint64_t *radix_sort_keys(uint64_t *a, uint64_t *b, int64_t n, int lo, int bits, Work &w, hipStream_t s) {
     if (n <= 1 || bits <= 0) return a;
@@ -1537,7 +1545,7 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
     // idle and a workgroup's rounds be the time (20 000 particles: the two
     // kernels took 14 and 17 us, 5 and 8 with the smaller tiles)
     const bool fine = n <= kFineTilesMost;
-    const int64_t lt = fine ? (n + kFineTile - 1) / kFineTile : scan_tiles(n);
+    const int64_t lt = bin_tiles(n);
     // the index words are zeroed by the marks' workgroups, by a launch of their
     // own when there are too many for them (a nearly empty grid)
     const int64_t words = occ_words(ncell);

@@ -213,12 +213,11 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->sloc = c.take<float4>(n);
     w->pq = c.take<float4>(n + 32);
     w->scell = c.take<uint32_t>(n);
-    w->marks.chunk = c.take<uint64_t>(n / 64 + 1);
-    w->marks.dcell = c.take<uint64_t>(n / 64 + 1);
-    w->marks.sparse = c.take<uint64_t>(n / 64 + 1);
-    w->marks.head = c.take<uint64_t>(n / 64 + 1);
-    w->marks.before = c.take<uint32_t>(n / 64 + 1);
-    w->marks.dbefore = c.take<uint32_t>(n / 64 + 1);
+    const int64_t nw = n / 64 + 1;
+    uint64_t *const marks = c.take<uint64_t>(5 * nw);
+    if (marks) w->marks = hf::Marks{marks, marks + nw, marks + 2 * nw, marks + 3 * nw,
+                                    reinterpret_cast<uint32_t *>(marks + 4 * nw),
+                                    reinterpret_cast<uint32_t *>(marks + 4 * nw) + nw};
     w->tmp_a = c.take<uint32_t>(n1);
     w->tmp_b = c.take<uint32_t>(n1);
     w->tmp_c = c.take<uint32_t>(n1);
@@ -256,9 +255,7 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->h_count = c.take<uint32_t>(n1);
     w->tflag = c.take<uint32_t>(n / 32 + 2);
     w->tpos = c.take<uint32_t>(n / 32 + 3);
-    int64_t scan_len = ncell > n ? ncell : n;
-    if (rhl > scan_len) scan_len = rhl;
-    w->scan_tmp = c.take<uint32_t>(hf::scan_tmp_words(scan_len + 1));
+    w->scan_tmp = c.take<uint32_t>(hf::scan_tmp_words(n));
     w->counters = c.take<int32_t>(16);
     w->err = c.take<int32_t>(4);
     w->geo = c.take<Geo>(nbox);

@@ -596,10 +596,11 @@ hipError_t publish_words(const WordSrc &src, int k, uint32_t *host, hipStream_t 
 void collect_words(const uint32_t *host, int k, uint32_t *out);
 void fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
-// Exclusive scan: out[0..n] with out[n] = total.  tmp: scan_tmp_words(n) words.
+// Exclusive scan: out[0..n] with out[n] = total.  tmp: a word per 4096 elements.
 void scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
 // Exclusive scan of the number of set bits of every word (same layout and tmp).
 void scan_bits_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
+// Words of Work::scan_tmp for n particles.
 int64_t scan_tmp_words(int64_t n);
 
 // Every launcher works on all boxes of the call at once: n is the particle
@@ -612,6 +613,8 @@ void launch_halo_stats(int64_t n, int64_t G, int64_t M, const Geo &g, double par
                        int32_t *group_members, hipStream_t s);
 // Length of the radix count arrays for n particles.
 int64_t radix_hist_len(int64_t n);
+// Tiles of the kernels that mark and list n sorted particles.
+int64_t bin_tiles(int64_t n);
 // Stable LSD radix sort of n 64-bit keys a[] by their bits [lo, lo + bits),
 // using b[] as the second buffer and w's count arrays; returns the buffer
 // (a or b) that holds the result.

@@ -180,9 +180,12 @@ bool scan_sums(uint32_t *sums, int64_t tiles, int64_t stride, int arrays, hipStr
     return true;
 }
 
-// Four runs of tile sums (the binning scans four quantities at once, of up to
-// 4096 smaller tiles when there are few particles).
-int64_t scan_tmp_words(int64_t n) { return 4 * scan_tiles(n) + 4 * 4096 + 16; }
+// Tile sums of the longest scans: of four quantities at once over the binning's
+// tiles, two over the keys, and one over the radix counts.
+int64_t scan_tmp_words(int64_t n) {
+    const int64_t bin = 4 * bin_tiles(n), keys = 2 * scan_tiles(n), counts = scan_tiles(radix_hist_len(n));
+    return (bin > keys ? (bin > counts ? bin : counts) : (keys > counts ? keys : counts)) + 16;
+}
 
 template <bool kBits>
 static void scan_impl(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {

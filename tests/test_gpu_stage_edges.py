@@ -427,3 +427,22 @@ def test_candidates_inside_the_first_nucleus_cost_little(m):
         assert r["n_halos"] >= 1 and (c.stats()["n_candidates"] > 1) == noisy
     print(f"[gpu] ms_accept {ms}", file=sys.stderr, flush=True)
     assert ms[1] < 2.0 * ms[0]
+
+
+@pytest.mark.parametrize("n,side,kw,budget", [
+    (1, 1.5, {"mean_density": 1.0}, 18696), (1, 1.5, {"mean_density": 30.0, "l_fof": 0.6}, 20232),
+    (30, 0.0, {"l_fof": 0.6}, 19464), (30, 0.0, {}, 25352), (100, 0.0, {}, 50184), (257, 0.0, {"l_fof": 0.6}, 88584),
+    (1000, 0.0, {"l_fof": 0.6}, 291080), (2049, 13.0, {"mean_density": 0.001}, 758024)])
+def test_scratch_of_small_calls(n, side, kw, budget):
+    """The device memory that these calls have always done with is enough."""
+    import torch
+    from paper_2110_11408_amd import _lib
+    from paper_2110_11408_amd.api import Context
+    side = side or float(n) ** (1.0 / 3.0)
+    rng = np.random.default_rng(n)
+    pos = (rng.random((n, 3)) * side).astype(np.float32)
+    pos[pos >= np.float32(side)] = 0.0
+    print(f"[gpu] hf_density n={n} budget={budget}", file=sys.stderr, flush=True)
+    p = _lib.default_params(box=side, **kw)
+    dens = Context(0, budget).density(torch.from_numpy(pos).cuda(), p)
+    assert len(density_violations(dens.cpu().numpy(), oracle.density(pos, box=side, **kw))) == 0
