@@ -1411,15 +1411,16 @@ SortPlan sort_plan(int64_t n, int64_t ncell, int nsub_max) {
         if (r.top > r.bits) r.top = r.bits;
         return r;
     }
-    // the records' second buffer lies over the sub-cell tables (2 (nsub + 1)
-    // bytes per particle); buckets of 300 to 1000 particles on average, so many
-    // that the low bits fit beside the place in the bucket
+    // the records' second buffer (Work::rec2) lies over the sub-cell tables, 16
+    // bytes an entry, which hold an entry per particle from 7 sub-cells on;
+    // buckets of 300 to 1000 particles on average, so many that the low bits fit
+    // beside the place in the bucket
     int top = bit_width((uint64_t)((n - 1) / 1024));
     if (top < r.bits - kLowMost) top = r.bits - kLowMost;
     if (top > 2 * kRecBits) top = 2 * kRecBits;
     if (top > r.bits) top = r.bits;
     // (a grid of far more cells than particles would leave buckets of a few)
-    if (nsub_max + 1 >= 8 && top >= 2 && r.bits - top <= kLowMost && (n >> top) >= 128) {
+    if (sub_entries(n, nsub_max) >= n && top >= 2 && r.bits - top <= kLowMost && (n >> top) >= 128) {
         r.rec.low = r.bits - top;
         r.rec.dl = top / 2;
         r.rec.dh = top - r.rec.dl;
@@ -1485,11 +1486,11 @@ void launch_bin(const float *pos, int64_t n, int64_t ncell, const Boxes &bx, Wor
                            r.ib, to);
     } else if (r.rec.dl >= 0) {
         // first pass into the radix key block (16 bytes per particle), second
-        // into the sub-cell tables, which are written after the binning; the
+        // over the sub-cell tables, which are written after the binning; the
         // second digits lie in the sub-cell indices' array and the buckets'
         // starts in the radix payload (both free until the buckets are sorted,
         // which read neither after writing them)
-        float4 *ra = reinterpret_cast<float4 *>(w.rkey[0]), *rb = reinterpret_cast<float4 *>(w.subtab);
+        float4 *ra = reinterpret_cast<float4 *>(w.rkey[0]), *rb = w.rec2;
         const int nl = 1 << r.rec.dl, nh = 1 << r.rec.dh;
         const bool one = bx.nbox == 1;
         hipLaunchKernelGGL(one ? k_rec_count<true> : k_rec_count<false>, tiles, dim3(256), 0, s, pos, n, bx, r.rec,

@@ -226,9 +226,13 @@ size_t carve(char *base, int64_t n, int64_t ncell, int nsub, int64_t rhl, int nb
     w->sparse = c.take<int32_t>(n1);
     w->dcells = c.take<uint32_t>(n1);
     w->hardlist = c.take<int32_t>(n1);
-    w->subtab = c.take<uint32_t>((n / hf::kDenseMin + 1) * (nsub + 1));
-    w->submax = c.take<uint64_t>((n / hf::kDenseMin + 1) * (nsub + 1));
-    w->subarg = c.take<int32_t>((n / hf::kDenseMin + 1) * (nsub + 1));
+    // the tables of the dense sub-cells (4 + 4 + 8 bytes an entry) in one block,
+    // which the binning's second record buffer lies over
+    const int64_t nt = hf::sub_entries(n, nsub);
+    w->rec2 = c.take<float4>(nt);
+    w->submax = reinterpret_cast<uint64_t *>(w->rec2);
+    w->subtab = reinterpret_cast<uint32_t *>(w->submax + nt);
+    w->subarg = reinterpret_cast<int32_t *>(w->subtab + nt);
     w->dens_s = c.take<float>(n);
     w->parent = c.take<int32_t>(n);
     w->minorig = c.take<int32_t>(n);

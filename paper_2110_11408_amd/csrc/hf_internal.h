@@ -382,6 +382,10 @@ __device__ __forceinline__ uint32_t cell_range(const Cells &cells, uint32_t c, u
     return cell_range(cells, cells.occ[c / kOccCells], c, a, e);
 }
 
+// Entries of a table of the dense cells' sub-cells (at most n / kDenseMin dense
+// cells, a row of nsub + 1 entries each).
+inline int64_t sub_entries(int64_t n, int nsub) { return (n / kDenseMin + 1) * (nsub + 1); }
+
 struct Work {
     // binning
     Cells cells;                     // cell -> particles, dense-cell number
@@ -396,7 +400,9 @@ struct Work {
     Marks marks;                     // dense chunk and cell heads, sparse particles, cell heads
     uint32_t *tmp_a, *tmp_b, *tmp_c, *tmp_d;  // scratch of n + 1 words each, in one run
     int32_t *chunks, *sparse;
-    uint32_t *dcells, *subtab;
+    uint32_t *dcells;
+    float4 *rec2;                                      // sub_entries records, over the three tables:
+    uint32_t *subtab;                                  // first particle per dense sub-cell
     uint64_t *submax;                                  // densest particle per dense sub-cell
     int32_t *subarg;
     int32_t *hardlist;                                 // candidate tests left after stage 1
