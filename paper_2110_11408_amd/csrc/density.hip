@@ -269,7 +269,7 @@ __device__ __forceinline__ void density_chunk(const Geo &g, uint32_t h, uint32_t
             flush();
         };
         // The blocks in stream order come from a generator (range gk, next
-        // block gj, range end gb); four of them are loaded ahead in a ring.
+        // block gj, range end gb).
         int gk = k;
         uint32_t gj = j0, gb = b;
         auto gen = [&](int &ko, uint32_t &jo) {

@@ -109,11 +109,6 @@ __device__ __forceinline__ int hooks_map(const Hooks &h, int x) {
     return x;
 }
 
-// A value equal in every lane, moved to a scalar register.
-__device__ __forceinline__ float uniform(float v) {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-
 // The lanes lk are linked to a particle whose set has the local root r.  In
 // the wavefront's view of the forest (every root it holds is a node of its
 // set), the smallest of r and the lanes' roots becomes the root of all of

@@ -24,13 +24,11 @@ struct Geo {
     double inv_nc;         // 1 / nc (cell coordinates from a cell id)
     int ksub;              // sub-cells per cell side (sub-cell diagonal < l)
     int nsub;              // ksub^3
-    int rsub;              // FoF reach in sub-cells: ceil(l / sub-cell side)
     double inv_sub;        // ksub / cell
-    double sub2;           // squared sub-cell side
     int face_sub_in_b;     // any two points of face-adjacent sub-cells are closer than b
     double b2, l2;         // FP64 squared radii of the peak test and of FoF links
     float l2b_lo, l2b_hi;  // (l/b)^2 shrunk / grown by the FP32 prefilter margin
-    float b2b_lo, b2b_hi;  // 1 shrunk / grown by the same margin (peak test, units of b^2)
+    float b2b_hi;          // 1 grown by the same margin (peak test, units of b^2)
     double norm;           // density normalisation 15/(8 pi b^3 nbar)
     int self_count;
     double dl0;            // L0 density threshold
@@ -489,11 +487,6 @@ __device__ __forceinline__ void seg_append(const SegList &sl, const bool (&take)
         if (take[u]) sl.list[(int64_t)seg * sl.cap + at + (uint32_t)__popcll(m[u] & ((1ull << lane) - 1ull))] = i[u];
         at += (uint32_t)__popcll(m[u]);
     }
-}
-__device__ __forceinline__ void seg_append(const SegList &sl, bool take, int32_t i) {
-    const bool t[1] = {take};
-    const int32_t v[1] = {i};
-    seg_append<1>(sl, t, v);
 }
 
 // The share of one of kBlock / W lane groups per workgroup in a list: entries
