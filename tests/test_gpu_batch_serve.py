@@ -23,8 +23,8 @@ pytestmark = pytest.mark.gpu
 
 # (n, seed, nmax, halo_frac); n = 0 is an empty box of side 10.  The last box
 # (3.2M particles, haloes up to 20000 particles) is of the size of the largest
-# batched boxes and served requests: its largest L0 groups keep part of their
-# acceptance histograms in global memory.
+# batched boxes and served requests: its largest L0 groups are accepted with
+# 1024 threads a candidate.
 SPECS = [(3000, 201, 500, 0.5), (0, 0, 0, 0.0), (20000, 202, 3000, 0.6), (700, 203, 200, 0.4),
          (9001, 204, 1500, 0.5), (45000, 205, 6000, 0.3), (3200000, 206, 20000, 0.6)]
 BIG = 6

@@ -491,9 +491,12 @@ def test_separate_payload_sort_gives_same_result(ctx):
 
 
 def test_density_wide_record_loads_give_same_result(ctx):
-    """The dense-cell density loads its records through one buffer descriptor
-    while the byte offsets fit in 32 bits (below about 2.7e8 particles), else
-    through a descriptor per block; both forms give bit-identical densities."""
+    """The density of the dense cells loads its records through one buffer
+    descriptor while the byte offsets fit in 32 bits (below about 2.7e8
+    particles), else through a descriptor per block.  This box, whose chunks do
+    not fill the chip, takes a wavefront per row block with the one descriptor
+    and a wavefront per chunk with the others; the densities are the same bits.
+    (A wavefront per chunk with the one descriptor: test_density_and_fof_forms.)"""
     import os
     pos, L, _ = _case("s40123")
     a = gpu_find(ctx, pos, box=L)
@@ -577,5 +580,5 @@ def test_full_size_512_sampled(ctx):
     np.testing.assert_array_equal(tab["id"][in_pick], res["table"]["id"])
     np.testing.assert_array_equal(tab["n"][in_pick], res["table"]["n"])
     np.testing.assert_array_equal(tab["n_enclosed"][in_pick], res["table"]["ienc"])
-    # the largest sampled groups keep part of their histogram in global memory
+    # the largest sampled groups have more buckets than the histogram in LDS
     assert counts[np.isin(labels, big)].max() > 36864

@@ -9,9 +9,8 @@ search on the GPU densities.  The group order is compared element by element
 with the oracle's definition (rows in table order, ascending original index,
 then the particles of no halo).  Cases: boxes of 40k (many 256-thread tiles,
 ragged tails), 262k (the small benchmark box) and 3.2M particles (haloes of up
-to 20000 particles: groups run by 1024-thread workgroups and searched bins
-whose histograms spill to global memory), an empty input and a box without
-haloes.
+to 20000 particles: candidates run by 1024-thread workgroups), an empty input and
+a box without haloes.
 """
 from __future__ import annotations
 

@@ -259,6 +259,56 @@ def test_cell_index(ctx, clumps, background, mean_density):
     _check(ctx, pos, box=side, mean_density=mean_density)
 
 
+# Dense chunks: a wavefront per row block of 16 up to 40 chunks per compute unit,
+# one per chunk beyond; three wavefronts for the FoF links of a chunk up to 24
+# chunks per compute unit, one beyond.  A box alone takes the former, the same box
+# in a pass with boxes of many chunks the latter, and with HF_DENSITY_WIDE=1 alone a
+# wavefront per chunk with a buffer descriptor per block.  Chunks of 8 to 64
+# particles (one to four row blocks), cells of several chunks, and sparse cells
+# around them.
+def _chunk_box(seed):
+    rng = np.random.default_rng(seed)
+    side = 25.0
+    pos = [rng.random((6000, 3)) * side]
+    for k, m in enumerate(list(range(8, 66)) + [80, 127, 128, 129, 200, 333]):
+        at = np.array([k % 8, k // 8 % 8, k // 64]) * 3.0 + 0.5
+        pos.append(at + rng.random((m, 3)) * (0.03 if k % 3 else 0.5))
+    pos = np.concatenate(pos).astype(np.float32)
+    return pos[rng.permutation(len(pos))], side
+
+
+def test_density_and_fof_forms(ctx, monkeypatch):
+    import torch
+    from paper_2110_11408_amd import _lib
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    boxes = [_chunk_box(1) + ({"mean_density": 1.0},), synth.small_box(40123, seed=11, nmax=6000)[:2] + ({},),
+             synth.small_box(262144, seed=12, nmax=20000)[:2] + ({},)]
+    # a filler of cells of a dozen particles, none in a group
+    rng = np.random.default_rng(2)
+    n = 20 * 40 * ncu
+    side = float(n) ** (1.0 / 3.0)
+    fill = (rng.random((n, 3)) * side).astype(np.float32)
+    fill[fill >= np.float32(side)] = 0.0
+    boxes.append((fill, side, {"mean_density": 0.064 / 12.0, "delta_l0_min": 1e9}))
+    params = [_lib.default_params(box=b[1], **b[2]) for b in boxes]
+    pos = torch.from_numpy(np.concatenate([b[0] for b in boxes])).cuda()
+    offs = np.concatenate([[0], np.cumsum([len(b[0]) for b in boxes])])
+    print(f"[gpu] hf_find_batch forms n={len(pos)}", file=sys.stderr, flush=True)
+    r = ctx.find_batch(pos, offs, params, n_lanes=1)
+    assert ctx.stats()["n_dense_chunks"] > 40 * ncu
+    for k in range(3):
+        t = pos[offs[k]:offs[k + 1]].contiguous()
+        for wide in ("0", "1"):
+            monkeypatch.setenv("HF_DENSITY_WIDE", wide)
+            print(f"[gpu] hf_find forms box={k} wide={wide}", file=sys.stderr, flush=True)
+            one = ctx.find(t, params[k])
+            assert ctx.stats()["n_dense_chunks"] <= 24 * ncu
+            for key in ("density", "l0_id", "halo_id"):
+                assert torch.equal(one[key], r[key][offs[k]:offs[k + 1]])
+            assert torch.equal(one["halos"], r["halos"][k])
+        assert int((one["l0_id"] > 0).sum()) > 100
+
+
 # The three outputs of a find leave as records: scattered below 2^22 particles,
 # partitioned by original index beyond, in one pass up to 2^24 and two above.
 # The density and the L0 labels alone, and the halo labels alone, are written
