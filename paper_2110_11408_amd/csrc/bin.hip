@@ -459,7 +459,10 @@ __device__ __forceinline__ Share bin_share(const uint32_t *hist, int64_t m, int6
         at += c[q];
     }
     __syncthreads();
-    const Share r{s_sel[0], s_sel[1], (int64_t)s_sel[2], (int64_t)s_sel[3] - (int64_t)s_sel[2]};
+    // the same words for all, in scalar registers: the workgroup branches on them
+    // between barriers
+    auto word = [&](int k) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)s_sel[k]); };
+    const Share r{word(0), word(1), (int64_t)word(2), (int64_t)word(3) - (int64_t)word(2)};
     __syncthreads();  // hist and s_tot are free
     return r;
 }

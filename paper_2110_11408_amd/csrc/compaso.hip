@@ -611,12 +611,14 @@ __global__ __launch_bounds__(NT) void k_accept_eval(AcceptItems items, Boxes bx,
         const Geo &g = bx.geo[__builtin_amdgcn_readfirstlane(box_of(bx, (uint32_t)c))];
         const float4 pc = spos[c];
         if (cr != cs) {
-            // one answer for the workgroup: another one may write it meanwhile
+            // one answer for the workgroup: another one may write it meanwhile.
+            // Scalar, so that the workgroup leaves for its next item as one.
             if (tid == 0) s_c = (uint32_t)ldi(enc + cs);
             __syncthreads();
-            const int32_t i0 = (int32_t)s_c;
+            const int32_t i0 = __builtin_amdgcn_readfirstlane((int32_t)s_c);
             __syncthreads();
-            if (i0 >= 0 && g.K2 * e3(d2_exact(pc, spos[cand_sorted[cs]], g.L, g.half)) < g.A6 * ii(i0)) continue;
+            const bool inside = i0 >= 0 && g.K2 * e3(d2_exact(pc, spos[cand_sorted[cs]], g.L, g.half)) < g.A6 * ii(i0);
+            if (__builtin_amdgcn_readfirstlane((int)inside)) continue;
         }
         int64_t found = m;
         if constexpr (BINS) {
