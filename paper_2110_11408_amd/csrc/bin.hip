@@ -7,13 +7,13 @@
 //   1. key = cell * k^3 + sub-cell per particle (range check of the input), and
 //      the digit counts of the first pass on the way;
 //   2. the keys are put into buckets by their top bits, and a workgroup per
-//      bucket sorts it by the other bits in LDS and writes the sorted records.
+//      bucket (several for a long one) sorts it by the other bits in LDS and
+//      writes the sorted records.
 //      Up to kPartitionMost particles one pass over (key, index) words makes
 //      up to 1024 buckets; beyond, two passes make up to 2^18, and carry the
 //      positions with them, so that nothing is gathered from the unordered
 //      input.  (A least-significant-digit radix sort over all digits remains
-//      for keys and indices that need more than 64 bits, for sub-cells too few
-//      to lend their tables as a buffer, and for the later stages' lists.)
+//      for what neither takes, see sort_plan, and for the later stages' lists.)
 //      A pass over a digit: a block counts the digits of its tile of 2048
 //      consecutive elements; an exclusive scan of the digit-major [digit][tile]
 //      counts gives every (digit, tile) its output offset; the tile is then
@@ -1422,7 +1422,10 @@ SortPlan sort_plan(int64_t n, int64_t ncell, int nsub_max) {
     if (top < r.bits - kLowMost) top = r.bits - kLowMost;
     if (top > 2 * kRecBits) top = 2 * kRecBits;
     if (top > r.bits) top = r.bits;
-    // (a grid of far more cells than particles would leave buckets of a few)
+    // So this sort reaches keys of 36 bits, 18 top and 18 low ones: a 512^3 box at
+    // the defaults has just that many; a larger one, or more than 27 sub-cells a
+    // cell there, takes the radix sort below, and so does a grid of far more cells
+    // than particles, whose buckets would hold a few each.
     if (sub_entries(n, nsub_max) >= n && top >= 2 && r.bits - top <= kLowMost && (n >> top) >= 128) {
         r.rec.low = r.bits - top;
         r.rec.dl = top / 2;

@@ -6,9 +6,10 @@
 // before the sequential part of CompaSO.
 //
 // Two stages: most particles are settled by the densest particle of their own
-// sub-cell or of a face-adjacent one; the rest (sub-cell maxima and particles
-// of sparse cells) are listed and searched by half a wavefront each, with
-// pruning by the densest particle of every dense cell and sub-cell.
+// sub-cell, of their cell or of a face-adjacent sub-cell; the rest (sub-cell
+// maxima and particles of sparse cells) are listed and searched by half a
+// wavefront each, with pruning by the densest particle of every dense cell and
+// sub-cell.
 #include "hf_internal.h"
 #include "scan_tile.h"
 

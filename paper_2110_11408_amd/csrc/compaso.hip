@@ -20,7 +20,7 @@
 // "first k >= 1 with C(k) <= k", where C(k) counts particles with T <= k^2.
 // C is the prefix sum of a histogram over integer buckets
 // ceil(sqrt(T)) (computed exactly with integer-square comparisons), so each
-// accepted nucleus costs one pass over the group plus a prefix scan.
+// candidate costs a pass or two over the group and a prefix scan.
 #include "hf_internal.h"
 #include "scan_tile.h"
 
@@ -553,9 +553,9 @@ __device__ __forceinline__ int64_t first_possible(const uint32_t *s_hist, int64_
 // before it; i depends on the group and the candidate only.  Nearly every
 // candidate is accepted (28 072 of 28 141 on the 256^3 box), so i is found for
 // all of them at once instead of one after the other in the group's walk
-// (k_accept_walk), whose chain was the time of the stage (the three kernels took
-// 6.8 ms on the 512^3 box, 300 us on the 256^3 one and 152 us on 1.3e6 particles
-// at their labels; 3.8 ms, 195 us and 72 us now).  The groups'
+// (k_accept_walk), whose chain was the time of the stage (5.7 ms on the 512^3 box,
+// 289 us on the 256^3 one and 138 us on 1.3e6 particles at their labels; 2.9 ms,
+// 170 us and 59 us now).  The groups'
 // densest candidates come first; a candidate that lies inside alpha R of that
 // one, if its i is known by then, is left out (its i is never asked for).  In
 // large groups (accept_late) the others are a list and a launch of their own, so

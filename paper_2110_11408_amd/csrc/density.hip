@@ -448,7 +448,8 @@ __global__ __launch_bounds__(64, 6) void k_density_dense(int64_t nchunks, unsign
 // wavefront issues an instruction every few cycles, and a quarter of the rows
 // halves those of a block of neighbours (332 chunks: 37 us became 21; 4209: 83
 // became 67; 9699: 135 became 125; but about 40 000, which fill the chip: 330
-// became 385).
+// became 385; the line lies just above the largest count that gained, nothing
+// between those two was timed).
 constexpr int kRowParts = 5;
 __global__ __launch_bounds__(64, 4) void k_density_rows(int64_t nchunks, unsigned tile, int64_t n, Boxes bx,
                                                         const int32_t *__restrict__ chunks,

@@ -8,8 +8,8 @@
 //            its sub-cell;
 //   cells    a head start for the dense cells: sub-cells next to each other
 //            whose first members are friends are joined, inside a cell without
-//            atomics, then across cell faces, edges and corners; a cell whose
-//            members are all in one set then carries that set's root;
+//            atomics, then across cell faces; a cell whose members are all in
+//            one set then carries that set's root;
 //   dense    one wavefront per dense chunk gathers the neighbour members within
 //            reach 64 at a time and tests them against its lanes (FP32
 //            prefilter on the cell-local coordinates, canonical FP64 distance
@@ -938,8 +938,9 @@ void launch_fof(int64_t n, const Boxes &bx, Work &w, hipStream_t s) {
         // one wavefront per workgroup: chunk costs differ widely, and a
         // finished wavefront's slot is free at once.  Three per chunk up to
         // three quarters of the wavefronts the chip holds: with 4209 chunks 66 us
-        // became 44 and with 332 30 became 23, but with 9699 68 became 87 (and,
-        // in 64 boxes with longer chains, 9082 went from 82 to 64).
+        // became 44 and with 332 30 became 23, but with 9699 68 became 87.  (The
+        // line is one box's: in 64 boxes, whose chains are longer, 9082 chunks
+        // would still gain, 82 to 64 us, which the chunk count does not tell.)
         const int parts = w.nchunks <= 24 * (int64_t)(w.ncu > 0 ? w.ncu : 1) ? 3 : 1;
         hipLaunchKernelGGL(k_fof_dense, dim3((unsigned)(w.nchunks * parts)), dim3(64), 0, s, w.nchunks, xcd_tile(bx), parts, n, bx,
                            w.chunks, w.sloc, w.spos, w.cells, w.marks, w.subtab, w.subarg, w.dens_s, w.parent);
