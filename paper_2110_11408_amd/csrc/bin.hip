@@ -889,7 +889,7 @@ __device__ __forceinline__ void place_record(const float4 &r, uint32_t key, cons
 // the longer ones (in `big`, pairs of bucket and share), which 1024 threads take
 // with up to 16 each, one workgroup per listed share (a grid striding over the
 // list).  A bucket beyond kRecMost particles is listed as several shares
-// (rec_shares), found by bins of consecutive cells; a share beyond half of
+// (rec_shares), found by bins of consecutive cells; a share that is still beyond
 // kRecMost (a cell of so many) is sorted tile by tile in its part of `work` (16
 // bytes per particle, as two arrays of 64-bit words).  (256 threads with 16
 // elements and the tile sort beyond 4096 had 2.8 wavefronts per SIMD on average
@@ -898,10 +898,16 @@ __device__ __forceinline__ void place_record(const float4 &r, uint32_t key, cons
 // 64 us, the 256^3 box 332 -> 279, the 512^3 box 2250 -> 1917 for 256 threads.
 constexpr int kLowMost = 18;  // low key bits beside 14 bits of place
 constexpr int kRecMost = 1 << 14;
-// Shares of a bucket of m particles: each reads the whole bucket twice, so no
-// more than there are compute units to run them at once.
-__device__ __forceinline__ int64_t rec_shares(int64_t m) {
-    return m <= kRecMost ? 1 : min((m + kRecMost / 4 - 1) / (kRecMost / 4), (int64_t)256);
+// Shares of a bucket of m of all n particles: each reads the whole bucket twice,
+// so as many as would run at once (256) if all buckets were like it, of at least a
+// quarter of kRecMost, but of three quarters where that makes too many.  (Half of
+// 1e7 particles in a plane of cells, buckets of 1.7e5: the binning 1.49 ms with
+// quarters, 1.07 so; 1.11 by the radix sort when it came with a table over the
+// grid.)
+__device__ __forceinline__ int64_t rec_shares(int64_t m, int64_t n) {
+    if (m <= kRecMost) return 1;
+    const int64_t most = (m + kRecMost / 4 - 1) / (kRecMost / 4), least = (m + kRecMost / 4 * 3 - 1) / (kRecMost / 4 * 3);
+    return min(min(max(256 * m / n, least), most), (int64_t)256);
 }
 template <int NW, int ITERS, bool kListed, bool kOne>
 __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict__ rec, int64_t n,
@@ -929,7 +935,7 @@ __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict
         const int64_t r0 = starts[bucket], rm = (int64_t)starts[bucket + 1] - r0;
         if (rm <= 0) return;  // only unlisted buckets, one per workgroup, are empty
         if (!kListed && rm > kMost) {
-            const uint32_t parts = (uint32_t)rec_shares(rm);
+            const uint32_t parts = (uint32_t)rec_shares(rm, n);
             if (tid == 0) s_sel[0] = atomicAdd(nbig, parts);
             __syncthreads();
             const uint32_t at = s_sel[0];
@@ -949,7 +955,7 @@ __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict
         const uint32_t high = (uint32_t)((uint64_t)bucket << low);  // of the keys' low 32 bits
         int64_t b0 = r0, m = rm;  // the particles to sort: [b0, b0 + m) of the output
         const bool shared = kListed && rm > kMost;
-        uint32_t *const sidx = sk + kMost / 2;  // a share's places in the bucket, by place in the share
+        uint32_t *sidx = nullptr;  // a share's places in the bucket, by place in the share
         if constexpr (kListed) {
             if (shared) {
                 // bins of consecutive cells (no sub-cells: an eighth of the key's arithmetic)
@@ -980,12 +986,13 @@ __global__ __launch_bounds__(64 * NW) void k_rec_bucket(const float4 *__restrict
                         if (t + u * NT < rm) atomicAdd(&sk[bin(r[u])], 1u);
                 }
                 __syncthreads();
-                const Share sh = bin_share<kPer, NW>(sk, rm, big[2 * q + 1], rec_shares(rm), s_tot, s_sel);
+                const Share sh = bin_share<kPer, NW>(sk, rm, big[2 * q + 1], rec_shares(rm, n), s_tot, s_sel);
                 if (sh.cnt <= 0) continue;
                 b0 += sh.first;
                 m = sh.cnt;
                 uint64_t *src = work + 2 * b0, *dst = src + m;
-                const bool fits = m <= kMost / 2;
+                const bool fits = m <= kMost;
+                sidx = reinterpret_cast<uint32_t *>(src);
                 float4 r[kGather];
                 gather_share<NW>(
                     rm, s_tot, [&](int u, int64_t i) { r[u] = rec[r0 + i]; },

@@ -74,7 +74,7 @@ def test_fof_cell_links(ctx, n, side, kw):
 # passes that carry the positions beyond.  A bucket of the first is sorted in LDS
 # up to 4096 particles; one of the second by 256 threads up to 2048, by 1024 up to
 # 16 384.  A longer bucket is shared by several workgroups, which sort up to 4096
-# and 8192 particles each in LDS and more tile by tile.  HF_RADIX_PAYLOAD=1 takes
+# and 16 384 particles each in LDS and more tile by tile.  HF_RADIX_PAYLOAD=1 takes
 # the radix sort over all digits instead.  The sorted order is unique, so every
 # output is the same.
 def _same_in_both_sorts(ctx, monkeypatch, pos, side, **kw):
@@ -175,7 +175,7 @@ def _sheet(n, planes, seed):
     return pos, side
 
 
-@pytest.mark.parametrize("n", [20000, 262144, 2 ** 19, 600000, 2000003])
+@pytest.mark.parametrize("n", [20000, 262144, 2 ** 19, 600000, 2000003, 6000011])
 def test_buckets_of_a_sheet(ctx, monkeypatch, n):
     """Long buckets of many cells: the sorted order is that of the radix sort, and
     the binning takes no more than twice its time (a workgroup per bucket took
